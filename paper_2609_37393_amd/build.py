@@ -23,8 +23,9 @@ OBJDIR = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("RIFT_ILE_ARCH", "gfx950")
 KT_CLASSES = (2, 3, 5, 8)
-KINDS = (0, 1, 2, 3, 4, 5, 6, 7, 8)  # FP64 tiles, FP32 tiles, FP64 refine, gradient, distance / time / psi
-#                                      marginals, data passes of the band-limited time rule and of ERAI
+KINDS = (0, 1, 2, 3, 4, 5, 6, 7, 8, 9)  # FP64 tiles, FP32 tiles, FP64 refine, gradient, distance / time / psi
+#                                         marginals, data passes of the band-limited time rule and of ERAI,
+#                                         coefficients of the contracted series
 
 FLAGS = [
     "-O3",
@@ -45,6 +46,7 @@ def _objects():
     objs = [(os.path.join(CSRC, "rift_ile.hip"), os.path.join(OBJDIR, "rift_ile.o"), []),
             (os.path.join(CSRC, "wide.hip"), os.path.join(OBJDIR, "wide.o"), []),
             (os.path.join(CSRC, "sampler.hip"), os.path.join(OBJDIR, "sampler.o"), []),
+            (os.path.join(CSRC, "series.hip"), os.path.join(OBJDIR, "series.o"), []),
             (os.path.join(CSRC, "pregrid.hip"), os.path.join(OBJDIR, "pregrid.o"), []),
             (os.path.join(CSRC, "importance.hip"), os.path.join(OBJDIR, "importance.o"), [])]
     for kt in KT_CLASSES:

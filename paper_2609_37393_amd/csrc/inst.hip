@@ -3,9 +3,10 @@
 // 3: gradient, a lane or a group of lanes per sample, 4: FP64 tiles of the
 // distance marginal, 5: FP64 tiles of the time marginal, 6: FP64 tiles of
 // the polarisation marginal, 7: FP64 data pass of the band-limited time
-// rule, 8: FP64 data pass of the joint phiref / psi marginal).  The build compiles
-// this file once per (class, kind) so the instances build in parallel.
+// rule, 8: FP64 data pass of the joint phiref / psi marginal, 9: coefficients
+// of the time marginals' contracted series).  The build compiles this file once per (class, kind) so the instances build in parallel.
 #include "ile_kernels.h"
+#include "ile_series.h"
 
 #if !defined(RIFT_KT) || !defined(RIFT_KIND)
 #error "RIFT_KT and RIFT_KIND must be defined"
@@ -103,6 +104,16 @@ grad_dm_fn RIFT_CAT(get_gradwdm_kt, RIFT_KT)(int L) {
     case 3: return k_grad_wide_dm<RIFT_KT, 3>;
     case 4: return k_grad_wide_dm<RIFT_KT, 4>;
     case 8: return k_grad_wide_dm<RIFT_KT, 8>;
+    default: return nullptr;
+  }
+}
+#elif RIFT_KIND == 9
+series_coef_fn RIFT_CAT(get_series_kt, RIFT_KT)(int L) {
+  switch (L) {
+    case 2: return k_series_coef<RIFT_KT, 2>;
+    case 3: return k_series_coef<RIFT_KT, 3>;
+    case 4: return k_series_coef<RIFT_KT, 4>;
+    case 8: return k_series_coef<RIFT_KT, 8>;
     default: return nullptr;
   }
 }

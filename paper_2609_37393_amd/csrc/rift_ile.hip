@@ -28,6 +28,7 @@
 #include "../../include/rift_ile.h"
 #include "ile_host.h"
 #include "ile_kernels.h"
+#include "ile_series.h"
 
 using namespace rift;
 
@@ -764,91 +765,10 @@ __global__ void k_lse_tiles(const Tile* __restrict__ tiles, const double* __rest
   }
 }
 
-// The band-limited full-window rule over geocentric time (Eq. (ap:tband)),
-// after the data pass: x kappa at the n nodes t0 + j h of every sample is
-// reconstructed at the fine points t0 + (k / M) h, k = 0 .. (n - 1) M, by the
-// sinc series sum_j x kappa_j sinc(k / M - j), the time-independent remainder
-// is added and the exponentials are summed by the trapezoid rule under a
-// prior uniform on the window:
-//   ln L_t = ln[(1 / ((n - 1) M)) sum_k w_k e^{l_k}], w = 1, ends 1/2.
-// The sinc weights depend on (k mod M, k div M - j) only: a table
-// tab[s][d + NB - 1] = sinc(d + s / M), |d| < NB, read with uniform indices.
+// Bounds of the band-limited full-window rule (Eq. (ap:tband); its kernels are
+// in series.hip).
 constexpr int TBAND_MAX_NODES = 64;
 constexpr int TBAND_MAX_FINE = 64;
-
-// sin(pi (d + f)) = (-1)^d sin(pi f): exact zeros at the nodes (s = 0).
-__global__ void k_sinc_table(int NB, int M, double* __restrict__ tab) {
-  const int W = 2 * NB - 1;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < M * W; e += gridDim.x * blockDim.x) {
-    const int s = e / W, d = e - s * W - (NB - 1);
-    double v;
-    if (s == 0) {
-      v = d == 0 ? 1.0 : 0.0;
-    } else {
-      const double f = (double)s / (double)M;
-      v = ((d & 1) ? -1.0 : 1.0) * sinpi(f) / (3.14159265358979323846 * ((double)d + f));
-    }
-    tab[e] = v;
-  }
-}
-
-// One sample per lane; NB >= n nodes held in registers (zero past n, so the
-// unrolled sums need no bounds).  The fine points run by sub-offset s, whose
-// table row is staged in LDS, then in blocks of eight consecutive node
-// intervals, whose sums share the row's reads T_s[ii + q - j] (the same
-// address in every lane: broadcast reads).  The sample loop is uniform per
-// block (the staging synchronises).  L holds the remainder on entry and
-// ln L_t on return.
-constexpr int TBAND_BLK = 8;
-template <int NB>
-__global__ void __launch_bounds__(256) k_tband(int64_t N, int n, int M, const double* __restrict__ kap,
-                                               const double* __restrict__ tab, double ln_scale,
-                                               double* __restrict__ L) {
-  constexpr int W = 2 * NB - 1;
-  __shared__ double row[W + TBAND_BLK];
-  for (int64_t ib = blockIdx.x * (int64_t)blockDim.x; ib < N; ib += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = ib + threadIdx.x;
-    const bool live = i < N;
-    double y[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) y[j] = (live && j < n) ? kap[(int64_t)j * N + i] : 0.0;
-    const double base = live ? L[i] : 0.0;
-    double m = -__builtin_inf(), sum = 0.0;
-    for (int s = 0; s < M; ++s) {
-      __syncthreads();
-      for (int e = threadIdx.x; e < W + TBAND_BLK; e += blockDim.x) row[e] = e < W ? tab[s * W + e] : 0.0;
-      __syncthreads();
-      // fine points ii M + s <= (n - 1) M
-      const int last = s == 0 ? n - 1 : n - 2;
-      for (int ii = 0; ii <= last; ii += TBAND_BLK) {
-        const double* T = row + (NB - 1) + ii;  // T[q - j] = sinc(ii + q - j + s / M)
-        double v[TBAND_BLK];
-#pragma unroll
-        for (int q = 0; q < TBAND_BLK; ++q) v[q] = 0.0;
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-#pragma unroll
-          for (int q = 0; q < TBAND_BLK; ++q) v[q] = fma(y[j], T[q - j], v[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < TBAND_BLK; ++q) {
-          if (ii + q > last) break;
-          const bool end = s == 0 && (ii + q == 0 || ii + q == n - 1);
-          const double l = v[q] + base + (end ? -0.69314718055994530942 : 0.0);
-          // one exp and no divergent branch: e = exp(-|l - m|) rescales the
-          // sum when l is the new maximum and is the new term otherwise (the
-          // first point: m = -inf, e = 0, sum = 1); a NaN l poisons the sum
-          const double d = l - m;
-          const double e = exp(-fabs(d));
-          const bool up = d > 0.0;
-          sum = up ? fma(sum, e, 1.0) : sum + e;
-          m = up ? l : m;
-        }
-      }
-    }
-    if (live) L[i] = (m == m && sum == sum) ? m + log(sum) + ln_scale : __builtin_nan("");
-  }
-}
 
 // The joint phiref / psi marginal by exact reconstruction (ERAI), after the
 // data pass: per sample the angular coefficients at their sampling angles
@@ -1101,6 +1021,10 @@ struct rift_ile_plan_s {
   double* kap = nullptr;  // band-limited time rule: x kappa at the nodes (stream-ordered, per call)
   AngleRule am{};
   double* ang = nullptr;  // ERAI: the angular coefficients (stream-ordered, per call)
+  // workspace of the calls that need one, kept for the next call (take_space)
+  void* ws = nullptr;
+  size_t ws_bytes = 0;
+  hipStream_t ws_stream = nullptr;
 };
 
 namespace {
@@ -1124,6 +1048,50 @@ int palloc(rift_ile_plan p, size_t bytes, void** out) {
 void plan_free_all(rift_ile_plan p) {
   for (void* b : p->bufs) (void)hipFree(b);
   p->bufs.clear();
+  if (p->ws) (void)hipFree(p->ws);
+  p->ws = nullptr;
+}
+
+// Working memory of one call.  Up to WS_KEEP bytes stay with the plan (given
+// back with it): taking a few hundred MB from the stream-ordered pool again
+// after every synchronisation costs 0.1 - 0.4 ms.  Larger requests, and calls
+// that are being captured (a graph must own what it replays on), take
+// stream-ordered memory that drop_space releases.  Work of an earlier call on
+// another stream is waited for before its workspace is taken.
+constexpr int SERIES_POINT_TIMES = 40000;
+constexpr size_t WS_KEEP = (size_t)256 << 20;
+struct Space {
+  void* p = nullptr;
+  bool pooled = false;
+};
+int take_space(rift_ile_plan p, size_t bytes, hipStream_t st, Space* s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HCHK(hipStreamIsCapturing(st, &cap));
+  if (cap != hipStreamCaptureStatusNone || bytes > WS_KEEP) {
+    if (hipMallocAsync(&s->p, bytes, st) != hipSuccess) return RIFT_ENOMEM;
+    s->pooled = true;
+    return RIFT_OK;
+  }
+  if (p->ws && p->ws_stream != st) HCHK(hipDeviceSynchronize());
+  p->ws_stream = st;
+  if (p->ws_bytes < bytes) {
+    if (p->ws) {
+      HCHK(hipDeviceSynchronize());
+      (void)hipFree(p->ws);
+    }
+    p->ws = nullptr;
+    p->ws_bytes = 0;
+    if (hipMalloc(&p->ws, bytes) != hipSuccess) {
+      p->ws = nullptr;
+      return RIFT_ENOMEM;
+    }
+    p->ws_bytes = bytes;
+  }
+  s->p = p->ws;
+  return RIFT_OK;
+}
+int drop_space(const Space& s, hipStream_t st) {
+  return s.pooled && hipFreeAsync(s.p, st) != hipSuccess ? RIFT_EDEVICE : RIFT_OK;
 }
 
 int build_tiles(rift_ile_plan p) {
@@ -1836,6 +1804,51 @@ int set_dist_rule(rift_ile_plan p, const rift_ile_dist_prior* prior) {
   return RIFT_OK;
 }
 
+// Whether a time rule over the batch runs by contracted series
+// (ile_series.h): every point's rule has to lie close enough (series_takes),
+// and a batch of many points enough times per point for the few launches that
+// each then takes.
+bool by_series(rift_ile_plan p, double t0, double h, int n) {
+  for (const PointDesc& D : p->h_desc)
+    if (!series_takes(D, p->N, t0, h, n)) return false;
+  return p->n_points == 1 || p->N * n > (int64_t)SERIES_POINT_TIMES * p->n_points;
+}
+// Its workspace, and the run over the batch: every sample's result in L.
+size_t series_space(rift_ile_plan p, double h, int n, bool band) {
+  size_t b = 0;
+  for (const PointDesc& D : p->h_desc) b = std::max(b, series_bytes(D, h, n, band));
+  return b;
+}
+int series_batch(rift_ile_plan p, const double* theta, int fine, const double* sinc, void* ws, size_t bytes, double* L,
+                 hipStream_t st) {
+  for (int i = 0; i < p->n_points; ++i) {
+    SeriesJob j{};
+    j.d_desc = p->d_desc + i;
+    j.h_desc = &p->h_desc[i];
+    j.KT = p->KT;
+    j.theta = theta;
+    j.N = p->N;
+    j.tm = p->tm;
+    j.fine = fine;
+    j.sinc = sinc;
+    j.L = L;
+    j.ws = ws;
+    j.ws_bytes = bytes;
+    const int rc = run_series(j, st);
+    if (rc) return rc;
+  }
+  return RIFT_OK;
+}
+
+// ln Z and n_eff from every sample's value, in input order.
+int reduce_values(rift_ile_plan p, const double* L, const double* lnw, double* lnZ, double* neff, hipStream_t st) {
+  if (p->n_tiles > 0)
+    hipLaunchKernelGGL(k_lse_tiles, dim3(p->n_tiles), dim3(p->cfg.block), 0, st, p->d_tiles, L, lnw, p->d_part);
+  hipLaunchKernelGGL(k_merge, dim3(p->n_points), dim3(512), 0, st, p->d_desc, p->d_trange, p->d_part,
+                     (const double*)nullptr, lnZ, neff, (double*)nullptr);
+  return hipGetLastError() == hipSuccess ? RIFT_OK : RIFT_EDEVICE;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1897,6 +1910,16 @@ int rift_ile_plan_lnZ_tmarg(rift_ile_plan p, const double* theta, const double* 
   const bool sorted = p->cfg.sort != 0;
   double* L = lnLt ? lnLt : p->d_L;
   if (sorted && (!p->bin_ready || !L)) return RIFT_EUNSUPPORTED;
+  if (by_series(p, t.t0, t.h, t.n)) {
+    const size_t bytes = series_space(p, t.h, t.n, false);
+    Space sp;
+    if ((rc = take_space(p, bytes + (L ? 0 : sizeof(double) * (size_t)p->N), st, &sp))) return rc;
+    if (!L) L = (double*)((char*)sp.p + bytes);
+    rc = series_batch(p, theta, 0, nullptr, sp.p, bytes, L, st);
+    if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
+    const int rd = drop_space(sp, st);
+    return rc ? rc : rd;
+  }
   if (sorted && (rc = run_binning(p, theta, st))) return rc;
   if ((rc = launch_tiles(p, MODE_TMARG64, theta, lnw, sorted ? L : lnLt, st))) return rc;
   if (sorted)
@@ -1918,7 +1941,6 @@ int rift_ile_plan_lnZ_tband(rift_ile_plan p, const double* theta, const double* 
   if (!std::isfinite(rule->t_start) || !(rule->h > 0.0) || !std::isfinite(rule->h)) return RIFT_EINVAL;
   if (!std::isfinite(rule->t_start + (rule->n_t - 1) * rule->h)) return RIFT_EINVAL;
   const int n = rule->n_t, M = rule->n_fine;
-  const int NB = n <= 16 ? 16 : (n <= 32 ? 32 : 64);
   TimeRule t{};
   t.n = n;
   t.t0 = rule->t_start;
@@ -1929,39 +1951,29 @@ int rift_ile_plan_lnZ_tband(rift_ile_plan p, const double* theta, const double* 
   int rc;
   const bool sorted = p->cfg.sort != 0;
   if (sorted && !p->bin_ready) return RIFT_EUNSUPPORTED;
-  // stream-ordered scratch: kap [n][N], the sinc table [M][2 NB - 1], and
-  // the per-sample values when the caller takes none
+  // working memory: the series' own, or x kappa at the nodes [n][N]; the sinc
+  // matrix; and the per-sample values when the caller takes none
   const int64_t N = p->N;
-  const size_t tab_n = (size_t)M * (2 * NB - 1);
-  const size_t bytes = sizeof(double) * ((size_t)n * N + tab_n + (lnLt ? 0 : (size_t)N));
-  double* w = nullptr;
-  if (hipMallocAsync((void**)&w, bytes, st) != hipSuccess) return RIFT_ENOMEM;
-  double* tab = w + (size_t)n * N;
-  double* L = lnLt ? lnLt : tab + tab_n;
-  p->kap = w;
-  rc = sorted ? run_binning(p, theta, st) : RIFT_OK;
-  if (!rc) rc = launch_tiles(p, MODE_TBAND64, theta, lnw, L, st);
-  p->kap = nullptr;
-  if (!rc) {
-    hipLaunchKernelGGL(k_sinc_table, dim3((unsigned)((tab_n + 255) / 256)), dim3(256), 0, st, NB, M, tab);
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((N + 255) / 256, (int64_t)p->di.n_cu * 8));
-    const double ln_scale = -log((double)(n - 1) * (double)M);
-    const double* kc = w;
-    if (NB == 16)
-      hipLaunchKernelGGL(k_tband<16>, dim3(grid), dim3(256), 0, st, N, n, M, kc, (const double*)tab, ln_scale, L);
-    else if (NB == 32)
-      hipLaunchKernelGGL(k_tband<32>, dim3(grid), dim3(256), 0, st, N, n, M, kc, (const double*)tab, ln_scale, L);
-    else
-      hipLaunchKernelGGL(k_tband<64>, dim3(grid), dim3(256), 0, st, N, n, M, kc, (const double*)tab, ln_scale, L);
-    if (p->n_tiles > 0)
-      hipLaunchKernelGGL(k_lse_tiles, dim3(p->n_tiles), dim3(p->cfg.block), 0, st, p->d_tiles, (const double*)L,
-                         lnw, p->d_part);
-    hipLaunchKernelGGL(k_merge, dim3(p->n_points), dim3(512), 0, st, p->d_desc, p->d_trange, p->d_part,
-                       (const double*)nullptr, lnZ, neff, (double*)nullptr);
-    if (hipGetLastError() != hipSuccess) rc = RIFT_EDEVICE;
+  const bool series = by_series(p, t.t0, t.h, t.n);
+  const size_t need = series ? series_space(p, t.h, t.n, true) : sizeof(double) * (size_t)n * N;
+  const size_t sinc_n = sinc_matrix_len(n, M);
+  Space sp;
+  if ((rc = take_space(p, need + sizeof(double) * (sinc_n + (lnLt ? 0 : (size_t)N)), st, &sp))) return rc;
+  double* sinc = (double*)((char*)sp.p + need);
+  double* L = lnLt ? lnLt : sinc + sinc_n;
+  rc = sinc_matrix(n, M, sinc, st);
+  if (!rc && series) {
+    rc = series_batch(p, theta, M, sinc, sp.p, need, L, st);
+  } else if (!rc) {
+    p->kap = (double*)sp.p;
+    rc = sorted ? run_binning(p, theta, st) : RIFT_OK;
+    if (!rc) rc = launch_tiles(p, MODE_TBAND64, theta, lnw, L, st);
+    p->kap = nullptr;
+    if (!rc) rc = band_reconstruct(N, n, M, (const double*)sp.p, 1, N, sinc, L, st);
   }
-  if (hipFreeAsync(w, st) != hipSuccess && !rc) rc = RIFT_EDEVICE;
-  return rc;
+  if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
+  const int rd = drop_space(sp, st);
+  return rc ? rc : rd;
 }
 
 int rift_ile_plan_lnZ_erai(rift_ile_plan p, const double* theta, const double* lnw, const rift_ile_angle_rule* rule,
