@@ -111,80 +111,112 @@ inline int basis_count(int L) {
   return (NI + 1) + (NQ / 2) * 2 * (NI + 1) + ((NQ + 1) / 2) * 2 * NI;
 }
 
-// Harmonic-basis coefficients of g_c = (a_k/4, Re b_k/4, -Im b_k/4) for one
-// detector per block: sample g_c on an NG x NG grid of (incl, phi) over
-// [0, 2 pi)^2 (NG = 4L + 4, more than twice the degree 2L) and project
-// (discrete orthogonality of the basis on that grid).  U, V in caller order,
-// modes mapped through perm.  Writes column 3k..3k+2 of C64/C32 [B][3 KT].
-__global__ void k_basis(const PointDesc* __restrict__ P, const double* __restrict__ U,
-                        const double* __restrict__ V, const int32_t* __restrict__ perm,
-                        double* __restrict__ C64, float* __restrict__ C32) {
-  extern __shared__ double g[];  // [3][NG][NG]
+// Harmonic-basis coefficients of g_c = (a_k/4, Re b_k/4, -Im b_k/4), one
+// detector per block.  The dependence on phi is explicit: mode pair (i, j)
+// adds d_i d_j Re[U_ij e^{i (m_j - m_i) phi}] to a_k and
+// d_i d_j V_ij e^{i (m_i + m_j) phi} to b_k, so at every incl the cosine and
+// sine coefficients of q = |m_j - m_i| and |m_i + m_j| are sums over pairs.
+// They are taken at NG = 4L + 4 values of incl over [0, 2 pi) (more than twice
+// the degree 2L) and projected on cos, sin(n incl), whose values on that grid
+// are one table of NG entries.  A thread per (incl, q, share of the rows i);
+// 10 us for 21 modes at L = 4, where sampling g_c on an NG x NG grid of (incl,
+// phi) with a sincos per mode and grid point took 640 us (3 blocks of a serial
+// M^2 loop).  U, V in caller order, modes mapped through perm.  Writes columns
+// 3k..3k+2 of C64/C32 [B][3 KT].
+constexpr int BASIS_BLOCK = 1024;
+constexpr int BASIS_MAX_NG = 4 * LMAXC + 4;
+__global__ void __launch_bounds__(BASIS_BLOCK) k_basis(const PointDesc* __restrict__ P, const double* __restrict__ U,
+                                                       const double* __restrict__ V,
+                                                       const int32_t* __restrict__ perm, double* __restrict__ C64,
+                                                       float* __restrict__ C32) {
+  __shared__ double ct[BASIS_MAX_NG], st[BASIS_MAX_NG];
+  __shared__ double d[MMAX][BASIS_MAX_NG];
+  __shared__ double uv[MMAX * MMAX][4];
+  __shared__ int ms[MMAX];
+  __shared__ double part[BASIS_BLOCK][6];  // (cos, sin) x (a, Re b, -Im b), times 1/4
   const int k = blockIdx.x;
-  const int M = P->M, L = P->L, KT = P->KT, B = P->B;
-  const int NG = 4 * L + 4;
-  const double two_pi = 6.283185307179586476925286766559;
-  for (int gp = threadIdx.x; gp < NG * NG; gp += blockDim.x) {
-    const int pi_ = gp / NG, pf = gp % NG;
-    const double inc = two_pi * pi_ / NG, ph = two_pi * pf / NG;
-    double yr[MMAX], yi[MMAX];
-    for (int i = 0; i < M; ++i) {
-      double d = 0.0;
-      for (int n = 0; n <= L; ++n) {
-        const double c = P->ycoef[i][n];
-        d += P->odd[i] ? c * sin(n * inc) : c * cos(n * inc);
-      }
-      double s, cc;
-      sincos(P->m[i] * ph, &s, &cc);
-      yr[i] = d * cc;
-      yi[i] = d * s;
+  const int M = P->M, L = P->L, KT = P->KT, B = P->B, K = P->K;
+  const int NG = 4 * L + 4, NQ = 2 * L + 1;
+  for (int j = threadIdx.x; j < NG; j += blockDim.x) {
+    double sj, cj;
+    sincospi(2.0 * j / NG, &sj, &cj);
+    ct[j] = cj;
+    st[j] = sj;
+  }
+  for (int i = threadIdx.x; i < M; i += blockDim.x) ms[i] = P->m[i];
+  if (k < K) {
+    for (int e = threadIdx.x; e < M * M; e += blockDim.x) {
+      const int i = e / M, j = e - (e / M) * M;
+      const int64_t o = 2 * (((int64_t)k * M + perm[i]) * M + perm[j]);
+      uv[e][0] = U[o];
+      uv[e][1] = U[o + 1];
+      uv[e][2] = V[o];
+      uv[e][3] = V[o + 1];
     }
-    double ar = 0.0, br = 0.0, bi = 0.0;
-    if (k < P->K) {
-      for (int i = 0; i < M; ++i) {
-        const int ci = perm[i];
-        for (int j = 0; j < M; ++j) {
-          const int cj = perm[j];
-          const int64_t o = 2 * (((int64_t)k * M + ci) * M + cj);
-          const double ur = U[o], ui = U[o + 1], vr = V[o], vi = V[o + 1];
-          // Re[conj(Y_i) U_ij Y_j] and Y_i V_ij Y_j
-          const double wr = yr[i] * yr[j] + yi[i] * yi[j];
-          const double wi = yr[i] * yi[j] - yi[i] * yr[j];
-          ar += ur * wr - ui * wi;
-          const double sr = yr[i] * yr[j] - yi[i] * yi[j];
-          const double si = yr[i] * yi[j] + yi[i] * yr[j];
-          br += vr * sr - vi * si;
-          bi += vr * si + vi * sr;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < M * NG; e += blockDim.x) {
+    const int i = e / NG, p = e - (e / NG) * NG;
+    double v = 0.0;
+    for (int n = 0; n <= L; ++n) v += P->ycoef[i][n] * (P->odd[i] ? st[(n * p) % NG] : ct[(n * p) % NG]);
+    d[i][p] = v;
+  }
+  __syncthreads();
+  const int cells = NG * NQ;  // <= BASIS_BLOCK
+  const int shares = BASIS_BLOCK / cells;
+  const int sh = threadIdx.x / cells, cell = threadIdx.x - sh * cells;
+  const int p = cell / NQ, q = cell - (cell / NQ) * NQ;
+  double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  if (sh < shares && k < K) {
+    for (int i = sh; i < M; i += shares) {
+      const int mi = ms[i];
+      const double di = 0.25 * d[i][p];
+      for (int j = 0; j < M; ++j) {
+        const int df = ms[j] - mi, sm = ms[j] + mi;
+        const double w = di * d[j][p];
+        if (df == q || df == -q) {
+          v[0] = fma(w, uv[i * M + j][0], v[0]);
+          v[1] = fma(df < 0 ? w : -w, uv[i * M + j][1], v[1]);
+        }
+        if (sm == q || sm == -q) {
+          const double vr = uv[i * M + j][2], vi = uv[i * M + j][3];
+          const double ws = sm < 0 ? -w : w;
+          v[2] = fma(w, vr, v[2]);
+          v[3] = fma(-ws, vi, v[3]);
+          v[4] = fma(-w, vi, v[4]);
+          v[5] = fma(-ws, vr, v[5]);
         }
       }
     }
-    g[0 * NG * NG + gp] = 0.25 * ar;
-    g[1 * NG * NG + gp] = 0.25 * br;
-    g[2 * NG * NG + gp] = -0.25 * bi;
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c) part[threadIdx.x][c] = v[c];
+  __syncthreads();
+  if (sh == 0) {
+    for (int s = 1; s < shares; ++s)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) v[c] += part[s * cells + cell][c];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) part[cell][c] = v[c];
   }
   __syncthreads();
   for (int b = threadIdx.x; b < B; b += blockDim.x) {
-    int kind, n, q;
-    basis_index(L, b, &kind, &n, &q);
+    int kind, n, qq;
+    basis_index(L, b, &kind, &n, &qq);
+    const double* tab = kind >= 3 ? st : ct;
+    const int part0 = (kind == 2 || kind == 4) ? 1 : 0;  // the sine in phi
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int gp = 0; gp < NG * NG; ++gp) {
-      const int pi_ = gp / NG, pf = gp % NG;
-      const double inc = two_pi * pi_ / NG, ph = two_pi * pf / NG;
-      double t;
-      if (kind == 0) t = cos(n * inc);
-      else if (kind == 1) t = cos(n * inc) * cos(q * ph);
-      else if (kind == 2) t = cos(n * inc) * sin(q * ph);
-      else if (kind == 3) t = sin(n * inc) * cos(q * ph);
-      else t = sin(n * inc) * sin(q * ph);
-      for (int c = 0; c < 3; ++c) acc[c] += g[c * NG * NG + gp] * t;
+    for (int g = 0; g < NG; ++g) {
+      const double t = tab[(n * g) % NG];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc[c] = fma(part[g * NQ + qq][2 * c + part0], t, acc[c]);
     }
-    const double nu_i = (n == 0) ? 1.0 : 0.5;
-    const double nu_f = (q == 0) ? 1.0 : 0.5;
-    const double norm = 1.0 / ((double)NG * NG * nu_i * nu_f);
+    const double norm = 1.0 / ((double)NG * (n == 0 ? 1.0 : 0.5));
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const double v = acc[c] * norm;
-      C64[b * 3 * KT + 3 * k + c] = v;
-      if (C32) C32[b * 3 * KT + 3 * k + c] = (float)v;
+      const double r = acc[c] * norm;
+      C64[b * 3 * KT + 3 * k + c] = r;
+      if (C32) C32[b * 3 * KT + 3 * k + c] = (float)r;
     }
   }
 }
@@ -1610,8 +1642,7 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
     if (D.Q32)
       hipLaunchKernelGGL(k_repack<float>, dim3(gq), dim3(256), 0, st, pt.Q, (float*)D.Q32, d_perm[pi],
                          pt.n_det, KT, pt.n_modes, pt.n_t, QW32);
-    const int NG = 4 * D.L + 4;
-    hipLaunchKernelGGL(k_basis, dim3(KT), dim3(256), sizeof(double) * 3 * NG * NG, st,
+    hipLaunchKernelGGL(k_basis, dim3(KT), dim3(BASIS_BLOCK), 0, st,
                        p->d_desc + pi, pt.U, pt.V, d_perm[pi], (double*)D.C64, (float*)D.C32);
     if (mixed) {
       // error-bound constants of the mixed path, from the table maxima and
