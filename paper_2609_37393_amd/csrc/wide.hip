@@ -20,27 +20,33 @@
 //     e:aa = (X.a + i Y.a)^2 for the complex polarisation tensor e = e+ + i ex;
 //     static sky frame.
 //
-// One lane evaluates one sample, in FP64.  Per detector the lane's C~ goes to
-// LDS; the mode harmonics Y stay in registers (modes sorted by m, the phase
-// walked upward; the kernel is compiled for mode capacities 5, 12 and 25 so
-// that short mode sets keep few registers).  The quadratic term runs over
-// pairs a <= a' of composite terms, G_aa' = Y^H U_aa' Y and H_aa' = Y^T V_aa' Y,
-// and uses the symmetries G_a'a = conj(G_aa') (U Hermitian) and H_a'a = H_aa'
-// (V symmetric).  A set-up kernel packs U and V per call into the order the
-// contraction walks, [k][pair][i][j] (Re U, Im U, Re V, Im V) with internal
-// mode indices and row stride equal to the capacity, so that the uniform
-// entries reach the lanes through the scalar path at constant offsets.
+// A wavefront evaluates 64 samples, in FP64.  The front (sky frame, harmonics,
+// coefficients) and the data term take a lane per sample.
 //
-// For the longer mode sets (l <= 3 with 10 or more modes, l <= 4 with 13 or
-// more) the pair forms take the harmonic form of the static path instead:
-// each of Re G, Im G, Re H, Im H of a block is a trigonometric polynomial in
-// (incl, phiref) of degree 2L in each, with the parity that d_i d_j has in
-// incl (that of m_i - m_j, equal to that of m_i + m_j), so it lies in the
-// static path's real basis of class L (145 functions at L = 4).  A set-up
-// kernel projects every block onto that basis per call; a lane then sums
-// 4 B uniform coefficients against basis values built from cos(n incl),
-// sin(n incl), cos(q phiref), sin(q phiref), instead of 4 M^2 entries
-// (580 against 1764 at 21 modes).
+// The quadratic term is one real form.  With c_a = C~_a Y as real values,
+//   Re(c_a^H U_ab c_b) + Re(c_a^T V_ab c_b) = c_a^T S_ab c_b,
+//   S(i, j) = [ Ur + Vr   -Ui - Vi ]
+//             [ Ui - Vi    Ur - Vr ]  of the modes' entry (i, j),
+// summed over a <= b, off the diagonal twice (U Hermitian, V symmetric): a
+// quarter of the multiply-adds of the two complex forms over all pairs.  For
+// the 64 samples of a wavefront, S c is a dense product with one matrix for
+// all of them, so it runs on the FP64 matrix cores (16 x 16 x 4 tiles): the
+// matrix streams past as A operands in whole lines, each used for 64 samples,
+// with the values c as B operands in four tiles of 16 samples.  (On the vector
+// unit the matrix had to reach the lanes as scalar operands, and their
+// latency, not the multiply-adds, set the time: up to 3000 dependent scalar
+// loads a wavefront for the composite forms, with two wavefronts a SIMD.)
+// Measured (3 detectors, 6554-row windows, a call; the forms on the vector unit
+// before): rotation, 4 modes, 1e6 samples 724 -> 374 us; 9 modes, 1000 and 150k
+// samples 689 -> 131 and 1235 -> 354 us; 21 modes, 1000 and 150k samples
+// 600 -> 409 and 1144 -> 972 us; arms of 12 terms, 4 modes, 1e6 samples
+// 3.6 -> 1.47 ms.  At 1e6 samples of the rotation the rows of Q alone take
+// 0.15 ms to read, the matrix products 0.09 and the front about 0.13: a second
+// pair of wavefronts a SIMD (staging halved to make the LDS for it) or products
+// issued between the lines of Q, both of which spill, gave no more.
+//
+// The data term reads Q by rows: a set-up kernel lays every detector's
+// composite entries of one time out as whole 128-byte lines.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -57,13 +63,11 @@ namespace rift {
 namespace {
 
 constexpr int WIDE_ARMS_MAX_TERMS = 8;
-constexpr int WIDE_BLOCK = 256;     // lanes per block up to 12 terms
-constexpr int WIDE_BLOCK_21 = 128;  // up to 21 terms: the coefficient columns in 43 KB of LDS
-constexpr int WIDE_BASIS_BLOCK = 512;  // threads of the harmonic set-up: one per grid point
+constexpr int WIDE_MERGE = 1024;      // threads of the merge
+constexpr int WIDE_PACK_MIN = 16384;  // samples from which the rows are repacked
 
 struct WideDesc {
-  int32_t K, M, n_t, n_a, response, npairs;
-  int32_t hb, hb_pad;         // class L of the harmonic form of the pair forms, 0: the entries
+  int32_t K, M, n_t, n_a, response, pad;
   double t0, inv_dt, gmst, omega, d_ref;
   double dten[KMAX][6];      // D00, D11, D22, 2 D01, 2 D02, 2 D12
   double rpos[KMAX][3];      // light-seconds
@@ -73,25 +77,10 @@ struct WideDesc {
   int32_t odd[MMAX];
   double ycoef[MMAX][LMAXC + 1];
   const double* Q;           // caller's [K][n_a][M][n_t] complex
-  const double* UV;          // packed [K][pair][MC][MC][4], or [K][pair][B][4] coefficients (hb > 0)
+  const double* Qrows;       // the same by rows (k_wide_rows), where the call repacks it
+  const double* S;           // the real form's operands (k_wide_form)
 };
 static_assert(sizeof(WideDesc) <= 3584, "the description travels as a kernel argument");
-
-// Complex response D : (e+ + i ex) of the six-value tensor d at axes X, Y.
-__device__ __forceinline__ C2<double> response6(const double* d, const double* X, const double* Y) {
-  const double ep[6] = {X[0] * X[0] - Y[0] * Y[0], X[1] * X[1] - Y[1] * Y[1], X[2] * X[2] - Y[2] * Y[2],
-                        X[0] * X[1] - Y[0] * Y[1], X[0] * X[2] - Y[0] * Y[2], X[1] * X[2] - Y[1] * Y[2]};
-  const double ex[6] = {2 * X[0] * Y[0], 2 * X[1] * Y[1], 2 * X[2] * Y[2],
-                        X[0] * Y[1] + Y[0] * X[1], X[0] * Y[2] + Y[0] * X[2], X[1] * Y[2] + Y[1] * X[2]};
-  C2<double> f;
-  f.x = f.y = 0.0;
-#pragma unroll
-  for (int a = 0; a < 6; ++a) {
-    f.x += d[a] * ep[a];
-    f.y += d[a] * ex[a];
-  }
-  return f;
-}
 
 // Polarisation axes X, Y at hour angle g for dec, psi (the static sky frame).
 __device__ __forceinline__ void axes(double sg, double cg, double sd, double cd, double sp, double cp, double* X,
@@ -108,363 +97,220 @@ __device__ __forceinline__ void axes(double sg, double cg, double sd, double cd,
   N[2] = sd;
 }
 
-// Packs U and V of every detector into [k][pair][i][j][4] = (Re U, Im U,
-// Re V, Im V) of block (a, b), pair = the index of a <= b in row order, with
-// internal mode indices i, j < MC (entries past M are zero).
-template <int MC>
-__global__ void k_wide_pack(WideDesc D, const double* __restrict__ U, const double* __restrict__ V,
+// The composite values c_{a,m} = C~_a Y_m of one sample as real components in
+// steps of four: step b = 2 (a MB + mb) + part holds the part (0 real, 1
+// imaginary) of modes m = 4 mb + q at quad q = 0..3.  A tile is four steps
+// (16 components); a form's product with tile t as rows takes the steps from
+// the tile's own on.
+__host__ __device__ constexpr int wide_steps(int MB, int n_a) { return 2 * MB * n_a; }
+__host__ __device__ constexpr int wide_tiles(int MB, int n_a) { return (wide_steps(MB, n_a) + 3) / 4; }
+// Pairs of steps (both parts of four modes of a term) that tiles 0 .. t-1 take.
+__host__ __device__ constexpr int64_t wide_pairs(int steps, int t) { return (int64_t)t * (steps / 2) - (int64_t)t * (t - 1); }
+
+// The A operands of every detector, [k][tile][pair of steps][lane][2]: lane l
+// holds, for both steps b of the pair, the coefficient of row component
+// (step 4 t + (l & 15) / 4, quad l & 3) and column component (step b, quad
+// l >> 4): S summed over both orders of the two components where the column
+// lies beyond the row's tile, S itself inside the tile (whose rows and columns
+// meet in both orders).
+template <int MB>
+__global__ void k_wide_form(WideDesc D, const double* __restrict__ U, const double* __restrict__ V,
                             double* __restrict__ out) {
-  const int64_t per_det = (int64_t)D.npairs * MC * MC;
-  const int64_t total = (int64_t)D.K * per_det;
+  const int steps = wide_steps(MB, D.n_a), tiles = wide_tiles(MB, D.n_a);
+  const int64_t per_det = wide_pairs(steps, tiles) * 128;
   const int A = D.n_a * D.M;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int k = (int)(e / per_det);
-    int r = (int)(e - (int64_t)k * per_det);
-    const int pr = r / (MC * MC);
-    r -= pr * MC * MC;
-    const int i = r / MC, j = r - (r / MC) * MC;
-    int a = 0, rem = pr;
-    while (rem >= D.n_a - a) {
-      rem -= D.n_a - a;
-      ++a;
+  auto entry = [&](int k, int bi, int qi, int bj, int qj) {
+    const int ai = bi / (2 * MB), aj = bj / (2 * MB);
+    const int mi = 4 * ((bi % (2 * MB)) / 2) + qi, mj = 4 * ((bj % (2 * MB)) / 2) + qj;
+    if (ai > aj || aj >= D.n_a || mi >= D.M || mj >= D.M) return 0.0;
+    const int64_t o = 2 * (((int64_t)k * A + ai * D.M + D.perm[mi]) * A + aj * D.M + D.perm[mj]);
+    const double f = ai == aj ? 1.0 : 2.0;
+    const int pi = bi & 1, pj = bj & 1;
+    if (pi == pj) return f * (pi ? U[o] - V[o] : U[o] + V[o]);
+    return f * (pi ? U[o + 1] - V[o + 1] : -U[o + 1] - V[o + 1]);
+  };
+  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < D.K * per_det;
+       x += (int64_t)gridDim.x * blockDim.x) {
+    const int k = (int)(x / per_det);
+    const int64_t r = x - k * per_det;
+    const int e = (int)(r & 1), l = (int)((r >> 1) & 63);
+    const int64_t pr = r >> 7;
+    int t = 0;
+    while (t + 1 < tiles && wide_pairs(steps, t + 1) <= pr) ++t;
+    const int b = 4 * t + 2 * (int)(pr - wide_pairs(steps, t)) + e;
+    const int bi = 4 * t + ((l & 15) >> 2), qi = l & 3, qj = l >> 4;
+    double v = 0.0;
+    if (bi < steps) {
+      v = entry(k, bi, qi, b, qj);
+      if (b >= 4 * t + 4) v += entry(k, b, qj, bi, qi);
     }
-    const int b = a + rem;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (i < D.M && j < D.M) {
-      const int64_t o = 2 * (((int64_t)k * A + a * D.M + D.perm[i]) * A + b * D.M + D.perm[j]);
-      v[0] = U[o];
-      v[1] = U[o + 1];
-      v[2] = V[o];
-      v[3] = V[o + 1];
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) out[4 * e + c] = v[c];
+    out[x] = v;
   }
 }
 
-// G_ab = Y^H U_ab Y and H_ab = Y^T V_ab Y of one packed block, accumulated
-// into g[4] = (Re G, Im G, Re H, Im H): the rows II in turn (a template
-// recursion, so that every mode index and table offset is a compile-time
-// constant and Y stays in registers), each row's columns in an unrolled loop.
-template <int II, int MC>
-struct PairForms {
-  static __device__ __forceinline__ void run(const RIFT_CONST double* blk, int M, const double* yr,
-                                             const double* yi, double* g) {
-    if constexpr (II < MC) {
-      if (II < M) {
-        double tr = 0.0, ti = 0.0, vr = 0.0, vi = 0.0;  // (U Y)_II, (V Y)_II
-#pragma unroll
-        for (int jj = 0; jj < MC; ++jj) {
-          if (jj < M) {
-            const RIFT_CONST double* e = blk + 4 * (II * MC + jj);
-            const double ur = e[0], ui = e[1], wr = e[2], wi = e[3];
-            tr += ur * yr[jj] - ui * yi[jj];
-            ti += ur * yi[jj] + ui * yr[jj];
-            vr += wr * yr[jj] - wi * yi[jj];
-            vi += wr * yi[jj] + wi * yr[jj];
-          }
-        }
-        // conj(Y_II) (U Y)_II and Y_II (V Y)_II
-        g[0] += yr[II] * tr + yi[II] * ti;
-        g[1] += yr[II] * ti - yi[II] * tr;
-        g[2] += yr[II] * vr - yi[II] * vi;
-        g[3] += yr[II] * vi + yi[II] * vr;
-        PairForms<II + 1, MC>::run(blk, M, yr, yi, g);
-      }
-    }
-  }
-};
+// Slots of one term in a row of the repacked table (a multiple of eight, or
+// four for up to four modes), and the 128-byte lines (eight slots) of a row.
+__host__ __device__ constexpr int wide_slots(int MB) { return MB == 1 ? 4 : 8 * ((MB + 1) / 2); }
+__host__ __device__ constexpr int wide_lines(int MB, int n_a) { return (n_a * wide_slots(MB) + 7) / 8; }
 
-// The entry form for the 5-mode capacity with the coefficients streamed
-// through double-buffered 128-byte scalar chunks (four entries each; the
-// static path's prefetch): the whole MC x MC block is read, the entries past
-// M being zero in the pack and Y zero there, so every index is a template
-// constant.  Row i's (U Y)_i and (V Y)_i accumulate across chunk boundaries.
-template <int MC>
-struct PairFormsP {
-  static constexpr int NC = 4 * MC * MC;
-  static constexpr int CH = 16;
-  static constexpr int NCH = (NC + CH - 1) / CH;
-  struct Row {
-    double tr, ti, vr, vi;
-  };
-  template <int E>
-  static __device__ __forceinline__ void entry(const double* e, const double* yr, const double* yi, double* g,
-                                               Row& R) {
-    if constexpr (E < MC * MC) {
-      constexpr int i = E / MC, j = E % MC;
-      if constexpr (j == 0) R.tr = R.ti = R.vr = R.vi = 0.0;
-      R.tr += e[0] * yr[j] - e[1] * yi[j];
-      R.ti += e[0] * yi[j] + e[1] * yr[j];
-      R.vr += e[2] * yr[j] - e[3] * yi[j];
-      R.vi += e[2] * yi[j] + e[3] * yr[j];
-      if constexpr (j == MC - 1) {
-        g[0] += yr[i] * R.tr + yi[i] * R.ti;
-        g[1] += yr[i] * R.ti - yi[i] * R.tr;
-        g[2] += yr[i] * R.vr - yi[i] * R.vi;
-        g[3] += yr[i] * R.vi + yi[i] * R.vr;
+// Q [K][n_a][M][n_t] -> [K][n_t][lines of eight slots]: every row of a
+// detector's window is whole, aligned 128-byte lines holding all composite
+// entries (term a, internal mode m) at slot a SL + m, zero where there is
+// none.  A 64-row tile goes through LDS: series are read and rows written in
+// whole lines.
+constexpr int WIDE_QT = 64;
+__global__ void __launch_bounds__(256) k_wide_rows(WideDesc D, int SL, int lines, double* __restrict__ out) {
+  constexpr int CH = 8;  // one line of slots at a time
+  __shared__ double2 tile[WIDE_QT][CH + 1];
+  const int k = blockIdx.y, t0 = blockIdx.x * WIDE_QT;
+  const double* Q = D.Q + 2 * (int64_t)k * D.n_a * D.M * D.n_t;
+  double2* o = reinterpret_cast<double2*>(out) + (int64_t)k * D.n_t * lines * 8;
+  for (int l = blockIdx.z; l < lines; l += gridDim.z) {
+    for (int x = threadIdx.x; x < CH * WIDE_QT; x += blockDim.x) {
+      const int sl = x / WIDE_QT, t = x - (x / WIDE_QT) * WIDE_QT;
+      const int e = l * 8 + sl, a = e / SL, m = e - (e / SL) * SL;
+      double2 v = make_double2(0.0, 0.0);
+      if (a < D.n_a && m < D.M && t0 + t < D.n_t) {
+        const double* q = Q + 2 * (((int64_t)a * D.M + D.perm[m]) * D.n_t + t0 + t);
+        v = make_double2(q[0], q[1]);
       }
+      tile[t][sl] = v;
     }
-  }
-  template <int C>
-  static __device__ __forceinline__ void ld(double (&buf)[CH], const RIFT_CONST double* c) {
-    const RIFT_CONST double* p = c + C * CH;
-#pragma unroll
-    for (int i = 0; i < CH; ++i)
-      if (C * CH + i < NC) buf[i] = p[i];
-  }
-  template <int C>
-  static __device__ __forceinline__ void wait(const double (&buf)[CH]) {
-#pragma unroll
-    for (int i = 0; i < CH; ++i)
-      if (C * CH + i < NC) pin_s(buf[i]);
-  }
-  template <int C>
-  static __device__ __forceinline__ void step(const RIFT_CONST double* c, double (&cur)[CH], double (&nxt)[CH],
-                                              const double* yr, const double* yi, double* g, Row& R) {
-    if constexpr (C < NCH) {
-      wait<C>(cur);
-      if constexpr (C + 1 < NCH) ld<C + 1>(nxt, c);
-      entry<4 * C>(cur, yr, yi, g, R);
-      entry<4 * C + 1>(cur + 4, yr, yi, g, R);
-      entry<4 * C + 2>(cur + 8, yr, yi, g, R);
-      entry<4 * C + 3>(cur + 12, yr, yi, g, R);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) pin(g[k]);
-      pin(R.tr);
-      pin(R.ti);
-      pin(R.vr);
-      pin(R.vi);
-      step<C + 1>(c, nxt, cur, yr, yi, g, R);
+    __syncthreads();
+    for (int x = threadIdx.x; x < CH * WIDE_QT; x += blockDim.x) {
+      const int t = x / CH, sl = x - (x / CH) * CH;
+      if (t0 + t < D.n_t) o[((int64_t)(t0 + t) * lines + l) * 8 + sl] = tile[t][sl];
     }
-  }
-  static __device__ __forceinline__ void run(const RIFT_CONST double* c, const double* yr, const double* yi,
-                                             double* g) {
-    Row R;
-    R.tr = R.ti = R.vr = R.vi = 0.0;
-    double bA[CH], bB[CH];
-    ld<0>(bA, c);
-    step<0>(c, bA, bB, yr, yi, g, R);
-  }
-};
-
-// The same four forms of one block in the harmonic basis of class L, summed
-// per harmonic q in phi: the rows of one q are consecutive and q increases
-// along them (basis_row), so
-// g[c] += cos(q phi) sum_n C[(n, cos)][c] T_n(incl)
-//       + sin(q phi) sum_n C[(n, sin)][c] T_n(incl),
-// T_n = cos(n incl) for even q and sin(n incl) for odd q (q = 0: the first
-// sum alone), with e^{i q phi} advanced by one factor e^{i phi} per q.
-// Every row's kind and degrees are template constants; no product of basis
-// values is formed, so only the cos(n incl), sin(n incl) tables stay live
-// across the pairs.
-template <int L>
-struct HarmForms {
-  static constexpr int B = Cls<L>::B;
-  static constexpr int NC = 4 * B;              // coefficients of one block
-  static constexpr int CH = 16;                 // one 128-byte chunk: four rows
-  static constexpr int NCH = (NC + CH - 1) / CH;
-  struct Run {
-    double pc[4], ps[4];  // the two sums of the current q
-    double er, ei;        // e^{i q phi}
-  };
-  template <int J>
-  static __device__ __forceinline__ void term(const double* e, const double* cn, const double* sn, double cf,
-                                              double sf, double* g, Run& R) {
-    if constexpr (J < B) {
-      constexpr int rb = basis_row<L>(J);
-      constexpr int kind = rb & 15, nn = (rb >> 4) & 255, q = rb >> 12;
-      constexpr bool last = (J + 1 == B) || ((basis_row<L>(J + 1) >> 12) != q);
-      const double tn = (kind == 3 || kind == 4) ? sn[nn] : cn[nn];
-      if constexpr (kind == 0) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) g[k] = fma(e[k], tn, g[k]);
-      } else {
-        double* acc = (kind == 1 || kind == 3) ? R.pc : R.ps;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] = fma(e[k], tn, acc[k]);
-        if constexpr (last) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            g[k] = fma(R.pc[k], R.er, fma(R.ps[k], R.ei, g[k]));
-            R.pc[k] = 0.0;
-            R.ps[k] = 0.0;
-          }
-          const double nr = R.er * cf - R.ei * sf, ni = R.er * sf + R.ei * cf;
-          R.er = nr;
-          R.ei = ni;
-        }
-      }
-    }
-  }
-  // The uniform coefficients stream through SGPRs in 128-byte chunks, each
-  // chunk prefetched while the previous one is used (the static path's
-  // scheme): the wait for a chunk comes before the next chunk is issued, and
-  // the accumulators are pinned after each chunk's FMAs so that those FMAs
-  // stay ahead of the next wait.
-  template <int C>
-  static __device__ __forceinline__ void ld(double (&buf)[CH], const RIFT_CONST double* c) {
-    const RIFT_CONST double* p = c + C * CH;
-#pragma unroll
-    for (int i = 0; i < CH; ++i)
-      if (C * CH + i < NC) buf[i] = p[i];
-  }
-  template <int C>
-  static __device__ __forceinline__ void wait(const double (&buf)[CH]) {
-#pragma unroll
-    for (int i = 0; i < CH; ++i)
-      if (C * CH + i < NC) pin_s(buf[i]);
-  }
-  template <int C>
-  static __device__ __forceinline__ void step(const RIFT_CONST double* c, double (&cur)[CH], double (&nxt)[CH],
-                                              const double* cn, const double* sn, double cf, double sf, double* g,
-                                              Run& R) {
-    if constexpr (C < NCH) {
-      wait<C>(cur);
-      if constexpr (C + 1 < NCH) ld<C + 1>(nxt, c);
-      term<4 * C>(cur, cn, sn, cf, sf, g, R);
-      term<4 * C + 1>(cur + 4, cn, sn, cf, sf, g, R);
-      term<4 * C + 2>(cur + 8, cn, sn, cf, sf, g, R);
-      term<4 * C + 3>(cur + 12, cn, sn, cf, sf, g, R);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        pin(g[k]);
-        pin(R.pc[k]);
-        pin(R.ps[k]);
-      }
-      step<C + 1>(c, nxt, cur, cn, sn, cf, sf, g, R);
-    }
-  }
-  static __device__ __forceinline__ void run(const RIFT_CONST double* c, const double* cn, const double* sn,
-                                             double cf, double sf, double* g) {
-    Run R;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) R.pc[k] = R.ps[k] = 0.0;
-    R.er = cf;  // the first group after q = 0 is q = 1
-    R.ei = sf;
-    double bA[CH], bB[CH];
-    ld<0>(bA, c);
-    step<0>(c, bA, bB, cn, sn, cf, sf, g, R);
-  }
-};
-
-// Harmonic-basis coefficients of the pair forms, one block per (detector,
-// pair a <= b): Re G, Im G, Re H, Im H of the block sampled on an NG x NG
-// grid of (incl, phi) over [0, 2 pi)^2, NG = 4L + 4 (more than twice the
-// degree 2L in each), then projected on the basis rows (discrete
-// orthogonality on that grid).  Every angle on the grid is a multiple of
-// 2 pi / NG, so cos and sin come from one table of NG entries each; the
-// block's U and V entries are staged in LDS; a thread per grid point, then
-// each basis row's projection split over WIDE_BASIS_BLOCK / B threads.  U, V in the caller's order
-// [K][A][A] complex; out [K][pair][B][4].
-template <int L>
-__global__ void k_wide_basis(WideDesc D, const double* __restrict__ U, const double* __restrict__ V,
-                             double* __restrict__ out) {
-  constexpr int NG = 4 * L + 4, B = Cls<L>::B, MX = Cls<L>::MAXM;
-  constexpr int PS = WIDE_BASIS_BLOCK / B;  // threads per basis row in the projection
-  __shared__ double g[4][NG * NG];
-  __shared__ double part[PS][B][4];
-  __shared__ double ct[NG], st[NG];
-  __shared__ double uv[MX * MX][4];
-  const int k = blockIdx.x / D.npairs, pr = blockIdx.x - k * D.npairs;
-  int a = 0, rem = pr;
-  while (rem >= D.n_a - a) {
-    rem -= D.n_a - a;
-    ++a;
-  }
-  const int b = a + rem;
-  const int M = D.M, A = D.n_a * D.M;
-  for (int j = threadIdx.x; j < NG; j += blockDim.x) {
-    double sj, cj;
-    sincospi(2.0 * j / NG, &sj, &cj);
-    ct[j] = cj;
-    st[j] = sj;
-  }
-  for (int e = threadIdx.x; e < M * M; e += blockDim.x) {
-    const int i = e / M, j = e - (e / M) * M;
-    const int64_t o = 2 * (((int64_t)k * A + a * M + D.perm[i]) * A + b * M + D.perm[j]);
-    uv[e][0] = U[o];
-    uv[e][1] = U[o + 1];
-    uv[e][2] = V[o];
-    uv[e][3] = V[o + 1];
-  }
-  __syncthreads();
-  // index of the angle n * (2 pi c / NG) in the tables
-  auto ix = [](int n, int c) { return ((n * c) % NG + NG) % NG; };
-  for (int gp = threadIdx.x; gp < NG * NG; gp += blockDim.x) {
-    const int pi_ = gp / NG, pf = gp - (gp / NG) * NG;
-    double yr[MX], yi[MX];
-#pragma unroll
-    for (int i = 0; i < MX; ++i) {
-      yr[i] = yi[i] = 0.0;
-      if (i < M) {
-        double d = 0.0;
-        for (int q = 0; q <= L; ++q) d += D.ycoef[i][q] * (D.odd[i] ? st[ix(q, pi_)] : ct[ix(q, pi_)]);
-        const int r = ix(D.m[i], pf);
-        yr[i] = d * ct[r];
-        yi[i] = d * st[r];
-      }
-    }
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int i = 0; i < MX; ++i) {
-      if (i < M) {
-        double tr = 0.0, ti = 0.0, wr = 0.0, wi = 0.0;
-#pragma unroll
-        for (int j = 0; j < MX; ++j) {
-          if (j < M) {
-            const double* e = uv[i * M + j];
-            tr += e[0] * yr[j] - e[1] * yi[j];
-            ti += e[0] * yi[j] + e[1] * yr[j];
-            wr += e[2] * yr[j] - e[3] * yi[j];
-            wi += e[2] * yi[j] + e[3] * yr[j];
-          }
-        }
-        v[0] += yr[i] * tr + yi[i] * ti;
-        v[1] += yr[i] * ti - yi[i] * tr;
-        v[2] += yr[i] * wr - yi[i] * wi;
-        v[3] += yr[i] * wi + yi[i] * wr;
-      }
-    }
-    for (int c = 0; c < 4; ++c) g[c][gp] = v[c];
-  }
-  __syncthreads();
-  // each row's sum over the grid split over PS threads, then reduced
-  for (int w = threadIdx.x; w < PS * B; w += blockDim.x) {
-    const int r = w % B, sp = w / B;
-    const int rb = basis_row<L>(r);
-    const int kind = rb & 15, nn = (rb >> 4) & 255, q = rb >> 12;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int gp = sp; gp < NG * NG; gp += PS) {
-      const int pi_ = gp / NG, pf = gp - (gp / NG) * NG;
-      const double ti = (kind >= 3) ? st[ix(nn, pi_)] : ct[ix(nn, pi_)];
-      const double tf = (kind == 0) ? 1.0 : (kind == 1 || kind == 3) ? ct[ix(q, pf)] : st[ix(q, pf)];
-      const double t = ti * tf;
-      for (int c = 0; c < 4; ++c) acc[c] += g[c][gp] * t;
-    }
-    for (int c = 0; c < 4; ++c) part[sp][r][c] = acc[c];
-  }
-  __syncthreads();
-  for (int r = threadIdx.x; r < B; r += blockDim.x) {
-    const int rb = basis_row<L>(r);
-    const int nn = (rb >> 4) & 255, q = rb >> 12;
-    const double norm = 1.0 / ((double)NG * NG * (nn == 0 ? 1.0 : 0.5) * (q == 0 ? 1.0 : 0.5));
-    double* o = out + ((int64_t)blockIdx.x * B + r) * 4;
-    for (int c = 0; c < 4; ++c) {
-      double v = 0.0;
-      for (int sp = 0; sp < PS; ++sp) v += part[sp][r][c];
-      o[c] = v * norm;
-    }
+    __syncthreads();
   }
 }
 
-// cos(2 pi j / 5), sin(2 pi j / 5), j = 0..4: the five hour angles of the
-// rotation harmonics and the factors of their transform (e^{-2 pi i n j / 5}
-// is entry (n j) mod 5, conjugated).
-__constant__ double kC5[5] = {1.0, 0.30901699437494745, -0.80901699437494745, -0.80901699437494745,
-                              0.30901699437494745};
-__constant__ double kS5[5] = {0.0, 0.95105651629515353, 0.58778525229247314, -0.58778525229247314,
-                              -0.95105651629515353};
+// A wavefront's coefficients C~ [term][lane].
+typedef RIFT_LDS double2* WideCoef;
+
+// Re sum_a conj(C~_a) sum_m conj(Y_m) Qhat_{a,m} of one detector from the
+// repacked table: the stencil's four rows are 4 x lines aligned 128-byte lines
+// per lane, read cooperatively through LDS as the static path reads its
+// blocks (eight lanes fetch the eight 16-byte chunks of one lane's line,
+// straight to LDS, two 8 KB buffers per wavefront; the same chunk swizzle).
+// Rows jc .. jc + 3 at byte offset `boff` of detector k's table, tap weights
+// wr.  The whole wavefront calls this together.
+template <int MB>
+__device__ __forceinline__ double wide_data(const RIFT_GLOBAL char* tab, uint32_t boff, int n_a,
+                                            RIFT_LDS unsigned char* stage, const double* wr, const double* yr,
+                                            const double* yi, WideCoef C) {
+  typedef double R2 __attribute__((ext_vector_type(2)));
+  constexpr int SL = wide_slots(MB);
+  constexpr int LPT = SL <= 8 ? 1 : SL / 8;  // lines of a term, or
+  constexpr int TPL = SL <= 8 ? 8 / SL : 1;  // terms of a line
+  const int lines = wide_lines(MB, n_a);
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int q = lane >> 3;
+  const uint32_t cx0 = (uint32_t)((lane & 7) ^ (q >> 1)) << 4;
+  const uint32_t cx1 = (uint32_t)((lane & 7) ^ (4 | (q >> 1))) << 4;
+  uint32_t off[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) off[t] = (uint32_t)__shfl((int)boff, 8 * t + q) + ((t & 1) ? cx1 : cx0);
+  const uint32_t rbase = (uint32_t)lane * 128u + ((uint32_t)((lane >> 1) & 7) << 4);
+  auto issue = [&](int l, int tap) {
+    const RIFT_GLOBAL char* ser = uniform_ptr(tab + ((uint64_t)tap * lines + l) * 128u);
+    RIFT_LDS unsigned char* dst = stage + (tap & 1) * STAGE_UNIT;
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      __builtin_amdgcn_global_load_lds((const RIFT_GLOBAL void*)(ser + off[t]), (RIFT_LDS void*)(dst + t * 1024), 16, 0,
+                                       0);
+  };
+  double data = 0.0;
+  issue(0, 0);
+#pragma unroll 1
+  for (int l0 = 0; l0 < lines; l0 += LPT) {
+    double zr[TPL], zi[TPL];
+#pragma unroll
+    for (int a = 0; a < TPL; ++a) zr[a] = zi[a] = 0.0;
+#pragma unroll
+    for (int h = 0; h < LPT; ++h) {
+      const int l = l0 + h;
+      double qx[8], qy[8];
+#pragma unroll
+      for (int tap = 0; tap < 4; ++tap) {
+        // the other buffer's reads have completed: refill it, then wait for this one
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (tap < 3 || l + 1 < lines) {
+          issue(tap < 3 ? l : l + 1, (tap + 1) & 3);
+          asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        } else {
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        const RIFT_LDS unsigned char* src = stage + (tap & 1) * STAGE_UNIT;
+        R2 v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = *(const RIFT_LDS R2*)(src + (rbase ^ ((uint32_t)c << 4)));
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          qx[c] = tap == 0 ? wr[0] * v[c].x : fma(wr[tap], v[c].x, qx[c]);
+          qy[c] = tap == 0 ? wr[0] * v[c].y : fma(wr[tap], v[c].y, qy[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          pin(qx[c]);
+          pin(qy[c]);
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int a = SL <= 8 ? c / SL : 0, m = SL <= 8 ? c % SL : 8 * h + c;
+        if (m < 4 * MB) {
+          zr[a] = fma(yr[m], qx[c], fma(yi[m], qy[c], zr[a]));
+          zi[a] = fma(yr[m], qy[c], fma(-yi[m], qx[c], zi[a]));
+        }
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < TPL; ++a) {
+      const int ta = l0 / LPT * TPL + a;
+      if (ta < n_a) {
+        const double cx = C[ta * 64 + lane].x, cy = C[ta * 64 + lane].y;
+        data = fma(cx, zr[a], fma(cy, zi[a], data));
+      }
+    }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  return data;
+}
+
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The sidereal harmonics of the antenna factor times the post-phases,
+// C~_n = A_n e^{i n theta}, n = -2..2, theta = g(t_ref) + Omega (t_k - t_ref).
+// With e = X + i Y = -e^{-i psi} (e_ra - i e_dec), F(g) = D : e e is
+// e^{-2 i psi} times, in E = e^{i g}, p = 1 - sin dec and m = 1 + sin dec,
+//   E^2:  p^2 / 4 [(D11 - D00) - 2 i D01]     E^-2: m^2 / 4 [(D11 - D00) + 2 i D01]
+//   E:    -cos dec p [D02 + i D12]            E^-1: cos dec m [D02 - i D12]
+//   1:    p m [(D00 + D11) / 2 - D22]
+// (p m = cos^2 dec): about 60 operations a detector, where the five-point
+// transform of F at five hour angles takes 500.
+__device__ __forceinline__ void rotation_terms(const double* dten, double sd, double cd, double s2p, double c2p,
+                                               double ec, double es, double* cr, double* ci) {
+  const double p = 1.0 - sd, m = 1.0 + sd;
+  const double dd = dten[1] - dten[0];
+  const double e2c = ec * ec - es * es, e2s = 2.0 * ec * es;
+  // e^{-2 i psi} e^{i n theta}
+  const double fr[5] = {c2p * e2c - s2p * e2s, c2p * ec - s2p * es, c2p, c2p * ec + s2p * es, c2p * e2c + s2p * e2s};
+  const double fi[5] = {-c2p * e2s - s2p * e2c, -c2p * es - s2p * ec, -s2p, c2p * es - s2p * ec,
+                        c2p * e2s - s2p * e2c};
+  const double w2 = 0.25 * p * p, w1 = -0.5 * cd * p, w0 = p * m, v1 = 0.5 * cd * m, v2 = 0.25 * m * m;
+  const double ar[5] = {v2 * dd, v1 * dten[4], w0 * (0.5 * (dten[0] + dten[1]) - dten[2]), w1 * dten[4], w2 * dd};
+  const double ai[5] = {v2 * dten[3], -v1 * dten[5], 0.0, w1 * dten[5], -w2 * dten[3]};
+#pragma unroll
+  for (int n = 0; n < 5; ++n) {
+    cr[n] = ar[n] * fr[n] - ai[n] * fi[n];
+    ci[n] = ar[n] * fi[n] + ai[n] * fr[n];
+  }
+}
 
 // sin and cos of |x| <= 1 by their Taylor series through x^19 / 19! and
 // x^18 / 18! (truncation below 1e-17): the rotation over the light-travel
@@ -493,17 +339,24 @@ __device__ __forceinline__ void sincos_small(double x, double* s, double* c) {
   *c = fma(-pc, x2, 1.0);
 }
 
-// Occupancy: three wavefronts per SIMD (<= 168 VGPRs) for up to 5 modes, two
-// otherwise (the 25-mode capacity's Y alone holds 100 VGPRs).  NT is the
-// capacity of the coefficient columns in LDS (NT x BLK complex values).
-template <int MC, int NT, int BLK, int HL = 0>
-__global__ void __launch_bounds__(BLK, MC <= 5 && NT <= 12 ? 3 : 2) k_wide(WideDesc D, const double* __restrict__ theta, int64_t n,
-                                                              const double* __restrict__ lnw,
-                                                              double* __restrict__ lnL, double* __restrict__ part) {
-  __shared__ double cre[NT][BLK], cim[NT][BLK];
-  __shared__ MS sh[BLK / 64];
-  const int t = threadIdx.x;
-  const int64_t i0 = (int64_t)blockIdx.x * BLK + t;
+// Dynamic LDS of a wavefront: the staging of the data term's rows (the
+// harmonics' exchange reuses it), then the coefficients.
+__host__ __device__ constexpr int wide_stage_bytes(bool packed) { return packed ? STAGE_WAVE : 4 * 64 * 16; }
+
+// One wavefront per block: its LDS (21 KB at five terms) then packs seven to a
+// CU, within the registers of two per SIMD.
+template <int MB, bool PACKED>
+__global__ void __launch_bounds__(64, 2) k_wide(WideDesc D, const double* __restrict__ theta, int64_t n,
+                                                const double* __restrict__ lnw, double* __restrict__ lnL,
+                                                double* __restrict__ part) {
+  typedef double D4 __attribute__((ext_vector_type(4)));
+  constexpr int MC = 4 * MB;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ MS sh[1];
+  RIFT_LDS unsigned char* stage = (RIFT_LDS unsigned char*)smem;
+  const WideCoef C = (WideCoef)(stage + wide_stage_bytes(PACKED));
+  const int t = threadIdx.x, col = t & 15, quad = t >> 4;
+  const int64_t i0 = (int64_t)blockIdx.x * 64 + t;
   const bool live = i0 < n;
   const int64_t i = live ? i0 : n - 1;
   const RIFT_GLOBAL double* th = as_global(theta) + i;
@@ -524,11 +377,12 @@ __global__ void __launch_bounds__(BLK, MC <= 5 && NT <= 12 ? 3 : 2) k_wide(WideD
   axes(sg, cg, sd, cd, sp, cp, X, Y3, N);
 
   // harmonics Y_i = d_i(incl) e^{i m_i phi}, internal (m-sorted) modes
-  double ci, si, cf, sf;
-  sincos(incl, &si, &ci);
-  sincos(phi, &sf, &cf);
-  double cn[LMAXC + 1], sn[LMAXC + 1];
+  double yr[MC], yi[MC];
   {
+    double ci, si, cf, sf;
+    sincos(incl, &si, &ci);
+    sincos(phi, &sf, &cf);
+    double cn[LMAXC + 1], sn[LMAXC + 1];
     double c0 = 1.0, c1 = ci, s0 = 0.0, s1 = si;
 #pragma unroll
     for (int q = 0; q <= LMAXC; ++q) {
@@ -542,9 +396,6 @@ __global__ void __launch_bounds__(BLK, MC <= 5 && NT <= 12 ? 3 : 2) k_wide(WideD
         s1 = s2;
       }
     }
-  }
-  double yr[MC], yi[MC];
-  {
     C2<double> ph;
     ph.x = 1.0;
     ph.y = 0.0;
@@ -573,57 +424,28 @@ __global__ void __launch_bounds__(BLK, MC <= 5 && NT <= 12 ? 3 : 2) k_wide(WideD
       }
     }
   }
-
-  double data = 0.0, quad = 0.0;
-  bool bad = false;
-  for (int k = 0; k < K; ++k) {
+  // detector k's arrival time, its coefficients into this lane's column
+  auto coefficients = [&](int k) {
     const double tk = tref - (D.rpos[k][0] * N[0] + D.rpos[k][1] * N[1] + D.rpos[k][2] * N[2]);
-    // composite coefficients of this detector -> this lane's LDS column
+    auto set = [&](int a, double re, double im) {
+      C[a * 64 + t].x = re;
+      C[a * 64 + t].y = im;
+    };
     if (rot) {
-      // F_k at the five hour angles g_j = 2 pi j / 5, then A_n by the exact
-      // five-point transform, then the phases e^{i n theta_k}
-      // (the frames at the five hour angles do not depend on k; they are
-      // rebuilt per detector rather than kept live across the loop, which
-      // would hold 120 registers)
-      double sdk = sd, cdk = cd, spk = sp, cpk = cp;
-      asm volatile("" : "+v"(sdk), "+v"(cdk), "+v"(spk), "+v"(cpk));
-      C2<double> Fg[5];
-#pragma unroll
-      for (int j = 0; j < 5; ++j) {
-        double Xj[3], Yj[3], Nj[3];
-        axes(kS5[j], kC5[j], sdk, cdk, spk, cpk, Xj, Yj, Nj);
-        Fg[j] = response6(D.dten[k], Xj, Yj);
-      }
       // e^{i theta_k} = e^{i g(t_ref)} e^{i Omega (t_k - t_ref)}
       double sdl, cdl;
       sincos_small(D.omega * (tk - tref), &sdl, &cdl);
-      const double e1c = cg * cdl - sg * sdl, e1s = sg * cdl + cg * sdl;
-      const double e2c = e1c * e1c - e1s * e1s, e2s = 2.0 * e1c * e1s;
+      double c0r[5], c0i[5];
+      rotation_terms(D.dten[k], sd, cd, 2.0 * sp * cp, cp * cp - sp * sp, cg * cdl - sg * sdl, sg * cdl + cg * sdl, c0r,
+                     c0i);
 #pragma unroll
-      for (int a = 0; a < 5; ++a) {
-        const int nn = a - 2;
-        double ar = 0.0, ai = 0.0;
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-          const int r = ((nn * j) % 5 + 5) % 5;
-          const double c = kC5[r], s = -kS5[r];  // e^{-i n g_j}
-          ar += Fg[j].x * c - Fg[j].y * s;
-          ai += Fg[j].x * s + Fg[j].y * c;
-        }
-        ar *= 0.2;
-        ai *= 0.2;
-        // e^{i n theta_k}
-        const double er = (nn == 0) ? 1.0 : (nn == 1 || nn == -1) ? e1c : e2c;
-        const double ei = (nn == 0) ? 0.0 : (nn == 1) ? e1s : (nn == -1) ? -e1s : (nn == 2) ? e2s : -e2s;
-        cre[a][t] = ar * er - ai * ei;
-        cim[a][t] = ar * ei + ai * er;
-      }
+      for (int a = 0; a < 5; ++a) set(a, c0r[a], c0i[a]);
       if (drift) {
         // first order in the delay drift (Path B, p = 1).  The drift's
         // harmonics in the modulation phase, -dt: m = -1, 0, +1 from
         // rho e^{i g(t_ref)}, rho = r_x + i r_y.  With the post-phases
         // folded in, C~_(1, n) = sum_m C~_(0, n - m) D_m e^{i m Omega (t_k - t_ref)}
-        // for n = -3 .. 3, the order-0 terms read back from this lane's column
+        // for n = -3 .. 3
         const double rer = D.rpos[k][0] * cg - D.rpos[k][1] * sg, rei = D.rpos[k][0] * sg + D.rpos[k][1] * cg;
         // D_m e^{i m Omega (t_k - t_ref)}, m = -1, 0, +1
         const double hr = 0.5 * cd * rer, hi = 0.5 * cd * rei;
@@ -631,28 +453,22 @@ __global__ void __launch_bounds__(BLK, MC <= 5 && NT <= 12 ? 3 : 2) k_wide(WideD
         const double dmi[3] = {hr * (-sdl) - hi * cdl, 0.0, hr * sdl + hi * cdl};
 #pragma unroll
         for (int b = 0; b < 7; ++b) {
-          const int nn = b - 3;
           double cr = 0.0, ci = 0.0;
 #pragma unroll
           for (int m = -1; m <= 1; ++m) {
-            const int q = nn - m;
+            const int q = b - 3 - m;
             if (q < -2 || q > 2) continue;
-            const double xr = cre[q + 2][t], xi = cim[q + 2][t];
-            cr += xr * dmr[m + 1] - xi * dmi[m + 1];
-            ci += xr * dmi[m + 1] + xi * dmr[m + 1];
+            cr += c0r[q + 2] * dmr[m + 1] - c0i[q + 2] * dmi[m + 1];
+            ci += c0r[q + 2] * dmi[m + 1] + c0i[q + 2] * dmr[m + 1];
           }
-          cre[5 + b][t] = cr;
-          cim[5 + b][t] = ci;
+          set(5 + b, cr, ci);
         }
-        if (NT >= 21 && n_a >= 21) {
+        if (n_a >= 21) {
           // order 2: the drift's square, (D~ * D~)_m for m = -2..2, and
           // C~_(2, n) = 1/2 sum_m C~_(0, n - m) (D~ * D~)_m for n = -4..4
           double d2r[5], d2i[5];
 #pragma unroll
-          for (int m = 0; m < 5; ++m) {
-            d2r[m] = 0.0;
-            d2i[m] = 0.0;
-          }
+          for (int m = 0; m < 5; ++m) d2r[m] = d2i[m] = 0.0;
 #pragma unroll
           for (int m1 = 0; m1 < 3; ++m1)
 #pragma unroll
@@ -662,18 +478,15 @@ __global__ void __launch_bounds__(BLK, MC <= 5 && NT <= 12 ? 3 : 2) k_wide(WideD
             }
 #pragma unroll
           for (int b = 0; b < 9; ++b) {
-            const int nn = b - 4;
             double cr = 0.0, ci = 0.0;
 #pragma unroll
             for (int m = -2; m <= 2; ++m) {
-              const int q = nn - m;
+              const int q = b - 4 - m;
               if (q < -2 || q > 2) continue;
-              const double xr = cre[q + 2][t], xi = cim[q + 2][t];
-              cr += xr * d2r[m + 2] - xi * d2i[m + 2];
-              ci += xr * d2i[m + 2] + xi * d2r[m + 2];
+              cr += c0r[q + 2] * d2r[m + 2] - c0i[q + 2] * d2i[m + 2];
+              ci += c0r[q + 2] * d2i[m + 2] + c0i[q + 2] * d2r[m + 2];
             }
-            cre[12 + b][t] = 0.5 * cr;
-            cim[12 + b][t] = 0.5 * ci;
+            set(12 + b, 0.5 * cr, 0.5 * ci);
           }
         }
       }
@@ -690,12 +503,19 @@ __global__ void __launch_bounds__(BLK, MC <= 5 && NT <= 12 ? 3 : 2) k_wide(WideD
       const double uy = N[0] * ay[0] + N[1] * ay[1] + N[2] * ay[2];
       double px = 1.0, py = 1.0;
       for (int a = 0; a < n_a; ++a) {
-        cre[a][t] = 0.5 * (px * exr - py * eyr);
-        cim[a][t] = 0.5 * (px * exi - py * eyi);
+        set(a, 0.5 * (px * exr - py * eyr), 0.5 * (px * exi - py * eyi));
         px *= ux;
         py *= uy;
       }
     }
+    return tk;
+  };
+
+  double data = 0.0;
+  bool bad = false;
+#pragma unroll 1
+  for (int k = 0; k < K; ++k) {
+    const double tk = coefficients(k);
     // four-point Lagrange stencil at t_k (taps outside the window read zero)
     double u = (tk - D.t0) * D.inv_dt;
     if (!(fabs(u) <= 1.0e300)) {
@@ -724,86 +544,184 @@ __global__ void __launch_bounds__(BLK, MC <= 5 && NT <= 12 ? 3 : 2) k_wide(WideD
       wr[r] = v;
     }
     // data term: Re sum_a conj(C~_a) sum_i conj(Y_i) Qhat_{a,i}
-    for (int a = 0; a < n_a; ++a) {
-      double zr = 0.0, zi = 0.0;
+    if constexpr (PACKED) {
+      const int lines = wide_lines(MB, n_a);
+      const RIFT_GLOBAL char* tab = (const RIFT_GLOBAL char*)as_global(D.Qrows) + (uint64_t)k * n_t * lines * 128u;
+      data += wide_data<MB>(tab, (uint32_t)jc * (uint32_t)(lines * 128), n_a, stage, wr, yr, yi, C);
+    } else {
+      for (int a = 0; a < n_a; ++a) {
+        double zr = 0.0, zi = 0.0;
 #pragma unroll
-      for (int j = 0; j < MC; ++j) {
-        if (j < M) {
-          const RIFT_GLOBAL double* q =
-              as_global(D.Q) + 2 * ((((int64_t)k * n_a + a) * M + D.perm[j]) * (int64_t)n_t + jc);
-          double qr = 0.0, qi = 0.0;
+        for (int j = 0; j < MC; ++j) {
+          if (j < M) {
+            const RIFT_GLOBAL double* q =
+                as_global(D.Q) + 2 * ((((int64_t)k * n_a + a) * M + D.perm[j]) * (int64_t)n_t + jc);
+            double qr = 0.0, qi = 0.0;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            qr += wr[r] * q[2 * r];
-            qi += wr[r] * q[2 * r + 1];
+            for (int r = 0; r < 4; ++r) {
+              qr += wr[r] * q[2 * r];
+              qi += wr[r] * q[2 * r + 1];
+            }
+            // conj(Y) Qhat
+            zr += yr[j] * qr + yi[j] * qi;
+            zi += yr[j] * qi - yi[j] * qr;
           }
-          // conj(Y) Qhat
-          zr += yr[j] * qr + yi[j] * qi;
-          zi += yr[j] * qi - yi[j] * qr;
         }
-      }
-      // Re[conj(C~_a) z]
-      data += cre[a][t] * zr + cim[a][t] * zi;
-    }
-    // model-norm term over pairs a <= a'
-    constexpr int BS = HL > 0 ? 4 * Cls<(HL > 0 ? HL : 2)>::B : MC * MC * 4;
-    const RIFT_CONST double* blk = as_const(D.UV) + (int64_t)k * D.npairs * BS;
-    for (int a = 0; a < n_a; ++a) {
-      for (int b = a; b < n_a; ++b, blk += BS) {
-        double g[4] = {0.0, 0.0, 0.0, 0.0};  // Re G, Im G, Re H, Im H
-        if constexpr (HL > 0) {
-          // the phase sequence is rebuilt per pair, not hoisted out of the
-          // loops (it would hold 4 HL values in registers throughout)
-          double cfo = cf, sfo = sf;
-          asm volatile("" : "+v"(cfo), "+v"(sfo));
-          HarmForms<HL>::run(opaque(blk), cn, sn, cfo, sfo, g);
-        }
-        else if constexpr (MC == 5)
-          PairFormsP<5>::run(opaque(blk), yr, yi, g);
-        else
-          PairForms<0, MC>::run(opaque(blk), M, yr, yi, g);
-        const double gr = g[0], gi = g[1], hr = g[2], hi = g[3];
-        const double car = cre[a][t], cai = cim[a][t], cbr = cre[b][t], cbi = cim[b][t];
-        // conj(C_a) C_b G_ab and C_a C_b H_ab, counted twice off the diagonal
-        const double pr = car * cbr + cai * cbi, pim = car * cbi - cai * cbr;
-        const double qr = car * cbr - cai * cbi, qim = car * cbi + cai * cbr;
-        const double f = (a == b) ? 1.0 : 2.0;
-        quad += f * ((pr * gr - pim * gi) + (qr * hr - qim * hi));
+        // Re[conj(C~_a) z]
+        data += C[a * 64 + t].x * zr + C[a * 64 + t].y * zi;
       }
     }
   }
+
+  // the harmonics as the matrix tiles take them: sample 16 s + col, mode 4 mb + quad
+  double vr[4][MB], vi[4][MB];
+  {
+    RIFT_LDS double2* ex = (RIFT_LDS double2*)stage;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      wave_sync();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        ex[q * 64 + t].x = yr[4 * mb + q];
+        ex[q * 64 + t].y = yi[4 * mb + q];
+      }
+      wave_sync();
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        vr[s][mb] = ex[quad * 64 + 16 * s + col].x;
+        vi[s][mb] = ex[quad * 64 + 16 * s + col].y;
+      }
+    }
+  }
+  // model-norm term: per detector sum_t c_t^T (S c)_t, this lane's share of it
+  // the components (step, quad) of samples 16 s + col
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  const int steps = wide_steps(MB, n_a), tiles = wide_tiles(MB, n_a);
+  typedef double R2 __attribute__((ext_vector_type(2)));
+  const RIFT_GLOBAL R2* A = (const RIFT_GLOBAL R2*)as_global(D.S) + t;
+  R2 nxt = A[0];
+#pragma unroll 1
+  for (int k = 0; k < K; ++k) {
+    if (K > 1) {
+      wave_sync();
+      (void)coefficients(k);
+    }
+    wave_sync();
+#pragma unroll 1
+    for (int tl = 0; tl < tiles; ++tl) {
+      D4 d[4];
+      double keep[4][4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        d[s] = D4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) keep[s][r] = 0.0;
+      }
+      const int b0 = 4 * tl;
+      int a = b0 / (2 * MB);
+#pragma unroll 1
+      for (int b = a * 2 * MB; b < steps; ++a) {
+        double cr[4], ci[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          cr[s] = C[a * 64 + 16 * s + col].x;
+          ci[s] = C[a * 64 + 16 * s + col].y;
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb, b += 2) {
+          if (b < b0) continue;
+          const R2 cur = nxt;
+          A += 64;
+          nxt = A[0];  // one pair past the end is padding
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const double xr = cr[s] * vr[s][mb] - ci[s] * vi[s][mb], xi = cr[s] * vi[s][mb] + ci[s] * vr[s][mb];
+            d[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.x, xr, d[s], 0, 0, 0);
+            d[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.y, xi, d[s], 0, 0, 0);
+            if (b == b0) {
+              keep[s][0] = xr;
+              keep[s][1] = xi;
+            } else if (b == b0 + 2) {
+              keep[s][2] = xr;
+              keep[s][3] = xi;
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[s] = fma(d[s][r], keep[s][r], acc[s]);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    acc[s] += __shfl_xor(acc[s], 16);
+    acc[s] += __shfl_xor(acc[s], 32);
+  }
+  // sample t = 16 quad + col
+  const double quadratic = quad == 0 ? acc[0] : (quad == 1 ? acc[1] : (quad == 2 ? acc[2] : acc[3]));
   const double x = D.d_ref / dist;
-  double l = x * data - 0.25 * x * x * quad;
+  double l = x * data - 0.25 * x * x * quadratic;
   if (bad) l = __builtin_nan("");
   if (live && lnL) as_global_w(lnL)[i] = l;
   if (part) {
-    MS acc;
-    acc.m = -__builtin_inf();
-    acc.s = 0.0;
-    if (live) acc = ms_push(acc, l + (lnw ? as_global(lnw)[i] : 0.0));
-    const MS r = ms_block(acc, sh);
+    MS m;
+    m.m = -__builtin_inf();
+    m.s = 0.0;
+    if (live) m = ms_push(m, l + (lnw ? as_global(lnw)[i] : 0.0));
+    const MS r = ms_block(m, sh);
     if (t == 0) {
-      part[2 * blockIdx.x] = r.m;
-      part[2 * blockIdx.x + 1] = r.s;
+      part[2 * (int64_t)blockIdx.x] = r.m;
+      part[2 * (int64_t)blockIdx.x + 1] = r.s;
     }
+  }
+}
+
+template <int MB>
+void launch_wide(const WideDesc& D, bool packed, const double* U, const double* V, double* form, double* rows,
+                 const double* theta, int64_t n, const double* lnw, double* lnL, double* part, hipStream_t st) {
+  const int64_t total = (int64_t)D.K * wide_pairs(wide_steps(MB, D.n_a), wide_tiles(MB, D.n_a)) * 128;
+  hipLaunchKernelGGL(k_wide_form<MB>, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 4096)), dim3(256), 0, st, D,
+                     U, V, form);
+  const dim3 grid((unsigned)((n + 63) / 64)), block(64);
+  const size_t lds = wide_stage_bytes(packed) + (size_t)D.n_a * 64 * 16;
+  if (packed) {
+    const int lines = wide_lines(MB, D.n_a);
+    hipLaunchKernelGGL(k_wide_rows, dim3((unsigned)((D.n_t + WIDE_QT - 1) / WIDE_QT), (unsigned)D.K,
+                                         (unsigned)std::min(lines, 4)),
+                       dim3(256), 0, st, D, wide_slots(MB), lines, rows);
+    hipLaunchKernelGGL((k_wide<MB, true>), grid, block, lds, st, D, theta, n, lnw, lnL, part);
+  } else {
+    hipLaunchKernelGGL((k_wide<MB, false>), grid, block, lds, st, D, theta, n, lnw, lnL, part);
   }
 }
 
 // ln Z and n_eff from the blocks' (max, sum) pairs, one block, fixed order.
 __global__ void k_wide_merge(double lnN, const double* __restrict__ part, int nb, double* __restrict__ lnZ,
                              double* __restrict__ neff) {
-  __shared__ MS sh[WIDE_BLOCK / 64];
-  MS acc;
-  acc.m = -__builtin_inf();
-  acc.s = 0.0;
+  // the blocks' maximum first, then sums whose exponentials are independent
+  __shared__ double sm[WIDE_MERGE / 64];
+  double m = -__builtin_inf();
+  for (int b = threadIdx.x; b < nb; b += blockDim.x) m = fmax(m, part[2 * b]);
+  m = dmax_wave(m);
+  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = sm[0];
+  for (int w = 1; w < WIDE_MERGE / 64; ++w) m = fmax(m, sm[w]);
+  __syncthreads();
+  double s = 0.0;
   for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-    MS o;
-    o.m = part[2 * b];
-    o.s = part[2 * b + 1];
-    if (o.s != o.s) acc.s = o.s;
-    else if (o.s != 0.0) acc = ms_combine(acc, o);
+    const double o = part[2 * b + 1];
+    s += o == 0.0 ? 0.0 : o * exp(part[2 * b] - m);  // a NaN sum stays NaN
   }
-  const MS r = ms_block(acc, sh);
+  s = dsum_wave(s);
+  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = s;
+  __syncthreads();
+  MS r;
+  r.m = m;
+  r.s = sm[0];
+  for (int w = 1; w < WIDE_MERGE / 64; ++w) r.s += sm[w];
   if (threadIdx.x == 0) {
     double z;
     if (r.s != r.s) z = __builtin_nan("");
@@ -868,8 +786,7 @@ int wide_run(const rift_ile_point_wide* pt, int64_t n, const double* theta, cons
       (neff && bad_ptr(neff)))
     return RIFT_EINVAL;
   if (!lnL && !lnZ) return RIFT_EINVAL;
-  const int blk = pt->n_terms <= 12 ? WIDE_BLOCK : WIDE_BLOCK_21;
-  const int64_t nb = (n + blk - 1) / blk;
+  const int64_t nb = (n + 63) / 64;
   if (nb > 0x7fffffff) return RIFT_EUNSUPPORTED;
   WideDesc D;
   memset(&D, 0, sizeof(D));
@@ -877,7 +794,6 @@ int wide_run(const rift_ile_point_wide* pt, int64_t n, const double* theta, cons
   D.M = pt->n_modes;
   D.n_t = pt->n_t;
   D.n_a = pt->n_terms;
-  D.npairs = pt->n_terms * (pt->n_terms + 1) / 2;
   D.response = pt->response;
   D.t0 = pt->t0;
   D.inv_dt = 1.0 / pt->dt;
@@ -904,72 +820,44 @@ int wide_run(const rift_ile_point_wide* pt, int64_t n, const double* theta, cons
     ylm_fourier(l, m, D.ycoef[i]);
   }
   D.Q = pt->Q;
-  const int MC = pt->n_modes <= 5 ? 5 : (pt->n_modes <= 12 ? 12 : 25);
-  // the harmonic form where its basis is shorter than a block's entries
-  int lmax = 0;
-  for (int i = 0; i < pt->n_modes; ++i) lmax = std::max(lmax, (int)pt->lm[2 * i]);
-  const int M2 = pt->n_modes * pt->n_modes;
-  D.hb = (MC == 12 && lmax == 3 && Cls<3>::B < M2) ? 3 : (MC == 25 && lmax == 4 && Cls<4>::B < M2) ? 4 : 0;
-  const int blk_vals = D.hb == 3 ? 4 * Cls<3>::B : D.hb == 4 ? 4 * Cls<4>::B : 4 * MC * MC;
-  // stream-ordered scratch: the packed U/V blocks (or their coefficients),
-  // then the blocks' (max, sum) pairs
-  const size_t uv_bytes = sizeof(double) * (size_t)D.K * D.npairs * blk_vals;
+  const int MB = (pt->n_modes + 3) / 4;
+  // Reading Q by rows: repacking costs a pass over the table (10 us at 20
+  // composite entries, 25 us at 105); the stencils lane by lane cost about
+  // 0.4 ns per sample and 20 entries more than the rows.  The lines meet near
+  // this many samples at every width.
+  const size_t row_bytes = 128 * (size_t)wide_lines(MB, D.n_a);
+  const bool packed = n >= WIDE_PACK_MIN && (uint64_t)D.n_t * row_bytes <= 0xffffffffu;
+  // stream-ordered scratch: the repacked rows, the real form's operands (and
+  // one pair of steps that is fetched past the end), the blocks' (max, sum) pairs
+  const size_t q_bytes = packed ? (size_t)D.K * D.n_t * row_bytes : 0;
+  const int steps = wide_steps(MB, D.n_a);
+  const size_t form_bytes = sizeof(double) * 128 * (size_t)(D.K * wide_pairs(steps, wide_tiles(MB, D.n_a)) + 1);
   const size_t part_bytes = lnZ ? sizeof(double) * 2 * (size_t)nb : 0;
   hipStream_t st = (hipStream_t)stream;
-  void* scratch = nullptr;
-  if (hipMallocAsync(&scratch, uv_bytes + part_bytes, st) != hipSuccess) return RIFT_ENOMEM;
-  D.UV = (const double*)scratch;
-  double* d_part = lnZ ? (double*)((char*)scratch + uv_bytes) : nullptr;
-  const int64_t pe = (int64_t)D.K * D.npairs * MC * MC;
-  const unsigned pgrid = (unsigned)std::min<int64_t>((pe + 255) / 256, 1024);
-  const bool wide21 = blk == WIDE_BLOCK_21;
-  const dim3 grid((unsigned)nb), block(blk);
-  switch (MC) {
-    case 5:
-      hipLaunchKernelGGL(k_wide_pack<5>, dim3(pgrid), dim3(256), 0, st, D, pt->U, pt->V, (double*)scratch);
-      if (wide21)
-        hipLaunchKernelGGL((k_wide<5, 21, WIDE_BLOCK_21>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
-      else
-        hipLaunchKernelGGL((k_wide<5, 12, WIDE_BLOCK>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
-      break;
-    case 12:
-      if (D.hb == 3) {
-        hipLaunchKernelGGL(k_wide_basis<3>, dim3((unsigned)(D.K * D.npairs)), dim3(WIDE_BASIS_BLOCK), 0, st, D,
-                           pt->U, pt->V, (double*)scratch);
-        if (wide21)
-          hipLaunchKernelGGL((k_wide<12, 21, WIDE_BLOCK_21, 3>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
-        else
-          hipLaunchKernelGGL((k_wide<12, 12, WIDE_BLOCK, 3>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
-        break;
-      }
-      hipLaunchKernelGGL(k_wide_pack<12>, dim3(pgrid), dim3(256), 0, st, D, pt->U, pt->V, (double*)scratch);
-      if (wide21)
-        hipLaunchKernelGGL((k_wide<12, 21, WIDE_BLOCK_21>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
-      else
-        hipLaunchKernelGGL((k_wide<12, 12, WIDE_BLOCK>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
-      break;
-    default:
-      if (D.hb == 4) {
-        hipLaunchKernelGGL(k_wide_basis<4>, dim3((unsigned)(D.K * D.npairs)), dim3(WIDE_BASIS_BLOCK), 0, st, D,
-                           pt->U, pt->V, (double*)scratch);
-        if (wide21)
-          hipLaunchKernelGGL((k_wide<21, 21, WIDE_BLOCK_21, 4>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
-        else
-          hipLaunchKernelGGL((k_wide<21, 12, WIDE_BLOCK, 4>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
-        break;
-      }
-      hipLaunchKernelGGL(k_wide_pack<25>, dim3(pgrid), dim3(256), 0, st, D, pt->U, pt->V, (double*)scratch);
-      if (wide21)
-        hipLaunchKernelGGL((k_wide<25, 21, WIDE_BLOCK_21>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
-      else
-        hipLaunchKernelGGL((k_wide<25, 12, WIDE_BLOCK>), grid, block, 0, st, D, theta, n, lnw, lnL, d_part);
+  char* space = nullptr;
+  if (hipMallocAsync((void**)&space, q_bytes + form_bytes + part_bytes, st) != hipSuccess) return RIFT_ENOMEM;
+  double* form = (double*)(space + q_bytes);
+  double* d_part = lnZ ? (double*)(space + q_bytes + form_bytes) : nullptr;
+  D.Qrows = (const double*)space;
+  D.S = form;
+#define RIFT_WIDE(B) \
+  case B: launch_wide<B>(D, packed, pt->U, pt->V, form, (double*)space, theta, n, lnw, lnL, d_part, st); break;
+  switch (MB) {
+    RIFT_WIDE(1)
+    RIFT_WIDE(2)
+    RIFT_WIDE(3)
+    RIFT_WIDE(4)
+    RIFT_WIDE(5)
+    RIFT_WIDE(6)
+    RIFT_WIDE(7)
   }
+#undef RIFT_WIDE
   if (lnZ)
-    hipLaunchKernelGGL(k_wide_merge, dim3(1), dim3(WIDE_BLOCK), 0, st, log((double)n), (const double*)d_part, (int)nb,
+    hipLaunchKernelGGL(k_wide_merge, dim3(1), dim3(WIDE_MERGE), 0, st, log((double)n), (const double*)d_part, (int)nb,
                        lnZ, neff);
   rc = hipGetLastError() == hipSuccess ? RIFT_OK : RIFT_EDEVICE;
   // released in stream order, after the kernels above
-  if (hipFreeAsync(scratch, st) != hipSuccess && !rc) rc = RIFT_EDEVICE;
+  if (hipFreeAsync(space, st) != hipSuccess && !rc) rc = RIFT_EDEVICE;
   return rc;
 }
 

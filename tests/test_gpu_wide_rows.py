@@ -1,0 +1,64 @@
+"""The composite-index likelihood on the matrix cores, with the data term from
+the repacked rows (batches from 16384 samples on) and from the caller's series
+below, against the FP64 oracle: every count of mode blocks (1 to 25 modes in
+fours, full and with remainders), term counts that end inside a tile of the
+form, both readings of Q, windows shorter than a packing tile, times at and
+beyond the table's ends, non-finite ones, a last wavefront with one sample.
+Bar: the FP64 bar, 1e-9 S + 1e-12 with S the scale of the two cancelling terms."""
+import numpy as np
+import pytest
+
+from paper_2609_37393_amd import synth
+
+from .test_gpu_parity import _mode_set
+from .test_gpu_wide import wide_scale
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(oracle_mod, pt, th, idx):
+    from paper_2609_37393_amd import ile
+
+    z, ne, ll = ile.wide_lnZ(pt, th, want_lnL=True)
+    got, sub = ll.cpu().numpy()[idx], th[:, idx]
+    want = oracle_mod.lnL_wide(pt, sub)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    ok = np.isfinite(want)
+    S = wide_scale(oracle_mod, pt, sub[:, ok])
+    assert np.all(np.abs(got[ok] - want[ok]) <= 1e-9 * S + 1e-12)
+    return z, ne, ll
+
+
+@pytest.mark.parametrize("response,K,M,n_a,n_t", [
+    ("rotation", 3, 4, 5, 2000), ("rotation", 1, 1, 5, 70), ("rotation", 2, 2, 5, 65), ("rotation", 5, 3, 5, 1000),
+    ("rotation", 3, 5, 5, 64), ("arms", 3, 4, 4, 900), ("arms", 2, 2, 3, 500), ("arms", 8, 5, 1, 300),
+    ("arms", 2, 1, 2, 63), ("arms", 3, 4, 5, 300), ("arms", 3, 4, 6, 400), ("rotation_delay", 2, 2, 12, 400),
+    ("rotation_delay", 2, 5, 21, 400), ("rotation_delay", 3, 3, 5, 700), ("rotation", 3, 8, 5, 600),
+    ("rotation", 3, 9, 5, 600), ("rotation", 2, 16, 5, 400), ("rotation", 2, 17, 5, 300), ("rotation", 3, 21, 5, 400),
+    ("arms", 2, 13, 3, 300), ("arms", 1, 25, 2, 200), ("arms", 2, 6, 7, 200), ("rotation_delay", 1, 11, 21, 200)])
+@pytest.mark.parametrize("n", [16383, 16385])
+def test_rows(oracle_mod, response, K, M, n_a, n_t, n):
+    lm = None if M <= 21 else _mode_set(M, 6)
+    pt = synth.make_point_wide(K, M, n_a, n_t, 32768.0, 120.0, 30 + M + n_a, response=response, omega=40.0, lm=lm)
+    th = synth.prior_samples(n, M)
+    end = 0.5 * n_t / 32768.0
+    th[5, :14] = [-end, end, -end - 3e-5, end + 3e-5, 0.03, -0.03, 1.0, -1.0, 50.0, -50.0, np.nan, np.inf, end - 5e-5,
+                  -end + 5e-5]
+    th[:, n - 14:] = th[:, :14]
+    few = 100 if M * n_a <= 60 else 40
+    _check(oracle_mod, pt, th, np.r_[0:few, n - few:n])
+
+
+def test_rows_reduce(oracle_mod):
+    """ln Z and n_eff of a large batch, with weights that leave samples out."""
+    from paper_2609_37393_amd import ile
+
+    pt = synth.make_point_wide(3, 4, 5, 2000, 32768.0, 30.0, 41)
+    th = synth.prior_samples(40_001, 42)
+    lnw = np.random.default_rng(1).normal(size=th.shape[1])
+    lnw[::7] = -np.inf
+    z, ne, ll = ile.wide_lnZ(pt, th, lnw=lnw, want_lnL=True)
+    z_or, ne_or = oracle_mod.lnZ(ll.cpu().numpy(), lnw)
+    assert abs(z.item() - z_or) <= 1e-9 * max(1.0, abs(z_or)) and abs(ne.item() - ne_or) <= 1e-9 * ne_or
+    none = ile.wide_lnZ(pt, th, lnw=np.full(th.shape[1], -np.inf))
+    assert none[0].item() == -np.inf and none[1].item() == 0.0
