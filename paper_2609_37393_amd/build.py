@@ -24,7 +24,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("RIFT_ILE_ARCH", "gfx950")
 KT_CLASSES = (2, 3, 5, 8)
 KINDS = (0, 1, 2, 3, 4, 5, 6, 7, 8, 9)  # FP64 tiles, FP32 tiles, FP64 refine, gradient, distance / time / psi
-#                                         marginals, data passes of the band-limited time rule and of ERAI,
+#                                         marginals, data passes of the band-limited time rule and of ERAI (kind 6: of the psi rules),
 #                                         coefficients of the contracted series
 
 FLAGS = [
@@ -47,6 +47,7 @@ def _objects():
             (os.path.join(CSRC, "wide.hip"), os.path.join(OBJDIR, "wide.o"), []),
             (os.path.join(CSRC, "sampler.hip"), os.path.join(OBJDIR, "sampler.o"), []),
             (os.path.join(CSRC, "series.hip"), os.path.join(OBJDIR, "series.o"), []),
+            (os.path.join(CSRC, "angles.hip"), os.path.join(OBJDIR, "angles.o"), []),
             (os.path.join(CSRC, "pregrid.hip"), os.path.join(OBJDIR, "pregrid.o"), []),
             (os.path.join(CSRC, "importance.hip"), os.path.join(OBJDIR, "importance.o"), [])]
     for kt in KT_CLASSES:

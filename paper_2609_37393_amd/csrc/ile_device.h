@@ -978,237 +978,22 @@ __device__ __forceinline__ double eval_tkappa_with(PDesc P, R* __restrict__ trig
   return bad ? __builtin_nan("") : base;
 }
 
-// The rule over polarisation (Sec. "Angles: finite harmonic content"): at
-// fixed other parameters lnL is q(u) = a + Re(c1 e^{iu}) + Re(c2 e^{2iu}) in
-// u = 2 (psi' - psi) (Eq. (ap:psiexp)); with psi uniform on [0, pi),
-// L_psi = (1 / 2 pi) int_0^{2 pi} e^{q(u)} du by
-//   method 0: the periodic trapezoid rule on n points (the product grid),
-//   method 1: Laplace's method at the dominant maximum u* (Eq. (ap:psilaplace)),
-//             L_psi = e^{q(u*)} sqrt(2 pi / A) / (2 pi), A = -q''(u*), where
-//             A >= 100 (relative error O(1/A) below ~1e-3); a q without
-//             such a maximum (weak signal, or two peaks merging) is
-//             integrated by the periodic trapezoid rule on 256 points.
-constexpr double PSI_LAPLACE_MIN_A = 100.0;
-constexpr int PSI_FALLBACK_POINTS = 256;
-struct PsiRule {
-  int32_t method;
-  int32_t n;
-  double ln_n;
-};
-
-// q(u) and its first two derivatives.
-__device__ __forceinline__ void psi_q(double a, double c1r, double c1i, double c2r, double c2i, double su, double cu,
-                                      double* q, double* d1, double* d2) {
-  const double s2 = 2.0 * su * cu, c2 = cu * cu - su * su;
-  const double r1 = c1r * cu - c1i * su, i1 = c1r * su + c1i * cu;  // c1 e^{iu}
-  const double r2 = c2r * c2 - c2i * s2, i2 = c2r * s2 + c2i * c2;  // c2 e^{2iu}
-  *q = a + r1 + r2;
-  *d1 = -i1 - 2.0 * i2;
-  *d2 = -r1 - 4.0 * r2;
-}
-
-// The periodic trapezoid rule for q on n points: ln[(1/n) sum_j e^{q(2 pi j/n)}].
-__device__ __forceinline__ double psi_trapezoid(int n, double ln_n, double a, double c1r, double c1i, double c2r,
-                                                double c2i) {
-  double q, d1, d2;
-  double m = -__builtin_inf(), sum = 0.0;
-  for (int j = 0; j < n; ++j) {
-    double su, cu;
-    sincospi(2.0 * (double)j / (double)n, &su, &cu);
-    psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
-    if (q > m) {
-      sum = (sum == 0.0) ? 1.0 : fma(sum, exp(m - q), 1.0);
-      m = q;
-    } else {
-      sum += exp(q - m);
-    }
-  }
-  return m + log(sum) - ln_n;
-}
-
-// The cell partition of Eq. (ap:psicells).  With z = e^{iu}, 2 i z^2 q'(u) = 0
-// is the quartic 2 c2 z^4 + c1 z^3 - conj(c1) z - 2 conj(c2) = 0 (exact leading
-// zeros stripped); its roots, by the Aberth-Ehrlich iteration, that lie within
-// 1e-3 of the unit circle are polished by Newton's method on q'(u) and kept
-// if they settle on a zero of q'.  The sorted stationary angles cut the
-// circle into cells on which q is monotone; each cell is integrated by
-// 8-point Gauss-Legendre on sub-intervals of 2 sigma out to 8 sigma from its
-// higher end, then of doubling length to its far end, sigma =
-// min(A^{-1/2}, width / 8) from the curvature A = -q'' at that end.
-struct Cx {
-  double x, y;
-};
-__device__ __forceinline__ Cx cx_mul(Cx a, Cx b) { return Cx{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
-__device__ __forceinline__ Cx cx_add(Cx a, Cx b) { return Cx{a.x + b.x, a.y + b.y}; }
-__device__ __forceinline__ Cx cx_sub(Cx a, Cx b) { return Cx{a.x - b.x, a.y - b.y}; }
-__device__ __forceinline__ Cx cx_div(Cx a, Cx b) {
-  const double d = b.x * b.x + b.y * b.y;
-  return Cx{(a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d};
-}
-
-constexpr double PSI_GL8_X[8] = {-0.96028985649753623168, -0.79666647741362673959, -0.52553240991632898582,
-                                 -0.18343464249564980494, 0.18343464249564980494,  0.52553240991632898582,
-                                 0.79666647741362673959,  0.96028985649753623168};
-// ln of the 8-point Gauss-Legendre weights
-constexpr double PSI_GL8_LNW[8] = {-2.29037458272350180621, -1.50336299698040232187, -1.15929697855282975993,
-                                   -1.01422394453275765969, -1.01422394453275765969, -1.15929697855282975993,
-                                   -1.50336299698040232187, -2.29037458272350180621};
-
-__device__ __forceinline__ int psi_stationary(double c1r, double c1i, double c2r, double c2i, double* st) {
-  // coefficients, highest degree first: 2 c2, c1, 0, -conj(c1), -2 conj(c2)
-  Cx co[5] = {Cx{2.0 * c2r, 2.0 * c2i}, Cx{c1r, c1i}, Cx{0.0, 0.0}, Cx{-c1r, c1i}, Cx{-2.0 * c2r, 2.0 * c2i}};
-  int lead = 0;
-  while (lead < 4 && co[lead].x == 0.0 && co[lead].y == 0.0) ++lead;
-  const int D = 4 - lead;  // degree after stripping exact leading zeros
-  if (D < 1) return 0;
-  Cx z[4];
-  for (int k = 0; k < D; ++k) {
-    double sk, ck;
-    sincos(1.5707963267948966 * k + 0.4, &sk, &ck);
-    z[k] = Cx{ck, sk};
-  }
-  for (int it = 0; it < 60; ++it) {
-    double moved = 0.0;
-    for (int k = 0; k < D; ++k) {
-      Cx p = co[lead], dp = Cx{0.0, 0.0};
-      for (int j = lead + 1; j <= 4; ++j) {
-        dp = cx_add(cx_mul(dp, z[k]), p);
-        p = cx_add(cx_mul(p, z[k]), co[j]);
-      }
-      if (p.x == 0.0 && p.y == 0.0) continue;
-      const Cx ratio = cx_div(p, dp);
-      Cx sum{0.0, 0.0};
-      for (int j = 0; j < D; ++j)
-        if (j != k) sum = cx_add(sum, cx_div(Cx{1.0, 0.0}, cx_sub(z[k], z[j])));
-      const Cx w = cx_div(ratio, cx_sub(Cx{1.0, 0.0}, cx_mul(ratio, sum)));
-      z[k] = cx_sub(z[k], w);
-      moved = fmax(moved, fabs(w.x) + fabs(w.y));
-    }
-    if (!(moved > 1e-16)) break;
-  }
-  const double scale = sqrt(c1r * c1r + c1i * c1i) + 2.0 * sqrt(c2r * c2r + c2i * c2i);
-  int n = 0;
-  for (int k = 0; k < D; ++k) {
-    const double r = sqrt(z[k].x * z[k].x + z[k].y * z[k].y);
-    if (!(fabs(r - 1.0) <= 1e-3)) continue;
-    double u = atan2(z[k].y, z[k].x);
-    double q, d1, d2;
-    for (int it = 0; it < 30; ++it) {
-      double su, cu;
-      sincos(u, &su, &cu);
-      psi_q(0.0, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
-      if (d2 == 0.0) break;
-      const double step = d1 / d2;
-      u -= step;
-      if (fabs(step) < 1e-15) break;
-    }
-    double su, cu;
-    sincos(u, &su, &cu);
-    psi_q(0.0, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
-    if (!(fabs(d1) <= 1e-9 * fmax(scale, 1e-300))) continue;
-    u = fmod(u, 6.283185307179586477);
-    if (u < 0.0) u += 6.283185307179586477;
-    st[n++] = u;
-  }
-  // sort, and drop repeats (two roots settling on one point)
-  for (int a = 1; a < n; ++a)
-    for (int b = a; b > 0 && st[b] < st[b - 1]; --b) {
-      const double t = st[b];
-      st[b] = st[b - 1];
-      st[b - 1] = t;
-    }
-  int m = 0;
-  for (int a = 0; a < n; ++a)
-    if (m == 0 || st[a] - st[m - 1] > 1e-12) st[m++] = st[a];
-  return m;
-}
-
-__device__ __forceinline__ double psi_cells(double a, double c1r, double c1i, double c2r, double c2i) {
-  double st[4];
-  const int ns = psi_stationary(c1r, c1i, c2r, c2i, st);
-  const int nc = ns < 2 ? 1 : ns;
-  double m = -__builtin_inf(), sum = 0.0;
-  for (int c = 0; c < nc; ++c) {
-    const double lo = ns < 2 ? 0.0 : st[c];
-    const double hi = ns < 2 ? 6.283185307179586477 : (c + 1 < ns ? st[c + 1] : st[0] + 6.283185307179586477);
-    const double width = hi - lo;
-    double ql, qh, d1, d2l, d2h, s, cc;
-    sincos(lo, &s, &cc);
-    psi_q(a, c1r, c1i, c2r, c2i, s, cc, &ql, &d1, &d2l);
-    sincos(hi, &s, &cc);
-    psi_q(a, c1r, c1i, c2r, c2i, s, cc, &qh, &d1, &d2h);
-    const bool top_lo = ql >= qh;
-    const double A = -(top_lo ? d2l : d2h);
-    const double sigma = A > 0.0 ? fmin(1.0 / sqrt(A), width / 8.0) : width / 8.0;
-    double d0 = 0.0;
-    for (int j = 1; d0 < width; ++j) {
-      const double d1e = fmin(width, j <= 4 ? 2.0 * sigma * j : 2.0 * d0);
-      const double h = d1e - d0;
-      const double lnh = log(0.5 * h);
-      for (int g = 0; g < 8; ++g) {
-        const double dist = d0 + 0.5 * h + 0.5 * h * PSI_GL8_X[g];
-        const double u = top_lo ? lo + dist : hi - dist;
-        double su, cu, q, dd1, dd2;
-        sincos(u, &su, &cu);
-        psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &dd1, &dd2);
-        const double l = q + lnh + PSI_GL8_LNW[g];
-        const double dl = l - m;
-        const double e = exp(-fabs(dl));
-        const bool up = dl > 0.0;
-        sum = up ? fma(sum, e, 1.0) : sum + e;
-        m = up ? l : m;
-      }
-      d0 = d1e;
-    }
-  }
-  return m + log(sum) - 1.8378770664093454836;  // ln(2 pi)
-}
-
-// ln L_psi from the coefficients of q (see PsiRule).  Laplace: the best of 32
-// equally spaced points, then Newton steps on q' = 0 (the maximum is then the
-// dominant one unless another lies within the grid's resolution of it).
-__device__ __forceinline__ double psi_marginal(const PsiRule& G, double a, double c1r, double c1i, double c2r,
-                                               double c2i) {
-  double q, d1, d2;
-  if (G.method == 0) return psi_trapezoid(G.n, G.ln_n, a, c1r, c1i, c2r, c2i);
-  if (G.method == 2) return psi_cells(a, c1r, c1i, c2r, c2i);
-  double best = -__builtin_inf(), ub = 0.0;
-  for (int j = 0; j < 32; ++j) {
-    double su, cu;
-    sincospi((double)j / 16.0, &su, &cu);
-    psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
-    if (q > best) {
-      best = q;
-      ub = 3.14159265358979323846 * (double)j / 16.0;
-    }
-  }
-  double u = ub;
-  for (int it = 0; it < 8; ++it) {
-    double su, cu;
-    sincos(u, &su, &cu);
-    psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
-    if (!(d2 < 0.0)) break;
-    u -= d1 / d2;
-  }
-  double su, cu;
-  sincos(u, &su, &cu);
-  psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
-  const double A = -d2;
-  if (!(A >= PSI_LAPLACE_MIN_A))
-    return psi_trapezoid(PSI_FALLBACK_POINTS, 5.5451774444795623, a, c1r, c1i, c2r, c2i);  // ln 256
-  return q - 0.5 * log(2.0 * 3.14159265358979323846 * A);
-}
-
-// ln of the likelihood marginalised over polarisation, per sample: the data
-// term as the complex W = sum_k conj(F_k) Z_k (one gather), the model-norm
-// term as A0 = sum_k |F_k|^2 a_k / 4 and B = sum_k F_k^2 b_k / 4 (one
-// contraction), then, with F_k(psi + u/2) = e^{-iu} F_k(psi),
+// The data pass of the polarisation marginal: at fixed other parameters lnL is
+//   q(u) = a + Re(c1 e^{iu}) + Re(c2 e^{2iu}),  u = 2 (psi' - psi)
+// (Eq. (ap:psiexp)).  With the data term as the complex W = sum_k conj(F_k) Z_k
+// (one gather), the model-norm term as A0 = sum_k |F_k|^2 a_k / 4 and
+// B = sum_k F_k^2 b_k / 4 (one contraction), and F_k(psi + u/2) = e^{-iu} F_k(psi),
 //   q(u) = x Re(e^{iu} W) - x^2 [A0 + Re(e^{-2iu} B)]:
-//   a = -x^2 A0, c1 = x W, c2 = -x^2 conj(B).
+//   a = -x^2 A0, c1 = x W, c2 = -x^2 conj(B),
+// into out rows (a, Re c1, Im c1, Re c2, Im c2) of stride N (when `live`).
+// Returns whether the sample is poisoned.  The rules over u run in a kernel of
+// their own over these five values.
+constexpr int PSI_ROWS = 5;
 template <class R, int KT, int L, class DataFn>
-__device__ __forceinline__ double eval_pmarg_with(PDesc P, R* __restrict__ trig, int ts, double ra, double dec,
-                                                  double psi, double incl, double phi, double tref, double dist,
-                                                  const PsiRule& G, DataFn&& data_fn) {
+__device__ __forceinline__ bool eval_pmarg_with(PDesc P, R* __restrict__ trig, int ts, double ra, double dec,
+                                                double psi, double incl, double phi, double tref, double dist,
+                                                RIFT_GLOBAL double* out, int64_t N, int64_t i, bool live,
+                                                DataFn&& data_fn) {
   constexpr int NY = Cls<L>::NY;
   reduce_angles<R>(psi, incl, phi);
   Sky<R, KT> S;
@@ -1236,82 +1021,379 @@ __device__ __forceinline__ double eval_pmarg_with(PDesc P, R* __restrict__ trig,
     Bim += (double)(g2i * acc[3 * k + 1]) - (double)(g2r * acc[3 * k + 2]);
   }
   const double x = P->d_ref / dist;
-  if (S.bad || !(fabs(x) <= 1.0e300) || !(fabs(wre) <= 1.0e300) || !(fabs(wim) <= 1.0e300) ||
-      !(fabs(A0) <= 1.0e300) || !(fabs(Bre) + fabs(Bim) <= 1.0e300))
-    return __builtin_nan("");
   const double x2 = x * x;
-  return psi_marginal(G, -x2 * A0, x * wre, x * wim, -x2 * Bre, x2 * Bim);
+  if (live) {
+    out[i] = -x2 * A0;
+    out[N + i] = x * wre;
+    out[2 * N + i] = x * wim;
+    out[3 * N + i] = -x2 * Bre;
+    out[4 * N + i] = x2 * Bim;
+  }
+  return S.bad || !(fabs(x) <= 1.0e300) || !(fabs(wre) <= 1.0e300) || !(fabs(wim) <= 1.0e300) ||
+         !(fabs(A0) <= 1.0e300) || !(fabs(Bre) + fabs(Bim) <= 1.0e300);
 }
 
 // The data pass of the joint phiref / psi marginal by exact reconstruction
 // (ERAI, Eqs. (ap:angleharm), (ap:nyquist)).  At fixed sky, inclination,
-// time and distance, lnL in the offsets (alpha, u = 2 (psi' - psi)) is
+// time and distance, lnL in the offsets (alpha of phiref, u = 2 (psi' - psi)) is
 //   q(alpha, u) = a(alpha) + Re(c1(alpha) e^{iu}) + Re(c2(alpha) e^{2iu}),
-// c1 = x W (the complex data term, degree m_max in alpha), a = -x^2 A0 and
-// c2 = -x^2 conj(B) (the model norm, degree 2 m_max), as in the polarisation
-// marginal.  This pass samples c1 at the G.nd = 2 m_max + 1 angles
-// phi + 2 pi j / nd (one gather each, the same stencils) and (a, c2) at the
-// G.nq = 4 m_max + 1 angles phi + 2 pi j / nq (one contraction each), which
-// determine them exactly, into out rows [2 j], [2 j + 1] (c1) and
-// [2 nd + 3 j + 0 .. 2] (a, c2) of stride N (when `live`).  Returns whether
-// the sample is poisoned.  The whole wavefront calls this together.
+// c1 = x W (the complex data term), a = -x^2 A0 and c2 = -x^2 conj(B) (the model
+// norm), as in the polarisation marginal.  In alpha, c1 is a trigonometric
+// polynomial of degree m_max and a, c2 of degree 2 m_max, and their
+// coefficients come out of one evaluation:
+//   W(alpha) = sum_m T_m e^{-i m alpha}, T_m = e^{-i m phi} sum_k conj(F_k) sum_{i: m_i = m} d_i Qhat_{k,i},
+// the sums of one gather kept apart by m, and the model norm's basis rows kept
+// apart by q.  (Sampling q at 2 m_max + 1 data-term and 4 m_max + 1 model-norm
+// phases took nine gathers and seventeen contractions at m_max = 4: 2.5 ms for
+// 1e6 samples at 3 detectors and 21 modes, now 0.7 ms.)
+//   out rows [2 j], [2 j + 1], j < nd = 2 m_max + 1: Re, Im c1 along 1, cos alpha,
+//   sin alpha, .., sin m_max alpha; rows [2 nd + 3 j + 0 .. 2], j < nq = 4 m_max + 1:
+//   a, Re c2, Im c2 along 1, cos alpha, .., sin 2 m_max alpha; stride N (when `live`).
+// Returns whether the sample is poisoned.  The whole wavefront calls this together.
 struct AngleRule {
   int32_t nd, nq;
-  double dd, dq;  // 2 pi / nd, 2 pi / nq
+};
+constexpr int ERAI_MAX_M = 4;
+
+// sum_k conj(F_k) sum_{i: m_i = m} d_i Qhat_{k,i} of detectors K0 .. K0+G-1,
+// added to T[m + ERAI_MAX_M]: data_group's reads and pipeline, with the running
+// sum of each detector folded into T where m changes (modes are sorted by m).
+template <int NY, int K0, int G>
+__device__ __forceinline__ void data_harmonics(PDesc P, const RIFT_GLOBAL char* Qb, uint64_t gstride, uint64_t kstride,
+                                               int M, int NGR, const uint32_t* boff, RIFT_LDS unsigned char* stage,
+                                               const double* sfr, const double* Fre, const double* Fim,
+                                               const double* cn, const double* sn, C2<double>* T) {
+  constexpr int W = QW64;
+  typedef double R2 __attribute__((ext_vector_type(2)));
+  double w[G][4];
+#pragma unroll
+  for (int g = 0; g < G; ++g) lagrange4(sfr[K0 + g], w[g]);
+  C2<double> Z[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) Z[g].x = Z[g].y = 0.0;
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int q = lane >> 3;
+  const uint32_t cx0 = (uint32_t)((lane & 7) ^ (q >> 1)) << 4;
+  const uint32_t cx1 = (uint32_t)((lane & 7) ^ (4 | (q >> 1))) << 4;
+  uint32_t offt[G][8];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) offt[g][t] = (uint32_t)__shfl((int)boff[K0 + g], 8 * t + q) + ((t & 1) ? cx1 : cx0);
+  const uint32_t rbase = (uint32_t)lane * 128u + ((uint32_t)((lane >> 1) & 7) << 4);
+  auto issue = [&](int p, int g, int b) {
+    const RIFT_GLOBAL char* ser = uniform_ptr(Qb + (uint64_t)(K0 + g) * kstride + (uint64_t)p * gstride);
+    RIFT_LDS unsigned char* dst = stage + b * STAGE_UNIT;
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      __builtin_amdgcn_global_load_lds((const RIFT_GLOBAL void*)(ser + offt[g][t]), (RIFT_LDS void*)(dst + t * 1024),
+                                       16, 0, 0);
+  };
+  auto fold = [&](int g, int m) {
+    const double tr = Fre[K0 + g] * Z[g].x + Fim[K0 + g] * Z[g].y;
+    const double ti = Fre[K0 + g] * Z[g].y - Fim[K0 + g] * Z[g].x;
+#pragma unroll
+    for (int j = 0; j < 2 * ERAI_MAX_M + 1; ++j) {
+      if (j == m + ERAI_MAX_M) {  // uniform
+        T[j].x += tr;
+        T[j].y += ti;
+      }
+    }
+    Z[g].x = Z[g].y = 0.0;
+  };
+  // a group's modes: d, and the m before each (a repeated slot past M adds zeros to the last m)
+  double d[W];
+  int before[W], mlast = P->m_min;
+  auto modes = [&](int p) {
+#pragma unroll
+    for (int s = 0; s < W; ++s) {
+      const int i = p * W + s < M ? p * W + s : M - 1;
+      before[s] = mlast;
+      mlast = uniform_i(P->m[i]);
+      d[s] = mode_d<double, NY>(P, i, cn, sn);
+    }
+  };
+  auto consume = [&](int b, int g) {
+    const RIFT_LDS unsigned char* src = stage + b * STAGE_UNIT;
+    C2<double> u[4][W];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const R2 v = *(const RIFT_LDS R2*)(src + (rbase ^ ((uint32_t)c << 4)));
+      u[c >> 1][c & 1].x = v.x;
+      u[c >> 1][c & 1].y = v.y;
+    }
+#pragma unroll
+    for (int s = 0; s < W; ++s) {
+      const int m = s + 1 < W ? before[s + 1] : mlast;
+      if (before[s] != m) fold(g, before[s]);
+      const double qx = fma(w[g][3], u[3][s].x, fma(w[g][2], u[2][s].x, fma(w[g][1], u[1][s].x, w[g][0] * u[0][s].x)));
+      const double qy = fma(w[g][3], u[3][s].y, fma(w[g][2], u[2][s].y, fma(w[g][1], u[1][s].y, w[g][0] * u[0][s].y)));
+      Z[g].x = fma(d[s], qx, Z[g].x);
+      Z[g].y = fma(d[s], qy, Z[g].y);
+    }
+    pin(Z[g].x);
+    pin(Z[g].y);
+  };
+  constexpr int UPI = (G % 2 == 0) ? G : 2 * G;
+  const int total = NGR * G;
+  issue(0, 0, 0);
+#pragma unroll 1
+  for (int p0 = 0; p0 < NGR; p0 += UPI / G) {
+#pragma unroll
+    for (int v = 0; v < UPI; ++v) {
+      const int p = p0 + v / G;
+      const int g = v % G;
+      if (g == 0 && p >= NGR) break;
+      if (p * G + g + 1 < total) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        issue(g + 1 == G ? p + 1 : p, (g + 1) % G, (v + 1) & 1);
+        if (g == 0) modes(p);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      } else {
+        if (g == 0) modes(p);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      consume(v & 1, g);
+    }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int g = 0; g < G; ++g) fold(g, mlast);
+}
+
+// The model norm's harmonics in alpha: for every q, the basis rows' sums over
+// the degrees in incl along cos(q phi) and sin(q phi) for all 3 KT columns,
+// combined with the detectors' F and turned by q phi.  The coefficients
+// stream as in Contract; `emit(q, s, A, Br, Bi)` takes the parts along
+// cos q alpha (s = 0) and sin q alpha (s = 1) of A0, Re B and Im B.
+template <int KT, int L>
+struct NormHarmonics {
+  static constexpr int NI = 2 * L, W = 3 * KT, B = Cls<L>::B;
+  static constexpr int NC = B * W, CH = 16, NCH = (NC + CH - 1) / CH;
+  struct State {
+    double ct[NI + 1], st[NI + 1];  // cos(n incl), sin(n incl)
+    double pc[W], ps[W];            // the sums of the current q
+    double ex, ey;                  // e^{i q phi}
+  };
+  template <int C>
+  static __device__ __forceinline__ void ld(double (&buf)[CH], const RIFT_CONST double* Cc) {
+    const RIFT_CONST double* p = opaque(Cc) + C * CH;
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+      if (C * CH + i < NC) buf[i] = p[i];
+  }
+  template <class Emit>
+  static __device__ __forceinline__ void close(int q, const double* Fre, const double* Fim, State& S, Emit&& emit) {
+    double v[2][3];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const double* p = s ? S.ps : S.pc;
+      double A = 0.0, Br = 0.0, Bi = 0.0;
+#pragma unroll
+      for (int k = 0; k < KT; ++k) {
+        const double f2 = Fre[k] * Fre[k] + Fim[k] * Fim[k];
+        const double gr = Fre[k] * Fre[k] - Fim[k] * Fim[k], gi = 2 * Fre[k] * Fim[k];
+        A = fma(f2, p[3 * k], A);
+        Br = fma(gr, p[3 * k + 1], fma(gi, p[3 * k + 2], Br));
+        Bi = fma(gi, p[3 * k + 1], fma(-gr, p[3 * k + 2], Bi));
+      }
+      v[s][0] = A;
+      v[s][1] = Br;
+      v[s][2] = Bi;
+    }
+    // cos q (phi + alpha), sin q (phi + alpha) along cos q alpha, sin q alpha
+    emit(q, 0, fma(v[0][0], S.ex, v[1][0] * S.ey), fma(v[0][1], S.ex, v[1][1] * S.ey),
+         fma(v[0][2], S.ex, v[1][2] * S.ey));
+    if (q > 0)
+      emit(q, 1, fma(v[1][0], S.ex, -v[0][0] * S.ey), fma(v[1][1], S.ex, -v[0][1] * S.ey),
+           fma(v[1][2], S.ex, -v[0][2] * S.ey));
+#pragma unroll
+    for (int c = 0; c < W; ++c) S.pc[c] = S.ps[c] = 0.0;
+  }
+  template <int J, class Emit>
+  static __device__ __forceinline__ void coef(double c, double cf, double sf, const double* Fre, const double* Fim,
+                                              State& S, Emit&& emit) {
+    if constexpr (J < NC) {
+      constexpr int b = J / W, col = J % W, rb = basis_row<L>(b);
+      constexpr int kind = rb & 15, n = (rb >> 4) & 255, q = rb >> 12;
+      const double t = kind >= 3 ? S.st[n] : S.ct[n];
+      double& p = (kind == 2 || kind == 4) ? S.ps[col] : S.pc[col];
+      p = fma(c, t, p);
+      if constexpr (col == W - 1 && (b + 1 == B || (basis_row<L>(b + 1) >> 12) != q)) {
+        close(q, Fre, Fim, S, emit);
+        phase_up_to(S, cf, sf);
+      }
+    }
+  }
+  static __device__ __forceinline__ void phase_up_to(State& S, double cf, double sf) {
+    const double a = S.ex * cf - S.ey * sf, b = S.ex * sf + S.ey * cf;
+    S.ex = a;
+    S.ey = b;
+  }
+  template <int C, class Emit, int... I>
+  static __device__ __forceinline__ void fm(const double (&buf)[CH], double cf, double sf, const double* Fre,
+                                            const double* Fim, State& S, Emit&& emit, std::integer_sequence<int, I...>) {
+    (coef<C * CH + I>(buf[I], cf, sf, Fre, Fim, S, emit), ...);
+  }
+  template <int C, class Emit>
+  static __device__ __forceinline__ void step(const RIFT_CONST double* Cc, double (&cur)[CH], double (&nxt)[CH],
+                                              double cf, double sf, const double* Fre, const double* Fim, State& S,
+                                              Emit&& emit) {
+    if constexpr (C < NCH) {
+#pragma unroll
+      for (int i = 0; i < CH; ++i)
+        if (C * CH + i < NC) pin_s(cur[i]);
+      if constexpr (C + 1 < NCH) ld<C + 1>(nxt, Cc);
+      fm<C>(cur, cf, sf, Fre, Fim, S, emit, std::make_integer_sequence<int, CH>{});
+#pragma unroll
+      for (int c = 0; c < W; ++c) {
+        pin(S.pc[c]);
+        pin(S.ps[c]);
+      }
+      step<C + 1>(Cc, nxt, cur, cf, sf, Fre, Fim, S, emit);
+    }
+  }
+  template <class Emit>
+  static __device__ __forceinline__ void run(PDesc P, double* __restrict__ trig, int ts, double ci, double si,
+                                             double cf, double sf, const double* Fre, const double* Fim, Emit&& emit) {
+    State S;
+    S.ex = 1.0;
+    S.ey = 0.0;
+#pragma unroll
+    for (int c = 0; c < W; ++c) S.pc[c] = S.ps[c] = 0.0;
+    const RIFT_CONST double* Cc = as_const(P->C64);
+    if constexpr (L <= 4) {
+      S.ct[0] = 1.0;
+      S.st[0] = 0.0;
+      S.ct[1] = ci;
+      S.st[1] = si;
+#pragma unroll
+      for (int n = 2; n <= NI; ++n) {
+        S.ct[n] = 2.0 * ci * S.ct[n - 1] - S.ct[n - 2];
+        S.st[n] = 2.0 * ci * S.st[n - 1] - S.st[n - 2];
+      }
+      double bA[CH], bB[CH];
+      ld<0>(bA, Cc);
+      step<0>(Cc, bA, bB, cf, sf, Fre, Fim, S, emit);
+    } else {
+      // runtime rows; cos, sin(n incl) in this lane's column of the scratch
+      double c0 = 1.0, c1 = ci, s0 = 0.0, s1 = si;
+#pragma unroll
+      for (int n = 0; n <= NI; ++n) {
+        trig[n * ts] = n == 0 ? c0 : c1;
+        trig[(NI + 1 + n) * ts] = n == 0 ? s0 : s1;
+        if (n > 0) {
+          const double c2 = 2.0 * ci * c1 - c0, s2 = 2.0 * ci * s1 - s0;
+          c0 = c1;
+          c1 = c2;
+          s0 = s1;
+          s1 = s2;
+        }
+      }
+      int b = 0;
+#pragma unroll 1
+      for (int q = 0; q <= 4 * ERAI_MAX_M / 2; ++q) {  // the rows of higher q are zero for |m| <= ERAI_MAX_M
+        const int odd = q & 1, base = odd ? NI + 1 : 0;
+#pragma unroll 1
+        for (int n = odd; n <= NI; ++n) {
+          const double t = trig[(base + n) * ts];
+#pragma unroll
+          for (int c = 0; c < W; ++c) S.pc[c] = fma(Cc[b * W + c], t, S.pc[c]);
+          ++b;
+          if (q > 0) {
+#pragma unroll
+            for (int c = 0; c < W; ++c) S.ps[c] = fma(Cc[b * W + c], t, S.ps[c]);
+            ++b;
+          }
+        }
+        close(q, Fre, Fim, S, emit);
+        phase_up_to(S, cf, sf);
+      }
+    }
+  }
 };
 
-template <class R, int KT, int L, class DataFn>
-__device__ __forceinline__ bool eval_erai_with(PDesc P, R* __restrict__ trig, int ts, double ra, double dec,
-                                               double psi, double incl, double phi, double tref, double dist,
-                                               const AngleRule& G, RIFT_GLOBAL double* out, int64_t N, int64_t i,
-                                               bool live, DataFn&& data_fn) {
+template <int KT, int L>
+__device__ __forceinline__ bool eval_erai(PDesc P, double* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
+                                          double ra, double dec, double psi, double incl, double phi, double tref,
+                                          double dist, const AngleRule& R, RIFT_GLOBAL double* out, int64_t N,
+                                          int64_t i, bool live) {
   constexpr int NY = Cls<L>::NY;
-  reduce_angles<R>(psi, incl, phi);
-  Sky<R, KT> S;
-  sky_eval<R, KT, true>(P, ra, dec, psi, tref, S);
-  R si, ci;
-  sincos_((R)incl, &si, &ci);
-  R cn[NY], sn[NY];
-  incl_harmonics<R, NY>(ci, si, cn, sn);
+  Sky<double, KT> S;
+  sky_eval<double, KT, true>(P, ra, dec, psi, tref, S);
+  double si, ci;
+  sincos(incl, &si, &ci);
+  double cn[NY], sn[NY];
+  incl_harmonics<double, NY>(ci, si, cn, sn);
   const double x = P->d_ref / dist;
   const double x2 = x * x;
-  bool bad = S.bad || !(fabs(x) <= 1.0e300);
-  for (int j = 0; j < G.nd; ++j) {
-    R sf, cf;
-    sincos_((R)fma((double)j, G.dd, phi), &sf, &cf);
-    double wim = 0.0;
-    __builtin_amdgcn_s_setprio(1);
-    const double wre = data_fn(S.row, S.sfr, S.Fre, S.Fim, cn, sn, cf, sf, &wim);
-    __builtin_amdgcn_s_setprio(0);
-    bad = bad || !(fabs(wre) <= 1.0e300) || !(fabs(wim) <= 1.0e300);
-    if (live) {
-      out[(int64_t)(2 * j) * N + i] = x * wre;
-      out[(int64_t)(2 * j + 1) * N + i] = x * wim;
-    }
-  }
-  const int r0 = 2 * G.nd;
-  for (int j = 0; j < G.nq; ++j) {
-    R sf, cf;
-    sincos_((R)fma((double)j, G.dq, phi), &sf, &cf);
-    R acc[3 * KT];
-    norm_contract<R, KT, L>(P, trig, ts, ci, si, cf, sf, acc);
-    double A0 = 0.0, Bre = 0.0, Bim = 0.0;
+  double sf, cf;
+  sincos(phi, &sf, &cf);
+  C2<double> T[2 * ERAI_MAX_M + 1];
 #pragma unroll
-    for (int k = 0; k < KT; ++k) {
-      const R f2 = S.Fre[k] * S.Fre[k] + S.Fim[k] * S.Fim[k];
-      const R g2r = S.Fre[k] * S.Fre[k] - S.Fim[k] * S.Fim[k];
-      const R g2i = 2 * S.Fre[k] * S.Fim[k];
-      A0 += (double)(f2 * acc[3 * k]);
-      Bre += (double)(g2r * acc[3 * k + 1]) + (double)(g2i * acc[3 * k + 2]);
-      Bim += (double)(g2i * acc[3 * k + 1]) - (double)(g2r * acc[3 * k + 2]);
-    }
-    bad = bad || !(fabs(A0) <= 1.0e300) || !(fabs(Bre) + fabs(Bim) <= 1.0e300);
-    if (live) {
-      out[(int64_t)(r0 + 3 * j) * N + i] = -x2 * A0;
-      out[(int64_t)(r0 + 3 * j + 1) * N + i] = -x2 * Bre;
-      out[(int64_t)(r0 + 3 * j + 2) * N + i] = x2 * Bim;
+  for (int j = 0; j < 2 * ERAI_MAX_M + 1; ++j) T[j].x = T[j].y = 0.0;
+  {
+    const int M = P->M, NGR = q_groups(M, QW64);
+    uint32_t boff[KT];
+#pragma unroll
+    for (int k = 0; k < KT; ++k) boff[k] = (uint32_t)S.row[k] * (uint32_t)(QW64 * sizeof(C2<double>));
+    const RIFT_GLOBAL char* Qb = (const RIFT_GLOBAL char*)as_global(P->Q64);
+    const uint64_t gstride = (uint64_t)(P->n_t + 2 * QPAD) * (QW64 * sizeof(C2<double>));
+    const uint64_t kstride = (uint64_t)NGR * gstride;
+    constexpr int G0 = det_group_size(KT, 0), G1 = det_group_size(KT, 1), G2 = det_group_size(KT, 2);
+    __builtin_amdgcn_s_setprio(1);
+    data_harmonics<NY, 0, G0>(P, Qb, gstride, kstride, M, NGR, boff, stage, S.sfr, S.Fre, S.Fim, cn, sn, T);
+    if constexpr (G1 > 0)
+      data_harmonics<NY, det_group_start(KT, 1), G1>(P, Qb, gstride, kstride, M, NGR, boff, stage, S.sfr, S.Fre, S.Fim,
+                                                     cn, sn, T);
+    if constexpr (G2 > 0)
+      data_harmonics<NY, det_group_start(KT, 2), G2>(P, Qb, gstride, kstride, M, NGR, boff, stage, S.sfr, S.Fre, S.Fim,
+                                                     cn, sn, T);
+    __builtin_amdgcn_s_setprio(0);
+  }
+  bool bad = S.bad || !(fabs(x) <= 1.0e300);
+  // x T_m e^{-i m phi}, then c1 along 1, cos m alpha, sin m alpha
+  const int mm = (R.nd - 1) / 2;
+  {
+    double ex = 1.0, ey = 0.0;
+#pragma unroll
+    for (int m = 0; m <= ERAI_MAX_M; ++m) {
+      const C2<double> p = T[ERAI_MAX_M + m], n = T[ERAI_MAX_M - m];
+      // T_m e^{-i m phi} and T_-m e^{i m phi}
+      const double pr = x * (p.x * ex + p.y * ey), pi = x * (p.y * ex - p.x * ey);
+      const double nr = x * (n.x * ex - n.y * ey), ni = x * (n.y * ex + n.x * ey);
+      bad = bad || !(fabs(pr) + fabs(pi) + fabs(nr) + fabs(ni) <= 1.0e300);
+      if (live && m <= mm) {
+        if (m == 0) {
+          out[i] = pr;
+          out[N + i] = pi;
+        } else {
+          RIFT_GLOBAL double* o = out + (int64_t)(2 * (2 * m - 1)) * N + i;
+          o[0] = pr + nr;
+          o[N] = pi + ni;
+          o[2 * N] = pi - ni;
+          o[3 * N] = nr - pr;
+        }
+      }
+      const double a = ex * cf - ey * sf, b = ex * sf + ey * cf;
+      ex = a;
+      ey = b;
     }
   }
+  const int r0 = 2 * R.nd;
+  NormHarmonics<KT, L>::run(P, trig, ts, ci, si, cf, sf, S.Fre, S.Fim,
+                            [&](int q, int s, double A, double Br, double Bi) {
+                              bad = bad || !(fabs(A) <= 1.0e300) || !(fabs(Br) + fabs(Bi) <= 1.0e300);
+                              if (live && q <= 2 * mm) {
+                                RIFT_GLOBAL double* o =
+                                    out + (int64_t)(r0 + 3 * (q == 0 ? 0 : 2 * q - 1 + s)) * N + i;
+                                o[0] = -x2 * A;
+                                o[N] = -x2 * Br;
+                                o[2 * N] = x2 * Bi;
+                              }
+                            });
+  // this class's degrees end at 2 L; another point of the plan may have more
+  for (int r = r0 + 3 * (4 * L + 1); live && r < r0 + 3 * R.nq; ++r) out[(int64_t)r * N + i] = 0.0;
   return bad;
 }
 
@@ -1364,11 +1446,11 @@ __device__ __forceinline__ Terms eval_terms(PDesc P, R* __restrict__ trig, int t
           R sf) { return data_direct<R, KT, L>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf); });
 }
 template <class R, int KT, int L>
-__device__ __forceinline__ double eval_pmarg(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
-                                            double ra, double dec, double psi, double incl, double phi, double tref,
-                                            double dist, const PsiRule& G) {
+__device__ __forceinline__ bool eval_pmarg(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
+                                          double ra, double dec, double psi, double incl, double phi, double tref,
+                                          double dist, RIFT_GLOBAL double* out, int64_t N, int64_t i, bool live) {
   return eval_pmarg_with<R, KT, L>(
-      P, trig, ts, ra, dec, psi, incl, phi, tref, dist, G,
+      P, trig, ts, ra, dec, psi, incl, phi, tref, dist, out, N, i, live,
       [&](const int32_t* row, const R* sfr, const R* Fre, const R* Fim, const R* cn, const R* sn, R cf, R sf,
           double* im) { return data_direct<R, KT, L, true>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf, im); });
 }
@@ -1380,16 +1462,6 @@ __device__ __forceinline__ double eval_tmarg(PDesc P, R* __restrict__ trig, int 
       P, trig, ts, ra, dec, psi, incl, phi, dist, T,
       [&](const int32_t* row, const R* sfr, const R* Fre, const R* Fim, const R* cn, const R* sn, R cf,
           R sf) { return data_direct<R, KT, L>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf); });
-}
-template <class R, int KT, int L>
-__device__ __forceinline__ bool eval_erai(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
-                                         double ra, double dec, double psi, double incl, double phi, double tref,
-                                         double dist, const AngleRule& G, RIFT_GLOBAL double* out, int64_t N,
-                                         int64_t i, bool live) {
-  return eval_erai_with<R, KT, L>(
-      P, trig, ts, ra, dec, psi, incl, phi, tref, dist, G, out, N, i, live,
-      [&](const int32_t* row, const R* sfr, const R* Fre, const R* Fim, const R* cn, const R* sn, R cf, R sf,
-          double* im) { return data_direct<R, KT, L, true>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf, im); });
 }
 template <class R, int KT, int L>
 __device__ __forceinline__ double eval_tkappa(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,

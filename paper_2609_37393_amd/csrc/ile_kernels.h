@@ -16,18 +16,21 @@ namespace rift {
 // distance (Eq. (ap:dgh)) in place of lnL, and its tile (max, sum);
 // MODE_TMARG64: FP64, the likelihood marginalised over geocentric time by the
 // fixed-spacing rule (Eq. (ap:tfixed)) in place of lnL, and its tile pair.
-// MODE_PMARG64: FP64, the likelihood marginalised over polarisation
-// (Eqs. (ap:psiexp), (ap:psilaplace)) in place of lnL, and its tile pair.
+// MODE_PMARG64: FP64, the data pass of the polarisation marginal: the five
+// coefficients of Eq. (ap:psiexp) into `ang`, NaN or 0 (poisoned or not) in
+// place of lnL, no reduction.
 // MODE_TBAND64: FP64, the data pass of the band-limited time rule
 // (Eq. (ap:tband)): x kappa at every node into `kap`, the time-independent
 // remainder in place of lnL, and no reduction (a later pass finishes the
 // rule per sample and reduces).
 // MODE_ERAI64: FP64, the data pass of the joint phiref / psi marginal by
-// exact reconstruction: the angular coefficients at their sampling angles
-// into `ang`, NaN or 0 (poisoned or not) in place of lnL, no reduction.
+// exact reconstruction: the angular harmonics into `ang`, NaN or 0 (poisoned
+// or not) in place of lnL, no reduction.
 enum : int { MODE_LSE64 = 0, MODE_PASS32 = 1, MODE_DMARG64 = 2, MODE_TMARG64 = 3, MODE_PMARG64 = 4,
              MODE_TBAND64 = 5, MODE_ERAI64 = 6 };
-constexpr bool mode_reduces(int mode) { return mode != MODE_TBAND64 && mode != MODE_ERAI64; }
+constexpr bool mode_reduces(int mode) {
+  return mode != MODE_TBAND64 && mode != MODE_ERAI64 && mode != MODE_PMARG64;
+}
 
 struct TileArgs {
   const PointDesc* descs;
@@ -51,10 +54,10 @@ struct TileArgs {
   const double* theta_aos;
   DistRule dm;  // MODE_DMARG64: the distance rule and prior
   TimeRule tm;  // MODE_TMARG64, MODE_TBAND64: the time nodes
-  PsiRule pm;   // MODE_PMARG64: the polarisation rule
   double* kap;  // MODE_TBAND64: [tm.n][N], x kappa at the nodes
-  AngleRule am; // MODE_ERAI64: the sampling angles
-  double* ang;  // MODE_ERAI64: [2 nd + 3 nq][N], the angular coefficients
+  AngleRule am; // MODE_ERAI64: the harmonics' counts
+  double* ang;  // MODE_ERAI64: [2 nd + 3 nq][ang_stride], MODE_PMARG64: [PSI_ROWS][ang_stride]; column i of sample i
+  int64_t ang_stride;
 };
 
 // One tile: every sample's lnL (and bound), then a block reduction.
@@ -90,8 +93,8 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, do
         e.lnL = eval_tkappa<R, KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[1], th[2], th[3], th[4], th[6],
                                       a.tm, as_global_w(a.kap), N, i, live);
       } else if constexpr (MODE == MODE_ERAI64) {
-        e.lnL = eval_erai<R, KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[1], th[2], th[3], th[4], th[5],
-                                    th[6], a.am, as_global_w(a.ang), N, i, live)
+        e.lnL = eval_erai<KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[1], th[2], th[3], th[4], th[5],
+                                    th[6], a.am, as_global_w(a.ang), a.ang_stride, i, live)
                     ? __builtin_nan("")
                     : 0.0;
       } else if constexpr (MODE == MODE_DMARG64) {
@@ -103,7 +106,9 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, do
                                      a.tm);
       } else if constexpr (MODE == MODE_PMARG64) {
         e.lnL = eval_pmarg<R, KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[1], th[2], th[3], th[4], th[5],
-                                     th[6], a.pm);
+                                     th[6], as_global_w(a.ang), a.ang_stride, i, live)
+                    ? __builtin_nan("")
+                    : 0.0;
       } else {
         e = eval_sample<R, KT, L, MODE == MODE_PASS32>(opaque(P), trig, blockDim.x, stage, th[0], th[1], th[2],
                                                        th[3], th[4], th[5], th[6]);
@@ -125,8 +130,8 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, do
       e.lnL = eval_tkappa<R, KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[N], th[2 * N], th[3 * N],
                                     th[4 * N], th[6 * N], a.tm, as_global_w(a.kap), N, i, live);
     } else if constexpr (MODE == MODE_ERAI64) {
-      e.lnL = eval_erai<R, KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[N], th[2 * N], th[3 * N],
-                                  th[4 * N], th[5 * N], th[6 * N], a.am, as_global_w(a.ang), N, i, live)
+      e.lnL = eval_erai<KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[N], th[2 * N], th[3 * N],
+                                  th[4 * N], th[5 * N], th[6 * N], a.am, as_global_w(a.ang), a.ang_stride, i, live)
                   ? __builtin_nan("")
                   : 0.0;
     } else if constexpr (MODE == MODE_DMARG64) {
@@ -138,7 +143,9 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, do
                                    th[4 * N], th[6 * N], a.tm);
     } else if constexpr (MODE == MODE_PMARG64) {
       e.lnL = eval_pmarg<R, KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[N], th[2 * N], th[3 * N],
-                                   th[4 * N], th[5 * N], th[6 * N], a.pm);
+                                   th[4 * N], th[5 * N], th[6 * N], as_global_w(a.ang), a.ang_stride, i, live)
+                  ? __builtin_nan("")
+                  : 0.0;
     } else {
       e = eval_sample<R, KT, L, MODE == MODE_PASS32>(opaque(P), trig, blockDim.x, stage, th[0], th[N],
                                                      th[2 * N], th[3 * N], th[4 * N], th[5 * N], th[6 * N]);

@@ -2,7 +2,7 @@
 // kernel kind RIFT_KIND (0: FP64 tiles, 1: FP32 tiles, 2: FP64 refine,
 // 3: gradient, a lane or a group of lanes per sample, 4: FP64 tiles of the
 // distance marginal, 5: FP64 tiles of the time marginal, 6: FP64 tiles of
-// the polarisation marginal, 7: FP64 data pass of the band-limited time
+// the polarisation marginal's data pass, 7: FP64 data pass of the band-limited time
 // rule, 8: FP64 data pass of the joint phiref / psi marginal, 9: coefficients
 // of the time marginals' contracted series).  The build compiles this file once per (class, kind) so the instances build in parallel.
 #include "ile_kernels.h"

@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "../../include/rift_ile.h"
+#include "ile_angles.h"
 #include "ile_host.h"
 #include "ile_kernels.h"
 #include "ile_series.h"
@@ -802,102 +803,6 @@ __global__ void k_lse_tiles(const Tile* __restrict__ tiles, const double* __rest
 constexpr int TBAND_MAX_NODES = 64;
 constexpr int TBAND_MAX_FINE = 64;
 
-// The joint phiref / psi marginal by exact reconstruction (ERAI), after the
-// data pass: per sample the angular coefficients at their sampling angles
-// (c1 at nd = 2 m_max + 1, a and c2 at nq = 4 m_max + 1 angles) determine
-//   q(alpha, u) = a(alpha) + Re(c1(alpha) e^{iu}) + Re(c2(alpha) e^{2iu})
-// exactly; e^q is averaged over the periodic grid alpha_a = 2 pi a / n_phi,
-// u_b = 2 pi b / n_psi (psi offset pi b / n_psi), the trapezoid rule on the
-// torus with phiref uniform on [0, 2 pi) and psi on [0, pi).
-constexpr int ERAI_MAX_M = 4;
-
-// (a N - j n) / (n N) turns between fine angle a of n and sampling angle j
-// of N; the Dirichlet kernel of odd N, sin(pi N d) / (N sin(pi d)), is 1 at
-// the coincident angles (tested exactly on integers).
-__device__ __forceinline__ double dirichlet_weight(int a, int n, int j, int N) {
-  const int64_t num = (int64_t)a * N - (int64_t)j * n;
-  if (num % ((int64_t)n * N) == 0) return 1.0;
-  return sinpi((double)num / (double)n) / ((double)N * sinpi((double)num / ((double)n * (double)N)));
-}
-
-// Uniform tables: interpolation weights wd [n_phi][NDM] and wq [n_phi][NQM]
-// (zero past nd, nq), and tu [n_psi][4] = cos u, sin u, cos 2u, sin 2u.
-__global__ void k_erai_tables(int n_phi, int n_psi, int nd, int nq, int NDM, int NQM, double* __restrict__ wd,
-                              double* __restrict__ wq, double* __restrict__ tu) {
-  const int stride = gridDim.x * blockDim.x;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n_phi * NDM; e += stride) {
-    const int a = e / NDM, j = e - a * NDM;
-    wd[e] = j < nd ? dirichlet_weight(a, n_phi, j, nd) : 0.0;
-  }
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n_phi * NQM; e += stride) {
-    const int a = e / NQM, j = e - a * NQM;
-    wq[e] = j < nq ? dirichlet_weight(a, n_phi, j, nq) : 0.0;
-  }
-  for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < n_psi; b += stride) {
-    double s1, c1, s2, c2;
-    sincospi(2.0 * (double)b / (double)n_psi, &s1, &c1);
-    sincospi(4.0 * (double)b / (double)n_psi, &s2, &c2);
-    tu[4 * b] = c1;
-    tu[4 * b + 1] = s1;
-    tu[4 * b + 2] = c2;
-    tu[4 * b + 3] = s2;
-  }
-}
-
-// One sample per lane, its coefficients in registers (zero past nd, nq);
-// the grid loops are uniform, the tables read with uniform addresses.  L
-// holds NaN (poisoned) or 0 on entry and ln L_{phi psi} on return.
-template <int NDM, int NQM>
-__global__ void __launch_bounds__(256) k_erai(int64_t N, int nd, int nq, int n_phi, int n_psi,
-                                              const double* __restrict__ ang, const double* __restrict__ wd,
-                                              const double* __restrict__ wq, const double* __restrict__ tu,
-                                              double ln_scale, double* __restrict__ L) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
-    double c1r[NDM], c1i[NDM], ca[NQM], c2r[NQM], c2i[NQM];
-#pragma unroll
-    for (int j = 0; j < NDM; ++j) {
-      c1r[j] = j < nd ? ang[(int64_t)(2 * j) * N + i] : 0.0;
-      c1i[j] = j < nd ? ang[(int64_t)(2 * j + 1) * N + i] : 0.0;
-    }
-#pragma unroll
-    for (int j = 0; j < NQM; ++j) {
-      const int64_t r = 2 * nd + 3 * j;
-      ca[j] = j < nq ? ang[r * N + i] : 0.0;
-      c2r[j] = j < nq ? ang[(r + 1) * N + i] : 0.0;
-      c2i[j] = j < nq ? ang[(r + 2) * N + i] : 0.0;
-    }
-    const double flag = L[i];
-    double m = -__builtin_inf(), sum = 0.0;
-    for (int p = 0; p < n_phi; ++p) {
-      const double* __restrict__ Wd = wd + p * NDM;
-      const double* __restrict__ Wq = wq + p * NQM;
-      double C1r = 0.0, C1i = 0.0, A = 0.0, C2r = 0.0, C2i = 0.0;
-#pragma unroll
-      for (int j = 0; j < NDM; ++j) {
-        C1r = fma(Wd[j], c1r[j], C1r);
-        C1i = fma(Wd[j], c1i[j], C1i);
-      }
-#pragma unroll
-      for (int j = 0; j < NQM; ++j) {
-        A = fma(Wq[j], ca[j], A);
-        C2r = fma(Wq[j], c2r[j], C2r);
-        C2i = fma(Wq[j], c2i[j], C2i);
-      }
-      for (int b = 0; b < n_psi; ++b) {
-        const double* __restrict__ U = tu + 4 * b;
-        const double l = A + C1r * U[0] - C1i * U[1] + C2r * U[2] - C2i * U[3];
-        // one exp, no divergent branch (as in k_tband)
-        const double d = l - m;
-        const double e = exp(-fabs(d));
-        const bool up = d > 0.0;
-        sum = up ? fma(sum, e, 1.0) : sum + e;
-        m = up ? l : m;
-      }
-    }
-    L[i] = (flag == flag && m == m && sum == sum) ? m + log(sum) + ln_scale : __builtin_nan("");
-  }
-}
-
 // Per-tile max(lnL32 + lnw - bound) in input order (mixed path).
 __global__ void k_tmax_tiles(const Tile* __restrict__ tiles, const double* __restrict__ lnL,
                              const double* __restrict__ lnw, const float* __restrict__ bnd,
@@ -1048,11 +953,11 @@ struct rift_ile_plan_s {
   DistRule dm{};
   // time marginal: the rule of the last rift_ile_plan_lnZ_tmarg call
   TimeRule tm{};
-  // polarisation marginal: the rule of the last rift_ile_plan_lnZ_pmarg call
-  PsiRule pm{};
   double* kap = nullptr;  // band-limited time rule: x kappa at the nodes (stream-ordered, per call)
+  // angular rules: the harmonics' counts, and the coefficients of this call
   AngleRule am{};
-  double* ang = nullptr;  // ERAI: the angular coefficients (stream-ordered, per call)
+  double* ang = nullptr;
+  int64_t ang_stride = 0;
   // workspace of the calls that need one, kept for the next call (take_space)
   void* ws = nullptr;
   size_t ws_bytes = 0;
@@ -1247,12 +1152,13 @@ size_t eval_lds_bytes(int lset, int block, size_t rsz) {
   return (size_t)(block / 64) * STAGE_WAVE + trig;
 }
 
+// The likelihood kernel over tiles [first, first + count) (count < 0: all).
 int launch_tiles(rift_ile_plan p, int mode, const double* theta, const double* lnw, double* lnL,
-                 hipStream_t st) {
+                 hipStream_t st, int first = 0, int count = -1) {
   TileArgs a;
   a.descs = p->d_desc;
-  a.tiles = p->d_tiles;
-  a.n_tiles = p->n_tiles;
+  a.tiles = p->d_tiles + first;
+  a.n_tiles = count < 0 ? p->n_tiles : count;
   a.persistent = p->cfg.blocks_per_cu > 0 ? 1 : 0;
   a.counter = p->d_counter;
   a.theta = theta;
@@ -1266,17 +1172,17 @@ int launch_tiles(rift_ile_plan p, int mode, const double* theta, const double* l
   a.theta_aos = p->cfg.sort ? p->d_aos : nullptr;
   a.dm = p->dm;
   a.tm = p->tm;
-  a.pm = p->pm;
   a.kap = p->kap;
   a.am = p->am;
   a.ang = p->ang;
+  a.ang_stride = p->ang_stride;
   const size_t rsz = (mode == MODE_PASS32 ? sizeof(float) : sizeof(double));
   const size_t shm = eval_lds_bytes(p->lset, p->cfg.block, rsz);
   if (shm + 1024 > (size_t)p->di.max_lds) return RIFT_EUNSUPPORTED;
   tile_fn f = pick_tiles_kt(mode, p->KT, p->lset);
   if (!f) return RIFT_EUNSUPPORTED;
-  int grid = p->n_tiles;
-  if (a.persistent) grid = std::min(p->n_tiles, p->cfg.blocks_per_cu * p->di.n_cu);
+  int grid = a.n_tiles;
+  if (a.persistent) grid = std::min(a.n_tiles, p->cfg.blocks_per_cu * p->di.n_cu);
   if (grid <= 0) return RIFT_OK;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (p->profiling) {
@@ -1871,6 +1777,54 @@ int series_batch(rift_ile_plan p, const double* theta, int fine, const double* s
   return RIFT_OK;
 }
 
+// An angular rule over the batch: the data pass `mode` leaves `rows`
+// coefficients per sample, and `rule(first, count, coef, stride)` turns them
+// into the samples' values in L.  The batch runs in pieces whose coefficients
+// fit ANG_KEEP bytes, each read back while it is in cache; the data pass takes
+// whole tiles, consecutive in samples.  A binned batch's tiles scatter over the
+// samples, so it runs whole.  `tail` bytes follow the coefficients.
+constexpr size_t ANG_KEEP = (size_t)96 << 20;
+struct AngPiece {
+  int tile, tiles;
+  int64_t first, count;
+};
+int64_t ang_pieces(rift_ile_plan p, int rows, std::vector<AngPiece>* out) {
+  const size_t per = sizeof(double) * (size_t)rows;
+  if (p->cfg.sort || (size_t)p->N * per <= ANG_KEEP) {
+    out->push_back(AngPiece{0, p->n_tiles, 0, p->N});
+    return p->N;
+  }
+  const int64_t cap = std::max<int64_t>((int64_t)(ANG_KEEP / per), 1);
+  int64_t most = 0;
+  for (int t = 0; t < p->n_tiles; ++t) {
+    const Tile& T = p->h_tiles[t];
+    AngPiece* b = out->empty() ? nullptr : &out->back();
+    if (b && b->first + b->count == T.s && b->count + T.cnt <= cap) {
+      b->tiles += 1;
+      b->count += T.cnt;
+    } else {
+      out->push_back(AngPiece{t, 1, T.s, T.cnt});
+    }
+    most = std::max(most, out->back().count);
+  }
+  return most;
+}
+template <class Rule>
+int ang_batch(rift_ile_plan p, int mode, const std::vector<AngPiece>& pieces, int64_t stride, double* coef,
+              const double* theta, double* L, hipStream_t st, Rule&& rule) {
+  int rc = p->cfg.sort ? run_binning(p, theta, st) : RIFT_OK;
+  for (const AngPiece& b : pieces) {
+    if (rc) break;
+    // sample i of the batch lands in column i - b.first
+    p->ang = coef - b.first;
+    p->ang_stride = stride;
+    rc = launch_tiles(p, mode, theta, nullptr, L, st, b.tile, b.tiles);
+    p->ang = nullptr;
+    if (!rc) rc = rule(b.first, b.count);
+  }
+  return rc;
+}
+
 // ln Z and n_eff from every sample's value, in input order.
 int reduce_values(rift_ile_plan p, const double* L, const double* lnw, double* lnZ, double* neff, hipStream_t st) {
   if (p->n_tiles > 0)
@@ -2016,55 +1970,33 @@ int rift_ile_plan_lnZ_erai(rift_ile_plan p, const double* theta, const double* l
   int m_max = 0;
   for (const PointDesc& D : p->h_desc) m_max = std::max(m_max, std::max(std::abs(D.m[0]), std::abs(D.m[D.M - 1])));
   if (m_max > ERAI_MAX_M) return RIFT_EUNSUPPORTED;
-  const int nd = 2 * m_max + 1, nq = 4 * m_max + 1;
-  const int NDM = m_max <= 2 ? 5 : 9, NQM = m_max <= 2 ? 9 : 17;
   AngleRule g{};
-  g.nd = nd;
-  g.nq = nq;
-  g.dd = 2.0 * 3.14159265358979323846 / nd;
-  g.dq = 2.0 * 3.14159265358979323846 / nq;
+  g.nd = 2 * m_max + 1;
+  g.nq = 4 * m_max + 1;
   p->am = g;
   hipStream_t st = (hipStream_t)stream;
   p->last = st;
-  const bool sorted = p->cfg.sort != 0;
-  if (sorted && !p->bin_ready) return RIFT_EUNSUPPORTED;
-  // stream-ordered scratch: the coefficients [2 nd + 3 nq][N], the tables,
-  // and the per-sample values when the caller takes none
-  const int64_t N = p->N;
-  const size_t rows = (size_t)(2 * nd + 3 * nq);
-  const size_t nwd = (size_t)rule->n_phi * NDM, nwq = (size_t)rule->n_phi * NQM, ntu = 4 * (size_t)rule->n_psi;
-  const size_t bytes = sizeof(double) * (rows * N + nwd + nwq + ntu + (lnLa ? 0 : (size_t)N));
-  double* w = nullptr;
-  if (hipMallocAsync((void**)&w, bytes, st) != hipSuccess) return RIFT_ENOMEM;
-  double* wd = w + rows * N;
-  double* wq = wd + nwd;
-  double* tu = wq + nwq;
-  double* L = lnLa ? lnLa : tu + ntu;
-  p->ang = w;
-  int rc = sorted ? run_binning(p, theta, st) : RIFT_OK;
-  if (!rc) rc = launch_tiles(p, MODE_ERAI64, theta, lnw, L, st);
-  p->ang = nullptr;
-  if (!rc) {
-    const size_t big = std::max(std::max(nwd, nwq), (size_t)rule->n_psi);
-    hipLaunchKernelGGL(k_erai_tables, dim3((unsigned)std::min<size_t>((big + 255) / 256, 1024)), dim3(256), 0, st,
-                       rule->n_phi, rule->n_psi, nd, nq, NDM, NQM, wd, wq, tu);
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((N + 255) / 256, (int64_t)p->di.n_cu * 8));
-    const double ln_scale = -log((double)rule->n_phi * (double)rule->n_psi);
-    if (NDM == 5)
-      hipLaunchKernelGGL((k_erai<5, 9>), dim3(grid), dim3(256), 0, st, N, nd, nq, rule->n_phi, rule->n_psi,
-                         (const double*)w, (const double*)wd, (const double*)wq, (const double*)tu, ln_scale, L);
-    else
-      hipLaunchKernelGGL((k_erai<9, 17>), dim3(grid), dim3(256), 0, st, N, nd, nq, rule->n_phi, rule->n_psi,
-                         (const double*)w, (const double*)wd, (const double*)wq, (const double*)tu, ln_scale, L);
-    if (p->n_tiles > 0)
-      hipLaunchKernelGGL(k_lse_tiles, dim3(p->n_tiles), dim3(p->cfg.block), 0, st, p->d_tiles, (const double*)L,
-                         lnw, p->d_part);
-    hipLaunchKernelGGL(k_merge, dim3(p->n_points), dim3(512), 0, st, p->d_desc, p->d_trange, p->d_part,
-                       (const double*)nullptr, lnZ, neff, (double*)nullptr);
-    if (hipGetLastError() != hipSuccess) rc = RIFT_EDEVICE;
-  }
-  if (hipFreeAsync(w, st) != hipSuccess && !rc) rc = RIFT_EDEVICE;
-  return rc;
+  if (p->cfg.sort && !p->bin_ready) return RIFT_EUNSUPPORTED;
+  // working memory: the coefficients of a piece, the tables, and the
+  // per-sample values when the caller takes none
+  const int rows = 2 * g.nd + 3 * g.nq;
+  std::vector<AngPiece> pieces;
+  const int64_t stride = ang_pieces(p, rows, &pieces);
+  const size_t ntab = erai_tables_len(rule->n_phi, rule->n_psi, m_max);
+  Space sp;
+  int rc = take_space(p, sizeof(double) * ((size_t)rows * stride + ntab + (lnLa ? 0 : (size_t)p->N)), st, &sp);
+  if (rc) return rc;
+  double* coef = (double*)sp.p;
+  double* tab = coef + (size_t)rows * stride;
+  double* L = lnLa ? lnLa : tab + ntab;
+  rc = erai_tables(rule->n_phi, rule->n_psi, m_max, tab, st);
+  if (!rc)
+    rc = ang_batch(p, MODE_ERAI64, pieces, stride, coef, theta, L, st, [&](int64_t first, int64_t count) {
+      return run_erai(count, rule->n_phi, rule->n_psi, m_max, coef, stride, tab, L + first, st);
+    });
+  if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
+  const int rd = drop_space(sp, st);
+  return rc ? rc : rd;
 }
 
 int rift_ile_plan_lnZ_pmarg(rift_ile_plan p, const double* theta, const double* lnw, const rift_ile_psi_rule* rule,
@@ -2078,23 +2010,27 @@ int rift_ile_plan_lnZ_pmarg(rift_ile_plan p, const double* theta, const double* 
   PsiRule g{};
   g.method = rule->method == RIFT_PSI_TRAPEZOID ? 0 : (rule->method == RIFT_PSI_LAPLACE ? 1 : 2);
   g.n = rule->method == RIFT_PSI_TRAPEZOID ? rule->n_points : 0;
-  g.ln_n = g.n > 0 ? log((double)g.n) : 0.0;
-  p->pm = g;
   hipStream_t st = (hipStream_t)stream;
   p->last = st;
-  int rc;
   const bool sorted = p->cfg.sort != 0;
-  double* L = lnLp ? lnLp : p->d_L;
-  if (sorted && (!p->bin_ready || !L)) return RIFT_EUNSUPPORTED;
-  if (sorted && (rc = run_binning(p, theta, st))) return rc;
-  if ((rc = launch_tiles(p, MODE_PMARG64, theta, lnw, sorted ? L : lnLp, st))) return rc;
-  if (sorted)
-    hipLaunchKernelGGL(k_lse_tiles, dim3(p->n_tiles), dim3(p->cfg.block), 0, st, p->d_tiles, (const double*)L, lnw,
-                       p->d_part);
-  hipLaunchKernelGGL(k_merge, dim3(p->n_points), dim3(512), 0, st, p->d_desc, p->d_trange, p->d_part,
-                     (const double*)nullptr, lnZ, neff, (double*)nullptr);
-  HCHK(hipGetLastError());
-  return RIFT_OK;
+  if (sorted && (!p->bin_ready || !(lnLp || p->d_L))) return RIFT_EUNSUPPORTED;
+  std::vector<AngPiece> pieces;
+  const int64_t stride = ang_pieces(p, PSI_ROWS, &pieces);
+  const size_t ntab = psi_tables_len(g);
+  Space sp;
+  int rc = take_space(p, sizeof(double) * ((size_t)PSI_ROWS * stride + ntab + (lnLp ? 0 : (size_t)p->N)), st, &sp);
+  if (rc) return rc;
+  double* coef = (double*)sp.p;
+  double* tab = coef + (size_t)PSI_ROWS * stride;
+  double* L = lnLp ? lnLp : tab + ntab;
+  rc = psi_tables(g, tab, st);
+  if (!rc)
+    rc = ang_batch(p, MODE_PMARG64, pieces, stride, coef, theta, L, st, [&](int64_t first, int64_t count) {
+      return run_psi(g, count, coef, stride, tab, L + first, st);
+    });
+  if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
+  const int rd = drop_space(sp, st);
+  return rc ? rc : rd;
 }
 
 int rift_ile_plan_refined(rift_ile_plan p, int64_t* n_refined) {
