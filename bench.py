@@ -694,13 +694,15 @@ def extra_tmarg(ile, synth, torch, steps, cpu=True):
     kms, nl = plan.profile_read()
     plan.profile(False)
     plan.close()
+    # the contracted series run no likelihood kernel: the call's own time then
+    kms = kms / nl if nl else 1e3 * per
     # the model-norm term once, the data term (antenna, stencils, gather, interpolation, coefficients) per time
     fps = survey_flops_per_sample(3, 21) + (n_t - 1) * 3 * (57 + 26 * 21)
     res = {"workload": "3 detectors, 21 modes (l<=4), Q 6554 samples at 32768 Hz, SNR 600; 1e5 samples of the other "
                        "parameters, Simpson rule on 657 times (32768 Hz) over 20 ms",
            "lnLt_evals_per_s": n / per, "data_terms_per_s": n * n_t / per, "ms_per_call": 1e3 * per,
-           "kernel_ms": kms / max(1, nl), "flops_per_sample": fps,
-           "alu_frac": fps * n / (kms / max(1, nl) / 1e3) / (PEAK_FP64_TFLOPS * 1e12), "lnZt": z.item()}
+           "kernel_ms": kms, "flops_per_sample": fps,
+           "alu_frac": fps * n / (kms / 1e3) / (PEAK_FP64_TFLOPS * 1e12), "lnZt": z.item()}
     if cpu:
         import oracle
 
@@ -743,9 +745,9 @@ def extra_tband(ile, synth, torch, steps, cpu=True):
         kms, nl = plan.profile_read()
         plan.profile(False)
         fine = 63 * M + 1
-        rest = 1e3 * per - kms / max(1, nl)
+        rest = 1e3 * per - kms  # all of the call where no likelihood kernel runs
         r = {"lnLt_evals_per_s": n / per, "data_terms_per_s": n * 64 / per, "ms_per_call": 1e3 * per,
-             "data_pass_kernel_ms": kms / max(1, nl), "reconstruction_and_reduction_ms": rest, "fine_times": fine,
+             "data_pass_kernel_ms": kms, "reconstruction_and_reduction_ms": rest, "fine_times": fine,
              "reconstruction_flops_per_sample": 2 * fine * 64,
              "reconstruction_tflops": 2 * fine * 64 * n / (rest / 1e3) / 1e12, "lnZt": z.item()}
         if cpu:
@@ -787,8 +789,8 @@ def extra_erai(ile, synth, torch, steps, cpu=True):
         step()
         kms, nl = plan.profile_read()
         plan.profile(False)
-        r = {"lnL_evals_per_s": n / per, "ms_per_call": 1e3 * per, "data_pass_kernel_ms": kms / max(1, nl),
-             "grid_and_reduction_ms": 1e3 * per - kms / max(1, nl), "exp_per_sample": n_phi * n_psi,
+        r = {"lnL_evals_per_s": n / per, "ms_per_call": 1e3 * per, "data_pass_kernel_ms": kms,  # all pieces
+             "grid_and_reduction_ms": 1e3 * per - kms, "exp_per_sample": n_phi * n_psi,
              "lnZ": z.item()}
         if cpu:
             import oracle

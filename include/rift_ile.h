@@ -706,11 +706,13 @@ int rift_ile_mixture_is(int64_t n, const rift_ile_mixture *mix, const rift_ile_h
  * the same arguments, semantics and results (the same kernels and launch
  * shape), whose working memory -- repacked tables, basis coefficients, tiles,
  * partial sums and, in mixed precision, the per-sample scratch of the
- * recompute -- lives in a fixed device array of RIFT_ILE_NOALLOC_SCRATCH_BYTES
- * that the library holds on each GPU it runs on until the process ends.  It
+ * recompute -- lives in a fixed device array that the library holds on each
+ * GPU it runs on until the process ends.  It
  * calls no hipMalloc or hipFree (the host bookkeeping uses the host heap).
- * A request whose working memory does not fit returns RIFT_ESCRATCH before
- * anything is enqueued; about 7 MB serve a 3-detector, 21-mode point of 6554
+ * A request whose working memory counts more than
+ * RIFT_ILE_NOALLOC_SCRATCH_BYTES returns RIFT_ESCRATCH before anything is
+ * enqueued (the FP64 tables count as two modes per row; the array is half as
+ * long again, since those of long mode sets hold eight); about 7 MB serve a 3-detector, 21-mode point of 6554
  * samples per series in FP64 (16 more bytes per sample in mixed precision).
  * Every call on one GPU uses that GPU's one array: calls that overlap on a
  * GPU (other threads, other streams) race and must be serialised by the

@@ -124,13 +124,13 @@ __global__ void __launch_bounds__(256) k_psi(PsiRule G, int64_t cnt, const doubl
     }
     for (int it = 0; it < 8; ++it) {
       double su, cu;
-      sincos(u, &su, &cu);
+      sincos_many<1>(&u, &su, &cu);
       psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
       if (!(d2 < 0.0)) break;
       u -= d1 / d2;
     }
     double su, cu;
-    sincos(u, &su, &cu);
+    sincos_many<1>(&u, &su, &cu);
     psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
     if (-d2 >= PSI_LAPLACE_MIN_A) {
       L[i] = q - 0.5 * log(TWO_PI * -d2);
@@ -199,7 +199,7 @@ __device__ __forceinline__ void psi_stationary(double a, double c1r, double c1i,
     for (int k = 0; k < 2; ++k) {
       double u = top + 3.14159265358979323846 * k;
       u = u < 0.0 ? u + TWO_PI : u;
-      sincos(u, &su, &cu);
+      sincos_many<1>(&u, &su, &cu);
       psi_q(a, c1r, c1i, 0.0, 0.0, su, cu, &q, &d1, &d2);
       st[k] = CellPoint{u, q, d2};
     }
@@ -240,14 +240,14 @@ __device__ __forceinline__ void psi_stationary(double a, double c1r, double c1i,
       if (!(r2 >= 0.998001 && r2 <= 1.002001)) continue;
       double u = atan2(z[k].y, z[k].x);
       for (int it = 0; it < 30; ++it) {
-        sincos(u, &su, &cu);
+        sincos_many<1>(&u, &su, &cu);
         psi_q(0.0, g1.x, g1.y, 0.5 * g2.x, 0.5 * g2.y, su, cu, &q, &d1, &d2);
         if (d2 == 0.0) break;
         const double step = d1 / d2;
         u -= step;
         if (fabs(step) < 1e-12) break;
       }
-      sincos(u, &su, &cu);
+      sincos_many<1>(&u, &su, &cu);
       psi_q(0.0, g1.x, g1.y, 0.5 * g2.x, 0.5 * g2.y, su, cu, &q, &d1, &d2);
       if (!(fabs(d1) <= 1e-9)) continue;
       psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
@@ -391,7 +391,8 @@ __global__ void __launch_bounds__(128) k_psi_cells(int64_t cnt, const double* __
       const double d1 = fmin(width, j <= 4 ? 2.0 * sigma * j : 2.0 * d0);
       const double h = d1 - d0;
       double su, cu, q, q1, q2;
-      sincos(fma(sgn, fma(h, xg, d0), start), &su, &cu);
+      const double u = fma(sgn, fma(h, xg, d0), start);
+      sincos_near<1>(&u, &su, &cu);
       psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &q1, &q2);
       const double qfar = __shfl(q, lane | 7);
       if (on) {

@@ -36,12 +36,20 @@ constexpr int KMAX = 8;    // detectors
 constexpr int MMAX = 25;   // modes
 constexpr int LMAXC = 8;   // largest l
 constexpr int QPAD = 4;    // zero rows on each side of every Q series
-// Q tables hold W consecutive (internal) modes per time row, W = 2 for FP64
-// and 4 for FP32: a row is 32 bytes in both, and a four-row stencil of one
-// mode group is 128 bytes.
-constexpr int QW64 = 2;
+// Q tables hold W consecutive (internal) modes per time row.  FP64: W = 8, a row
+// of a group one aligned 128-byte line, from 13 modes on; fewer modes take W = 2,
+// whose four stencil rows of a group are 128 bytes at any multiple of 32.  Per
+// detector the reads are 4 units of 128 bytes per eight modes against one per two:
+// 12 against 11 at 21 modes, where every line is used whole (12 lines against 19)
+// and the contraction runs between the units (headline batch 245 -> 232 us), but 8
+// against 5 at 9 modes (3 detectors, 5e5 samples: 111 us against 95) and 4 against
+// 1 at 2 (10^4 samples: the kernel 10.8 us against 9.2).  FP32: W = 4, 32-byte rows.
+constexpr int QW64 = 8;
+constexpr int QW64_SHORT = 2;
+constexpr int QW64_SHORT_MODES = 12;
 constexpr int QW32 = 4;
 __host__ __device__ constexpr int q_groups(int M, int W) { return (M + W - 1) / W; }
+__host__ __device__ constexpr int q_width64(int M) { return M <= QW64_SHORT_MODES ? QW64_SHORT : QW64; }
 // LDS staging of the data term: one unit is the 128-byte stencil block of a
 // (mode group, detector) pair for each of the 64 lanes of a wavefront; every
 // wavefront owns two unit buffers.
@@ -62,7 +70,7 @@ struct PointDesc {
   int32_t B;        // basis functions of the class
   int32_t KT;       // detector class (padded K)
   int32_t m_min;    // smallest m (modes are stored sorted by m)
-  int32_t pad0;
+  int32_t w64;      // modes per row of the FP64 table (q_width64)
   int64_t n;        // samples of this point in a batch
   int64_t s0;       // first sample column of this point in a batch
   double t0, inv_dt, gmst, d_ref;
@@ -121,8 +129,6 @@ struct Cls {
   static constexpr int B = (NI + 1) + (NQ / 2) * 2 * (NI + 1) + ((NQ + 1) / 2) * 2 * NI;
 };
 
-__device__ __forceinline__ void sincos_(double a, double* s, double* c) { sincos(a, s, c); }
-__device__ __forceinline__ void sincos_(float a, float* s, float* c) { sincosf(a, s, c); }
 
 __device__ __forceinline__ int uniform_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -176,6 +182,81 @@ template <class R>
 __device__ __forceinline__ void pin_s(R v) {
   asm volatile("" ::"s"(v));
 }
+// Element k (uniform) of a per-detector value in registers.  The operands are
+// opaque: a selection between plain elements turns into an indexed read, and
+// puts the array into scratch.
+template <int KT, class T>
+__device__ __forceinline__ T by_det(const T* v, int k) {
+  T r = v[0];
+  pin(r);
+#pragma unroll
+  for (int j = 1; j < KT; ++j) {
+    T t = v[j];
+    pin(t);
+    r = k == j ? t : r;
+  }
+  return r;
+}
+// sin and cos of N angles at once: reduction by pi/2 in three parts with fused
+// multiply-adds, then the Taylor series through r^17 and r^18 on |r| <= pi/4
+// (truncation below 1e-18), the N angles side by side, so that each constant is
+// fetched once and the chains of one angle fill the latencies of another's:
+// 36 vector operations an angle, where the library's function takes 105.
+// Angles beyond 2^30 go to that.
+struct SinCosTab {
+  double two_over_pi, p1, p2, p3;
+  double s[8], c[9];
+};
+__constant__ const SinCosTab kSinCos = {
+    0.6366197723675814,
+    1.5707963267948966,
+    6.123233995736766e-17,
+    -1.4973849048591698e-33,
+    {-1.0 / 6.0, 1.0 / 120.0, -1.0 / 5040.0, 1.0 / 362880.0, -1.0 / 39916800.0, 1.0 / 6227020800.0,
+     -1.0 / 1307674368000.0, 1.0 / 355687428096000.0},
+    {-0.5, 1.0 / 24.0, -1.0 / 720.0, 1.0 / 40320.0, -1.0 / 3628800.0, 1.0 / 479001600.0, -1.0 / 87178291200.0,
+     1.0 / 20922789888000.0, -1.0 / 6402373705728000.0}};
+template <int N>
+__device__ __forceinline__ void sincos_near(const double* x, double* s, double* c) {  // |x| <= 2^30
+  const RIFT_CONST SinCosTab* T = opaque(&kSinCos);
+  double r[N], z[N], ps[N], pc[N];
+  int q[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const double k = rint(x[j] * T->two_over_pi);
+    r[j] = fma(-k, T->p3, fma(-k, T->p2, fma(-k, T->p1, x[j])));
+    q[j] = (int)k;
+    z[j] = r[j] * r[j];
+    ps[j] = T->s[7];
+    pc[j] = T->c[8];
+  }
+#pragma unroll
+  for (int t = 7; t >= 0; --t)
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      if (t < 7) ps[j] = fma(ps[j], z[j], T->s[t]);
+      pc[j] = fma(pc[j], z[j], T->c[t]);
+    }
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const double sr = fma(ps[j] * z[j], r[j], r[j]), cr = fma(pc[j], z[j], 1.0);
+    const double a = (q[j] & 1) ? cr : sr, b = (q[j] & 1) ? sr : cr;
+    s[j] = (q[j] & 2) ? -a : a;
+    c[j] = ((q[j] + 1) & 2) ? -b : b;
+  }
+}
+template <int N>
+__device__ __forceinline__ void sincos_many(const double* x, double* s, double* c) {
+  sincos_near<N>(x, s, c);
+  bool far = false;
+#pragma unroll
+  for (int j = 0; j < N; ++j) far = far || fabs(x[j]) > 1073741824.0;
+  if (__any(far)) {
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if (fabs(x[j]) > 1073741824.0) sincos(x[j], &s[j], &c[j]);
+  }
+}
 // Pin a (uniform) global pointer to SGPRs, so that per-lane accesses at a
 // 32-bit offset from it use the scalar-base addressing form.
 __device__ __forceinline__ const RIFT_GLOBAL char* uniform_ptr(const RIFT_GLOBAL char* p) {
@@ -195,7 +276,7 @@ template <class R>
 struct Tab;
 template <>
 struct Tab<double> {
-  static constexpr int W = QW64;
+  static constexpr int W = QW64_SHORT;
   static __device__ __forceinline__ const RIFT_GLOBAL double* Q(PDesc P) { return as_global(P->Q64); }
   static __device__ __forceinline__ const RIFT_CONST double* C(PDesc P) { return as_const(P->C64); }
   static __device__ __forceinline__ double y(PDesc P, int i, int n) { return P->ycoef[i][n]; }
@@ -571,13 +652,7 @@ __device__ __forceinline__ double data_group(PDesc P, const RIFT_GLOBAL char* Qb
   return acc;
 }
 
-// Result of one sample evaluation.
-struct Eval {
-  double lnL;
-  float bound;  // a-priori |lnL - lnL_FP64| bound (FP32 arithmetic only)
-};
-
-// Data term of one sample with its taps read straight from the table.
+// Data term of one sample from a table of short rows.
 template <class R, int KT, int L, bool CPLX = false>
 __device__ __forceinline__ double data_direct(PDesc P, RIFT_LDS unsigned char* stage, const int32_t* row,
                                               const R* sfr, const R* Fre, const R* Fim, const R* cn,
@@ -604,6 +679,445 @@ __device__ __forceinline__ double data_direct(PDesc P, RIFT_LDS unsigned char* s
                                                                 Fre, Fim, cn, sn, cf, sf, im);
   return data;
 }
+
+// The model-norm contraction of FP64 (up to three detectors) in steps, for
+// interleaving with the data term's reads: acc[c] = sum_b C[b][c] beta_b(incl, phi),
+// the rows of the basis in pairs of one degree n and phase q,
+//   q = 0: (T_n, T_n+1), n = 1, 3, ..;  q >= 1: T_n (cos q phi, sin q phi),
+// T_n = cos(n incl) for even q and sin(n incl) for odd q, from three-term
+// recurrences in n: no table of the harmonics is kept.  A cycle is the pairs of
+// an odd and the next even q, unrolled; step<S> takes RPS rows of the cycle,
+// whose coefficients were loaded into SGPRs one step ahead.
+template <int KT, int L>
+struct NormWalk {
+  static constexpr int NI = 2 * L, W = 3 * KT;
+  static constexpr int PAIRS = 2 * NI + 1, CYCLES = NI / 2;
+  static constexpr int RPS = KT == 2 ? 4 : 2;                // at most 48 SGPRs (KT <= 3)
+  static constexpr int STEPS = (2 * PAIRS + RPS - 1) / RPS;  // the last may be short
+  static_assert(Cls<L>::B == 1 + NI + 2 * CYCLES * PAIRS, "row 0, the pairs of q = 0, and the cycles");
+  static constexpr int rows(int S, int all) { return all - S * RPS < RPS ? all - S * RPS : RPS; }
+  const RIFT_CONST double* C;
+  double buf[RPS * W];
+  double bx, by, px, py;  // the pair's values, and those before
+  double ex, ey;          // e^{i q phi}
+  double ci, si, cf, sf;
+
+  template <int ROWS>
+  __device__ __forceinline__ void load() {
+    const RIFT_CONST double* p = opaque(C);
+#pragma unroll
+    for (int i = 0; i < ROWS * W; ++i) buf[i] = p[i];
+  }
+  template <int ROWS>
+  __device__ __forceinline__ void wait() {
+#pragma unroll
+    for (int i = 0; i < ROWS * W; ++i) pin_s(buf[i]);
+  }
+  __device__ __forceinline__ void add(int row, double b, double* acc) {
+#pragma unroll
+    for (int c = 0; c < W; ++c) acc[c] = fma(buf[row * W + c], b, acc[c]);
+  }
+  template <int ROWS, int NEXT>
+  __device__ __forceinline__ void done(double* acc) {
+#pragma unroll
+    for (int c = 0; c < W; ++c) pin(acc[c]);
+    C += ROWS * W;
+    load<NEXT>();
+  }
+  // step S of the rows after row 0 with q = 0
+  template <int S>
+  __device__ __forceinline__ void first(double* acc) {
+    if constexpr (S * RPS < NI) {
+      constexpr int N = rows(S, NI);
+      wait<N>();
+#pragma unroll
+      for (int r = 0; r < N; ++r) {
+        add(r, bx, acc);
+        const double t = fma(2.0 * ci, bx, -px);
+        px = bx;
+        bx = t;
+      }
+      done<N, (S + 1) * RPS < NI ? rows(S + 1, NI) : rows(0, 2 * PAIRS)>(acc);
+      first<S + 1>(acc);
+    }
+  }
+  __device__ __forceinline__ void start(const RIFT_CONST double* C0, double ci_, double si_, double cf_, double sf_,
+                                        double* acc) {
+    ci = ci_;
+    si = si_;
+    cf = cf_;
+    sf = sf_;
+    C = C0 + W;
+    load<rows(0, NI)>();
+#pragma unroll
+    for (int c = 0; c < W; ++c) acc[c] = C0[c];
+    bx = ci;
+    px = 1.0;
+    first<0>(acc);
+    ex = 1.0;
+    ey = 0.0;
+  }
+  __device__ __forceinline__ void turn() {
+    const double t = ex * cf - ey * sf;
+    ey = ex * sf + ey * cf;
+    ex = t;
+  }
+  // pair J of the cycle's
+  template <int J>
+  __device__ __forceinline__ void pair() {
+    if constexpr (J == 0) {
+      turn();
+      bx = si * ex;
+      by = si * ey;
+      px = py = 0.0;
+    } else if constexpr (J == NI) {
+      turn();
+      bx = ex;
+      by = ey;
+      px = ci * ex;
+      py = ci * ey;
+    } else {
+      const double x = fma(2.0 * ci, bx, -px), y = fma(2.0 * ci, by, -py);
+      px = bx;
+      py = by;
+      bx = x;
+      by = y;
+    }
+  }
+  template <int S>
+  __device__ __forceinline__ void step(double* acc, bool last) {
+    constexpr int N = rows(S, 2 * PAIRS);
+    wait<N>();
+    pair<S * RPS / 2>();
+    add(0, bx, acc);
+    add(1, by, acc);
+    if constexpr (N == 4) {
+      pair<S * RPS / 2 + 1>();
+      add(2, bx, acc);
+      add(3, by, acc);
+    }
+    if constexpr (S + 1 < STEPS) {
+      done<N, rows(S + 1, 2 * PAIRS)>(acc);
+    } else {  // the next cycle's; the last reads its own rows again
+      static_assert(rows(0, 2 * PAIRS) >= N, "a short step is read again in part of a whole one");
+      if (last) C -= (rows(0, 2 * PAIRS) - N) * W + N * W;
+      done<N, rows(0, 2 * PAIRS)>(acc);
+    }
+  }
+  // steps A .. B - 1
+  template <int A, int B>
+  __device__ __forceinline__ void steps(double* acc, bool last) {
+    if constexpr (A < B) {
+      step<A>(acc, last);
+      steps<A + 1, B>(acc, last);
+    }
+  }
+};
+// The detector counts that walk: the accumulators and antenna factors of five spill
+// beside the reads (5 detectors, 21 modes, 3e5 samples: 198 us with the walk, 189
+// with the contraction after the reads).
+constexpr bool walks(int KT) { return KT <= 3; }
+constexpr int WALK_GROUPS = 2;  // groups of eight modes (of one detector) per cycle
+
+// The modes of a group of eight, two per unit of the group's first detector:
+// their coefficients are loaded (fetch) before the unit's share of the norm and
+// used (take(slot, m, d_i(incl))) after it.
+template <int NY>
+struct ModeWalk {
+  double c[2][NY];
+  int m[2], odd[2];
+  __device__ __forceinline__ void fetch(PDesc P, int i0, int M) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int i = i0 + j < M ? i0 + j : M - 1;  // the slots past M repeat it (their taps are zero)
+      m[j] = P->m[i];
+      odd[j] = P->odd[i];
+#pragma unroll
+      for (int n = 0; n < NY; ++n) c[j][n] = P->ycoef[i][n];
+    }
+  }
+  // d_i(incl) from cos incl and sin incl alone (Clenshaw's recurrence): no
+  // table of the harmonics is kept through the reads
+  __device__ __forceinline__ double d(int j, double ci, double si) const {
+    const double c2 = 2.0 * ci;
+    double b1 = 0.0, b2 = 0.0;
+#pragma unroll
+    for (int n = NY - 1; n >= 1; --n) {
+      const double b = fma(c2, b1, c[j][n] - b2);
+      b2 = b1;
+      b1 = b;
+    }
+    return odd[j] ? si * b1 : fma(ci, b1, c[j][0] - b2);
+  }
+};
+
+// The FP64 reads of the data term, detector by detector in each group of eight
+// modes.
+//
+// The unit is one aligned 128-byte line per lane, one stencil row of a group:
+// every line that a read brings into the vector cache is used whole (blocks of
+// four rows of two modes straddled two lines three times in four: 19.25 lines a
+// sample and detector at 21 modes, where this reads 12).  The lines are read
+// cooperatively, straight to LDS: eight lanes fetch the eight 16-byte chunks of
+// one lane's line, so that a read instruction touches 8 lines.  Lane
+// l = 8 q + c' of read t fetches chunk c = c' ^ key(j) of the line of lane
+// j = 8 t + q, which lands at j * 128 + c' * 16; with key(j) = (j >> 1) & 7
+// the eight lanes of equal j * 128 mod 256 within any sixteen consecutive lanes
+// read eight different 16-byte columns, so lane j's own reads of its chunks
+// are free of bank conflicts.
+//
+// Units stream through the wavefront's two LDS buffers: unit u + 1 is in
+// flight while unit u is combined.  The whole wavefront calls this together.
+// Offsets are 32-bit, so a table is read in windows of 2^24 rows: one, but for
+// the longest.
+constexpr int ROWS_WINDOW = 1 << 24;
+typedef double Cplx __attribute__((ext_vector_type(2)));
+template <int KT, int W>
+struct RowReader {
+  static constexpr int UNITS = W / 2;                        // of a group: of 4 / UNITS rows each
+  static constexpr uint32_t ROW = W * sizeof(C2<double>);    // bytes
+  static constexpr int LAST = UNITS - 1;
+  static_assert(4 * ROW == 128 * UNITS && (W == QW64 || W == QW64_SHORT), "units of 128 bytes");
+  static constexpr uint32_t BIAS = 3072;
+  PDesc P;
+  const int32_t* row;
+  RIFT_LDS unsigned char* lds;
+  const RIFT_GLOBAL char *series, *first, *next;  // this group, detector 0's, and the next
+  uint64_t kstride, gstride;
+  uint32_t off[8], rbase;
+  int K, window, left, k, p;  // left: groups of all detectors still to come, this one included
+  int flip;                   // the buffer of a group's first unit (0 where a group has four)
+
+  __device__ __forceinline__ void offsets(int kk) {
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const int q = lane >> 3;
+    // key(8 t + q) = ((t & 1) << 2) | (q >> 1): the chunks of even and odd reads
+    const uint32_t cx0 = (uint32_t)((lane & 7) ^ (q >> 1)) << 4;
+    const uint32_t r = (uint32_t)(by_det<KT>(row, kk) - window);
+    const uint32_t b = (r < (uint32_t)ROWS_WINDOW ? r : 0u) * ROW + BIAS;
+    // read t's immediate offset, (t & 3) KB, goes to both addresses: the
+    // source offsets are biased by the largest
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      off[t] = (uint32_t)__shfl((int)b, 8 * t + q) + ((t & 1) ? cx0 ^ 64u : cx0) - (uint32_t)(t & 3) * 1024u;
+  }
+  __device__ __forceinline__ void issue(const RIFT_GLOBAL char* from, int tap) {
+    const RIFT_GLOBAL char* ser = uniform_ptr(from + (tap % UNITS) * 128 - BIAS);
+    RIFT_LDS unsigned char* dst = lds + ((tap + flip) & 1) * STAGE_UNIT;
+#define RIFT_READ(t) \
+  __builtin_amdgcn_global_load_lds((const RIFT_GLOBAL void*)(ser + off[t]), (RIFT_LDS void*)(dst + (t & 4) * 1024), 16, \
+                                   (t & 3) * 1024, 0)
+    RIFT_READ(0);
+    RIFT_READ(1);
+    RIFT_READ(2);
+    RIFT_READ(3);
+    RIFT_READ(4);
+    RIFT_READ(5);
+    RIFT_READ(6);
+    RIFT_READ(7);
+#undef RIFT_READ
+  }
+  __device__ __forceinline__ void start(PDesc P_, RIFT_LDS unsigned char* stage, const int32_t* row_, int window_) {
+    P = P_;
+    row = row_;
+    window = window_;
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    // chunk c of this lane's line: rbase ^ (c << 4)
+    lds = (RIFT_LDS unsigned char*)(uintptr_t)(uint32_t)uniform_i((int)(uintptr_t)stage);
+    rbase = (uint32_t)lane * 128u + ((uint32_t)((lane >> 1) & 7) << 4);
+    K = P->K;
+    const int NGR = q_groups(P->M, W);
+    left = K * NGR;
+    flip = 0;
+    gstride = (uint64_t)(P->n_t + 2 * QPAD) * ROW;
+    kstride = (uint64_t)NGR * gstride;
+    series = first = (const RIFT_GLOBAL char*)as_global(P->Q64) + (uint64_t)(uint32_t)window * ROW;
+    k = p = 0;
+    offsets(0);
+    issue(series, 0);
+  }
+  // Before unit `tap` of the current group is combined: the next unit's reads.
+  __device__ __forceinline__ void ahead(int tap) {
+    // the other buffer's values are in registers already
+    asm volatile("" ::: "memory");
+    if (tap == 0) next = k + 1 < K ? series + kstride : first + gstride;
+    if (tap < LAST) {
+      issue(series, tap + 1);
+    } else if (left > 1) {
+      if constexpr (UNITS == 1) offsets(k + 1 < K ? k + 1 : 0);
+      issue(next, UNITS);
+    }
+  }
+  // Unit `tap` of the current group.
+  __device__ __forceinline__ void fetch(int tap, Cplx* v) {
+    // the newer unit's eight reads may still be in flight
+    if (tap == LAST && left == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    if (UNITS > 1 && tap == LAST - 1 && left > 1) offsets(k + 1 < K ? k + 1 : 0);
+    const RIFT_LDS unsigned char* src = lds + ((tap + flip) & 1) * STAGE_UNIT;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = *(const RIFT_LDS Cplx*)(src + (rbase ^ ((uint32_t)c << 4)));
+    // all of them at once, in registers before the buffer's next refill
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
+                 :
+                 : "memory");
+  }
+  __device__ __forceinline__ void advance() {
+    --left;
+    if (UNITS & 1) flip ^= 1;
+    series = next;
+    if (++k == K) {
+      k = 0;
+      ++p;
+      first = next;
+    }
+  }
+};
+// Whether a sample's stencil starts in the window of rows.
+__device__ __forceinline__ bool in_window(int32_t row, int window) {
+  return (uint32_t)(row - window) < (uint32_t)ROWS_WINDOW;
+}
+
+// The data term of one sample in FP64 and, with NORM, the model-norm contraction
+// acc (see NormWalk) in the shadow of its reads.  Y_i = d_i(incl) e^{i m_i phi};
+// the modes are sorted by m, so the phase walks upward from e^{i m_min phi}.
+// With CPLX, the imaginary part goes to *im.
+template <int KT, int L, bool NORM, bool CPLX>
+struct DataNorm {
+  static constexpr int W = QW64;
+  static constexpr int UNITS = RowReader<KT, W>::UNITS;
+  PDesc P;
+  const int32_t* row;
+  const double *sfr, *Fre, *Fim;
+  double* acc;
+  double ci, si, cf, sf;
+  double re, im;
+  RowReader<KT, W> R;
+  NormWalk<KT, L> walk;
+  ModeWalk<L + 1> mode;
+  C2<double> ph;
+  int mc;
+  double w[4], yx[W], yy[W], qx[W], qy[W];
+
+  __device__ __forceinline__ void modes(int t) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      while (mc < mode.m[j]) {
+        phase_up(ph, cf, sf);
+        ++mc;
+      }
+      const double d = mode.d(j, ci, si);
+      yx[2 * t + j] = d * ph.x;
+      yy[2 * t + j] = d * ph.y;
+    }
+  }
+  __device__ __forceinline__ void take(int t) {
+    Cplx v[8];
+    R.fetch(t, v);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {  // row t 8 / W + c / W of the stencil, mode c % W
+      const int r = t * (8 / W) + c / W, s = c % W;
+      qx[s] = r == 0 ? w[r] * v[c].x : fma(w[r], v[c].x, qx[s]);
+      qy[s] = r == 0 ? w[r] * v[c].y : fma(w[r], v[c].y, qy[s]);
+      pin(qx[s]);
+      pin(qy[s]);
+    }
+  }
+  __device__ __forceinline__ void fold() {
+    double zr = 0.0, zi = 0.0;
+#pragma unroll
+    for (int s = 0; s < W; ++s) {
+      zr = fma(yx[s], qx[s], zr);
+      zr = fma(yy[s], qy[s], zr);
+      zi = fma(yx[s], qy[s], zi);
+      zi = fma(-yy[s], qx[s], zi);
+    }
+    if (P->n_t + 2 * QPAD > ROWS_WINDOW && !in_window(by_det<KT>(row, R.k), R.window)) zr = zi = 0.0;
+    const double fr = by_det<KT>(Fre, R.k), fi = by_det<KT>(Fim, R.k);
+    re = fma(fr, zr, re);
+    re = fma(fi, zi, re);
+    if constexpr (CPLX) {
+      im = fma(fr, zi, im);
+      im = fma(-fi, zr, im);
+      pin(im);
+    }
+    pin(re);
+    R.advance();
+  }
+  // Unit u of a cycle's, with the cycle's steps spread over both halves of the
+  // units (CYCLE), or alone.
+  template <int U, int N, bool CYCLE>
+  __device__ __forceinline__ void unit(bool last) {
+    constexpr int T = U % UNITS, S = NormWalk<KT, L>::STEPS;
+    if (!CYCLE || R.left > 0) {
+      if constexpr (T == 0) lagrange4(by_det<KT>(sfr, R.k), w);
+      R.ahead(T);
+      if (R.k == 0) mode.fetch(P, R.p * W + 2 * T, P->M);
+    }
+    if constexpr (CYCLE) walk.template steps<2 * U * S / (2 * N), (2 * U + 1) * S / (2 * N)>(acc, last);
+    if (!CYCLE || R.left > 0) {
+      if (R.k == 0) modes(T);
+      take(T);
+    }
+    if constexpr (CYCLE) walk.template steps<(2 * U + 1) * S / (2 * N), (2 * U + 2) * S / (2 * N)>(acc, last);
+    if (T == UNITS - 1 && (!CYCLE || R.left > 0)) fold();
+  }
+  template <int U, int N, bool CYCLE>
+  __device__ __forceinline__ void units(bool last) {
+    if constexpr (U < N) {
+      unit<U, N, CYCLE>(last);
+      units<U + 1, N, CYCLE>(last);
+    }
+  }
+  __device__ __forceinline__ void run(RIFT_LDS unsigned char* stage) {
+    const int rows = P->n_t + 2 * QPAD;
+    re = im = 0.0;
+#pragma unroll 1
+    for (int window = 0; window < rows; window += ROWS_WINDOW) {
+      R.start(P, stage, row, window);
+      ph.x = 1.0;
+      ph.y = 0.0;
+      const int mmin = P->m_min;
+      for (int t = 0; t < -mmin; ++t) phase_down(ph, cf, sf);
+      mc = mmin < 0 ? mmin : 0;
+      if constexpr (NORM) {
+        if (window == 0) {
+          walk.start(as_const(P->C64), ci, si, cf, sf, acc);
+#pragma unroll 1
+          for (int it = 0; it < NormWalk<KT, L>::CYCLES; ++it)
+            units<0, UNITS * WALK_GROUPS, true>(it + 1 == NormWalk<KT, L>::CYCLES);
+        }
+      }
+#pragma unroll 1
+      while (R.left > 0) units<0, UNITS, false>(false);
+    }
+  }
+};
+template <int KT, int L, bool NORM, bool CPLX>
+__device__ __forceinline__ double data_rows(PDesc P, RIFT_LDS unsigned char* stage, const int32_t* row,
+                                            const double* sfr, const double* Fre, const double* Fim,
+                                            double ci, double si, double cf, double sf, double* acc, double* im) {
+  DataNorm<KT, L, NORM, CPLX> D;
+  D.P = P;
+  D.row = row;
+  D.sfr = sfr;
+  D.Fre = Fre;
+  D.Fim = Fim;
+  D.acc = acc;
+  D.ci = ci;
+  D.si = si;
+  D.cf = cf;
+  D.sf = sf;
+  D.run(stage);
+  if constexpr (CPLX) *im = D.im;
+  return D.re;
+}
+// Result of one sample evaluation.
+struct Eval {
+  double lnL;
+  float bound;  // a-priori |lnL - lnL_FP64| bound (FP32 arithmetic only)
+};
 
 // Antenna factors of one sample and, for the data term, its stencils: the sky
 // frame (FP64), the polarisation tensors and F_k = F+ + i Fx (R), and per
@@ -635,17 +1149,42 @@ __device__ __forceinline__ void sky_stencils(PDesc P, double t, Sky<R, KT>& S) {
     S.sfr[k] = s;
   }
 }
+// (sin, cos) of incl and phi, which the harmonics take, come out with them.
 template <class R, int KT, bool STENCIL>
-__device__ __forceinline__ void sky_eval(PDesc P, double ra, double dec, double psi, double tref, Sky<R, KT>& S) {
+__device__ __forceinline__ void sky_eval(PDesc P, double ra, double dec, double psi, double incl, double phi,
+                                         double tref, Sky<R, KT>& S, R& si, R& ci, R& sf, R& cf) {
   double sg, cg, sd, cd;
-  sincos_(P->gmst - ra, &sg, &cg);
-  sincos_(dec, &sd, &cd);
+  R sp, cp;
+  if constexpr (sizeof(R) == 8) {
+    const double a[5] = {P->gmst - ra, dec, psi, incl, phi};
+    double s[5], c[5];
+    sincos_many<5>(a, s, c);
+    sg = s[0];
+    cg = c[0];
+    sd = s[1];
+    cd = c[1];
+    sp = s[2];
+    cp = c[2];
+    si = s[3];
+    ci = c[3];
+    sf = s[4];
+    cf = c[4];
+  } else {
+    const double a[2] = {P->gmst - ra, dec};
+    double s[2], c[2];
+    sincos_many<2>(a, s, c);
+    sg = s[0];
+    cg = c[0];
+    sd = s[1];
+    cd = c[1];
+    sincosf((R)psi, &sp, &cp);
+    sincosf((R)incl, &si, &ci);
+    sincosf((R)phi, &sf, &cf);
+  }
   const double N0 = cd * cg, N1 = -cd * sg, N2 = sd;
   S.N[0] = N0;
   S.N[1] = N1;
   S.N[2] = N2;
-  R sp, cp;
-  sincos_((R)psi, &sp, &cp);
   const R ea0 = (R)sg, ea1 = (R)cg;
   const R ed0 = (R)(-sd * cg), ed1 = (R)(sd * sg), ed2 = (R)cd;
   const R X0 = -cp * ea0 + sp * ed0, X1 = -cp * ea1 + sp * ed1, X2 = sp * ed2;
@@ -776,11 +1315,8 @@ __device__ __forceinline__ void norm_contract(PDesc P, R* __restrict__ trig, int
   }
 }
 
-template <class R, int KT, int L, bool BOUND>
-__device__ __forceinline__ double quad_term(PDesc P, R* __restrict__ trig, int ts, R ci, R si, R cf, R sf,
-                                            const R* Fre, const R* Fim, double* wq_out) {
-  R acc[3 * KT];
-  norm_contract<R, KT, L>(P, trig, ts, ci, si, cf, sf, acc);
+template <class R, int KT, bool BOUND>
+__device__ __forceinline__ double quad_of(PDesc P, const R* acc, const R* Fre, const R* Fim, double* wq_out) {
   double quad = 0.0;
   double wq = 0.0;  // model-norm part of the error bound (see PointDesc)
 #pragma unroll
@@ -799,6 +1335,13 @@ __device__ __forceinline__ double quad_term(PDesc P, R* __restrict__ trig, int t
   if (BOUND) *wq_out = wq;
   return quad;
 }
+template <class R, int KT, int L, bool BOUND>
+__device__ __forceinline__ double quad_term(PDesc P, R* __restrict__ trig, int ts, R ci, R si, R cf, R sf,
+                                            const R* Fre, const R* Fim, double* wq_out) {
+  R acc[3 * KT];
+  norm_contract<R, KT, L>(P, trig, ts, ci, si, cf, sf, acc);
+  return quad_of<R, KT, BOUND>(P, acc, Fre, Fim, wq_out);
+}
 
 // cos(n incl), sin(n incl) for n < NY by the Chebyshev recurrences.
 template <class R, int NY>
@@ -816,6 +1359,35 @@ __device__ __forceinline__ void incl_harmonics(R ci, R si, R* cn, R* sn) {
       s1 = s2;
     }
   }
+}
+
+// The data term of one sample in FP64 and, with NORM, the model-norm contraction
+// acc: from 13 modes on by rows, up to three detectors with the contraction between
+// the units; otherwise one after the other.
+template <int KT, int L, bool NORM, bool CPLX>
+__device__ __forceinline__ double data_norm(PDesc P, double* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
+                                            const int32_t* row, const double* sfr, const double* Fre,
+                                            const double* Fim, double ci, double si, double cf, double sf, double* acc,
+                                            double* im) {
+  double data;
+  if constexpr (Cls<L>::MAXM > QW64_SHORT_MODES) {
+    if (P->w64 == QW64) {
+      __builtin_amdgcn_s_setprio(1);
+      data = data_rows<KT, L, NORM && walks(KT), CPLX>(P, stage, row, sfr, Fre, Fim, ci, si, cf, sf, acc, im);
+      __builtin_amdgcn_s_setprio(0);
+      if constexpr (NORM && !walks(KT)) norm_contract<double, KT, L>(P, trig, ts, ci, si, cf, sf, acc);
+      return data;
+    }
+  }
+  constexpr int NY = Cls<L>::NY;
+  double cn[NY], sn[NY];
+  incl_harmonics<double, NY>(ci, si, cn, sn);
+  if constexpr (CPLX) *im = 0.0;
+  __builtin_amdgcn_s_setprio(1);
+  data = data_direct<double, KT, L, CPLX>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf, im);
+  __builtin_amdgcn_s_setprio(0);
+  if constexpr (NORM) norm_contract<double, KT, L>(P, trig, ts, ci, si, cf, sf, acc);
+  return data;
 }
 
 // lnL = x data - x^2 quad with x = D_ref / D (FP64), NaN for a poisoned
@@ -898,20 +1470,15 @@ struct TimeRule {
 // data term once per time (new stencils, the same F and Y).  The log-sum
 // runs online with one exp per time.  A poisoned sample gives NaN.  The
 // whole wavefront calls this together (the data term reads cooperatively).
-template <class R, int KT, int L, class DataFn>
-__device__ __forceinline__ double eval_tmarg_with(PDesc P, R* __restrict__ trig, int ts, double ra, double dec,
-                                                  double psi, double incl, double phi, double dist,
-                                                  const TimeRule& T, DataFn&& data_fn) {
-  constexpr int NY = Cls<L>::NY;
+template <class R, int KT, int L>
+__device__ __forceinline__ double eval_tmarg(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
+                                             double ra, double dec, double psi, double incl, double phi, double dist,
+                                             const TimeRule& T) {
+  static_assert(sizeof(R) == 8, "FP64");
   reduce_angles<R>(psi, incl, phi);
   Sky<R, KT> S;
-  sky_eval<R, KT, false>(P, ra, dec, psi, 0.0, S);
-  R si, ci;
-  sincos_((R)incl, &si, &ci);
-  R cn[NY], sn[NY];
-  incl_harmonics<R, NY>(ci, si, cn, sn);
-  R sf, cf;
-  sincos_((R)phi, &sf, &cf);
+  R si, ci, sf, cf;
+  sky_eval<R, KT, false>(P, ra, dec, psi, incl, phi, 0.0, S, si, ci, sf, cf);
   double wq = 0.0;
   const double quad = quad_term<R, KT, L, false>(P, trig, ts, ci, si, cf, sf, S.Fre, S.Fim, &wq);
   const double x = P->d_ref / dist;
@@ -922,9 +1489,8 @@ __device__ __forceinline__ double eval_tmarg_with(PDesc P, R* __restrict__ trig,
     S.bad = false;
     sky_stencils<R, KT>(P, fma((double)k, T.h, T.t0), S);
     bad = bad || S.bad;
-    __builtin_amdgcn_s_setprio(1);
-    const double data = data_fn(S.row, S.sfr, S.Fre, S.Fim, cn, sn, cf, sf);
-    __builtin_amdgcn_s_setprio(0);
+    const double data = data_norm<KT, L, false, false>(P, trig, ts, stage, S.row, S.sfr, S.Fre, S.Fim, ci, si, cf, sf,
+                                                       nullptr, nullptr);
     const double lw = (k == 0 || k == T.n - 1) ? T.lw_end : ((k & 1) ? T.lw_odd : T.lw_even);
     const double l = fma(x, data, base) + lw;
     if (l > m) {
@@ -946,21 +1512,16 @@ __device__ __forceinline__ double eval_tmarg_with(PDesc P, R* __restrict__ trig,
 // The reconstruction between the nodes and the exponential sum run in a
 // separate kernel over these values.  The whole wavefront calls this
 // together (the data term reads cooperatively).
-template <class R, int KT, int L, class DataFn>
-__device__ __forceinline__ double eval_tkappa_with(PDesc P, R* __restrict__ trig, int ts, double ra, double dec,
-                                                   double psi, double incl, double phi, double dist,
-                                                   const TimeRule& T, RIFT_GLOBAL double* kap, int64_t N, int64_t i,
-                                                   bool live, DataFn&& data_fn) {
-  constexpr int NY = Cls<L>::NY;
+template <class R, int KT, int L>
+__device__ __forceinline__ double eval_tkappa(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
+                                              double ra, double dec, double psi, double incl, double phi, double dist,
+                                              const TimeRule& T, RIFT_GLOBAL double* kap, int64_t N, int64_t i,
+                                              bool live) {
+  static_assert(sizeof(R) == 8, "FP64");
   reduce_angles<R>(psi, incl, phi);
   Sky<R, KT> S;
-  sky_eval<R, KT, false>(P, ra, dec, psi, 0.0, S);
-  R si, ci;
-  sincos_((R)incl, &si, &ci);
-  R cn[NY], sn[NY];
-  incl_harmonics<R, NY>(ci, si, cn, sn);
-  R sf, cf;
-  sincos_((R)phi, &sf, &cf);
+  R si, ci, sf, cf;
+  sky_eval<R, KT, false>(P, ra, dec, psi, incl, phi, 0.0, S, si, ci, sf, cf);
   double wq = 0.0;
   const double quad = quad_term<R, KT, L, false>(P, trig, ts, ci, si, cf, sf, S.Fre, S.Fim, &wq);
   const double x = P->d_ref / dist;
@@ -970,9 +1531,8 @@ __device__ __forceinline__ double eval_tkappa_with(PDesc P, R* __restrict__ trig
     S.bad = false;
     sky_stencils<R, KT>(P, fma((double)k, T.h, T.t0), S);
     bad = bad || S.bad;
-    __builtin_amdgcn_s_setprio(1);
-    const double data = data_fn(S.row, S.sfr, S.Fre, S.Fim, cn, sn, cf, sf);
-    __builtin_amdgcn_s_setprio(0);
+    const double data = data_norm<KT, L, false, false>(P, trig, ts, stage, S.row, S.sfr, S.Fre, S.Fim, ci, si, cf, sf,
+                                                       nullptr, nullptr);
     if (live) kap[(int64_t)k * N + i] = x * data;
   }
   return bad ? __builtin_nan("") : base;
@@ -989,27 +1549,19 @@ __device__ __forceinline__ double eval_tkappa_with(PDesc P, R* __restrict__ trig
 // Returns whether the sample is poisoned.  The rules over u run in a kernel of
 // their own over these five values.
 constexpr int PSI_ROWS = 5;
-template <class R, int KT, int L, class DataFn>
-__device__ __forceinline__ bool eval_pmarg_with(PDesc P, R* __restrict__ trig, int ts, double ra, double dec,
-                                                double psi, double incl, double phi, double tref, double dist,
-                                                RIFT_GLOBAL double* out, int64_t N, int64_t i, bool live,
-                                                DataFn&& data_fn) {
-  constexpr int NY = Cls<L>::NY;
+template <class R, int KT, int L>
+__device__ __forceinline__ bool eval_pmarg(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
+                                           double ra, double dec, double psi, double incl, double phi, double tref,
+                                           double dist, RIFT_GLOBAL double* out, int64_t N, int64_t i, bool live) {
   reduce_angles<R>(psi, incl, phi);
   Sky<R, KT> S;
-  sky_eval<R, KT, true>(P, ra, dec, psi, tref, S);
-  R si, ci;
-  sincos_((R)incl, &si, &ci);
-  R cn[NY], sn[NY];
-  incl_harmonics<R, NY>(ci, si, cn, sn);
-  R sf, cf;
-  sincos_((R)phi, &sf, &cf);
+  R si, ci, sf, cf;
+  sky_eval<R, KT, true>(P, ra, dec, psi, incl, phi, tref, S, si, ci, sf, cf);
+  static_assert(sizeof(R) == 8, "FP64");
   double wim = 0.0;
-  __builtin_amdgcn_s_setprio(1);
-  const double wre = data_fn(S.row, S.sfr, S.Fre, S.Fim, cn, sn, cf, sf, &wim);
-  __builtin_amdgcn_s_setprio(0);
   R acc[3 * KT];
-  norm_contract<R, KT, L>(P, trig, ts, ci, si, cf, sf, acc);
+  const double wre = data_norm<KT, L, true, true>(P, trig, ts, stage, S.row, S.sfr, S.Fre, S.Fim, ci, si, cf, sf, acc,
+                                                  &wim);
   double A0 = 0.0, Bre = 0.0, Bim = 0.0;
 #pragma unroll
   for (int k = 0; k < KT; ++k) {
@@ -1055,110 +1607,87 @@ struct AngleRule {
 };
 constexpr int ERAI_MAX_M = 4;
 
-// sum_k conj(F_k) sum_{i: m_i = m} d_i Qhat_{k,i} of detectors K0 .. K0+G-1,
-// added to T[m + ERAI_MAX_M]: data_group's reads and pipeline, with the running
-// sum of each detector folded into T where m changes (modes are sorted by m).
-template <int NY, int K0, int G>
-__device__ __forceinline__ void data_harmonics(PDesc P, const RIFT_GLOBAL char* Qb, uint64_t gstride, uint64_t kstride,
-                                               int M, int NGR, const uint32_t* boff, RIFT_LDS unsigned char* stage,
-                                               const double* sfr, const double* Fre, const double* Fim,
-                                               const double* cn, const double* sn, C2<double>* T) {
-  constexpr int W = QW64;
-  typedef double R2 __attribute__((ext_vector_type(2)));
-  double w[G][4];
-#pragma unroll
-  for (int g = 0; g < G; ++g) lagrange4(sfr[K0 + g], w[g]);
-  C2<double> Z[G];
-#pragma unroll
-  for (int g = 0; g < G; ++g) Z[g].x = Z[g].y = 0.0;
-  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  const int q = lane >> 3;
-  const uint32_t cx0 = (uint32_t)((lane & 7) ^ (q >> 1)) << 4;
-  const uint32_t cx1 = (uint32_t)((lane & 7) ^ (4 | (q >> 1))) << 4;
-  uint32_t offt[G][8];
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int t = 0; t < 8; ++t) offt[g][t] = (uint32_t)__shfl((int)boff[K0 + g], 8 * t + q) + ((t & 1) ? cx1 : cx0);
-  const uint32_t rbase = (uint32_t)lane * 128u + ((uint32_t)((lane >> 1) & 7) << 4);
-  auto issue = [&](int p, int g, int b) {
-    const RIFT_GLOBAL char* ser = uniform_ptr(Qb + (uint64_t)(K0 + g) * kstride + (uint64_t)p * gstride);
-    RIFT_LDS unsigned char* dst = stage + b * STAGE_UNIT;
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-      __builtin_amdgcn_global_load_lds((const RIFT_GLOBAL void*)(ser + offt[g][t]), (RIFT_LDS void*)(dst + t * 1024),
-                                       16, 0, 0);
-  };
-  auto fold = [&](int g, int m) {
-    const double tr = Fre[K0 + g] * Z[g].x + Fim[K0 + g] * Z[g].y;
-    const double ti = Fre[K0 + g] * Z[g].y - Fim[K0 + g] * Z[g].x;
-#pragma unroll
-    for (int j = 0; j < 2 * ERAI_MAX_M + 1; ++j) {
-      if (j == m + ERAI_MAX_M) {  // uniform
-        T[j].x += tr;
-        T[j].y += ti;
-      }
-    }
-    Z[g].x = Z[g].y = 0.0;
-  };
-  // a group's modes: d, and the m before each (a repeated slot past M adds zeros to the last m)
-  double d[W];
-  int before[W], mlast = P->m_min;
-  auto modes = [&](int p) {
-#pragma unroll
-    for (int s = 0; s < W; ++s) {
-      const int i = p * W + s < M ? p * W + s : M - 1;
-      before[s] = mlast;
-      mlast = uniform_i(P->m[i]);
-      d[s] = mode_d<double, NY>(P, i, cn, sn);
-    }
-  };
-  auto consume = [&](int b, int g) {
-    const RIFT_LDS unsigned char* src = stage + b * STAGE_UNIT;
-    C2<double> u[4][W];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const R2 v = *(const RIFT_LDS R2*)(src + (rbase ^ ((uint32_t)c << 4)));
-      u[c >> 1][c & 1].x = v.x;
-      u[c >> 1][c & 1].y = v.y;
-    }
-#pragma unroll
-    for (int s = 0; s < W; ++s) {
-      const int m = s + 1 < W ? before[s + 1] : mlast;
-      if (before[s] != m) fold(g, before[s]);
-      const double qx = fma(w[g][3], u[3][s].x, fma(w[g][2], u[2][s].x, fma(w[g][1], u[1][s].x, w[g][0] * u[0][s].x)));
-      const double qy = fma(w[g][3], u[3][s].y, fma(w[g][2], u[2][s].y, fma(w[g][1], u[1][s].y, w[g][0] * u[0][s].y)));
-      Z[g].x = fma(d[s], qx, Z[g].x);
-      Z[g].y = fma(d[s], qy, Z[g].y);
-    }
-    pin(Z[g].x);
-    pin(Z[g].y);
-  };
-  constexpr int UPI = (G % 2 == 0) ? G : 2 * G;
-  const int total = NGR * G;
-  issue(0, 0, 0);
+// T[m + ERAI_MAX_M] += sum_k conj(F_k) sum_{i: m_i = m} d_i Qhat_{k,i}.
+template <int KT, int L, int W>
+__device__ __forceinline__ void data_harmonics_w(PDesc P, RIFT_LDS unsigned char* stage, const int32_t* row,
+                                               const double* sfr, const double* Fre, const double* Fim, double ci,
+                                               double si, C2<double>* T) {
+  const int M = P->M, rows = P->n_t + 2 * QPAD;
+  double d[W], qx[W], qy[W];
+  int m[W];
+  RowReader<KT, W> R;
+  ModeWalk<L + 1> mode;
 #pragma unroll 1
-  for (int p0 = 0; p0 < NGR; p0 += UPI / G) {
+  for (int window = 0; window < rows; window += ROWS_WINDOW) {
+    R.start(P, stage, row, window);
+#pragma unroll 1
+    while (R.left > 0) {
+      double w[4];
+      lagrange4(by_det<KT>(sfr, R.k), w);
 #pragma unroll
-    for (int v = 0; v < UPI; ++v) {
-      const int p = p0 + v / G;
-      const int g = v % G;
-      if (g == 0 && p >= NGR) break;
-      if (p * G + g + 1 < total) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        issue(g + 1 == G ? p + 1 : p, (g + 1) % G, (v + 1) & 1);
-        if (g == 0) modes(p);
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-      } else {
-        if (g == 0) modes(p);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      for (int t = 0; t < RowReader<KT, W>::UNITS; ++t) {
+        R.ahead(t);
+        if (R.k == 0) {
+          mode.fetch(P, R.p * W + 2 * t, M);
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            m[2 * t + j] = uniform_i(mode.m[j]);
+            d[2 * t + j] = mode.d(j, ci, si);
+          }
+        }
+        Cplx v[8];
+        R.fetch(t, v);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          const int r = t * (8 / W) + c / W, s = c % W;
+          qx[s] = r == 0 ? w[r] * v[c].x : fma(w[r], v[c].x, qx[s]);
+          qy[s] = r == 0 ? w[r] * v[c].y : fma(w[r], v[c].y, qy[s]);
+          pin(qx[s]);
+          pin(qy[s]);
+        }
       }
-      consume(v & 1, g);
+      const double fr = by_det<KT>(Fre, R.k), fi = by_det<KT>(Fim, R.k);
+      const bool in = rows <= ROWS_WINDOW || in_window(by_det<KT>(row, R.k), window);
+      // the modes are sorted by m: the running sum goes to T where m changes
+      double zr = 0.0, zi = 0.0;
+#pragma unroll
+      for (int s = 0; s < W; ++s) {
+        zr = fma(d[s], qx[s], zr);
+        zi = fma(d[s], qy[s], zi);
+        if (s + 1 == W || m[s + 1] != m[s]) {
+          if (!in) zr = zi = 0.0;
+          const double tr = fma(fr, zr, fi * zi), ti = fma(fr, zi, -fi * zr);
+#pragma unroll
+          for (int j = 0; j < 2 * ERAI_MAX_M + 1; ++j) {
+            if (j == m[s] + ERAI_MAX_M) {  // uniform
+              T[j].x += tr;
+              T[j].y += ti;
+            }
+          }
+          zr = zi = 0.0;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 2 * ERAI_MAX_M + 1; ++j) {
+        pin(T[j].x);
+        pin(T[j].y);
+      }
+      R.advance();
     }
   }
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-  for (int g = 0; g < G; ++g) fold(g, mlast);
+}
+
+template <int KT, int L>
+__device__ __forceinline__ void data_harmonics(PDesc P, RIFT_LDS unsigned char* stage, const int32_t* row,
+                                               const double* sfr, const double* Fre, const double* Fim, double ci,
+                                               double si, C2<double>* T) {
+  if constexpr (Cls<L>::MAXM > QW64_SHORT_MODES) {
+    if (P->w64 == QW64) {
+      data_harmonics_w<KT, L, QW64>(P, stage, row, sfr, Fre, Fim, ci, si, T);
+      return;
+    }
+  }
+  data_harmonics_w<KT, L, QW64_SHORT>(P, stage, row, sfr, Fre, Fim, ci, si, T);
 }
 
 // The model norm's harmonics in alpha: for every q, the basis rows' sums over
@@ -1318,39 +1847,17 @@ __device__ __forceinline__ bool eval_erai(PDesc P, double* __restrict__ trig, in
                                           double ra, double dec, double psi, double incl, double phi, double tref,
                                           double dist, const AngleRule& R, RIFT_GLOBAL double* out, int64_t N,
                                           int64_t i, bool live) {
-  constexpr int NY = Cls<L>::NY;
   Sky<double, KT> S;
-  sky_eval<double, KT, true>(P, ra, dec, psi, tref, S);
-  double si, ci;
-  sincos(incl, &si, &ci);
-  double cn[NY], sn[NY];
-  incl_harmonics<double, NY>(ci, si, cn, sn);
+  double si, ci, sf, cf;
+  sky_eval<double, KT, true>(P, ra, dec, psi, incl, phi, tref, S, si, ci, sf, cf);
   const double x = P->d_ref / dist;
   const double x2 = x * x;
-  double sf, cf;
-  sincos(phi, &sf, &cf);
   C2<double> T[2 * ERAI_MAX_M + 1];
 #pragma unroll
   for (int j = 0; j < 2 * ERAI_MAX_M + 1; ++j) T[j].x = T[j].y = 0.0;
-  {
-    const int M = P->M, NGR = q_groups(M, QW64);
-    uint32_t boff[KT];
-#pragma unroll
-    for (int k = 0; k < KT; ++k) boff[k] = (uint32_t)S.row[k] * (uint32_t)(QW64 * sizeof(C2<double>));
-    const RIFT_GLOBAL char* Qb = (const RIFT_GLOBAL char*)as_global(P->Q64);
-    const uint64_t gstride = (uint64_t)(P->n_t + 2 * QPAD) * (QW64 * sizeof(C2<double>));
-    const uint64_t kstride = (uint64_t)NGR * gstride;
-    constexpr int G0 = det_group_size(KT, 0), G1 = det_group_size(KT, 1), G2 = det_group_size(KT, 2);
-    __builtin_amdgcn_s_setprio(1);
-    data_harmonics<NY, 0, G0>(P, Qb, gstride, kstride, M, NGR, boff, stage, S.sfr, S.Fre, S.Fim, cn, sn, T);
-    if constexpr (G1 > 0)
-      data_harmonics<NY, det_group_start(KT, 1), G1>(P, Qb, gstride, kstride, M, NGR, boff, stage, S.sfr, S.Fre, S.Fim,
-                                                     cn, sn, T);
-    if constexpr (G2 > 0)
-      data_harmonics<NY, det_group_start(KT, 2), G2>(P, Qb, gstride, kstride, M, NGR, boff, stage, S.sfr, S.Fre, S.Fim,
-                                                     cn, sn, T);
-    __builtin_amdgcn_s_setprio(0);
-  }
+  __builtin_amdgcn_s_setprio(1);
+  data_harmonics<KT, L>(P, stage, S.row, S.sfr, S.Fre, S.Fim, ci, si, T);
+  __builtin_amdgcn_s_setprio(0);
   bool bad = S.bad || !(fabs(x) <= 1.0e300);
   // x T_m e^{-i m phi}, then c1 along 1, cos m alpha, sin m alpha
   const int mm = (R.nd - 1) / 2;
@@ -1399,88 +1906,42 @@ __device__ __forceinline__ bool eval_erai(PDesc P, double* __restrict__ trig, in
 
 // Everything per sample up to the distance: the terms.  R is the arithmetic
 // type of the bulk (FP64 or FP32); the sky frame, delays and the final
-// combination are always FP64.  The data term comes from
-// data_fn(row, sfr, Fre, Fim, cn, sn, cf, sf).
-template <class R, int KT, int L, bool BOUND, class DataFn>
-__device__ __forceinline__ Terms eval_terms_with(PDesc P, R* __restrict__ trig, int ts, double ra, double dec,
-                                                 double psi, double incl, double phi, double tref,
-                                                 DataFn&& data_fn) {
-  constexpr int NY = Cls<L>::NY;
+// combination are always FP64.  `stage` is this wavefront's STAGE_WAVE bytes of
+// LDS; the whole wavefront must call these together.
+template <class R, int KT, int L, bool BOUND>
+__device__ __forceinline__ Terms eval_terms(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
+                                            double ra, double dec, double psi, double incl, double phi,
+                                            double tref) {
   reduce_angles<R>(psi, incl, phi);
   Sky<R, KT> S;
-  sky_eval<R, KT, true>(P, ra, dec, psi, tref, S);
-  R si, ci;
-  sincos_((R)incl, &si, &ci);
-  R cn[NY], sn[NY];
-  incl_harmonics<R, NY>(ci, si, cn, sn);
-  R sf, cf;
-  sincos_((R)phi, &sf, &cf);
-  __builtin_amdgcn_s_setprio(1);
-  const double data = data_fn(S.row, S.sfr, S.Fre, S.Fim, cn, sn, cf, sf);
-  __builtin_amdgcn_s_setprio(0);
+  R si, ci, sf, cf;
+  sky_eval<R, KT, true>(P, ra, dec, psi, incl, phi, tref, S, si, ci, sf, cf);
   Terms t;
   t.wq = 0.0;
-  t.data = data;
-  t.quad = quad_term<R, KT, L, BOUND>(P, trig, ts, ci, si, cf, sf, S.Fre, S.Fim, &t.wq);
+  if constexpr (sizeof(R) == 8) {
+    static_assert(!BOUND, "the bound is the FP32 pass's");
+    double acc[3 * KT];
+    t.data = data_norm<KT, L, true, false>(P, trig, ts, stage, S.row, S.sfr, S.Fre, S.Fim, ci, si, cf, sf, acc, nullptr);
+    t.quad = quad_of<double, KT, false>(P, acc, S.Fre, S.Fim, &t.wq);
+  } else {
+    constexpr int NY = Cls<L>::NY;
+    R cn[NY], sn[NY];
+    incl_harmonics<R, NY>(ci, si, cn, sn);
+    __builtin_amdgcn_s_setprio(1);
+    t.data = data_direct<R, KT, L>(P, stage, S.row, S.sfr, S.Fre, S.Fim, cn, sn, cf, sf);
+    __builtin_amdgcn_s_setprio(0);
+    t.quad = quad_term<R, KT, L, BOUND>(P, trig, ts, ci, si, cf, sf, S.Fre, S.Fim, &t.wq);
+  }
   t.bad = S.bad;
   return t;
 }
 
-template <class R, int KT, int L, bool BOUND, class DataFn>
-__device__ __forceinline__ Eval eval_sample_with(PDesc P, R* __restrict__ trig, int ts, double ra,
-                                                 double dec, double psi, double incl, double phi,
-                                                 double tref, double dist, DataFn&& data_fn) {
-  const Terms t = eval_terms_with<R, KT, L, BOUND>(P, trig, ts, ra, dec, psi, incl, phi, tref, data_fn);
-  return combine<BOUND>(P, dist, t.data, t.quad, t.wq, t.bad);
-}
-
-// `stage` is this wavefront's STAGE_WAVE bytes of LDS; the whole wavefront
-// must call these together.
-template <class R, int KT, int L>
-__device__ __forceinline__ Terms eval_terms(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
-                                           double ra, double dec, double psi, double incl, double phi,
-                                           double tref) {
-  return eval_terms_with<R, KT, L, false>(
-      P, trig, ts, ra, dec, psi, incl, phi, tref,
-      [&](const int32_t* row, const R* sfr, const R* Fre, const R* Fim, const R* cn, const R* sn, R cf,
-          R sf) { return data_direct<R, KT, L>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf); });
-}
-template <class R, int KT, int L>
-__device__ __forceinline__ bool eval_pmarg(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
-                                          double ra, double dec, double psi, double incl, double phi, double tref,
-                                          double dist, RIFT_GLOBAL double* out, int64_t N, int64_t i, bool live) {
-  return eval_pmarg_with<R, KT, L>(
-      P, trig, ts, ra, dec, psi, incl, phi, tref, dist, out, N, i, live,
-      [&](const int32_t* row, const R* sfr, const R* Fre, const R* Fim, const R* cn, const R* sn, R cf, R sf,
-          double* im) { return data_direct<R, KT, L, true>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf, im); });
-}
-template <class R, int KT, int L>
-__device__ __forceinline__ double eval_tmarg(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
-                                            double ra, double dec, double psi, double incl, double phi, double dist,
-                                            const TimeRule& T) {
-  return eval_tmarg_with<R, KT, L>(
-      P, trig, ts, ra, dec, psi, incl, phi, dist, T,
-      [&](const int32_t* row, const R* sfr, const R* Fre, const R* Fim, const R* cn, const R* sn, R cf,
-          R sf) { return data_direct<R, KT, L>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf); });
-}
-template <class R, int KT, int L>
-__device__ __forceinline__ double eval_tkappa(PDesc P, R* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
-                                             double ra, double dec, double psi, double incl, double phi, double dist,
-                                             const TimeRule& T, RIFT_GLOBAL double* kap, int64_t N, int64_t i,
-                                             bool live) {
-  return eval_tkappa_with<R, KT, L>(
-      P, trig, ts, ra, dec, psi, incl, phi, dist, T, kap, N, i, live,
-      [&](const int32_t* row, const R* sfr, const R* Fre, const R* Fim, const R* cn, const R* sn, R cf,
-          R sf) { return data_direct<R, KT, L>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf); });
-}
 template <class R, int KT, int L, bool BOUND>
 __device__ __forceinline__ Eval eval_sample(PDesc P, R* __restrict__ trig, int ts,
                                             RIFT_LDS unsigned char* stage, double ra, double dec, double psi,
                                             double incl, double phi, double tref, double dist) {
-  return eval_sample_with<R, KT, L, BOUND>(
-      P, trig, ts, ra, dec, psi, incl, phi, tref, dist,
-      [&](const int32_t* row, const R* sfr, const R* Fre, const R* Fim, const R* cn, const R* sn, R cf,
-          R sf) { return data_direct<R, KT, L>(P, stage, row, sfr, Fre, Fim, cn, sn, cf, sf); });
+  const Terms t = eval_terms<R, KT, L, BOUND>(P, trig, ts, stage, ra, dec, psi, incl, phi, tref);
+  return combine<BOUND>(P, dist, t.data, t.quad, t.wq, t.bad);
 }
 
 // ---------------------------------------------------------------------------

@@ -163,7 +163,8 @@ __device__ __forceinline__ double eval_grad(PDesc P, double* __restrict__ trig, 
   double w[KT][4], wd[KT][4];
   int soff[KT];
   const int ntp = n_t + 2 * QPAD;
-  const int NGR = q_groups(M, QW64);
+  const int QW = P->w64, qsh = QW == QW64 ? 3 : 1;
+  const int NGR = q_groups(M, QW);
   bool bad = false;
 #pragma unroll
   for (int k = 0; k < KT; ++k) {
@@ -252,9 +253,9 @@ __device__ __forceinline__ double eval_grad(PDesc P, double* __restrict__ trig, 
       const double mv = (double)mi;
 #pragma unroll
       for (int k = 0; k < KT; ++k) {
-        const RIFT_GLOBAL double* ser = Qt + 2 * ((int64_t)(k * NGR + i / QW64) * ntp * QW64 + i % QW64);
-        const C2<double> q0 = ldq(ser, soff[k] * QW64), q1 = ldq(ser, (soff[k] + 1) * QW64);
-        const C2<double> q2 = ldq(ser, (soff[k] + 2) * QW64), q3 = ldq(ser, (soff[k] + 3) * QW64);
+        const RIFT_GLOBAL double* ser = Qt + 2 * ((int64_t)(k * NGR + (i >> qsh)) * ntp * QW + (i & (QW - 1)));
+        const C2<double> q0 = ldq(ser, soff[k] * QW), q1 = ldq(ser, (soff[k] + 1) * QW);
+        const C2<double> q2 = ldq(ser, (soff[k] + 2) * QW), q3 = ldq(ser, (soff[k] + 3) * QW);
         const double qx = w[k][0] * q0.x + w[k][1] * q1.x + w[k][2] * q2.x + w[k][3] * q3.x;
         const double qy = w[k][0] * q0.y + w[k][1] * q1.y + w[k][2] * q2.y + w[k][3] * q3.y;
         const double tx = wd[k][0] * q0.x + wd[k][1] * q1.x + wd[k][2] * q2.x + wd[k][3] * q3.x;
@@ -514,7 +515,8 @@ __device__ __forceinline__ double eval_grad_group(PDesc P, double ra, double dec
   // data term and its derivatives: pairs (k, i)
   const RIFT_GLOBAL double* Q = as_global(P->Q64);
   const int64_t ntp = n_t + 2 * QPAD;
-  const int NGR = q_groups(M, QW64);
+  const int QW = P->w64, qsh = QW == QW64 ? 3 : 1;
+  const int NGR = q_groups(M, QW);
   const double idt = P->inv_dt;
   double data = 0.0, gg = 0.0, gdec = 0.0, gpsi = 0.0, gi = 0.0, gf = 0.0, gt = 0.0;
   for (int pr = lg; pr < K * M; pr += G) {
@@ -531,11 +533,11 @@ __device__ __forceinline__ double eval_grad_group(PDesc P, double ra, double dec
     wd[2] = -(3.0 * s2 - 2.0 * s - 2.0) * 0.5 * idt;
     wd[3] = (3.0 * s2 - 1.0) / 6.0 * idt;
     const RIFT_GLOBAL double* q =
-        Q + 2 * ((((int64_t)k * NGR + i / QW64) * ntp + (int64_t)dk[8]) * QW64 + i % QW64);
+        Q + 2 * ((((int64_t)k * NGR + (i >> qsh)) * ntp + (int64_t)dk[8]) * QW + (i & (QW - 1)));
     double qx = 0.0, qy = 0.0, tx = 0.0, ty = 0.0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const double vx = q[2 * QW64 * j], vy = q[2 * QW64 * j + 1];
+      const double vx = q[2 * QW * j], vy = q[2 * QW * j + 1];
       qx += w[j] * vx;
       qy += w[j] * vy;
       tx += wd[j] * vx;

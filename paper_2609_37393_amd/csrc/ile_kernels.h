@@ -36,6 +36,7 @@ struct TileArgs {
   const PointDesc* descs;
   const Tile* tiles;
   int32_t n_tiles;
+  int32_t split;  // work units per tile (modes without a reduction; 1 otherwise)
   int32_t persistent;
   int32_t* counter;  // [0]: next tile, [1]: finished blocks (persistent form; both 0 at launch)
   const double* theta;  // [7][N]
@@ -66,7 +67,13 @@ struct TileArgs {
 template <class R, int KT, int L, int MODE>
 __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, double* shd, R* trig,
                                          RIFT_LDS unsigned char* stage) {
-  const Tile t = a.tiles[tidx];
+  Tile t = a.tiles[mode_reduces(MODE) ? tidx : tidx / a.split];
+  if (!mode_reduces(MODE) && a.split > 1) {
+    const int len = ((t.cnt + a.split - 1) / a.split + 63) & ~63;
+    const int at = tidx % a.split * len;
+    t.s += at;
+    t.cnt = t.cnt - at < len ? t.cnt - at : len;
+  }
   const PointDesc* P = a.descs + __builtin_amdgcn_readfirstlane(t.p);
   const RIFT_GLOBAL double* theta = as_global(a.theta);
   const RIFT_GLOBAL double* lnw = as_global(a.lnw);
@@ -98,7 +105,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, do
                     ? __builtin_nan("")
                     : 0.0;
       } else if constexpr (MODE == MODE_DMARG64) {
-        const Terms tm = eval_terms<R, KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[1], th[2], th[3],
+        const Terms tm = eval_terms<R, KT, L, false>(opaque(P), trig, blockDim.x, stage, th[0], th[1], th[2], th[3],
                                               th[4], th[5]);
         e.lnL = dist_marginal(a.dm, as_const(P)->d_ref, tm);
       } else if constexpr (MODE == MODE_TMARG64) {
@@ -135,7 +142,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, do
                   ? __builtin_nan("")
                   : 0.0;
     } else if constexpr (MODE == MODE_DMARG64) {
-      const Terms tm = eval_terms<R, KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[N], th[2 * N],
+      const Terms tm = eval_terms<R, KT, L, false>(opaque(P), trig, blockDim.x, stage, th[0], th[N], th[2 * N],
                                             th[3 * N], th[4 * N], th[5 * N]);
       e.lnL = dist_marginal(a.dm, as_const(P)->d_ref, tm);
     } else if constexpr (MODE == MODE_TMARG64) {
@@ -186,7 +193,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, do
 template <class R, int KT, int LSET, int MODE>
 __device__ __forceinline__ void dispatch_tile(const TileArgs& a, int tidx, MS* sh, double* shd, R* trig,
                                               RIFT_LDS unsigned char* stage) {
-  const int L = __builtin_amdgcn_readfirstlane(as_const(a.descs)[as_const(a.tiles)[tidx].p].L);
+  const int L = __builtin_amdgcn_readfirstlane(as_const(a.descs)[as_const(a.tiles)[mode_reduces(MODE) ? tidx : tidx / a.split].p].L);
   if ((LSET & 1) && L == 2) run_tile<R, KT, 2, MODE>(a, tidx, sh, shd, trig, stage);
   else if ((LSET & 2) && L == 3) run_tile<R, KT, 3, MODE>(a, tidx, sh, shd, trig, stage);
   else if ((LSET & 4) && L == 4) run_tile<R, KT, 4, MODE>(a, tidx, sh, shd, trig, stage);
@@ -254,20 +261,20 @@ __device__ __forceinline__ double eval_wide(PDesc P, double ra, double dec, doub
   double* sq = tab + 3 * (NI + 1);
   double* det = tab + 4 * (NI + 1);  // per detector: fp, fx, f2, g2r, g2i, row, s, bad
   if (lane <= NI) {
-    double s, c;
-    sincos((double)lane * incl, &s, &c);
-    ctab[lane] = c;
-    stab[lane] = s;
-    sincos((double)lane * phi, &s, &c);
-    cq[lane] = c;
-    sq[lane] = s;
+    const double a2[2] = {(double)lane * incl, (double)lane * phi};
+    double s2[2], c2[2];
+    sincos_many<2>(a2, s2, c2);
+    ctab[lane] = c2[0];
+    stab[lane] = s2[0];
+    cq[lane] = c2[1];
+    sq[lane] = s2[1];
   }
   if (lane < K) {
     const int k = lane;
-    double sg, cg, sd, cd, sp, cp;
-    sincos(P->gmst - ra, &sg, &cg);
-    sincos(dec, &sd, &cd);
-    sincos(psi, &sp, &cp);
+    const double a3[3] = {P->gmst - ra, dec, psi};
+    double s3[3], c3[3];
+    sincos_many<3>(a3, s3, c3);
+    const double sg = s3[0], cg = c3[0], sd = s3[1], cd = c3[1], sp = s3[2], cp = c3[2];
     const double N0 = cd * cg, N1 = -cd * sg, N2 = sd;
     const double ed0 = -sd * cg, ed1 = sd * sg, ed2 = cd;
     const double X0 = -cp * sg + sp * ed0, X1 = -cp * cg + sp * ed1, X2 = sp * ed2;
@@ -304,7 +311,8 @@ __device__ __forceinline__ double eval_wide(PDesc P, double ra, double dec, doub
   // data term: pairs (k, i)
   const RIFT_GLOBAL double* Q = as_global(P->Q64);
   const int64_t ntp = n_t + 2 * QPAD;
-  const int NGR = q_groups(M, QW64);
+  const int QW = P->w64, qsh = QW == QW64 ? 3 : 1;
+  const int NGR = q_groups(M, QW);
   double data = 0.0;
   for (int pr = lane; pr < K * M; pr += 64) {
     const int k = pr / M, i = pr % M;
@@ -312,12 +320,12 @@ __device__ __forceinline__ double eval_wide(PDesc P, double ra, double dec, doub
     double w[4];
     lagrange4(dk[6], w);
     const RIFT_GLOBAL double* q =
-        Q + 2 * ((((int64_t)k * NGR + i / QW64) * ntp + (int64_t)dk[5]) * QW64 + i % QW64);
+        Q + 2 * ((((int64_t)k * NGR + (i >> qsh)) * ntp + (int64_t)dk[5]) * QW + (i & (QW - 1)));
     double qx = 0.0, qy = 0.0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      qx += w[j] * q[2 * QW64 * j];
-      qy += w[j] * q[2 * QW64 * j + 1];
+      qx += w[j] * q[2 * QW * j];
+      qy += w[j] * q[2 * QW * j + 1];
     }
     // Y_i = d_i(incl) e^{i m_i phi}
     const int m = P->m[i];

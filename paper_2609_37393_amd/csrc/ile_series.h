@@ -83,10 +83,8 @@ __global__ void __launch_bounds__(128) k_series_coef(SeriesArgs a) {
   const int64_t N = a.N;
   const double dist = th[6 * N];
   Sky<double, KT> S;
-  sky_eval<double, KT, false>(P, th[0], th[N], th[2 * N], 0.0, S);
   double si, ci, sf, cf;
-  sincos(th[3 * N], &si, &ci);
-  sincos(th[4 * N], &sf, &cf);
+  sky_eval<double, KT, false>(P, th[0], th[N], th[2 * N], th[3 * N], th[4 * N], 0.0, S, si, ci, sf, cf);
   double cn[NY], sn[NY];
   incl_harmonics<double, NY>(ci, si, cn, sn);
   double wq = 0.0;

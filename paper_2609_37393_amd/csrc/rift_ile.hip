@@ -913,6 +913,7 @@ struct rift_ile_plan_s {
   char* arena = nullptr;
   size_t arena_cap = 0;
   size_t arena_off = 0;
+  size_t arena_counted = 0;
   // tiles (depend on the config)
   rift_ile_config cfg{256, 4, 0, 0};
   std::vector<Tile> h_tiles;
@@ -966,13 +967,18 @@ struct rift_ile_plan_s {
 
 namespace {
 
-int palloc(rift_ile_plan p, size_t bytes, void** out) {
+// `count`, if given, is what an allocation in the fixed scratch counts against
+// its limit: the FP64 tables count as rows of two modes, the least that holds
+// them, whatever the rows that the reads take (24 against 18 at 17 modes, the
+// most; the array is half as long again as the limit).
+int palloc(rift_ile_plan p, size_t bytes, void** out, size_t count = 0) {
   if (p->arena) {
-    const size_t off = (p->arena_off + 255) & ~(size_t)255;
-    const size_t len = bytes < 256 ? 256 : bytes;
-    if (off > p->arena_cap || len > p->arena_cap - off) return RIFT_ESCRATCH;
-    *out = p->arena + off;
-    p->arena_off = off + len;
+    auto next = [](size_t at, size_t len) { return ((at + 255) & ~(size_t)255) + (len < 256 ? 256 : len); };
+    if (bytes > p->arena_cap || next(p->arena_off, bytes) > p->arena_cap) return RIFT_ESCRATCH;
+    if (next(p->arena_counted, count ? count : bytes) > RIFT_ILE_NOALLOC_SCRATCH_BYTES) return RIFT_ESCRATCH;
+    *out = p->arena + ((p->arena_off + 255) & ~(size_t)255);
+    p->arena_off = next(p->arena_off, bytes);
+    p->arena_counted = next(p->arena_counted, count ? count : bytes);
     return RIFT_OK;
   }
   void* d = nullptr;
@@ -1152,6 +1158,10 @@ size_t eval_lds_bytes(int lset, int block, size_t rsz) {
   return (size_t)(block / 64) * STAGE_WAVE + trig;
 }
 
+// Blocks of the FP64 likelihood kernels that the chip holds at once: two
+// wavefronts per SIMD.
+int resident_blocks(rift_ile_plan p) { return std::max(1, p->di.n_cu) * std::max(1, 512 / p->cfg.block); }
+
 // The likelihood kernel over tiles [first, first + count) (count < 0: all).
 int launch_tiles(rift_ile_plan p, int mode, const double* theta, const double* lnw, double* lnL,
                  hipStream_t st, int first = 0, int count = -1) {
@@ -1159,6 +1169,12 @@ int launch_tiles(rift_ile_plan p, int mode, const double* theta, const double* l
   a.descs = p->d_desc;
   a.tiles = p->d_tiles + first;
   a.n_tiles = count < 0 ? p->n_tiles : count;
+  // a launch of fewer tiles than the chip holds blocks runs their parts of one
+  // block each as units of their own, where no reduction needs the tile: 131072
+  // samples of a data pass are 128 blocks as tiles, a quarter of a round, and
+  // 512 in parts
+  a.split = !mode_reduces(mode) && a.n_tiles < resident_blocks(p) ? p->cfg.tile_blocks : 1;
+  a.n_tiles *= a.split;
   a.persistent = p->cfg.blocks_per_cu > 0 ? 1 : 0;
   a.counter = p->d_counter;
   a.theta = theta;
@@ -1432,7 +1448,9 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
     D.m_min = D.m[0];
     // device tables
     const int64_t qrows = (int64_t)KT * (pt.n_t + 2 * QPAD);
-    PCHK(palloc(p, sizeof(double) * 2 * qrows * q_groups(M, QW64) * QW64, &v));
+    D.w64 = q_width64(M);
+    PCHK(palloc(p, sizeof(double) * 2 * qrows * q_groups(M, D.w64) * D.w64, &v,
+                sizeof(double) * 2 * qrows * q_groups(M, 2) * 2));
     D.Q64 = (const double*)v;
     if (mixed) {
       PCHK(palloc(p, sizeof(float) * 2 * qrows * q_groups(M, QW32) * QW32, &v));
@@ -1541,10 +1559,10 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
     const rift_ile_point& pt = pts[pi];
     PointDesc& D = p->h_desc[pi];
     PHIP(hipMemcpyAsync(d_perm[pi], h_perm[pi].data(), sizeof(int32_t) * pt.n_modes, hipMemcpyHostToDevice, st));
-    const int64_t qper = (int64_t)(pt.n_t + 2 * QPAD) * q_groups(pt.n_modes, QW64) * QW64;
+    const int64_t qper = (int64_t)(pt.n_t + 2 * QPAD) * q_groups(pt.n_modes, D.w64) * D.w64;
     const int gq = (int)std::min<int64_t>((KT * qper + 255) / 256, 65535);
     hipLaunchKernelGGL(k_repack<double>, dim3(gq), dim3(256), 0, st, pt.Q, (double*)D.Q64, d_perm[pi],
-                       pt.n_det, KT, pt.n_modes, pt.n_t, QW64);
+                       pt.n_det, KT, pt.n_modes, pt.n_t, D.w64);
     if (D.Q32)
       hipLaunchKernelGGL(k_repack<float>, dim3(gq), dim3(256), 0, st, pt.Q, (float*)D.Q32, d_perm[pi],
                          pt.n_det, KT, pt.n_modes, pt.n_t, QW32);
@@ -1794,7 +1812,9 @@ int64_t ang_pieces(rift_ile_plan p, int rows, std::vector<AngPiece>* out) {
     out->push_back(AngPiece{0, p->n_tiles, 0, p->N});
     return p->N;
   }
-  const int64_t cap = std::max<int64_t>((int64_t)(ANG_KEEP / per), 1);
+  // whole rounds of the chip where they fit
+  const int64_t fit = (int64_t)(ANG_KEEP / per), round = (int64_t)resident_blocks(p) * p->cfg.block;
+  const int64_t cap = std::max<int64_t>(fit >= round ? fit / round * round : fit, 1);
   int64_t most = 0;
   for (int t = 0; t < p->n_tiles; ++t) {
     const Tile& T = p->h_tiles[t];
@@ -2219,7 +2239,8 @@ int rift_ile_grad(const rift_ile_point* pt, int64_t n, const double* theta, int 
 // array's name to a kernel or a copy: it passes the device address that
 // hipGetSymbolAddress returns for the current device (kept per device).
 // ---------------------------------------------------------------------------
-static __device__ __align__(256) unsigned char scratch[RIFT_ILE_NOALLOC_SCRATCH_BYTES];
+constexpr size_t SCRATCH_BYTES = (size_t)3 * RIFT_ILE_NOALLOC_SCRATCH_BYTES / 2;  // see palloc
+static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -2251,7 +2272,7 @@ extern "C" int rift_ile_lnZ_noalloc(const rift_ile_point* pts, int32_t n_points,
   int rc = scratch_of_current_device(&base);
   if (rc) return rc;
   rift_ile_plan p = nullptr;
-  rc = plan_create_impl(pts, n_points, n_per_point, precision, stream, base, RIFT_ILE_NOALLOC_SCRATCH_BYTES, &p);
+  rc = plan_create_impl(pts, n_points, n_per_point, precision, stream, base, SCRATCH_BYTES, &p);
   if (rc) return rc;
   rc = rift_ile_plan_lnZ(p, theta, lnw, lnZ, neff, lnL, nullptr, nullptr, stream);
   int rc2 = rift_ile_plan_destroy(p);

@@ -33,7 +33,7 @@ __global__ void __launch_bounds__(256) k_series_rows(SeriesArgs a) {
   const int wave = threadIdx.x >> 6;
   const int tile = __builtin_amdgcn_readfirstlane(a.tile0 + (int)(blockIdx.x * 4) + wave);
   PDesc P = as_const(a.P);
-  const int K = P->K, NR = P->n_t + 2 * QPAD, NGR = q_groups(P->M, QW64);
+  const int K = P->K, NR = P->n_t + 2 * QPAD, W2 = 2 * P->w64, sh = P->w64 == QW64 ? 4 : 2, NGR = q_groups(P->M, P->w64);
   const int lo = tile * 64;
   if (lo >= NR) return;
   const int k = blockIdx.y;
@@ -55,25 +55,30 @@ __global__ void __launch_bounds__(256) k_series_rows(SeriesArgs a) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  // B: element e = quad NG + b of row lo + 16 t + col (mode e / 2, part e & 1)
+  // B: element e of row lo + 16 t + col (mode e / 2, part e & 1).  The products'
+  // steps take the elements in pairs, so that a quad reads 16 bytes at a time
+  // and the four of a row 64 (58 us for a chunk's rows of 21 modes; 63 with NG
+  // elements in a run per quad).
+  auto element = [&](int b) { return b < NG / 2 * 2 ? 8 * (b / 2) + 2 * quad + (b & 1) : 4 * (NG - 1) + quad; };
   double B[4][NG];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const int row = lo + 16 * t + col;
-    const RIFT_GLOBAL double* Q = as_global(P->Q64) + 4 * ((int64_t)k * NGR * NR + (row < NR ? row : NR - 1));
+    const RIFT_GLOBAL double* Q =
+        as_global(P->Q64) + W2 * ((int64_t)k * NGR * NR + (row < NR ? row : NR - 1));
 #pragma unroll
     for (int b = 0; b < NG; ++b) {
-      const int e = quad * NG + b;
-      B[t][b] = (e >> 2) < NGR ? Q[4 * (int64_t)(e >> 2) * NR + (e & 3)] : 0.0;
+      const int e = element(b), grp = e >> sh;
+      B[t][b] = grp < NGR ? Q[W2 * (int64_t)grp * NR + (e & (W2 - 1))] : 0.0;
     }
   }
   double A[NG];
   auto load = [&](int j, int* s, int* r) {
     *s = s0 + list[wave][j < count ? j : count - 1];
     *r = r0[*s];
-    const RIFT_GLOBAL double* c = as_global(a.coef) + ((int64_t)(a.off + *s) * K + k) * series_coef_len(NG) + quad * NG;
+    const RIFT_GLOBAL double* c = as_global(a.coef) + ((int64_t)(a.off + *s) * K + k) * series_coef_len(NG);
 #pragma unroll
-    for (int b = 0; b < NG; ++b) A[b] = c[b];
+    for (int b = 0; b < NG; ++b) A[b] = c[element(b)];
   };
   int s, rs;
   load(col, &s, &rs);
@@ -309,12 +314,12 @@ __global__ void __launch_bounds__(256) k_band(int64_t cnt, int n, int M, int fp,
 }
 
 int series_groups(int M) {
-  const int g = q_groups(M, QW64);
+  const int g = (M + 1) / 2;
   for (int c : {1, 2, 3, 5, 8, 11})
     if (g <= c) return c;
   return 13;
 }
-static_assert(q_groups(MMAX, QW64) <= 13, "the largest instance holds every mode");
+static_assert((MMAX + 1) / 2 <= 13, "the largest instance holds every mode");
 
 // Workspace of a run: the samples' coefficients (and node values) of one
 // outer chunk, and the contracted rows of one inner chunk.

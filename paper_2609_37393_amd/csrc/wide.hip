@@ -369,19 +369,17 @@ __global__ void __launch_bounds__(64, 2) k_wide(WideDesc D, const double* __rest
   // sky frame at t_ref (the rotation response advances the sidereal angle)
   const double gm = rot ? D.gmst + D.omega * tref : D.gmst;
   const double gref = gm - ra;
-  double sg, cg, sd, cd, sp, cp;
-  sincos(gref, &sg, &cg);
-  sincos(dec, &sd, &cd);
-  sincos(psi, &sp, &cp);
+  const double a5[5] = {gref, dec, psi, incl, phi};
+  double s5[5], c5[5];
+  sincos_many<5>(a5, s5, c5);
+  const double sg = s5[0], cg = c5[0], sd = s5[1], cd = c5[1], sp = s5[2], cp = c5[2];
   double X[3], Y3[3], N[3];
   axes(sg, cg, sd, cd, sp, cp, X, Y3, N);
 
   // harmonics Y_i = d_i(incl) e^{i m_i phi}, internal (m-sorted) modes
   double yr[MC], yi[MC];
   {
-    double ci, si, cf, sf;
-    sincos(incl, &si, &ci);
-    sincos(phi, &sf, &cf);
+    const double si = s5[3], ci = c5[3], sf = s5[4], cf = c5[4];
     double cn[LMAXC + 1], sn[LMAXC + 1];
     double c0 = 1.0, c1 = ci, s0 = 0.0, s1 = si;
 #pragma unroll
