@@ -116,10 +116,11 @@ __device__ __forceinline__ double eval_grad(PDesc P, double* __restrict__ trig, 
   const int n_t = P->n_t;
   const RIFT_GLOBAL double* Qt = as_global(P->Q64);
 
-  double sg, cg, sd, cd, sp, cp;
-  sincos(P->gmst - ra, &sg, &cg);
-  sincos(dec, &sd, &cd);
-  sincos(psi, &sp, &cp);
+  const double a5[5] = {P->gmst - ra, dec, psi, incl, phi};
+  double s5[5], c5[5];
+  sincos_many<5>(a5, s5, c5);
+  const double sg = s5[0], cg = c5[0], sd = s5[1], cd = c5[1], sp = s5[2], cp = c5[2];
+  const double si = s5[3], ci = c5[3], sf = s5[4], cf = c5[4];
   const double N[3] = {cd * cg, -cd * sg, sd};
   const double ea[3] = {sg, cg, 0.0};
   const double ed[3] = {-sd * cg, sd * sg, cd};
@@ -131,8 +132,6 @@ __device__ __forceinline__ double eval_grad(PDesc P, double* __restrict__ trig, 
   }
 
   // harmonics in incl (registers up to l, scratch column up to 2l)
-  double si, ci;
-  sincos(incl, &si, &ci);
   double cn[NY], sn[NY];
   {
     double c0 = 1.0, c1 = ci, s0 = 0.0, s1 = si;
@@ -155,16 +154,14 @@ __device__ __forceinline__ double eval_grad(PDesc P, double* __restrict__ trig, 
       }
     }
   }
-  double sf, cf;
-  sincos(phi, &sf, &cf);
 
   // antenna factors, their derivatives and the stencils
   double Fp[KT], Fx[KT], dFg[KT][2], dFd[KT][2], dtg[KT], dtd[KT];
   double w[KT][4], wd[KT][4];
   int soff[KT];
   const int ntp = n_t + 2 * QPAD;
-  const int QW = P->w64, qsh = QW == QW64 ? 3 : 1;
-  const int NGR = q_groups(M, QW);
+  const int W = P->w64, qsh = W == QW64 ? 3 : 1;
+  const int NGR = q_groups(M, W);
   bool bad = false;
 #pragma unroll
   for (int k = 0; k < KT; ++k) {
@@ -253,9 +250,9 @@ __device__ __forceinline__ double eval_grad(PDesc P, double* __restrict__ trig, 
       const double mv = (double)mi;
 #pragma unroll
       for (int k = 0; k < KT; ++k) {
-        const RIFT_GLOBAL double* ser = Qt + 2 * ((int64_t)(k * NGR + (i >> qsh)) * ntp * QW + (i & (QW - 1)));
-        const C2<double> q0 = ldq(ser, soff[k] * QW), q1 = ldq(ser, (soff[k] + 1) * QW);
-        const C2<double> q2 = ldq(ser, (soff[k] + 2) * QW), q3 = ldq(ser, (soff[k] + 3) * QW);
+        const RIFT_GLOBAL double* ser = Qt + 2 * ((int64_t)(k * NGR + (i >> qsh)) * ntp * W + (i & (W - 1)));
+        const C2<double> q0 = ldq(ser, soff[k] * W), q1 = ldq(ser, (soff[k] + 1) * W);
+        const C2<double> q2 = ldq(ser, (soff[k] + 2) * W), q3 = ldq(ser, (soff[k] + 3) * W);
         const double qx = w[k][0] * q0.x + w[k][1] * q1.x + w[k][2] * q2.x + w[k][3] * q3.x;
         const double qy = w[k][0] * q0.y + w[k][1] * q1.y + w[k][2] * q2.y + w[k][3] * q3.y;
         const double tx = wd[k][0] * q0.x + wd[k][1] * q1.x + wd[k][2] * q2.x + wd[k][3] * q3.x;
@@ -395,31 +392,59 @@ __device__ __forceinline__ double eval_grad(PDesc P, double* __restrict__ trig, 
   return lnL;
 }
 
-// The same value and gradient with a group of G lanes (a power of two, at
-// most 64) per sample, for batches too small to fill the GPU one lane per
-// sample.  The group shares its sample's tables through `tab` (GRAD_TAB(L, KT)
-// doubles of LDS per group):
+// The same value and gradient with a group of 16 lanes per sample, for batches
+// too small to fill the GPU one lane per sample.  A group shares its sample's
+// tables through `tab` (GRAD_TAB(L, KT) doubles of LDS per group):
 //   cos/sin(n incl) and cos/sin(q phi) for n, q = 0..2L;
 //   per detector: F+, Fx, dF/dgha (2), dF/ddec (2), dt/dgha, dt/ddec, stencil
 //   row and fraction, a bad flag, and the model-norm weights (|F|^2,
 //   Re F^2, Im F^2) with their changes along gha, dec and psi (12 values).
 // The (detector, mode) pairs of the data term and the basis rows of the
-// model-norm contraction are spread over the group's lanes; 14 group sums
-// finish it.  Every lane of the group returns the value and g[].  The whole
-// wavefront calls this together (one sample per group).
+// model-norm contraction are spread over the group's lanes, a row's
+// coefficients against the four weight vectors first (in registers for all of
+// a lane's rows) and the basis value and its derivatives after.  The 14 sums
+// are exchanged and halved together, four steps that leave one sum per lane.
+// Every lane of the group returns the value and g[].  The whole wavefront
+// calls this together (one sample per group).
+//
+// A launch of 16384 chains is four wavefronts per SIMD, bound by the latency of
+// these serial phases; what every sample reads, the point's modes and
+// contraction table, is staged in LDS by the block (GradPoint).  9 modes, 3
+// detectors, 16384 chains: 20 us a launch, 31 with per-lane reads of both, a
+// division and five library sincos in sequence, and a butterfly per sum.
 #define GRAD_TAB(L, KT) (4 * (2 * (L) + 1) + 24 * (KT))
-template <int G>
-__device__ __forceinline__ double gsum(double v) {
-#pragma unroll
-  for (int off = G / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-template <int KT, int L, int G, bool MARG = false>
-__device__ __forceinline__ double eval_grad_group(PDesc P, double ra, double dec, double psi, double incl,
-                                                  double phi, double tref, double dist, double* tab,
-                                                  double g[7], const DistRule* dm = nullptr) {
+constexpr int GRAD_G = 16;
+
+// What a block's samples share: the modes, the basis rows and, while it fits
+// 32 KB, the contraction table.
+template <int KT, int L>
+struct GradPoint {
+  static constexpr int W = 3 * KT, B = Cls<L>::B, NY = L + 1;
+  static constexpr bool TABLE = B * W * 8 <= 32768;
+  double y[MMAX * NY];
+  double c[TABLE ? B * W : 1];
+  int32_t mode[MMAX];  // 2 m + (sine series)
+  int32_t row[B];      // basis_row
+  __device__ __forceinline__ void load(PDesc P) {
+    const int M = P->M;
+    for (int e = threadIdx.x; e < M * NY; e += blockDim.x) y[e] = P->ycoef[e / NY][e % NY];
+    for (int i = threadIdx.x; i < M; i += blockDim.x) mode[i] = 2 * P->m[i] + (P->odd[i] ? 1 : 0);
+    for (int r = threadIdx.x; r < B; r += blockDim.x) row[r] = basis_row<L>(r);
+    if constexpr (TABLE) {
+      const RIFT_GLOBAL double* C = as_global(P->C64);
+      for (int e = threadIdx.x; e < B * W; e += blockDim.x) c[e] = C[e];
+    }
+    __syncthreads();
+  }
+};
+
+template <int KT, int L, bool MARG = false>
+__device__ __forceinline__ double eval_grad_group(PDesc P, const GradPoint<KT, L>& S, double ra, double dec,
+                                                  double psi, double incl, double phi, double tref, double dist,
+                                                  double* tab, double g[7], const DistRule* dm = nullptr) {
   constexpr int NI = 2 * L;
   constexpr int NY = L + 1;
+  constexpr int G = GRAD_G;
   const int lg = (int)(threadIdx.x & (G - 1));
   const int K = P->K, M = P->M, n_t = P->n_t;
   double* ctab = tab;
@@ -427,22 +452,30 @@ __device__ __forceinline__ double eval_grad_group(PDesc P, double ra, double dec
   double* cq = tab + 2 * (NI + 1);
   double* sq = tab + 3 * (NI + 1);
   double* det = tab + 4 * (NI + 1);
-  for (int n = lg; n <= NI; n += G) {
-    double s, c;
-    sincos((double)n * incl, &s, &c);
-    ctab[n] = c;
-    stab[n] = s;
-    sincos((double)n * phi, &s, &c);
-    cq[n] = c;
-    sq[n] = s;
+  const double a5[5] = {P->gmst - ra, dec, psi, (double)lg * incl, (double)lg * phi};
+  double s5[5], c5[5];
+  sincos_many<5>(a5, s5, c5);
+  if (lg <= NI) {
+    ctab[lg] = c5[3];
+    stab[lg] = s5[3];
+    cq[lg] = c5[4];
+    sq[lg] = s5[4];
   }
+  if constexpr (NI >= G) {
+    for (int n = lg + G; n <= NI; n += G) {
+      const double a2[2] = {(double)n * incl, (double)n * phi};
+      double s2[2], c2[2];
+      sincos_many<2>(a2, s2, c2);
+      ctab[n] = c2[0];
+      stab[n] = s2[0];
+      cq[n] = c2[1];
+      sq[n] = s2[1];
+    }
+  }
+  const double sg = s5[0], cg = c5[0], sd = s5[1], cd = c5[1], sp = s5[2], cp = c5[2];
   for (int k = lg; k < KT; k += G) {
     double* dk = det + 24 * k;
     if (k < K) {
-      double sg, cg, sd, cd, sp, cp;
-      sincos(P->gmst - ra, &sg, &cg);
-      sincos(dec, &sd, &cd);
-      sincos(psi, &sp, &cp);
       const double N[3] = {cd * cg, -cd * sg, sd};
       const double ea[3] = {sg, cg, 0.0};
       const double ed[3] = {-sd * cg, sd * sg, cd};
@@ -519,46 +552,51 @@ __device__ __forceinline__ double eval_grad_group(PDesc P, double ra, double dec
   const int NGR = q_groups(M, QW);
   const double idt = P->inv_dt;
   double data = 0.0, gg = 0.0, gdec = 0.0, gpsi = 0.0, gi = 0.0, gf = 0.0, gt = 0.0;
-  for (int pr = lg; pr < K * M; pr += G) {
-    const int k = pr / M, i = pr % M;
+  int k = 0, i = lg;
+  for (int pr = lg; pr < K * M; pr += G, i += G) {
+    while (i >= M) {
+      i -= M;
+      ++k;
+    }
     const double* dk = det + 24 * k;
-    const double s = dk[9], s2 = s * s;
-    double w[4], wd[4];
-    w[0] = -s * (s - 1.0) * (s - 2.0) / 6.0;
-    w[1] = (s + 1.0) * (s - 1.0) * (s - 2.0) * 0.5;
-    w[2] = -(s + 1.0) * s * (s - 2.0) * 0.5;
-    w[3] = (s + 1.0) * s * (s - 1.0) / 6.0;
-    wd[0] = -(3.0 * s2 - 6.0 * s + 2.0) / 6.0 * idt;
-    wd[1] = (3.0 * s2 - 4.0 * s - 1.0) * 0.5 * idt;
-    wd[2] = -(3.0 * s2 - 2.0 * s - 2.0) * 0.5 * idt;
-    wd[3] = (3.0 * s2 - 1.0) / 6.0 * idt;
     const RIFT_GLOBAL double* q =
         Q + 2 * ((((int64_t)k * NGR + (i >> qsh)) * ntp + (int64_t)dk[8]) * QW + (i & (QW - 1)));
-    double qx = 0.0, qy = 0.0, tx = 0.0, ty = 0.0;
+    double v[4][2];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const double vx = q[2 * QW * j], vy = q[2 * QW * j + 1];
-      qx += w[j] * vx;
-      qy += w[j] * vy;
-      tx += wd[j] * vx;
-      ty += wd[j] * vy;
+      v[j][0] = q[2 * QW * j];
+      v[j][1] = q[2 * QW * j + 1];
     }
-    const int m = P->m[i];
+    // d_i(incl) and its derivative: a sine series for odd m
+    const int mo = S.mode[i], m = mo >> 1;
+    const double* yc = S.y + i * NY;
+    const double* f0 = (mo & 1) ? stab : ctab;
+    const double* f1 = (mo & 1) ? ctab : stab;
     double d = 0.0, dd = 0.0;
-    if (P->odd[i]) {
-      for (int n = 1; n < NY; ++n) {
-        d += P->ycoef[i][n] * stab[n];
-        dd += P->ycoef[i][n] * (double)n * ctab[n];
-      }
-    } else {
-      for (int n = 0; n < NY; ++n) {
-        d += P->ycoef[i][n] * ctab[n];
-        dd -= P->ycoef[i][n] * (double)n * stab[n];
-      }
+#pragma unroll
+    for (int n = 0; n < NY; ++n) {
+      d = fma(yc[n], f0[n], d);
+      dd = fma(yc[n] * (double)n, f1[n], dd);
     }
+    if (!(mo & 1)) dd = -dd;
     const int am = m < 0 ? -m : m;
     const double ex = cq[am], ey = m < 0 ? -sq[am] : sq[am];  // e^{i m phi}
     const double yx = d * ex, yy = d * ey, ix = dd * ex, iy = dd * ey;
+    const double s = dk[9], s2 = s * s;
+    double w[4], wd[4];
+    lagrange4(s, w);
+    wd[0] = -(3.0 * s2 - 6.0 * s + 2.0) * (1.0 / 6.0) * idt;
+    wd[1] = (3.0 * s2 - 4.0 * s - 1.0) * 0.5 * idt;
+    wd[2] = -(3.0 * s2 - 2.0 * s - 2.0) * 0.5 * idt;
+    wd[3] = (3.0 * s2 - 1.0) * (1.0 / 6.0) * idt;
+    double qx = 0.0, qy = 0.0, tx = 0.0, ty = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      qx = fma(w[j], v[j][0], qx);
+      qy = fma(w[j], v[j][1], qy);
+      tx = fma(wd[j], v[j][0], tx);
+      ty = fma(wd[j], v[j][1], ty);
+    }
     const double zx = yx * qx + yy * qy, zy = yx * qy - yy * qx;  // conj(Y) Qhat
     const double ztx = yx * tx + yy * ty, zty = yx * ty - yy * tx;
     const double zix = ix * qx + iy * qy, ziy = ix * qy - iy * qx;
@@ -573,61 +611,95 @@ __device__ __forceinline__ double eval_grad_group(PDesc P, double ra, double dec
     gf += fp * (mv * zy) + fx * (-mv * zx);
     gt += dt_term;
   }
-  // model-norm term and its derivatives: basis rows b over the lanes, the
-  // 3 KT columns (3 k + c) of each row in turn
+  // model-norm term and its derivatives: basis rows b over the lanes
   double quad = 0.0, qg = 0.0, qdec = 0.0, qpsi = 0.0, qi = 0.0, qf = 0.0;
-  const RIFT_GLOBAL double* C = as_global(P->C64);
   constexpr int W = 3 * KT;
-  for (int b = lg; b < Cls<L>::B; b += G) {
-    const int rb = basis_row<L>(b);
-    const int kind = rb & 15, n = (rb >> 4) & 255, qq = rb >> 12;
-    // T_n(incl) and its incl-derivative
-    const double T = (kind >= 3) ? stab[n] : ctab[n];
-    const double Tp = (kind >= 3) ? (double)n * ctab[n] : -(double)n * stab[n];
-    double beta = T, bi = Tp, bf = 0.0;
-    if (kind != 0) {
-      const double cqv = cq[qq], sqv = sq[qq], qd = (double)qq;
-      if ((kind & 1) == 1) {  // cos(q phi)
-        beta = T * cqv;
-        bi = Tp * cqv;
-        bf = -qd * T * sqv;
-      } else {  // sin(q phi)
-        beta = T * sqv;
-        bi = Tp * sqv;
-        bf = qd * T * cqv;
-      }
-    }
-    const RIFT_GLOBAL double* cr = C + (int64_t)b * W;
+  {
+    auto weight = [&](int v, int col) { return det[24 * (col / 3) + 12 + 3 * v + col % 3]; };
+    double wt[4][W];
+    if constexpr (KT <= 5) {
 #pragma unroll
-    for (int col = 0; col < W; ++col) {
-      const int k = col / 3, c = col - 3 * k;
-      const double* dk = det + 24 * k;
-      const double cj = cr[col];
-      const double cb = cj * beta;
-      quad += cb * dk[12 + c];
-      qi += cj * bi * dk[12 + c];
-      qf += cj * bf * dk[12 + c];
-      qg += cb * dk[15 + c];
-      qdec += cb * dk[18 + c];
-      qpsi += cb * dk[21 + c];
+      for (int col = 0; col < W; ++col)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) wt[v][col] = weight(v, col);
+    }
+    for (int b = lg; b < Cls<L>::B; b += G) {
+      const int rb = S.row[b];
+      const int kind = rb & 15, n = (rb >> 4) & 255, qq = rb >> 12;
+      double r[4] = {0.0, 0.0, 0.0, 0.0};
+      auto add = [&](const auto* cr) {
+        if constexpr (KT <= 5) {
+#pragma unroll
+          for (int col = 0; col < W; ++col) {
+            const double cj = cr[col];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) r[v] = fma(cj, wt[v][col], r[v]);
+          }
+        } else {  // eight detectors' weights are read again for each row
+#pragma unroll 1
+          for (int j = 0; j < KT; ++j)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              const double cj = cr[3 * j + c];
+#pragma unroll
+              for (int v = 0; v < 4; ++v) r[v] = fma(cj, weight(v, 3 * j + c), r[v]);
+            }
+        }
+      };
+      if constexpr (GradPoint<KT, L>::TABLE) add(S.c + b * W);
+      else add(as_global(P->C64) + (int64_t)b * W);
+      // T_n(incl) and its incl-derivative; kinds 1, 3 take cos(q phi), 2, 4 sin(q phi)
+      const double T = (kind >= 3) ? stab[n] : ctab[n];
+      const double Tp = (kind >= 3) ? (double)n * ctab[n] : -(double)n * stab[n];
+      const double cqv = cq[qq], sqv = sq[qq], qd = (double)qq;
+      const bool cosine = kind == 0 || (kind & 1) == 1;  // kind 0: q = 0
+      const double ph = cosine ? cqv : sqv, dph = cosine ? -qd * sqv : qd * cqv;
+      const double beta = T * ph;
+      quad = fma(beta, r[0], quad);
+      qi = fma(Tp * ph, r[0], qi);
+      qf = fma(T * dph, r[0], qf);
+      qg = fma(beta, r[1], qg);
+      qdec = fma(beta, r[2], qdec);
+      qpsi = fma(beta, r[3], qpsi);
     }
   }
   double bad = 0.0;
-  for (int k = lg; k < K; k += G) bad += det[24 * k + 10];
-  data = gsum<G>(data);
-  gg = gsum<G>(gg);
-  gdec = gsum<G>(gdec);
-  gpsi = gsum<G>(gpsi);
-  gi = gsum<G>(gi);
-  gf = gsum<G>(gf);
-  gt = gsum<G>(gt);
-  quad = gsum<G>(quad);
-  qg = gsum<G>(qg);
-  qdec = gsum<G>(qdec);
-  qpsi = gsum<G>(qpsi);
-  qi = gsum<G>(qi);
-  qf = gsum<G>(qf);
-  bad = gsum<G>(bad);
+  for (int j = lg; j < K; j += G) bad += det[24 * j + 10];
+  // sum v of the group in lane v, then all of them to every lane
+  double v[G] = {data, gg, gdec, gpsi, gi, gf, gt, quad, qg, qdec, qpsi, qi, qf, bad, 0.0, 0.0};
+#pragma unroll
+  for (int off = G / 2; off >= 1; off >>= 1) {
+    const bool up = (lg & off) != 0;
+#pragma unroll
+    for (int j = 0; j < off; ++j) {
+      const double keep = up ? v[j + off] : v[j], give = up ? v[j] : v[j + off];
+      v[j] = keep + __shfl_xor(give, off);
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  tab[lg] = v[0];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  data = tab[0];
+  gg = tab[1];
+  gdec = tab[2];
+  gpsi = tab[3];
+  gi = tab[4];
+  gf = tab[5];
+  gt = tab[6];
+  quad = tab[7];
+  qg = tab[8];
+  qdec = tab[9];
+  qpsi = tab[10];
+  qi = tab[11];
+  qf = tab[12];
+  bad = tab[13];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   double x, x2, lnL;
   bool none = false;
   if constexpr (MARG) {

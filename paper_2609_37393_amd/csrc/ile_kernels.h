@@ -476,7 +476,6 @@ __global__ void __launch_bounds__(256) k_grad_dm(const PointDesc* __restrict__ P
 // GPU one lane per sample).  A wavefront holds 64 / GRAD_G samples; groups
 // past the end repeat the last sample and drop it.  Lanes 0..6 of a group
 // write the seven components.
-constexpr int GRAD_G = 16;
 template <int KT, int L, bool MARG>
 __device__ __forceinline__ void grad_groups(const PointDesc* __restrict__ P, const double* __restrict__ theta,
                                             int64_t n, double* __restrict__ lnL, double* __restrict__ grad,
@@ -486,6 +485,8 @@ __device__ __forceinline__ void grad_groups(const PointDesc* __restrict__ P, con
   const int lg = (int)(threadIdx.x & (GRAD_G - 1));
   const int gw = (int)((threadIdx.x & 63u) / GRAD_G);
   double* tab = tabs + ((threadIdx.x >> 6) * SPW + gw) * GRAD_TAB(L, KT);
+  __shared__ GradPoint<KT, L> S;
+  S.load(opaque(P));
   const int64_t per_launch = (int64_t)gridDim.x * (blockDim.x >> 6) * SPW;
   for (int64_t ib = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * SPW; ib < n;
        ib += per_launch) {
@@ -496,7 +497,7 @@ __device__ __forceinline__ void grad_groups(const PointDesc* __restrict__ P, con
     double incl = c3, dist = th[6 * n];
     const bool ok = theta_coords(coords, incl, dist);
     double g[7];
-    double l = eval_grad_group<KT, L, GRAD_G, MARG>(opaque(P), th[0], th[n], th[2 * n], incl, th[4 * n],
+    double l = eval_grad_group<KT, L, MARG>(opaque(P), S, th[0], th[n], th[2 * n], incl, th[4 * n],
                                                     th[5 * n], dist, tab, g, dm);
     grad_coords(coords, c3, dist, g[3], g[6]);
     if (!ok) {

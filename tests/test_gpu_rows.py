@@ -8,13 +8,16 @@ Bars: FP64 lnL within 1e-9 S + 1e-12 of the oracle, S = |x data| + |x^2 quad|, a
 in the parity tests.
 The row coordinate u of a table of 2^24 rows has an ulp of 3.7e-9; four roundings
 on the way to it move the data term, whose slope is at most pi per row, by
-5e-8 S."""
+5e-8 S.  Gradients as in their parity tests, 1e-7 (|g| + 1e-6 S + 1e-9), plus the
+absolute part of the lnL bar: where the one detector's response vanishes, S and
+g fall to 1e-11 and the rounding of the response's own O(1) terms remains."""
 import numpy as np
 import pytest
 
 from paper_2609_37393_amd import synth
 
 from ._helpers import lnL_scale
+from .test_gpu_gradient import oracle_in, to_coords
 from .test_gpu_parity import _mode_set
 
 pytestmark = pytest.mark.gpu
@@ -114,3 +117,16 @@ def test_fixed_scratch_holds_what_it_held(ile, oracle_mod):
             assert rc == 0 and np.array_equal(ll, l1)
         else:
             assert rc == ESCRATCH
+
+
+
+@pytest.mark.parametrize("K,M,lmax", [(1, 1, None), (2, 5, None), (3, 17, 4), (5, 21, None), (8, 9, None), (6, 25, 8)])
+def test_gradient_groups(ile, oracle_mod, K, M, lmax):
+    pt = synth.make_point(K, M, 600, 32768.0, 60.0, 40 + K, lm=None if lmax is None else _mode_set(M, lmax))
+    th = synth.prior_samples(101, 41)
+    th[3] = np.clip(th[3], 0.05, np.pi - 0.05)
+    l, g = ile.grad(pt, to_coords(th, 0), coords=0)
+    l_or, g_or = oracle_in(oracle_mod, pt, th, 0)
+    S = lnL_scale(oracle_mod, pt, th)
+    assert np.all(np.abs(l.cpu().numpy() - l_or) <= 1e-9 * S + 1e-12)
+    assert np.all(np.abs(g.cpu().numpy() - g_or) <= 1e-7 * (np.abs(g_or) + 1e-6 * S + 1e-9) + 1e-12)
