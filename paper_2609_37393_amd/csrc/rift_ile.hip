@@ -914,6 +914,9 @@ struct rift_ile_plan_s {
   size_t arena_cap = 0;
   size_t arena_off = 0;
   size_t arena_counted = 0;
+  char* slab = nullptr;  // the current piece of small allocations (palloc)
+  size_t slab_off = 0;
+  void* tile_block = nullptr;  // the tiling's buffers
   // tiles (depend on the config)
   rift_ile_config cfg{256, 4, 0, 0};
   std::vector<Tile> h_tiles;
@@ -967,6 +970,7 @@ struct rift_ile_plan_s {
 
 namespace {
 
+constexpr size_t SLAB_BYTES = (size_t)256 << 10, SLAB_PIECE = (size_t)32 << 10;
 // `count`, if given, is what an allocation in the fixed scratch counts against
 // its limit: the FP64 tables count as rows of two modes, the least that holds
 // them, whatever the rows that the reads take (24 against 18 at 17 modes, the
@@ -981,8 +985,22 @@ int palloc(rift_ile_plan p, size_t bytes, void** out, size_t count = 0) {
     p->arena_counted = next(p->arena_counted, count ? count : bytes);
     return RIFT_OK;
   }
+  // small pieces share one allocation: a plan's dozen took most of its set-up
+  if (bytes <= SLAB_PIECE) {
+    const size_t len = (bytes + 255) & ~(size_t)255;
+    if (!p->slab || SLAB_BYTES - p->slab_off < len) {
+      void* d = nullptr;
+      if (hipMalloc(&d, SLAB_BYTES) != hipSuccess) return RIFT_ENOMEM;
+      p->bufs.push_back(d);
+      p->slab = (char*)d;
+      p->slab_off = 0;
+    }
+    *out = p->slab + p->slab_off;
+    p->slab_off += len;
+    return RIFT_OK;
+  }
   void* d = nullptr;
-  if (hipMalloc(&d, bytes < 256 ? 256 : bytes) != hipSuccess) return RIFT_ENOMEM;
+  if (hipMalloc(&d, bytes) != hipSuccess) return RIFT_ENOMEM;
   p->bufs.push_back(d);
   *out = d;
   return RIFT_OK;
@@ -991,6 +1009,9 @@ int palloc(rift_ile_plan p, size_t bytes, void** out, size_t count = 0) {
 void plan_free_all(rift_ile_plan p) {
   for (void* b : p->bufs) (void)hipFree(b);
   p->bufs.clear();
+  p->slab = nullptr;
+  if (p->tile_block) (void)hipFree(p->tile_block);
+  p->tile_block = nullptr;
   if (p->ws) (void)hipFree(p->ws);
   p->ws = nullptr;
 }
@@ -1063,29 +1084,42 @@ int build_tiles(rift_ile_plan p) {
   }
   if (p->h_tiles.size() > (size_t)0x7fffffff) return RIFT_EUNSUPPORTED;
   p->n_tiles = (int)p->h_tiles.size();
-  // release the previous tiling's buffers (the caller has synchronised)
-  for (void* b : {(void*)p->d_tiles, (void*)p->d_trange, (void*)p->d_part, (void*)p->d_tmax, (void*)p->d_terr}) {
-    auto it = std::find(p->bufs.begin(), p->bufs.end(), b);
-    if (b && it != p->bufs.end()) {
-      (void)hipFree(b);
-      p->bufs.erase(it);
+  // the tiling's buffers, in one allocation that a new tiling gives back (the
+  // caller has synchronised); in the fixed scratch a piece each
+  auto pad = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  const size_t n = (size_t)p->n_tiles;
+  const size_t len[5] = {sizeof(Tile) * n, sizeof(int32_t) * 2 * p->n_points, sizeof(double) * 2 * n, sizeof(double) * n,
+                         sizeof(double) * n};
+  void* at[5];
+  int st;
+  if (p->arena) {
+    for (int i = 0; i < 5; ++i)
+      if ((st = palloc(p, len[i], &at[i]))) return st;
+  } else {
+    if (p->tile_block) (void)hipFree(p->tile_block);
+    p->tile_block = nullptr;
+    size_t total = 0;
+    for (size_t l : len) total += pad(l);
+    if (hipMalloc(&p->tile_block, total) != hipSuccess) {
+      p->tile_block = nullptr;
+      return RIFT_ENOMEM;
+    }
+    char* c = (char*)p->tile_block;
+    for (int i = 0; i < 5; ++i) {
+      at[i] = c;
+      c += pad(len[i]);
     }
   }
-  // (re)allocate tile-sized buffers
-  void* v;
-  int st;
-  if ((st = palloc(p, sizeof(Tile) * p->n_tiles, &v))) return st;
-  p->d_tiles = (Tile*)v;
-  if ((st = palloc(p, sizeof(int32_t) * 2 * p->n_points, &v))) return st;
-  p->d_trange = (int32_t*)v;
-  if ((st = palloc(p, sizeof(double) * 2 * p->n_tiles, &v))) return st;
-  p->d_part = (double*)v;
-  if ((st = palloc(p, sizeof(double) * p->n_tiles, &v))) return st;
-  p->d_tmax = (double*)v;
-  if ((st = palloc(p, sizeof(double) * p->n_tiles, &v))) return st;
-  p->d_terr = (double*)v;
-  HCHK(hipMemcpy(p->d_tiles, p->h_tiles.data(), sizeof(Tile) * p->n_tiles, hipMemcpyHostToDevice));
-  HCHK(hipMemcpy(p->d_trange, trange.data(), sizeof(int32_t) * 2 * p->n_points, hipMemcpyHostToDevice));
+  p->d_tiles = (Tile*)at[0];
+  p->d_trange = (int32_t*)at[1];
+  p->d_part = (double*)at[2];
+  p->d_tmax = (double*)at[3];
+  p->d_terr = (double*)at[4];
+  // tiles and ranges in one copy
+  std::vector<char> h((size_t)((char*)at[1] - (char*)at[0]) + len[1]);
+  memcpy(h.data(), p->h_tiles.data(), len[0]);
+  memcpy(h.data() + ((char*)at[1] - (char*)at[0]), trange.data(), len[1]);
+  HCHK(hipMemcpy(at[0], h.data(), h.size(), hipMemcpyHostToDevice));
   return RIFT_OK;
 }
 
@@ -1381,7 +1415,10 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
   } while (0)
 
   void* v = nullptr;
-  PCHK(palloc(p, sizeof(PointDesc) * n_points, &v));
+  // the descriptions, then the mode orders of every point
+  const size_t desc_bytes = (sizeof(PointDesc) * n_points + 255) & ~(size_t)255;
+  constexpr size_t PERM = ((MMAX * sizeof(int32_t) + 255) / 256) * 256;
+  PCHK(palloc(p, desc_bytes + PERM * n_points, &v, sizeof(PointDesc) * n_points));
   p->d_desc = (PointDesc*)v;
   std::vector<int32_t*> d_perm(n_points);
   std::vector<double*> d_qmax(n_points);
@@ -1462,8 +1499,8 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
       PCHK(palloc(p, sizeof(float) * D.B * 3 * KT, &v));
       D.C32 = (const float*)v;
     }
-    PCHK(palloc(p, sizeof(int32_t) * M, &v));
-    d_perm[pi] = (int32_t*)v;
+    d_perm[pi] = (int32_t*)((char*)p->d_desc + desc_bytes + PERM * pi);
+    if (p->arena) p->arena_counted += PERM;
     PCHK(palloc(p, sizeof(double) * KT, &v));
     d_qmax[pi] = (double*)v;
   }
@@ -1554,11 +1591,14 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
   }
   PCHK(build_tiles(p));
   // set-up on the stream
-  PHIP(hipMemcpyAsync(p->d_desc, p->h_desc.data(), sizeof(PointDesc) * n_points, hipMemcpyHostToDevice, st));
+  std::vector<char> h_set(desc_bytes + PERM * n_points);
+  memcpy(h_set.data(), p->h_desc.data(), sizeof(PointDesc) * n_points);
+  for (int pi = 0; pi < n_points; ++pi)
+    memcpy(h_set.data() + desc_bytes + PERM * pi, h_perm[pi].data(), sizeof(int32_t) * h_perm[pi].size());
+  PHIP(hipMemcpyAsync(p->d_desc, h_set.data(), h_set.size(), hipMemcpyHostToDevice, st));
   for (int pi = 0; pi < n_points; ++pi) {
     const rift_ile_point& pt = pts[pi];
     PointDesc& D = p->h_desc[pi];
-    PHIP(hipMemcpyAsync(d_perm[pi], h_perm[pi].data(), sizeof(int32_t) * pt.n_modes, hipMemcpyHostToDevice, st));
     const int64_t qper = (int64_t)(pt.n_t + 2 * QPAD) * q_groups(pt.n_modes, D.w64) * D.w64;
     const int gq = (int)std::min<int64_t>((KT * qper + 255) / 256, 65535);
     hipLaunchKernelGGL(k_repack<double>, dim3(gq), dim3(256), 0, st, pt.Q, (double*)D.Q64, d_perm[pi],
