@@ -1424,18 +1424,29 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
   std::vector<double*> d_qmax(n_points);
   // host copies staged to the device: they live until the final synchronisation
   std::vector<std::vector<int32_t>> h_perm(n_points);
+  // kernel instances exist for one class (1, 2, 4, 8) and for any mix of the
+  // l <= 4 classes (7); a batch mixing l > 4 with smaller points runs every
+  // point in the l <= 8 class (exact for any l <= 8).  The class comes first:
+  // the tables are sized for it, and none is replaced.
+  std::vector<int> own_class(n_points);
+  for (int pi = 0; pi < n_points; ++pi) {
+    int lmax = 2;
+    for (int i = 0; i < pts[pi].n_modes; ++i) lmax = std::max(lmax, (int)pts[pi].lm[2 * i]);
+    own_class[pi] = l_class(lmax);
+    p->lset |= lbit(own_class[pi]);
+  }
+  if (p->lset & 8) p->lset = 8;
+  else if (p->lset != 1 && p->lset != 2 && p->lset != 4) p->lset = 7;
   int64_t s0 = 0;
   for (int pi = 0; pi < n_points; ++pi) {
     const rift_ile_point& pt = pts[pi];
     PointDesc& D = p->h_desc[pi];
     memset(&D, 0, sizeof(D));
     const int K = pt.n_det, M = pt.n_modes;
-    int lmax = 2;
-    for (int i = 0; i < M; ++i) lmax = std::max(lmax, (int)pt.lm[2 * i]);
     D.K = K;
     D.M = M;
     D.n_t = pt.n_t;
-    D.L = l_class(lmax);
+    D.L = p->lset == 8 ? 8 : own_class[pi];
     D.B = basis_count(D.L);
     D.KT = KT;
     D.n = n_per_point[pi];
@@ -1460,7 +1471,6 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
     }
     // refinement margin: an unrefined sample weighs < e^{-T} of the best one
     D.T = log((double)D.n) + 12.0;
-    p->lset |= lbit(D.L);
     for (int k = 0; k < K; ++k) {
       const double* d = pt.det_tensor + 9 * k;
       const double six[6] = {d[0], d[4], d[8], d[1] + d[3], d[2] + d[6], d[5] + d[7]};
@@ -1500,35 +1510,18 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
       D.C32 = (const float*)v;
     }
     d_perm[pi] = (int32_t*)((char*)p->d_desc + desc_bytes + PERM * pi);
-    if (p->arena) p->arena_counted += PERM;
-    PCHK(palloc(p, sizeof(double) * KT, &v));
-    d_qmax[pi] = (double*)v;
-  }
-  // kernel instances exist for one class (1, 2, 4, 8) and for any mix of the
-  // l <= 4 classes (7); a batch mixing l > 4 with smaller points runs every
-  // point in the l <= 8 class (exact for any l <= 8)
-  if (!(p->lset & 8) && p->lset != 1 && p->lset != 2 && p->lset != 4) p->lset = 7;
-  if ((p->lset & 8) && p->lset != 8) {
-    p->lset = 8;
-    for (int pi = 0; pi < n_points; ++pi) {
-      PointDesc& D = p->h_desc[pi];
-      if (D.L != 8) {
-        D.L = 8;
-        D.B = basis_count(8);
-        for (auto* b : {(void*)D.C64, (void*)D.C32}) {
-          if (!b) continue;
-          auto it = std::find(p->bufs.begin(), p->bufs.end(), b);
-          if (it != p->bufs.end()) { (void)hipFree(*it); p->bufs.erase(it); }
-        }
-        PCHK(palloc(p, sizeof(double) * D.B * 3 * KT, &v));
-        D.C64 = (const double*)v;
-        D.C32 = nullptr;
-        if (mixed) {
-          PCHK(palloc(p, sizeof(float) * D.B * 3 * KT, &v));
-          D.C32 = (const float*)v;
-        }
+    if (p->arena) {
+      p->arena_counted += PERM;
+      // what the fixed scratch serves stays: a point that runs in a class above
+      // its own counts the tables of both
+      if (own_class[pi] != D.L) {
+        auto pad = [](size_t b) { return (b + 255) & ~(size_t)255; };
+        const size_t entries = (size_t)basis_count(own_class[pi]) * 3 * KT;
+        p->arena_counted += pad(sizeof(double) * entries) + (mixed ? pad(sizeof(float) * entries) : 0);
       }
     }
+    PCHK(palloc(p, sizeof(double) * KT, &v));
+    d_qmax[pi] = (double*)v;
   }
   // binning layout: sort tiles, count-matrix blocks and coarse buckets per
   // point, all in point order (so the matrix scan starts point p at s0)

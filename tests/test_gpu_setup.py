@@ -8,6 +8,8 @@ import pytest
 
 from paper_2609_37393_amd import synth
 
+from ._helpers import lnL_scale
+
 pytestmark = pytest.mark.gpu
 
 SETS = [[(2, 2)], [(2, 0)], [(2, -2), (2, 2)], [(2, 1), (2, -1), (2, 0)], [(3, 3), (2, -2), (3, -1)],
@@ -32,3 +34,25 @@ def test_norm_coefficients(oracle_mod, K):
                           want_lnL=True)
     for got in (alone, mixed.cpu().numpy()):
         assert np.all(np.abs(got - want) <= 1e-9 * np.abs(want) + 1e-12)
+
+
+@pytest.mark.parametrize("lead,precision", [(1, "fp64"), (5, "mixed")])
+def test_mixed_classes_of_long_tables(oracle_mod, lead, precision):
+    """Tables too long to share an allocation with the coefficients, a first
+    point with l <= 4 and one further on with l > 4."""
+    import torch
+
+    from paper_2609_37393_amd import ile
+
+    pts = [synth.make_point(3, 4, 1000, 32768.0, 40.0, 80 + j) for j in range(9)]
+    pts[lead] = synth.make_point(3, 3, 1000, 32768.0, 40.0, 99, lm=[(8, 8), (2, 2), (6, -3)])
+    ths = [synth.prior_samples(200, 90 + j) for j in range(9)]
+    want = np.concatenate([oracle_mod.lnL(p, t) for p, t in zip(pts, ths)])
+    z, _, got = ile.lnZ(pts, torch.as_tensor(np.concatenate(ths, axis=1)), n_per_point=[200] * 9, precision=precision,
+                        want_lnL=True)
+    top = want.reshape(9, 200).max(axis=1, keepdims=True)
+    lnZ = (top + np.log(np.exp(want.reshape(9, 200) - top).mean(axis=1, keepdims=True)))[:, 0]
+    if precision == "fp64":
+        S = np.concatenate([lnL_scale(oracle_mod, p, t) for p, t in zip(pts, ths)])
+        assert np.all(np.abs(got.cpu().numpy() - want) <= 1e-9 * S + 1e-12)
+    assert np.all(np.abs(z.cpu().numpy() - lnZ) <= 1e-3)

@@ -1,0 +1,101 @@
+"""The library's host code on the CPU, against a stand-in for the GPU runtime
+(host_runtime.c): no kernel runs, every runtime call is logged, and freed
+memory is never reused, so that an address into it is seen wherever it is
+copied to the device.  Each test is a process of its own, whose first loaded
+library is the stand-in: the library's runtime calls bind to it."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+pytestmark = pytest.mark.skipif(shutil.which("gcc") is None, reason="needs gcc")
+
+# Everything a test program has in hand: the structures of the C ABI (as plain
+# ctypes, without torch, which brings the real runtime) and small points.
+PRELUDE = r"""
+import ctypes, sys
+import numpy as np
+vp, i32, i64, f64, ci = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_double, ctypes.c_int
+rt = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+rt.host_log.restype = ctypes.c_char_p
+rt.host_limit.argtypes = [ctypes.c_size_t]
+lib = ctypes.CDLL(sys.argv[2])
+OK, ENOMEM, ESCRATCH = 0, -3, -5
+FP64, MIXED = 0, 1
+PTR = 1 << 12  # a device address that no code on the host reads
+
+
+class Point(ctypes.Structure):
+    _fields_ = [("n_det", i32), ("n_modes", i32), ("n_t", i32), ("lm", vp), ("t0", f64), ("dt", f64), ("Q", vp), ("U", vp),
+                ("V", vp), ("det_tensor", vp), ("det_pos", vp), ("gmst_rad", f64), ("d_ref", f64)]
+
+
+keep = []
+
+
+def point(K, lm, n_t):
+    lm = np.ascontiguousarray(lm, np.int32)
+    D, R = np.zeros((K, 3, 3)), np.full((K, 3), 0.01)
+    keep.extend([lm, D, R])
+    return Point(K, len(lm), n_t, lm.ctypes.data, -0.5 * n_t / 32768, 1 / 32768, PTR, PTR, PTR, D.ctypes.data,
+                 R.ctypes.data, 0.1, 100.0)
+
+
+def modes(M, lmax=4):
+    return [(l, m) for l in range(lmax, 1, -1) for m in range(-l, l + 1)][:M]
+
+
+def create(pts, counts, prec=FP64, stream=None):
+    c = (Point * len(pts))(*pts)
+    n = np.asarray(counts, np.int64)
+    h = vp()
+    rc = lib.rift_ile_plan_create(c, len(pts), vp(n.ctypes.data), prec, vp(stream), ctypes.byref(h))
+    return rc, h
+
+
+def log():
+    out = [l.split(" ", 4) for l in rt.host_log().decode().splitlines()]
+    return [(op, int(p, 16) if p != "(nil)" else 0, int(n), int(st, 16) if st != "(nil)" else 0, name)
+            for op, p, n, st, name in out]
+
+
+def clear():
+    rt.host_clear()
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    from paper_2609_37393_amd import build
+
+    if not os.path.exists(build.LIB):
+        build.build()
+    so = str(tmp_path_factory.mktemp("host") / "runtime.so")
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", os.path.join(HERE, "host_runtime.c"), "-o", so])
+
+    def go(program):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + program, so, build.LIB], capture_output=True, text=True,
+                           timeout=120, cwd=ROOT)
+        assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+
+    return go
+
+
+@pytest.mark.parametrize("prec", ["FP64", "MIXED"])
+@pytest.mark.parametrize("lead,n_points,n_t", [(1, 8, 1000), (3, 12, 700), (7, 40, 64), (0, 9, 900)])
+def test_plan_of_mixed_classes_keeps_what_it_holds(run, prec, lead, n_points, n_t):
+    """A batch that mixes l > 4 with smaller points runs in one class: no
+    address that reaches the device lies in memory that was given back, and a
+    destroyed plan leaves nothing."""
+    run(f"""
+pts = [point(3, modes(9), {n_t}) for _ in range({n_points})]
+pts[{lead}] = point(3, [(8, 8), (2, 2), (6, -3)], {n_t})
+rc, h = create(pts, [100] * len(pts), {prec})
+assert rc == OK and rt.host_faults() == 0, (rc, [l for l in log() if l[0] == "FAULT"])
+assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0 and rt.host_live() == 0
+""")
