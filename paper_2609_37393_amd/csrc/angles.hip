@@ -150,13 +150,17 @@ __global__ void __launch_bounds__(256) k_psi(PsiRule G, int64_t cnt, const doubl
 //   2 c2 z^4 + c1 z^3 - conj(c1) z - 2 conj(c2) = 0;
 // its roots, by the Aberth-Ehrlich iteration, that lie within 1e-3 of the unit
 // circle are polished by Newton's method on q'(u) and kept if they settle on a
-// zero of q'.  Without c2 the two stationary points are closed forms.  The
+// zero of q'.  Without c2, or with one below the rounding of c1 (the quartic's
+// other two roots then lie near 0 and far out, beyond what the iteration's
+// squares can hold), the two stationary points are closed forms.  The
 // sorted angles cut the circle into cells on which q is monotone; each cell is
 // integrated by 8-point Gauss-Legendre on sub-intervals of 2 sigma out to
 // 8 sigma from its higher end, then of doubling length to its far end, sigma =
 // min(A^{-1/2}, width / 8) from the curvature A = -q'' at that end.  A cell
 // ends early where q, monotone in it, has fallen so far below the largest
-// stationary value that nothing further on can count.
+// stationary value that nothing further on can count.  With fewer than two
+// points found the circle is one cell, in which q need not be monotone: it is
+// covered whole.
 //
 // A wavefront takes 64 samples: a lane per sample for the stationary points,
 // then eight lanes per sample, one per node of a sub-interval.  Measured for 1e6
@@ -178,6 +182,7 @@ __device__ __forceinline__ Cx cx_inv(Cx b) {
 }
 
 constexpr int CELL_MAX = 4;
+constexpr double C2_COUNTS = 1e-18;  // of c1: below it c2 moves neither a stationary point nor its value
 constexpr double CELL_FAR = 50.0;  // nats below the largest value at which a cell ends
 constexpr int CELL_STEPS = 1200;  // sub-intervals of a cell: doublings from the smallest sigma to a whole turn
 struct CellPoint {
@@ -193,14 +198,14 @@ __device__ __forceinline__ void psi_stationary(double a, double c1r, double c1i,
   const double scale = fmax(fmax(fabs(c1r), fabs(c1i)), 2.0 * fmax(fabs(c2r), fabs(c2i)));
   if (!(scale > 0.0)) return;
   double q, d1, d2, su, cu;
-  if (c2r == 0.0 && c2i == 0.0) {
+  if (2.0 * fmax(fabs(c2r), fabs(c2i)) <= C2_COUNTS * scale) {
     const double top = -atan2(c1i, c1r);
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       double u = top + 3.14159265358979323846 * k;
       u = u < 0.0 ? u + TWO_PI : u;
       sincos_many<1>(&u, &su, &cu);
-      psi_q(a, c1r, c1i, 0.0, 0.0, su, cu, &q, &d1, &d2);
+      psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
       st[k] = CellPoint{u, q, d2};
     }
   } else {
@@ -403,7 +408,7 @@ __global__ void __launch_bounds__(128) k_psi_cells(int64_t cnt, const double* __
         sum = fma(h * wg, exp(q - m), sum);
         d0 = d1;
         ++j;
-        if (!(d0 < width) || qfar < m0 - CELL_FAR || j > CELL_STEPS) next();
+        if (!(d0 < width) || (nc > 1 && qfar < m0 - CELL_FAR) || j > CELL_STEPS) next();
       }
     }
     double mx = m;

@@ -133,3 +133,19 @@ def test_captured_calls_replay(ile, rule):
         torch.cuda.synchronize()
         assert torch.equal(out[0], ll) and torch.equal(out[1], z) and torch.equal(out[2], ne)
     plan.close()
+
+
+@pytest.mark.parametrize("method,n_points", [("cells", 0), ("laplace", 0), ("trapezoid", 64)])
+@pytest.mark.parametrize("factor", [0.0, 1e-200, 1e-70, 1e-45, 1e-30, 1e-19, 1e-12])
+def test_norm_without_polarisation(ile, oracle_mod, factor, method, n_points):
+    """V = 0: q(u) = a + Re(c1 e^{iu}), two stationary points in closed form; and a
+    V too small to count beside the data term, where the quartic has roots near
+    0 and far out.  The peak lies anywhere on the circle, far above the value at
+    u = 0 for most samples."""
+    pt = synth.make_point(3, 9, 900, 32768.0, 600.0, 43)
+    th = synth.prior_samples(1500, 44)
+    with_v, without = dict(pt, V=pt["V"] * factor), dict(pt, V=pt["V"] * 0.0)
+    got = _run(ile, with_v, th, lambda p, t, ll: p.lnZ_pmarg(t, method, n_points, lnL_out=ll))
+    ref = without if factor < 1e-20 else with_v
+    _compare(got, oracle_mod.lnL_pmarg(ref, th, method, n_points),
+             _bar_psi(oracle_mod, ref, th, n_points, method != "trapezoid"), (factor, method))
