@@ -43,6 +43,10 @@
  * Streams: `stream` is a hipStream_t (NULL = the null stream).  Evaluation
  * calls on a plan only enqueue work and return; outputs are valid once the
  * stream has reached them, and such calls can be captured into a HIP graph.
+ * The marginals over time, polarisation and both angles need working memory:
+ * it is stream-ordered (hipMallocAsync), up to 256 MB of it stay with the plan
+ * until it is destroyed, and a call on another stream than the last waits for
+ * it on the device; a captured call's memory belongs to the graph.
  * Plan creation and destruction synchronise the stream (they allocate and
  * free device memory and stage small host tables).  The one-shot entry points
  * (rift_ile_lnL, rift_ile_lnZ, rift_ile_grad) create and destroy a plan

@@ -965,7 +965,7 @@ struct rift_ile_plan_s {
   // workspace of the calls that need one, kept for the next call (take_space)
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  hipStream_t ws_stream = nullptr;
+  hipEvent_t ws_done = nullptr;  // after the last use of ws
 };
 
 namespace {
@@ -1012,16 +1012,23 @@ void plan_free_all(rift_ile_plan p) {
   p->slab = nullptr;
   if (p->tile_block) (void)hipFree(p->tile_block);
   p->tile_block = nullptr;
-  if (p->ws) (void)hipFree(p->ws);
+  if (p->ws) {
+    (void)hipEventSynchronize(p->ws_done);
+    (void)hipFreeAsync(p->ws, nullptr);
+  }
   p->ws = nullptr;
+  if (p->ws_done) (void)hipEventDestroy(p->ws_done);
+  p->ws_done = nullptr;
 }
 
 // Working memory of one call.  Up to WS_KEEP bytes stay with the plan (given
 // back with it): taking a few hundred MB from the stream-ordered pool again
 // after every synchronisation costs 0.1 - 0.4 ms.  Larger requests, and calls
 // that are being captured (a graph must own what it replays on), take
-// stream-ordered memory that drop_space releases.  Work of an earlier call on
-// another stream is waited for before its workspace is taken.
+// stream-ordered memory that drop_space releases.  No call waits on the host:
+// the kept memory is stream-ordered too, an event marks the end of its last
+// use, and a call's stream waits for that event before it takes the memory (or
+// gives it back for more), whichever stream or thread the last call was on.
 constexpr int SERIES_POINT_TIMES = 40000;
 constexpr size_t WS_KEEP = (size_t)256 << 20;
 struct Space {
@@ -1029,33 +1036,33 @@ struct Space {
   bool pooled = false;
 };
 int take_space(rift_ile_plan p, size_t bytes, hipStream_t st, Space* s) {
+  auto take = [&](void** d) {
+    if (hipMallocAsync(d, bytes, st) == hipSuccess) return RIFT_OK;
+    (void)hipGetLastError();  // reported here, not by the next launch
+    *d = nullptr;
+    return RIFT_ENOMEM;
+  };
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   HCHK(hipStreamIsCapturing(st, &cap));
   if (cap != hipStreamCaptureStatusNone || bytes > WS_KEEP) {
-    if (hipMallocAsync(&s->p, bytes, st) != hipSuccess) return RIFT_ENOMEM;
     s->pooled = true;
-    return RIFT_OK;
+    return take(&s->p);
   }
-  if (p->ws && p->ws_stream != st) HCHK(hipDeviceSynchronize());
-  p->ws_stream = st;
+  if (!p->ws_done) HCHK(hipEventCreateWithFlags(&p->ws_done, hipEventDisableTiming));
+  if (p->ws) HCHK(hipStreamWaitEvent(st, p->ws_done, 0));
   if (p->ws_bytes < bytes) {
-    if (p->ws) {
-      HCHK(hipDeviceSynchronize());
-      (void)hipFree(p->ws);
-    }
+    if (p->ws) HCHK(hipFreeAsync(p->ws, st));
     p->ws = nullptr;
     p->ws_bytes = 0;
-    if (hipMalloc(&p->ws, bytes) != hipSuccess) {
-      p->ws = nullptr;
-      return RIFT_ENOMEM;
-    }
+    const int rc = take(&p->ws);
+    if (rc) return rc;
     p->ws_bytes = bytes;
   }
   s->p = p->ws;
   return RIFT_OK;
 }
-int drop_space(const Space& s, hipStream_t st) {
-  return s.pooled && hipFreeAsync(s.p, st) != hipSuccess ? RIFT_EDEVICE : RIFT_OK;
+int drop_space(rift_ile_plan p, const Space& s, hipStream_t st) {
+  return (s.pooled ? hipFreeAsync(s.p, st) : hipEventRecord(p->ws_done, st)) == hipSuccess ? RIFT_OK : RIFT_EDEVICE;
 }
 
 int build_tiles(rift_ile_plan p) {
@@ -1955,7 +1962,7 @@ int rift_ile_plan_lnZ_tmarg(rift_ile_plan p, const double* theta, const double* 
     if (!L) L = (double*)((char*)sp.p + bytes);
     rc = series_batch(p, theta, 0, nullptr, sp.p, bytes, L, st);
     if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
-    const int rd = drop_space(sp, st);
+    const int rd = drop_space(p, sp, st);
     return rc ? rc : rd;
   }
   if (sorted && (rc = run_binning(p, theta, st))) return rc;
@@ -2010,7 +2017,7 @@ int rift_ile_plan_lnZ_tband(rift_ile_plan p, const double* theta, const double* 
     if (!rc) rc = band_reconstruct(N, n, M, (const double*)sp.p, 1, N, sinc, L, st);
   }
   if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
-  const int rd = drop_space(sp, st);
+  const int rd = drop_space(p, sp, st);
   return rc ? rc : rd;
 }
 
@@ -2048,7 +2055,7 @@ int rift_ile_plan_lnZ_erai(rift_ile_plan p, const double* theta, const double* l
       return run_erai(count, rule->n_phi, rule->n_psi, m_max, coef, stride, tab, L + first, st);
     });
   if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
-  const int rd = drop_space(sp, st);
+  const int rd = drop_space(p, sp, st);
   return rc ? rc : rd;
 }
 
@@ -2082,7 +2089,7 @@ int rift_ile_plan_lnZ_pmarg(rift_ile_plan p, const double* theta, const double* 
       return run_psi(g, count, coef, stride, tab, L + first, st);
     });
   if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
-  const int rd = drop_space(sp, st);
+  const int rd = drop_space(p, sp, st);
   return rc ? rc : rd;
 }
 

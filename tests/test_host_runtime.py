@@ -99,3 +99,99 @@ rc, h = create(pts, [100] * len(pts), {prec})
 assert rc == OK and rt.host_faults() == 0, (rc, [l for l in log() if l[0] == "FAULT"])
 assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0 and rt.host_live() == 0
 """)
+
+
+MARGINALS = r"""
+class Psi(ctypes.Structure):
+    _fields_ = [("method", i32), ("n_points", i32)]
+
+
+class Angle(ctypes.Structure):
+    _fields_ = [("n_phi", i32), ("n_psi", i32)]
+
+
+class Time(ctypes.Structure):
+    _fields_ = [("t_start", f64), ("h", f64), ("n_t", i32)]
+
+
+class Band(ctypes.Structure):
+    _fields_ = [("t_start", f64), ("h", f64), ("n_t", i32), ("n_fine", i32)]
+
+
+RULES = {"pmarg": Psi(0, 64), "erai": Angle(8, 4), "tmarg": Time(-1e-3, 1 / 32768, 65), "tband": Band(-2e-3, 1 / 4096, 16, 8)}
+
+
+def marginal(h, name, stream=None, values=PTR):
+    r = RULES[name]
+    keep.append(r)
+    return getattr(lib, "rift_ile_plan_lnZ_" + name)(h, vp(PTR), None, ctypes.byref(r), vp(PTR), None, vp(values), vp(stream))
+
+
+S1, S2 = 0x111000, 0x222000
+HOST = ("device_sync", "stream_sync", "event_sync", "malloc", "free", "copy", "copy_async")
+"""
+
+
+@pytest.mark.parametrize("first,second", [("pmarg", "erai"), ("tmarg", "tband"), ("erai", "tmarg"), ("pmarg", "tband")])
+def test_marginals_only_enqueue(run, first, second):
+    """A marginal neither waits on the host nor takes or frees device memory but in
+    stream order: on the first call, on another stream, where the working memory
+    has to grow, and on one stream again; each call waits for the last use of the
+    memory before anything of its own, and marks its own after its last kernel."""
+    run(MARGINALS + f"""
+rc, h = create([point(3, modes(9), 900)], [5000])
+assert rc == OK
+clear()
+last, held = None, None
+for name, stream in (({first!r}, S1), ({first!r}, S2), ({second!r}, S1), ({second!r}, S1), ({first!r}, S2), ({second!r}, S2)):
+    for values in (PTR, None):
+        assert marginal(h, name, stream, values) == OK
+        calls = log()
+        clear()
+        assert not [c for c in calls if c[0] in HOST + ("FAULT",)], calls
+        assert all(c[3] == stream for c in calls if c[0] in ("launch", "wait", "record", "malloc_async", "free_async"))
+        kinds = [c[0] for c in calls if c[0] != "event"]
+        if held:
+            assert kinds[0] == "wait" and calls[0][1] == last, calls
+        assert kinds[-1] == "record" and "record" not in kinds[:-1], kinds
+        last = calls[-1][1]
+        taken = [c for c in calls if c[0] == "malloc_async"]
+        assert len(taken) <= 1
+        if taken:
+            given = [c for c in calls if c[0] == "free_async"]
+            assert [c[1] for c in given] == ([held] if held else [])
+            held = taken[0][1]
+assert rt.host_faults() == 0
+assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0 and rt.host_live() == 0
+""")
+
+
+@pytest.mark.parametrize("name", ["pmarg", "erai", "tmarg", "tband"])
+def test_captured_marginals_own_their_memory(run, name):
+    run(MARGINALS + f"""
+rc, h = create([point(3, modes(9), 900)], [5000])
+assert rc == OK and marginal(h, {name!r}, S1) == OK
+clear()
+rt.host_capture(1)
+assert marginal(h, {name!r}, S2) == OK
+calls = log()
+taken = [c[1] for c in calls if c[0] == "malloc_async"]
+assert len(taken) == 1 and taken == [c[1] for c in calls if c[0] == "free_async"]
+assert not [c for c in calls if c[0] in HOST + ("wait", "record", "FAULT")]
+rt.host_capture(0)
+assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0 and rt.host_live() == 0
+""")
+
+
+@pytest.mark.parametrize("name", ["pmarg", "erai", "tmarg", "tband"])
+def test_marginal_without_memory_leaves_the_plan(run, name):
+    """RIFT_ENOMEM launches nothing, and the plan serves the next call."""
+    run(MARGINALS + f"""
+rc, h = create([point(3, modes(9), 900)], [5000])
+rt.host_limit(1000)
+clear()
+assert marginal(h, {name!r}, S1) == ENOMEM and not [c for c in log() if c[0] == "launch"]
+rt.host_limit(1 << 40)
+assert marginal(h, {name!r}, S1) == OK and lib.rift_ile_plan_lnZ(h, vp(PTR), None, vp(PTR), None, None, None, None, vp(S1)) == OK
+assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0 and rt.host_live() == 0
+""")
