@@ -824,16 +824,27 @@ int wide_run(const rift_ile_point_wide* pt, int64_t n, const double* theta, cons
   // 0.4 ns per sample and 20 entries more than the rows.  The lines meet near
   // this many samples at every width.
   const size_t row_bytes = 128 * (size_t)wide_lines(MB, D.n_a);
-  const bool packed = n >= WIDE_PACK_MIN && (uint64_t)D.n_t * row_bytes <= 0xffffffffu;
+  bool packed = n >= WIDE_PACK_MIN && (uint64_t)D.n_t * row_bytes <= 0xffffffffu;
   // stream-ordered scratch: the repacked rows, the real form's operands (and
   // one pair of steps that is fetched past the end), the blocks' (max, sum) pairs
-  const size_t q_bytes = packed ? (size_t)D.K * D.n_t * row_bytes : 0;
+  size_t q_bytes = packed ? (size_t)D.K * D.n_t * row_bytes : 0;
   const int steps = wide_steps(MB, D.n_a);
   const size_t form_bytes = sizeof(double) * 128 * (size_t)(D.K * wide_pairs(steps, wide_tiles(MB, D.n_a)) + 1);
   const size_t part_bytes = lnZ ? sizeof(double) * 2 * (size_t)nb : 0;
   hipStream_t st = (hipStream_t)stream;
   char* space = nullptr;
-  if (hipMallocAsync((void**)&space, q_bytes + form_bytes + part_bytes, st) != hipSuccess) return RIFT_ENOMEM;
+  auto take = [&]() {
+    if (hipMallocAsync((void**)&space, q_bytes + form_bytes + part_bytes, st) == hipSuccess) return true;
+    (void)hipGetLastError();  // handled here, not by the next launch
+    return false;
+  };
+  bool have = take();
+  if (!have && packed) {  // no room for a second copy of the table: its series are read as they are
+    packed = false;
+    q_bytes = 0;
+    have = take();
+  }
+  if (!have) return RIFT_ENOMEM;
   double* form = (double*)(space + q_bytes);
   double* d_part = lnZ ? (double*)(space + q_bytes + form_bytes) : nullptr;
   D.Qrows = (const double*)space;

@@ -195,3 +195,43 @@ rt.host_limit(1 << 40)
 assert marginal(h, {name!r}, S1) == OK and lib.rift_ile_plan_lnZ(h, vp(PTR), None, vp(PTR), None, None, None, None, vp(S1)) == OK
 assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0 and rt.host_live() == 0
 """)
+
+
+WIDE = r"""
+class Wide(ctypes.Structure):
+    _fields_ = [("n_det", i32), ("n_modes", i32), ("n_t", i32), ("lm", vp), ("t0", f64), ("dt", f64), ("response", i32),
+                ("n_terms", i32), ("Q", vp), ("U", vp), ("V", vp), ("det_tensor", vp), ("det_pos", vp), ("det_arms", vp),
+                ("gmst_rad", f64), ("omega", f64), ("d_ref", f64)]
+
+
+def wide_point(K, lm, n_a, n_t, response=1):
+    lm = np.ascontiguousarray(lm, np.int32)
+    D, R, A = np.zeros((K, 3, 3)), np.full((K, 3), 0.01), np.zeros((K, 2, 3))
+    keep.extend([lm, D, R, A])
+    return Wide(K, len(lm), n_t, lm.ctypes.data, -0.5 * n_t / 32768, 1 / 32768, response, n_a, PTR, PTR, PTR, D.ctypes.data,
+                R.ctypes.data, A.ctypes.data, 0.1, 7e-5, 100.0)
+
+
+def wide(pt, n, stream=None):
+    return lib.rift_ile_wide_lnZ(ctypes.byref(pt), i64(n), vp(PTR), None, vp(PTR), None, None, vp(stream))
+"""
+
+
+def test_composite_call_without_room_for_rows(run):
+    """A table whose repacked copy does not fit is read as it is."""
+    run(WIDE + """
+pt = wide_point(3, modes(4), 5, 20000)
+assert wide(pt, 20000, 0x111000) == OK
+size = [c[2] for c in log() if c[0] == "malloc_async"][0]
+assert size > 8 << 20  # the rows
+clear()
+rt.host_limit(1 << 20)
+assert wide(pt, 20000, 0x111000) == OK, "no room"
+names = [c[4] for c in log() if c[0] == "launch"]
+assert not any("k_wide_rows" in n for n in names) and any("k_wide_merge" in n for n in names)
+rt.host_limit(100)
+clear()
+assert wide(pt, 20000, 0x111000) == ENOMEM and not [c for c in log() if c[0] == "launch"]
+rt.host_limit(1 << 40)
+assert wide(pt, 20000, 0x111000) == OK and rt.host_faults() == 0 and rt.host_live() == 0
+""")
