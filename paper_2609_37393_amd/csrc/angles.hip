@@ -98,12 +98,13 @@ __device__ __forceinline__ void circle_push(const RIFT_CONST double* tu, int n, 
 
 // The trapezoid and Laplace rules, a lane per sample.
 __global__ void __launch_bounds__(256) k_psi(PsiRule G, int64_t cnt, const double* __restrict__ coef, int64_t stride,
-                                             const double* __restrict__ tab, double* __restrict__ L) {
+                                             const double* __restrict__ tab, PsiOut out) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= cnt) return;
+  RIFT_GLOBAL double* value = as_global_w(out.L) + out.at(i);
   const RIFT_GLOBAL double* c = as_global(coef) + i;
   const double a = c[0], c1r = c[stride], c1i = c[2 * stride], c2r = c[3 * stride], c2i = c[4 * stride];
-  const double flag = L[i];
+  const double flag = *value;
   const RIFT_CONST double* tu = as_const(tab);
   if (flag != flag) return;
   double q, d1, d2;
@@ -133,14 +134,14 @@ __global__ void __launch_bounds__(256) k_psi(PsiRule G, int64_t cnt, const doubl
     sincos_many<1>(&u, &su, &cu);
     psi_q(a, c1r, c1i, c2r, c2i, su, cu, &q, &d1, &d2);
     if (-d2 >= PSI_LAPLACE_MIN_A) {
-      L[i] = q - 0.5 * log(TWO_PI * -d2);
+      *value = q - 0.5 * log(TWO_PI * -d2);
       return;
     }
     n = PSI_FALLBACK_POINTS;
   }
   double m = -__builtin_inf(), sum = 0.0;
   circle_push(tu, n, a, c1r, c1i, c2r, c2i, m, sum);
-  L[i] = m + log(sum) - log((double)n);
+  *value = m + log(sum) - log((double)n);
 }
 
 // ---------------------------------------------------------------------------
@@ -281,6 +282,7 @@ struct CellLds {
   double c[5][64];                // a, c1, c2
   double m[64];                   // the largest value at an end
   double start[CELL_MAX][64], width[CELL_MAX][64], sigma[CELL_MAX][64], top[CELL_MAX][64];
+  int64_t at[64];                 // where its value goes
   int32_t n[64], dir[64];         // cells; bit c: cell c runs downwards from its higher end
 };
 
@@ -292,7 +294,7 @@ __constant__ double kGL8W[8] = {0.10122853629037625915, 0.22238103445337447054, 
                                 0.22238103445337447054, 0.10122853629037625915};
 
 __global__ void __launch_bounds__(128) k_psi_cells(int64_t cnt, const double* __restrict__ coef, int64_t stride,
-                                                   double* __restrict__ L) {
+                                                   PsiOut out) {
   __shared__ CellLds lds[2];
   const int lane = threadIdx.x & 63;
   CellLds& S = lds[threadIdx.x >> 6];
@@ -302,7 +304,10 @@ __global__ void __launch_bounds__(128) k_psi_cells(int64_t cnt, const double* __
     const int64_t i = base + lane < cnt ? base + lane : cnt - 1;
     const RIFT_GLOBAL double* p = as_global(coef) + i;
     const double a = p[0], c1r = p[stride], c1i = p[2 * stride], c2r = p[3 * stride], c2i = p[4 * stride];
-    const bool bad = L[i] != L[i];
+    const int64_t o = out.at(i);
+    const double flag = as_global(out.L)[o];
+    const bool bad = flag != flag;
+    S.at[lane] = o;
     S.c[0][lane] = a;
     S.c[1][lane] = c1r;
     S.c[2][lane] = c1i;
@@ -417,7 +422,7 @@ __global__ void __launch_bounds__(128) k_psi_cells(int64_t cnt, const double* __
     if (m != mx) sum *= exp(m - mx);
 #pragma unroll
     for (int o = 4; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
-    if (g == 0 && base + s < cnt && nc > 0) as_global_w(L)[base + s] = mx + log(sum) - 1.8378770664093454836;  // ln 2 pi
+    if (g == 0 && base + s < cnt && nc > 0) as_global_w(out.L)[S.at[s]] = mx + log(sum) - 1.8378770664093454836;  // ln 2 pi
   }
 }
 
@@ -453,9 +458,10 @@ template <int NDM, int NQM>
 __global__ void __launch_bounds__(256) k_erai(int64_t cnt, int nd, int nq, int n_phi, int n_psi,
                                               const double* __restrict__ ang, int64_t stride,
                                               const double* __restrict__ wd, const double* __restrict__ wq,
-                                              const double* __restrict__ tu, double ln_scale, double* __restrict__ L) {
+                                              const double* __restrict__ tu, double ln_scale, PsiOut out) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= cnt) return;
+  RIFT_GLOBAL double* value = as_global_w(out.L) + out.at(i);
   double c1r[NDM], c1i[NDM], ca[NQM], c2r[NQM], c2i[NQM];
   const RIFT_GLOBAL double* p = as_global(ang) + i;
 #pragma unroll
@@ -470,7 +476,7 @@ __global__ void __launch_bounds__(256) k_erai(int64_t cnt, int nd, int nq, int n
     c2r[j] = j < nq ? p[(r + 1) * stride] : 0.0;
     c2i[j] = j < nq ? p[(r + 2) * stride] : 0.0;
   }
-  const double flag = L[i];
+  const double flag = *value;
   double m = -__builtin_inf(), sum = 0.0;
   for (int f = 0; f < n_phi; ++f) {
     const RIFT_CONST double* Wd = as_const(wd) + f * NDM;
@@ -489,7 +495,7 @@ __global__ void __launch_bounds__(256) k_erai(int64_t cnt, int nd, int nq, int n
     }
     circle_push(as_const(tu), n_psi, A, C1r, C1i, C2r, C2i, m, sum);
   }
-  L[i] = (flag == flag && sum == sum) ? m + log(sum) + ln_scale : __builtin_nan("");
+  *value = (flag == flag && sum == sum) ? m + log(sum) + ln_scale : __builtin_nan("");
 }
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
@@ -511,13 +517,13 @@ int psi_tables(const PsiRule& r, double* tab, hipStream_t st) {
   return launched();
 }
 
-int run_psi(const PsiRule& r, int64_t cnt, const double* coef, int64_t stride, const double* tab, double* L,
-            hipStream_t st) {
+int run_psi(const PsiRule& r, int64_t cnt, const double* coef, int64_t stride, const double* tab,
+            const PsiOut& out, hipStream_t st) {
   if ((cnt + 127) / 128 > 0x7fffffff) return RIFT_EUNSUPPORTED;
   if (r.method == 2)
-    hipLaunchKernelGGL(k_psi_cells, dim3(blocks_for(cnt, 128)), dim3(128), 0, st, cnt, coef, stride, L);
+    hipLaunchKernelGGL(k_psi_cells, dim3(blocks_for(cnt, 128)), dim3(128), 0, st, cnt, coef, stride, out);
   else
-    hipLaunchKernelGGL(k_psi, dim3(blocks_for(cnt, 256)), dim3(256), 0, st, r, cnt, coef, stride, tab, L);
+    hipLaunchKernelGGL(k_psi, dim3(blocks_for(cnt, 256)), dim3(256), 0, st, r, cnt, coef, stride, tab, out);
   return launched();
 }
 
@@ -536,7 +542,7 @@ int erai_tables(int n_phi, int n_psi, int m_max, double* tab, hipStream_t st) {
 }
 
 int run_erai(int64_t cnt, int n_phi, int n_psi, int m_max, const double* ang, int64_t stride, const double* tab,
-             double* L, hipStream_t st) {
+             const PsiOut& out, hipStream_t st) {
   if ((cnt + 255) / 256 > 0x7fffffff) return RIFT_EUNSUPPORTED;
   const int nd = 2 * m_max + 1, nq = 4 * m_max + 1;
   const double* wq = tab + (size_t)n_phi * dm_of(m_max);
@@ -545,10 +551,10 @@ int run_erai(int64_t cnt, int n_phi, int n_psi, int m_max, const double* ang, in
   const dim3 grid(blocks_for(cnt, 256)), block(256);
   if (m_max <= 2)
     hipLaunchKernelGGL((k_erai<5, 9>), grid, block, 0, st, cnt, nd, nq, n_phi, n_psi, ang, stride, tab, wq, tu, ln_scale,
-                       L);
+                       out);
   else
     hipLaunchKernelGGL((k_erai<9, 17>), grid, block, 0, st, cnt, nd, nq, n_phi, n_psi, ang, stride, tab, wq, tu,
-                       ln_scale, L);
+                       ln_scale, out);
   return launched();
 }
 

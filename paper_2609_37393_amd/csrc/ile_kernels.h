@@ -57,7 +57,8 @@ struct TileArgs {
   TimeRule tm;  // MODE_TMARG64, MODE_TBAND64: the time nodes
   double* kap;  // MODE_TBAND64: [tm.n][N], x kappa at the nodes
   AngleRule am; // MODE_ERAI64: the harmonics' counts
-  double* ang;  // MODE_ERAI64: [2 nd + 3 nq][ang_stride], MODE_PMARG64: [PSI_ROWS][ang_stride]; column i of sample i
+  double* ang;  // MODE_ERAI64: [2 nd + 3 nq][ang_stride], MODE_PMARG64: [PSI_ROWS][ang_stride]; column i of sample i,
+                // or of the record at i in a binned batch
   int64_t ang_stride;
 };
 
@@ -101,7 +102,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, do
                                       a.tm, as_global_w(a.kap), N, i, live);
       } else if constexpr (MODE == MODE_ERAI64) {
         e.lnL = eval_erai<KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[1], th[2], th[3], th[4], th[5],
-                                    th[6], a.am, as_global_w(a.ang), a.ang_stride, i, live)
+                                    th[6], a.am, as_global_w(a.ang), a.ang_stride, pos, live)
                     ? __builtin_nan("")
                     : 0.0;
       } else if constexpr (MODE == MODE_DMARG64) {
@@ -113,7 +114,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, int tidx, MS* sh, do
                                      a.tm);
       } else if constexpr (MODE == MODE_PMARG64) {
         e.lnL = eval_pmarg<R, KT, L>(opaque(P), trig, blockDim.x, stage, th[0], th[1], th[2], th[3], th[4], th[5],
-                                     th[6], as_global_w(a.ang), a.ang_stride, i, live)
+                                     th[6], as_global_w(a.ang), a.ang_stride, pos, live)
                     ? __builtin_nan("")
                     : 0.0;
       } else {

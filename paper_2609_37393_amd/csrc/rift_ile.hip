@@ -1836,11 +1836,10 @@ int series_batch(rift_ile_plan p, const double* theta, int fine, const double* s
 }
 
 // An angular rule over the batch: the data pass `mode` leaves `rows`
-// coefficients per sample, and `rule(first, count, coef, stride)` turns them
-// into the samples' values in L.  The batch runs in pieces whose coefficients
-// fit ANG_KEEP bytes, each read back while it is in cache; the data pass takes
-// whole tiles, consecutive in samples.  A binned batch's tiles scatter over the
-// samples, so it runs whole.  `tail` bytes follow the coefficients.
+// coefficients per sample, and `rule(count, out)` turns a piece's into its
+// samples' values.  The batch runs in pieces whose coefficients fit ANG_KEEP bytes, each read back while it is in cache; the data pass takes
+// whole tiles, consecutive in samples, or in a binned batch in records (a point's
+// records fill its range of samples).
 constexpr size_t ANG_KEEP = (size_t)96 << 20;
 struct AngPiece {
   int tile, tiles;
@@ -1848,7 +1847,7 @@ struct AngPiece {
 };
 int64_t ang_pieces(rift_ile_plan p, int rows, std::vector<AngPiece>* out) {
   const size_t per = sizeof(double) * (size_t)rows;
-  if (p->cfg.sort || (size_t)p->N * per <= ANG_KEEP) {
+  if ((size_t)p->N * per <= ANG_KEEP) {
     out->push_back(AngPiece{0, p->n_tiles, 0, p->N});
     return p->N;
   }
@@ -1875,12 +1874,13 @@ int ang_batch(rift_ile_plan p, int mode, const std::vector<AngPiece>& pieces, in
   int rc = p->cfg.sort ? run_binning(p, theta, st) : RIFT_OK;
   for (const AngPiece& b : pieces) {
     if (rc) break;
-    // sample i of the batch lands in column i - b.first
+    // sample (or record) i of the batch lands in column i - b.first
     p->ang = coef - b.first;
     p->ang_stride = stride;
     rc = launch_tiles(p, mode, theta, nullptr, L, st, b.tile, b.tiles);
     p->ang = nullptr;
-    if (!rc) rc = rule(b.first, b.count);
+    const bool binned = p->cfg.sort != 0;
+    if (!rc) rc = rule(b.count, PsiOut{binned ? L : L + b.first, binned ? p->d_aos + 8 * b.first : nullptr});
   }
   return rc;
 }
@@ -2051,8 +2051,8 @@ int rift_ile_plan_lnZ_erai(rift_ile_plan p, const double* theta, const double* l
   double* L = lnLa ? lnLa : tab + ntab;
   rc = erai_tables(rule->n_phi, rule->n_psi, m_max, tab, st);
   if (!rc)
-    rc = ang_batch(p, MODE_ERAI64, pieces, stride, coef, theta, L, st, [&](int64_t first, int64_t count) {
-      return run_erai(count, rule->n_phi, rule->n_psi, m_max, coef, stride, tab, L + first, st);
+    rc = ang_batch(p, MODE_ERAI64, pieces, stride, coef, theta, L, st, [&](int64_t count, const PsiOut& out) {
+      return run_erai(count, rule->n_phi, rule->n_psi, m_max, coef, stride, tab, out, st);
     });
   if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
   const int rd = drop_space(p, sp, st);
@@ -2085,8 +2085,8 @@ int rift_ile_plan_lnZ_pmarg(rift_ile_plan p, const double* theta, const double* 
   double* L = lnLp ? lnLp : tab + ntab;
   rc = psi_tables(g, tab, st);
   if (!rc)
-    rc = ang_batch(p, MODE_PMARG64, pieces, stride, coef, theta, L, st, [&](int64_t first, int64_t count) {
-      return run_psi(g, count, coef, stride, tab, L + first, st);
+    rc = ang_batch(p, MODE_PMARG64, pieces, stride, coef, theta, L, st, [&](int64_t count, const PsiOut& out) {
+      return run_psi(g, count, coef, stride, tab, out, st);
     });
   if (!rc) rc = reduce_values(p, L, lnw, lnZ, neff, st);
   const int rd = drop_space(p, sp, st);

@@ -149,3 +149,32 @@ def test_norm_without_polarisation(ile, oracle_mod, factor, method, n_points):
     ref = without if factor < 1e-20 else with_v
     _compare(got, oracle_mod.lnL_pmarg(ref, th, method, n_points),
              _bar_psi(oracle_mod, ref, th, n_points, method != "trapezoid"), (factor, method))
+
+
+@pytest.mark.parametrize("rule", ["joint", "trapezoid", "laplace", "cells"])
+def test_binned_batches_in_pieces(ile, rule):
+    """A binned batch of two points, in several pieces of records: every sample as in input order."""
+    import torch
+
+    rows = 69 if rule == "joint" else 5
+    piece = (96 << 20) // (8 * rows)
+    pts = synth.batched_points(2, 45, K=3, nt_range=(400, 1200))
+    counts = [piece + 501, piece // 2 + 77]
+    th = np.concatenate([synth.prior_samples(c, 46 + i) for i, c in enumerate(counts)], axis=1)
+    th[1, 5] = np.nan
+    t = torch.as_tensor(th, device="cuda").contiguous()
+    out = []
+    for binned in (0, 1):
+        plan = ile.Plan(pts, counts)
+        plan.config = {"sort": binned}
+        ll = torch.empty(th.shape[1], dtype=torch.float64, device="cuda")
+        if rule == "joint":
+            z, ne = plan.lnZ_erai(t, 4, 2, lnL_out=ll)
+        else:
+            z, ne = plan.lnZ_pmarg(t, rule, 4 if rule == "trapezoid" else 0, lnL_out=ll)
+        torch.cuda.synchronize()
+        out.append((z.cpu().numpy(), ne.cpu().numpy(), ll.cpu().numpy()))
+        plan.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b, equal_nan=True)
+    assert np.isnan(out[1][2][5]) and np.isnan(out[1][0][0]) and np.isfinite(out[1][0][1])

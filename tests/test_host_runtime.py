@@ -235,3 +235,20 @@ assert wide(pt, 20000, 0x111000) == ENOMEM and not [c for c in log() if c[0] == 
 rt.host_limit(1 << 40)
 assert wide(pt, 20000, 0x111000) == OK and rt.host_faults() == 0 and rt.host_live() == 0
 """)
+
+
+@pytest.mark.parametrize("name", ["pmarg", "erai"])
+def test_binned_angles_take_a_piece(run, name):
+    """The working memory of an angular rule does not grow with a binned batch."""
+    run(MARGINALS + f"""
+sizes = []
+for binned in (0, 1):
+    rc, h = create([point(2, modes(4), 400)], [6_000_000])
+    assert rc == OK and lib.rift_ile_plan_set_config(h, (i32 * 4)(256, 4, 0, binned)) == OK
+    clear()
+    assert marginal(h, {name!r}, S1) == OK
+    sizes.append([c[2] for c in log() if c[0] == "malloc_async"][0])
+    assert lib.rift_ile_plan_destroy(h) == OK
+assert sizes[1] == sizes[0] < 100 << 20, sizes
+assert rt.host_faults() == 0 and rt.host_live() == 0
+""")
