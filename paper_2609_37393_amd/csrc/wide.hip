@@ -45,6 +45,9 @@
 // pair of wavefronts a SIMD (staging halved to make the LDS for it) or products
 // issued between the lines of Q, both of which spill, gave no more.
 //
+// The complete l <= 4 set of 21 modes also has the form per pair of terms in the
+// static path's harmonic basis, which needs fewer operations (wide_harmonic).
+//
 // The data term reads Q by rows: a set-up kernel lays every detector's
 // composite entries of one time out as whole 128-byte lines.
 #include <hip/hip_runtime.h>
@@ -64,10 +67,12 @@ namespace {
 
 constexpr int WIDE_ARMS_MAX_TERMS = 8;
 constexpr int WIDE_MERGE = 1024;      // threads of the merge
+constexpr int WIDE_BASIS_BLOCK = 512;  // threads of the harmonic set-up: one per grid point
 constexpr int WIDE_PACK_MIN = 16384;  // samples from which the rows are repacked
 
 struct WideDesc {
-  int32_t K, M, n_t, n_a, response, pad;
+  int32_t K, M, n_t, n_a, response;
+  int32_t npairs;            // pairs of terms a <= b
   double t0, inv_dt, gmst, omega, d_ref;
   double dten[KMAX][6];      // D00, D11, D22, 2 D01, 2 D02, 2 D12
   double rpos[KMAX][3];      // light-seconds
@@ -78,7 +83,7 @@ struct WideDesc {
   double ycoef[MMAX][LMAXC + 1];
   const double* Q;           // caller's [K][n_a][M][n_t] complex
   const double* Qrows;       // the same by rows (k_wide_rows), where the call repacks it
-  const double* S;           // the real form's operands (k_wide_form)
+  const double* S;           // the real form's operands (k_wide_form), or [K][pair][B][4] (k_wide_basis)
 };
 static_assert(sizeof(WideDesc) <= 3584, "the description travels as a kernel argument");
 
@@ -312,6 +317,220 @@ __device__ __forceinline__ void rotation_terms(const double* dten, double sd, do
   }
 }
 
+// The pair forms of two terms a <= b, G_ab = Y^H U_ab Y and H_ab = Y^T V_ab Y, in
+// the harmonic basis of class L: each of Re G, Im G, Re H, Im H is a trigonometric
+// polynomial in (incl, phi) of degree 2L in each, with the parity that d_i d_j
+// has in incl, so it lies in the static path's real basis (145 functions at L = 4:
+// 580 coefficients a pair, where 21 modes have 1764 entries).  Summed per harmonic
+// q in phi: the rows of one q are consecutive and q increases
+// along them (basis_row), so
+// g[c] += cos(q phi) sum_n C[(n, cos)][c] T_n(incl)
+//       + sin(q phi) sum_n C[(n, sin)][c] T_n(incl),
+// T_n = cos(n incl) for even q and sin(n incl) for odd q (q = 0: the first
+// sum alone), with e^{i q phi} advanced by one factor e^{i phi} per q.
+// Every row's kind and degrees are template constants; no product of basis
+// values is formed, so only the cos(n incl), sin(n incl) tables stay live
+// across the pairs.
+template <int L>
+struct HarmForms {
+  static constexpr int B = Cls<L>::B;
+  static constexpr int NC = 4 * B;              // coefficients of one block
+  static constexpr int CH = 16;                 // one 128-byte chunk: four rows
+  static constexpr int NCH = (NC + CH - 1) / CH;
+  struct Run {
+    double pc[4], ps[4];  // the two sums of the current q
+    double er, ei;        // e^{i q phi}
+  };
+  template <int J>
+  static __device__ __forceinline__ void term(const double* e, const double* cn, const double* sn, double cf,
+                                              double sf, double* g, Run& R) {
+    if constexpr (J < B) {
+      constexpr int rb = basis_row<L>(J);
+      constexpr int kind = rb & 15, nn = (rb >> 4) & 255, q = rb >> 12;
+      constexpr bool last = (J + 1 == B) || ((basis_row<L>(J + 1) >> 12) != q);
+      const double tn = (kind == 3 || kind == 4) ? sn[nn] : cn[nn];
+      if constexpr (kind == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) g[k] = fma(e[k], tn, g[k]);
+      } else {
+        double* acc = (kind == 1 || kind == 3) ? R.pc : R.ps;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] = fma(e[k], tn, acc[k]);
+        if constexpr (last) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            g[k] = fma(R.pc[k], R.er, fma(R.ps[k], R.ei, g[k]));
+            R.pc[k] = 0.0;
+            R.ps[k] = 0.0;
+          }
+          const double nr = R.er * cf - R.ei * sf, ni = R.er * sf + R.ei * cf;
+          R.er = nr;
+          R.ei = ni;
+        }
+      }
+    }
+  }
+  // The uniform coefficients stream through SGPRs in 128-byte chunks, each
+  // chunk prefetched while the previous one is used (the static path's
+  // scheme): the wait for a chunk comes before the next chunk is issued, and
+  // the accumulators are pinned after each chunk's FMAs so that those FMAs
+  // stay ahead of the next wait.
+  template <int C>
+  static __device__ __forceinline__ void ld(double (&buf)[CH], const RIFT_CONST double* c) {
+    const RIFT_CONST double* p = c + C * CH;
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+      if (C * CH + i < NC) buf[i] = p[i];
+  }
+  template <int C>
+  static __device__ __forceinline__ void wait(const double (&buf)[CH]) {
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+      if (C * CH + i < NC) pin_s(buf[i]);
+  }
+  template <int C>
+  static __device__ __forceinline__ void step(const RIFT_CONST double* c, double (&cur)[CH], double (&nxt)[CH],
+                                              const double* cn, const double* sn, double cf, double sf, double* g,
+                                              Run& R) {
+    if constexpr (C < NCH) {
+      wait<C>(cur);
+      if constexpr (C + 1 < NCH) ld<C + 1>(nxt, c);
+      term<4 * C>(cur, cn, sn, cf, sf, g, R);
+      term<4 * C + 1>(cur + 4, cn, sn, cf, sf, g, R);
+      term<4 * C + 2>(cur + 8, cn, sn, cf, sf, g, R);
+      term<4 * C + 3>(cur + 12, cn, sn, cf, sf, g, R);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        pin(g[k]);
+        pin(R.pc[k]);
+        pin(R.ps[k]);
+      }
+      step<C + 1>(c, nxt, cur, cn, sn, cf, sf, g, R);
+    }
+  }
+  static __device__ __forceinline__ void run(const RIFT_CONST double* c, const double* cn, const double* sn,
+                                             double cf, double sf, double* g) {
+    Run R;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) R.pc[k] = R.ps[k] = 0.0;
+    R.er = cf;  // the first group after q = 0 is q = 1
+    R.ei = sf;
+    double bA[CH], bB[CH];
+    ld<0>(bA, c);
+    step<0>(c, bA, bB, cn, sn, cf, sf, g, R);
+  }
+};
+
+// Harmonic-basis coefficients of the pair forms, one block per (detector,
+// pair a <= b): Re G, Im G, Re H, Im H of the block sampled on an NG x NG
+// grid of (incl, phi) over [0, 2 pi)^2, NG = 4L + 4 (more than twice the
+// degree 2L in each), then projected on the basis rows (discrete
+// orthogonality on that grid).  Every angle on the grid is a multiple of
+// 2 pi / NG, so cos and sin come from one table of NG entries each; the
+// block's U and V entries are staged in LDS; a thread per grid point, then
+// each basis row's projection split over WIDE_BASIS_BLOCK / B threads.  U, V in the caller's order
+// [K][A][A] complex; out [K][pair][B][4].
+template <int L>
+__global__ void k_wide_basis(WideDesc D, const double* __restrict__ U, const double* __restrict__ V,
+                             double* __restrict__ out) {
+  constexpr int NG = 4 * L + 4, B = Cls<L>::B, MX = Cls<L>::MAXM;
+  constexpr int PS = WIDE_BASIS_BLOCK / B;  // threads per basis row in the projection
+  __shared__ double g[4][NG * NG];
+  __shared__ double part[PS][B][4];
+  __shared__ double ct[NG], st[NG];
+  __shared__ double uv[MX * MX][4];
+  const int k = blockIdx.x / D.npairs, pr = blockIdx.x - k * D.npairs;
+  int a = 0, rem = pr;
+  while (rem >= D.n_a - a) {
+    rem -= D.n_a - a;
+    ++a;
+  }
+  const int b = a + rem;
+  const int M = D.M, A = D.n_a * D.M;
+  for (int j = threadIdx.x; j < NG; j += blockDim.x) {
+    double sj, cj;
+    sincospi(2.0 * j / NG, &sj, &cj);
+    ct[j] = cj;
+    st[j] = sj;
+  }
+  for (int e = threadIdx.x; e < M * M; e += blockDim.x) {
+    const int i = e / M, j = e - (e / M) * M;
+    const int64_t o = 2 * (((int64_t)k * A + a * M + D.perm[i]) * A + b * M + D.perm[j]);
+    uv[e][0] = U[o];
+    uv[e][1] = U[o + 1];
+    uv[e][2] = V[o];
+    uv[e][3] = V[o + 1];
+  }
+  __syncthreads();
+  // index of the angle n * (2 pi c / NG) in the tables
+  auto ix = [](int n, int c) { return ((n * c) % NG + NG) % NG; };
+  for (int gp = threadIdx.x; gp < NG * NG; gp += blockDim.x) {
+    const int pi_ = gp / NG, pf = gp - (gp / NG) * NG;
+    double yr[MX], yi[MX];
+#pragma unroll
+    for (int i = 0; i < MX; ++i) {
+      yr[i] = yi[i] = 0.0;
+      if (i < M) {
+        double d = 0.0;
+        for (int q = 0; q <= L; ++q) d += D.ycoef[i][q] * (D.odd[i] ? st[ix(q, pi_)] : ct[ix(q, pi_)]);
+        const int r = ix(D.m[i], pf);
+        yr[i] = d * ct[r];
+        yi[i] = d * st[r];
+      }
+    }
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < MX; ++i) {
+      if (i < M) {
+        double tr = 0.0, ti = 0.0, wr = 0.0, wi = 0.0;
+#pragma unroll
+        for (int j = 0; j < MX; ++j) {
+          if (j < M) {
+            const double* e = uv[i * M + j];
+            tr += e[0] * yr[j] - e[1] * yi[j];
+            ti += e[0] * yi[j] + e[1] * yr[j];
+            wr += e[2] * yr[j] - e[3] * yi[j];
+            wi += e[2] * yi[j] + e[3] * yr[j];
+          }
+        }
+        v[0] += yr[i] * tr + yi[i] * ti;
+        v[1] += yr[i] * ti - yi[i] * tr;
+        v[2] += yr[i] * wr - yi[i] * wi;
+        v[3] += yr[i] * wi + yi[i] * wr;
+      }
+    }
+    for (int c = 0; c < 4; ++c) g[c][gp] = v[c];
+  }
+  __syncthreads();
+  // each row's sum over the grid split over PS threads, then reduced
+  for (int w = threadIdx.x; w < PS * B; w += blockDim.x) {
+    const int r = w % B, sp = w / B;
+    const int rb = basis_row<L>(r);
+    const int kind = rb & 15, nn = (rb >> 4) & 255, q = rb >> 12;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int gp = sp; gp < NG * NG; gp += PS) {
+      const int pi_ = gp / NG, pf = gp - (gp / NG) * NG;
+      const double ti = (kind >= 3) ? st[ix(nn, pi_)] : ct[ix(nn, pi_)];
+      const double tf = (kind == 0) ? 1.0 : (kind == 1 || kind == 3) ? ct[ix(q, pf)] : st[ix(q, pf)];
+      const double t = ti * tf;
+      for (int c = 0; c < 4; ++c) acc[c] += g[c][gp] * t;
+    }
+    for (int c = 0; c < 4; ++c) part[sp][r][c] = acc[c];
+  }
+  __syncthreads();
+  for (int r = threadIdx.x; r < B; r += blockDim.x) {
+    const int rb = basis_row<L>(r);
+    const int nn = (rb >> 4) & 255, q = rb >> 12;
+    const double norm = 1.0 / ((double)NG * NG * (nn == 0 ? 1.0 : 0.5) * (q == 0 ? 1.0 : 0.5));
+    double* o = out + ((int64_t)blockIdx.x * B + r) * 4;
+    for (int c = 0; c < 4; ++c) {
+      double v = 0.0;
+      for (int sp = 0; sp < PS; ++sp) v += part[sp][r][c];
+      o[c] = v * norm;
+    }
+  }
+}
+
 // sin and cos of |x| <= 1 by their Taylor series through x^19 / 19! and
 // x^18 / 18! (truncation below 1e-17): the rotation over the light-travel
 // time, Omega (t_k - t_ref), which the validation keeps within one radian.
@@ -339,13 +558,31 @@ __device__ __forceinline__ void sincos_small(double x, double* s, double* c) {
   *c = fma(-pc, x2, 1.0);
 }
 
+// The complete set of l <= 4 (21 modes) has a second form of the quadratic term:
+// the harmonic forms of the pairs on the vector unit, 52 kflop a sample at five
+// terms where the real form's tiles take 132.  It is bound by the latency of its
+// scalar stream, the same from one wavefront to two per SIMD, where the real form
+// takes the matrix cores' time twice: it takes calls that put two wavefronts on a
+// SIMD, of eight terms and more, and of five and more while they are one or two
+// rounds of the chip.  Measured (3 detectors, us; real form, harmonic form): 12
+// terms, 65536 samples 1571, 2213; 131072 3078, 2388; 200k 5673, 4495; 300k 6969,
+// 6772.  21 terms, 20k 4353, 6064; 65536 8169, 6100; 100k 9488, 6230.  Eight, 100k
+// 1445, 1162; 300k 3354, 3417.  Five, 131072 697, 641; 300k 1496, 1662.  With 17
+// modes the two meet (12 terms, 131072: 2246, 2255).
+constexpr int WIDE_HARMONIC_M = 21;
+bool wide_harmonic(int M, int lmax, int n_a, int64_t n) {
+  if (M != WIDE_HARMONIC_M || lmax > 4) return false;
+  if (n_a > 12) return n > 49152;
+  return n > 65536 && (n_a >= 8 || (n_a >= 5 && n <= 262144));
+}
+
 // Dynamic LDS of a wavefront: the staging of the data term's rows (the
 // harmonics' exchange reuses it), then the coefficients.
-__host__ __device__ constexpr int wide_stage_bytes(bool packed) { return packed ? STAGE_WAVE : 4 * 64 * 16; }
+__host__ __device__ constexpr int wide_stage_bytes(bool packed, int HL) { return packed ? STAGE_WAVE : (HL ? 0 : 4 * 64 * 16); }
 
 // One wavefront per block: its LDS (21 KB at five terms) then packs seven to a
 // CU, within the registers of two per SIMD.
-template <int MB, bool PACKED>
+template <int MB, bool PACKED, int HL = 0>
 __global__ void __launch_bounds__(64, 2) k_wide(WideDesc D, const double* __restrict__ theta, int64_t n,
                                                 const double* __restrict__ lnw, double* __restrict__ lnL,
                                                 double* __restrict__ part) {
@@ -354,7 +591,7 @@ __global__ void __launch_bounds__(64, 2) k_wide(WideDesc D, const double* __rest
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ MS sh[1];
   RIFT_LDS unsigned char* stage = (RIFT_LDS unsigned char*)smem;
-  const WideCoef C = (WideCoef)(stage + wide_stage_bytes(PACKED));
+  const WideCoef C = (WideCoef)(stage + wide_stage_bytes(PACKED, HL));
   const int t = threadIdx.x, col = t & 15, quad = t >> 4;
   const int64_t i0 = (int64_t)blockIdx.x * 64 + t;
   const bool live = i0 < n;
@@ -509,7 +746,7 @@ __global__ void __launch_bounds__(64, 2) k_wide(WideDesc D, const double* __rest
     return tk;
   };
 
-  double data = 0.0;
+  double data = 0.0, quadratic = 0.0;
   bool bad = false;
 #pragma unroll 1
   for (int k = 0; k < K; ++k) {
@@ -569,96 +806,134 @@ __global__ void __launch_bounds__(64, 2) k_wide(WideDesc D, const double* __rest
         data += C[a * 64 + t].x * zr + C[a * 64 + t].y * zi;
       }
     }
+    if constexpr (HL > 0) {
+      // model-norm term over pairs a <= b.  The angles' values are rebuilt per
+      // detector, the phase sequence per pair: hoisted, they would hold their
+      // registers through the reads
+      double co = c5[3], so = s5[3];
+      pin(co);
+      pin(so);
+      double cn[2 * HL + 1], sn[2 * HL + 1];
+      cn[0] = 1.0;
+      sn[0] = 0.0;
+      cn[1] = co;
+      sn[1] = so;
+#pragma unroll
+      for (int q = 2; q <= 2 * HL; ++q) {
+        cn[q] = 2.0 * co * cn[q - 1] - cn[q - 2];
+        sn[q] = 2.0 * co * sn[q - 1] - sn[q - 2];
+      }
+      constexpr int BS = 4 * Cls<(HL > 0 ? HL : 2)>::B;
+      const RIFT_CONST double* blk = as_const(D.S) + (int64_t)k * D.npairs * BS;
+#pragma unroll 1
+      for (int a = 0; a < n_a; ++a) {
+#pragma unroll 1
+        for (int b = a; b < n_a; ++b, blk += BS) {
+          double g[4] = {0.0, 0.0, 0.0, 0.0};  // Re G, Im G, Re H, Im H
+          double cf = c5[4], sf = s5[4];
+          pin(cf);
+          pin(sf);
+          HarmForms<(HL > 0 ? HL : 2)>::run(opaque(blk), cn, sn, cf, sf, g);
+          const double ar = C[a * 64 + t].x, ai = C[a * 64 + t].y, br = C[b * 64 + t].x, bi = C[b * 64 + t].y;
+          // conj(C_a) C_b G_ab and C_a C_b H_ab, counted twice off the diagonal
+          const double pr = ar * br + ai * bi, pim = ar * bi - ai * br;
+          const double qr = ar * br - ai * bi, qim = ar * bi + ai * br;
+          quadratic += (a == b ? 1.0 : 2.0) * ((pr * g[0] - pim * g[1]) + (qr * g[2] - qim * g[3]));
+        }
+      }
+    }
   }
 
-  // the harmonics as the matrix tiles take them: sample 16 s + col, mode 4 mb + quad
-  double vr[4][MB], vi[4][MB];
-  {
-    RIFT_LDS double2* ex = (RIFT_LDS double2*)stage;
+  if constexpr (HL == 0) {
+    // the harmonics as the matrix tiles take them: sample 16 s + col, mode 4 mb + quad
+    double vr[4][MB], vi[4][MB];
+    {
+      RIFT_LDS double2* ex = (RIFT_LDS double2*)stage;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      wave_sync();
+      for (int mb = 0; mb < MB; ++mb) {
+        wave_sync();
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        ex[q * 64 + t].x = yr[4 * mb + q];
-        ex[q * 64 + t].y = yi[4 * mb + q];
-      }
-      wave_sync();
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        vr[s][mb] = ex[quad * 64 + 16 * s + col].x;
-        vi[s][mb] = ex[quad * 64 + 16 * s + col].y;
-      }
-    }
-  }
-  // model-norm term: per detector sum_t c_t^T (S c)_t, this lane's share of it
-  // the components (step, quad) of samples 16 s + col
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  const int steps = wide_steps(MB, n_a), tiles = wide_tiles(MB, n_a);
-  typedef double R2 __attribute__((ext_vector_type(2)));
-  const RIFT_GLOBAL R2* A = (const RIFT_GLOBAL R2*)as_global(D.S) + t;
-  R2 nxt = A[0];
-#pragma unroll 1
-  for (int k = 0; k < K; ++k) {
-    if (K > 1) {
-      wave_sync();
-      (void)coefficients(k);
-    }
-    wave_sync();
-#pragma unroll 1
-    for (int tl = 0; tl < tiles; ++tl) {
-      D4 d[4];
-      double keep[4][4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        d[s] = D4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int r = 0; r < 4; ++r) keep[s][r] = 0.0;
-      }
-      const int b0 = 4 * tl;
-      int a = b0 / (2 * MB);
-#pragma unroll 1
-      for (int b = a * 2 * MB; b < steps; ++a) {
-        double cr[4], ci[4];
+        for (int q = 0; q < 4; ++q) {
+          ex[q * 64 + t].x = yr[4 * mb + q];
+          ex[q * 64 + t].y = yi[4 * mb + q];
+        }
+        wave_sync();
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          cr[s] = C[a * 64 + 16 * s + col].x;
-          ci[s] = C[a * 64 + 16 * s + col].y;
+          vr[s][mb] = ex[quad * 64 + 16 * s + col].x;
+          vi[s][mb] = ex[quad * 64 + 16 * s + col].y;
         }
+      }
+    }
+    // model-norm term: per detector sum_t c_t^T (S c)_t, this lane's share of it
+    // the components (step, quad) of samples 16 s + col
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const int steps = wide_steps(MB, n_a), tiles = wide_tiles(MB, n_a);
+    typedef double R2 __attribute__((ext_vector_type(2)));
+    const RIFT_GLOBAL R2* A = (const RIFT_GLOBAL R2*)as_global(D.S) + t;
+    R2 nxt = A[0];
+#pragma unroll 1
+    for (int k = 0; k < K; ++k) {
+      if (K > 1) {
+        wave_sync();
+        (void)coefficients(k);
+      }
+      wave_sync();
+#pragma unroll 1
+      for (int tl = 0; tl < tiles; ++tl) {
+        D4 d[4];
+        double keep[4][4];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb, b += 2) {
-          if (b < b0) continue;
-          const R2 cur = nxt;
-          A += 64;
-          nxt = A[0];  // one pair past the end is padding
+        for (int s = 0; s < 4; ++s) {
+          d[s] = D4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int r = 0; r < 4; ++r) keep[s][r] = 0.0;
+        }
+        const int b0 = 4 * tl;
+        int a = b0 / (2 * MB);
+#pragma unroll 1
+        for (int b = a * 2 * MB; b < steps; ++a) {
+          double cr[4], ci[4];
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
-            const double xr = cr[s] * vr[s][mb] - ci[s] * vi[s][mb], xi = cr[s] * vi[s][mb] + ci[s] * vr[s][mb];
-            d[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.x, xr, d[s], 0, 0, 0);
-            d[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.y, xi, d[s], 0, 0, 0);
-            if (b == b0) {
-              keep[s][0] = xr;
-              keep[s][1] = xi;
-            } else if (b == b0 + 2) {
-              keep[s][2] = xr;
-              keep[s][3] = xi;
+            cr[s] = C[a * 64 + 16 * s + col].x;
+            ci[s] = C[a * 64 + 16 * s + col].y;
+          }
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb, b += 2) {
+            if (b < b0) continue;
+            const R2 cur = nxt;
+            A += 64;
+            nxt = A[0];  // one pair past the end is padding
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+              const double xr = cr[s] * vr[s][mb] - ci[s] * vi[s][mb], xi = cr[s] * vi[s][mb] + ci[s] * vr[s][mb];
+              d[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.x, xr, d[s], 0, 0, 0);
+              d[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.y, xi, d[s], 0, 0, 0);
+              if (b == b0) {
+                keep[s][0] = xr;
+                keep[s][1] = xi;
+              } else if (b == b0 + 2) {
+                keep[s][2] = xr;
+                keep[s][3] = xi;
+              }
             }
           }
         }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[s] = fma(d[s][r], keep[s][r], acc[s]);
       }
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[s] = fma(d[s][r], keep[s][r], acc[s]);
     }
-  }
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    acc[s] += __shfl_xor(acc[s], 16);
-    acc[s] += __shfl_xor(acc[s], 32);
+    for (int s = 0; s < 4; ++s) {
+      acc[s] += __shfl_xor(acc[s], 16);
+      acc[s] += __shfl_xor(acc[s], 32);
+    }
+    // sample t = 16 quad + col
+    quadratic = quad == 0 ? acc[0] : (quad == 1 ? acc[1] : (quad == 2 ? acc[2] : acc[3]));
   }
-  // sample t = 16 quad + col
-  const double quadratic = quad == 0 ? acc[0] : (quad == 1 ? acc[1] : (quad == 2 ? acc[2] : acc[3]));
   const double x = D.d_ref / dist;
   double l = x * data - 0.25 * x * x * quadratic;
   if (bad) l = __builtin_nan("");
@@ -677,19 +952,27 @@ __global__ void __launch_bounds__(64, 2) k_wide(WideDesc D, const double* __rest
 }
 
 template <int MB>
-void launch_wide(const WideDesc& D, bool packed, const double* U, const double* V, double* form, double* rows,
-                 const double* theta, int64_t n, const double* lnw, double* lnL, double* part, hipStream_t st) {
-  const int64_t total = (int64_t)D.K * wide_pairs(wide_steps(MB, D.n_a), wide_tiles(MB, D.n_a)) * 128;
-  hipLaunchKernelGGL(k_wide_form<MB>, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 4096)), dim3(256), 0, st, D,
-                     U, V, form);
+void launch_wide(const WideDesc& D, bool packed, bool harmonic, const double* U, const double* V, double* form,
+                 double* rows, const double* theta, int64_t n, const double* lnw, double* lnL, double* part,
+                 hipStream_t st) {
+  constexpr int HL = MB == (WIDE_HARMONIC_M + 3) / 4 ? 4 : 0;
+  if (harmonic) {
+    hipLaunchKernelGGL(k_wide_basis<4>, dim3((unsigned)(D.K * D.npairs)), dim3(WIDE_BASIS_BLOCK), 0, st, D, U, V, form);
+  } else {
+    const int64_t total = (int64_t)D.K * wide_pairs(wide_steps(MB, D.n_a), wide_tiles(MB, D.n_a)) * 128;
+    hipLaunchKernelGGL(k_wide_form<MB>, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 4096)), dim3(256), 0, st,
+                       D, U, V, form);
+  }
   const dim3 grid((unsigned)((n + 63) / 64)), block(64);
-  const size_t lds = wide_stage_bytes(packed) + (size_t)D.n_a * 64 * 16;
+  const size_t lds = wide_stage_bytes(packed, harmonic ? HL : 0) + (size_t)D.n_a * 64 * 16;
   if (packed) {
     const int lines = wide_lines(MB, D.n_a);
     hipLaunchKernelGGL(k_wide_rows, dim3((unsigned)((D.n_t + WIDE_QT - 1) / WIDE_QT), (unsigned)D.K,
                                          (unsigned)std::min(lines, 4)),
                        dim3(256), 0, st, D, wide_slots(MB), lines, rows);
     hipLaunchKernelGGL((k_wide<MB, true>), grid, block, lds, st, D, theta, n, lnw, lnL, part);
+  } else if (harmonic) {
+    hipLaunchKernelGGL((k_wide<MB, false, HL>), grid, block, lds, st, D, theta, n, lnw, lnL, part);
   } else {
     hipLaunchKernelGGL((k_wide<MB, false>), grid, block, lds, st, D, theta, n, lnw, lnL, part);
   }
@@ -819,17 +1102,24 @@ int wide_run(const rift_ile_point_wide* pt, int64_t n, const double* theta, cons
   }
   D.Q = pt->Q;
   const int MB = (pt->n_modes + 3) / 4;
+  D.npairs = D.n_a * (D.n_a + 1) / 2;
+  int lmax = 0;
+  for (int i = 0; i < pt->n_modes; ++i) lmax = std::max(lmax, (int)pt->lm[2 * i]);
+  const bool harmonic = wide_harmonic(D.M, lmax, D.n_a, n);
   // Reading Q by rows: repacking costs a pass over the table (10 us at 20
   // composite entries, 25 us at 105); the stencils lane by lane cost about
   // 0.4 ns per sample and 20 entries more than the rows.  The lines meet near
   // this many samples at every width.
   const size_t row_bytes = 128 * (size_t)wide_lines(MB, D.n_a);
-  bool packed = n >= WIDE_PACK_MIN && (uint64_t)D.n_t * row_bytes <= 0xffffffffu;
+  bool packed = !harmonic && n >= WIDE_PACK_MIN && (uint64_t)D.n_t * row_bytes <= 0xffffffffu;
   // stream-ordered scratch: the repacked rows, the real form's operands (and
-  // one pair of steps that is fetched past the end), the blocks' (max, sum) pairs
+  // one pair of steps that is fetched past the end) or the harmonic form's
+  // coefficients, the blocks' (max, sum) pairs
   size_t q_bytes = packed ? (size_t)D.K * D.n_t * row_bytes : 0;
   const int steps = wide_steps(MB, D.n_a);
-  const size_t form_bytes = sizeof(double) * 128 * (size_t)(D.K * wide_pairs(steps, wide_tiles(MB, D.n_a)) + 1);
+  const size_t form_bytes =
+      harmonic ? sizeof(double) * 4 * (size_t)(D.K * D.npairs * Cls<4>::B)
+               : sizeof(double) * 128 * (size_t)(D.K * wide_pairs(steps, wide_tiles(MB, D.n_a)) + 1);
   const size_t part_bytes = lnZ ? sizeof(double) * 2 * (size_t)nb : 0;
   hipStream_t st = (hipStream_t)stream;
   char* space = nullptr;
@@ -850,7 +1140,7 @@ int wide_run(const rift_ile_point_wide* pt, int64_t n, const double* theta, cons
   D.Qrows = (const double*)space;
   D.S = form;
 #define RIFT_WIDE(B) \
-  case B: launch_wide<B>(D, packed, pt->U, pt->V, form, (double*)space, theta, n, lnw, lnL, d_part, st); break;
+  case B: launch_wide<B>(D, packed, harmonic, pt->U, pt->V, form, (double*)space, theta, n, lnw, lnL, d_part, st); break;
   switch (MB) {
     RIFT_WIDE(1)
     RIFT_WIDE(2)

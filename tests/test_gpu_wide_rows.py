@@ -62,3 +62,19 @@ def test_rows_reduce(oracle_mod):
     assert abs(z.item() - z_or) <= 1e-9 * max(1.0, abs(z_or)) and abs(ne.item() - ne_or) <= 1e-9 * ne_or
     none = ile.wide_lnZ(pt, th, lnw=np.full(th.shape[1], -np.inf))
     assert none[0].item() == -np.inf and none[1].item() == 0.0
+
+
+@pytest.mark.parametrize("response,K,n_a,n_t,n", [
+    ("rotation", 3, 5, 300, 65537), ("rotation", 1, 5, 64, 131072), ("arms", 2, 8, 300, 65600),
+    ("rotation_delay", 2, 12, 200, 65601), ("rotation_delay", 1, 21, 200, 49153), ("rotation", 2, 5, 300, 262145),
+    ("rotation_delay", 1, 21, 200, 49152)])
+def test_harmonic_pair_forms(oracle_mod, response, K, n_a, n_t, n):
+    """The complete l <= 4 set on both sides of the lines at which its pair forms
+    run in the harmonic basis, modes in the caller's own order."""
+    lm = np.array([(l, m) for l in range(4, 1, -1) for m in range(l, -l - 1, -1)], np.int32)
+    pt = synth.make_point_wide(K, 21, n_a, n_t, 32768.0, 120.0, 60 + n_a, response=response, omega=40.0, lm=lm)
+    th = synth.prior_samples(n, n_a)
+    end = 0.5 * n_t / 32768.0
+    th[5, :8] = [-end, end, 0.03, 50.0, -50.0, np.nan, np.inf, end - 5e-5]
+    th[4, 8:10] = [1e9, -1e12]
+    _check(oracle_mod, pt, th, np.r_[0:30, n - 20:n])

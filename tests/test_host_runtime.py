@@ -252,3 +252,19 @@ for binned in (0, 1):
 assert sizes[1] == sizes[0] < 100 << 20, sizes
 assert rt.host_faults() == 0 and rt.host_live() == 0
 """)
+
+
+@pytest.mark.parametrize("n_a,response,n,harmonic", [
+    (5, 1, 65536, False), (5, 1, 65537, True), (5, 1, 262145, False), (8, 2, 65537, True), (8, 2, 1000000, True),
+    (12, 3, 65536, False), (12, 3, 300000, True), (21, 3, 49152, False), (21, 3, 49153, True), (4, 2, 200000, False)])
+def test_quadratic_form_of_long_sets(run, n_a, response, n, harmonic):
+    """Which form the complete l <= 4 set takes; shorter sets and larger l keep the real form."""
+    run(WIDE + f"""
+for lm, long_set in ((modes(21), True), (modes(20), False), (modes(21, 5), False), (modes(4), False)):
+    clear()
+    assert wide(wide_point(3, lm, {n_a}, 500, {response}), {n}) == OK
+    names = [c[4] for c in log() if c[0] == "launch"]
+    assert any("k_wide_basis" in x for x in names) == ({harmonic} and long_set), names
+    assert any("k_wide_form" in x for x in names) != ({harmonic} and long_set), names
+assert rt.host_faults() == 0 and rt.host_live() == 0
+""")
