@@ -68,7 +68,6 @@ namespace {
 constexpr int WIDE_ARMS_MAX_TERMS = 8;
 constexpr int WIDE_MERGE = 1024;      // threads of the merge
 constexpr int WIDE_BASIS_BLOCK = 512;  // threads of the harmonic set-up: one per grid point
-constexpr int WIDE_PACK_MIN = 16384;  // samples from which the rows are repacked
 
 struct WideDesc {
   int32_t K, M, n_t, n_a, response;
@@ -188,6 +187,32 @@ __global__ void __launch_bounds__(256) k_wide_rows(WideDesc D, int SL, int lines
     }
     __syncthreads();
   }
+}
+
+// Whether a call reads Q by rows.  Repacking costs a launch and a pass over the
+// table (5 us at least), and its staging 12 KB of LDS a wavefront: from four terms
+// on seven wavefronts fit a CU instead of the eight that its registers hold, from
+// seven on fewer.  Measured (3 detectors, us, series as they are against rows):
+//   up to a wavefront on every SIMD, bound by the latency of the reads: 21 modes x
+//     5 terms 409, 366; 9 x 5 152, 143; 12 x 4 131, 112; 4 x 5 with 8 detectors
+//     124, 108; but 4 x 5 51, 54; 16 x 3 143, 144; 8 x 8 175, 184;
+//   more, bound by the lines that are read: 1e6 samples of 4 x 5 440, 370; 8 x 4
+//     772, 585; 16 x 5 2508, 2160; 21 x 2 1266, 1045; 12 x 1 282, 242.  Rows of which
+//     a quarter and more is empty read no fewer lines (4 x 1 131, 143; 2 x 5 311,
+//     365; 5 x 5 755, 793), and many terms lose more by the LDS (4 x 8 720, 661, but
+//     4 x 21 3355, 4388; 12 x 12 6085, 7617; 25 x 5 1662, 2082 at 262144).  Seven
+//     wavefronts instead of eight count where they begin another round (16 x 5,
+//     1e5 samples, one round each: 356, 306; 4 x 5, 131072: 76, 85; 2e5: 121, 108).
+bool wide_packs(int K, int M, int n_a, int64_t n) {
+  constexpr int64_t EIGHT = 131072, SEVEN = 114688;  // samples of a round on 256 CUs
+  const int MB = (M + 3) / 4;
+  if (n < 16384) return false;
+  if (n <= EIGHT / 2) return M >= 9 ? n_a >= 4 && M * n_a >= 45 : M == 4 && n_a <= 12 && K * n_a >= 36;
+  if (M < 4 || M > 24 || (M < 9 && 4 * M * n_a < 3 * 8 * wide_lines(MB, n_a))) return false;
+  if (n_a <= 3) return n * M * n_a >= 2400000;
+  if (n_a > 6) return M == 4 && n_a <= 8 && n >= 200000;
+  if (n >= 400000) return n_a == 4 || M <= 16;
+  return (n + SEVEN - 1) / SEVEN <= (n + EIGHT - 1) / EIGHT;
 }
 
 // A wavefront's coefficients C~ [term][lane].
@@ -1106,12 +1131,8 @@ int wide_run(const rift_ile_point_wide* pt, int64_t n, const double* theta, cons
   int lmax = 0;
   for (int i = 0; i < pt->n_modes; ++i) lmax = std::max(lmax, (int)pt->lm[2 * i]);
   const bool harmonic = wide_harmonic(D.M, lmax, D.n_a, n);
-  // Reading Q by rows: repacking costs a pass over the table (10 us at 20
-  // composite entries, 25 us at 105); the stencils lane by lane cost about
-  // 0.4 ns per sample and 20 entries more than the rows.  The lines meet near
-  // this many samples at every width.
   const size_t row_bytes = 128 * (size_t)wide_lines(MB, D.n_a);
-  bool packed = !harmonic && n >= WIDE_PACK_MIN && (uint64_t)D.n_t * row_bytes <= 0xffffffffu;
+  bool packed = !harmonic && wide_packs(D.K, D.M, D.n_a, n) && (uint64_t)D.n_t * row_bytes <= 0xffffffffu;
   // stream-ordered scratch: the repacked rows, the real form's operands (and
   // one pair of steps that is fetched past the end) or the harmonic form's
   // coefficients, the blocks' (max, sum) pairs

@@ -78,3 +78,18 @@ def test_harmonic_pair_forms(oracle_mod, response, K, n_a, n_t, n):
     th[5, :8] = [-end, end, 0.03, 50.0, -50.0, np.nan, np.inf, end - 5e-5]
     th[4, 8:10] = [1e9, -1e12]
     _check(oracle_mod, pt, th, np.r_[0:30, n - 20:n])
+
+
+@pytest.mark.parametrize("response,K,M,n_a,n_t,n", [
+    ("rotation", 3, 4, 5, 65, 300_001), ("arms", 2, 8, 2, 70, 262_145), ("arms", 3, 4, 3, 63, 400_000),
+    ("rotation", 3, 12, 5, 64, 16_385), ("rotation", 2, 13, 5, 300, 16_384), ("rotation", 2, 17, 5, 300, 20_001),
+    ("arms", 1, 25, 4, 200, 16_385), ("rotation_delay", 1, 9, 21, 200, 16_385), ("arms", 2, 21, 2, 300, 100_001)])
+def test_calls_that_repack(oracle_mod, response, K, M, n_a, n_t, n):
+    """Reading by rows in every count of mode blocks that takes it."""
+    lm = None if M <= 21 else _mode_set(M, 6)
+    pt = synth.make_point_wide(K, M, n_a, n_t, 32768.0, 120.0, 70 + M + n_a, response=response, omega=40.0, lm=lm)
+    th = synth.prior_samples(n, M)
+    end = 0.5 * n_t / 32768.0
+    th[5, :8] = [-end, end, -end - 3e-5, end + 3e-5, 0.03, np.nan, -50.0, end - 5e-5]
+    th[:, n - 8:] = th[:, :8]
+    _check(oracle_mod, pt, th, np.r_[0:40, n - 40:n])

@@ -220,7 +220,7 @@ def wide(pt, n, stream=None):
 def test_composite_call_without_room_for_rows(run):
     """A table whose repacked copy does not fit is read as it is."""
     run(WIDE + """
-pt = wide_point(3, modes(4), 5, 20000)
+pt = wide_point(3, modes(9), 5, 20000)
 assert wide(pt, 20000, 0x111000) == OK
 size = [c[2] for c in log() if c[0] == "malloc_async"][0]
 assert size > 8 << 20  # the rows
@@ -266,5 +266,18 @@ for lm, long_set in ((modes(21), True), (modes(20), False), (modes(21, 5), False
     names = [c[4] for c in log() if c[0] == "launch"]
     assert any("k_wide_basis" in x for x in names) == ({harmonic} and long_set), names
     assert any("k_wide_form" in x for x in names) != ({harmonic} and long_set), names
+assert rt.host_faults() == 0 and rt.host_live() == 0
+""")
+
+
+@pytest.mark.parametrize("M,n_a,response,n,rows", [
+    (4, 1, 2, 1000000, False), (4, 5, 1, 131072, False), (4, 5, 1, 1000000, True), (4, 5, 1, 65536, False),
+    (4, 5, 1, 100000, True), (4, 21, 3, 1000000, False), (2, 5, 1, 1000000, False), (12, 12, 3, 200000, False),
+    (21, 5, 1, 16383, False), (21, 5, 1, 65536, True), (21, 2, 2, 1000000, True), (9, 5, 1, 20000, True),
+    (9, 5, 1, 262144, False), (16, 5, 1, 200000, True), (25, 5, 1, 200000, False)])
+def test_composite_calls_that_repack(run, M, n_a, response, n, rows):
+    run(WIDE + f"""
+assert wide(wide_point(3, modes({M}, 5 if {M} > 21 else 4), {n_a}, 500, {response}), {n}) == OK
+assert any("k_wide_rows" in c[4] for c in log() if c[0] == "launch") == {rows}
 assert rt.host_faults() == 0 and rt.host_live() == 0
 """)
