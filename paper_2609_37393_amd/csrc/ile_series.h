@@ -162,8 +162,11 @@ struct SeriesJob {
   void* ws;                 // workspace of series_bytes()
   size_t ws_bytes;
 };
-// Whether a point's rule runs by contracted series, in a batch of N samples.
-bool series_takes(const PointDesc& D, int64_t N, double t0, double h, int n);
+// Whether a point's rule can run by contracted series; what that costs a point, and
+// one time of the per-time form on a lane (both us).
+bool series_holds(const PointDesc& D, double t0, double h, int n);
+double series_us(const PointDesc& D, double h, int n);
+double time_step_us(const PointDesc& D);
 // Workspace of a point's run (bounded; larger batches run in chunks).
 size_t series_bytes(const PointDesc& D, double h, int n, bool band);
 int run_series(const SeriesJob& j, hipStream_t st);

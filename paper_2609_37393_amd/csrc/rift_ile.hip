@@ -1029,7 +1029,6 @@ void plan_free_all(rift_ile_plan p) {
 // the kept memory is stream-ordered too, an event marks the end of its last
 // use, and a call's stream waits for that event before it takes the memory (or
 // gives it back for more), whichever stream or thread the last call was on.
-constexpr int SERIES_POINT_TIMES = 40000;
 constexpr size_t WS_KEEP = (size_t)256 << 20;
 struct Space {
   void* p = nullptr;
@@ -1799,14 +1798,19 @@ int set_dist_rule(rift_ile_plan p, const rift_ile_dist_prior* prior) {
   return RIFT_OK;
 }
 
-// Whether a time rule over the batch runs by contracted series
-// (ile_series.h): every point's rule has to lie close enough (series_takes),
-// and a batch of many points enough times per point for the few launches that
-// each then takes.
+// Whether a time rule over the batch runs by contracted series (ile_series.h), one
+// point after the other, or time by time in one launch for all points: the
+// smaller of the estimates, the series with a twentieth to spare.
 bool by_series(rift_ile_plan p, double t0, double h, int n) {
-  for (const PointDesc& D : p->h_desc)
-    if (!series_takes(D, p->N, t0, h, n)) return false;
-  return p->n_points == 1 || p->N * n > (int64_t)SERIES_POINT_TIMES * p->n_points;
+  double series = 0.0, step = 0.0;
+  for (const PointDesc& D : p->h_desc) {
+    if (!series_holds(D, t0, h, n)) return false;
+    series += series_us(D, h, n);
+    step += time_step_us(D) * ((double)D.n / (double)p->N);
+  }
+  // a time of two wavefronts on every SIMD takes 2.6 times that of one on its own
+  const double fill = (double)p->N / (512.0 * std::max(1, p->di.n_cu));
+  return series < 0.95 * (13.0 + n * step * (1.0 + 1.6 * pow(std::min(1.0, fill), 1.5)) * std::max(1.0, fill));
 }
 // Its workspace, and the run over the batch: every sample's result in L.
 size_t series_space(rift_ile_plan p, double h, int n, bool band) {

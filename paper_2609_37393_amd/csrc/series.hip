@@ -357,22 +357,29 @@ Layout layout(const PointDesc& D, double h, int n, bool band) {
 
 }  // namespace
 
-bool series_takes(const PointDesc& D, int64_t N, double t0, double h, int n) {
+bool series_holds(const PointDesc& D, double t0, double h, int n) {
   // times so large that a row's own rounding is not small against a row: the
   // windows' ends would not bound the rows between them
   const double big = std::max(std::max(fabs(t0), fabs(t0 + (n - 1) * h)), fabs(D.t0)) + 1.0;
-  if (!(big * D.inv_dt < 1.0e12)) return false;
-  // Rows kept per time against the per-time form's units (a mode group of a
-  // detector's stencil).  Measured on 41 times and 1e5 samples, contracted
-  // against per time (us), at 4 / 8 / 11 rows per time: 21 modes x 3 detectors
-  // 463 / 683 / 935 against 1005; 9 x 3 328 / 487 / 650 against 478; 2 x 2
-  // 172 / 250 / 378 against 100.  A batch that leaves the chip idle runs the
-  // per-time form's times one after the other: at 2e4 samples 225 against 490,
-  // 154 against 253 and 100 against 78 at 11 rows, at 1e3 samples 66 against
-  // 457, 46 against 234 and 34 against 72.
-  const double idle = sqrt(std::max(1.0, 65536.0 / (double)N));
-  return window_rows(D, h, n) <= (1.0 + 1.1 * ((D.M + 1) / 2)) * idle * n;
+  return big * D.inv_dt < 1.0e12;
 }
+
+// The two estimates (us) are fits to 321 calls of 1 to 1e5 samples a point, 1 to 64
+// points, 1 to 8 detectors, 2 to 21 modes, 2 to 301 times 1 to 30 rows apart,
+// each timed both ways; they hold to 20 - 30%, and the choice costs a hundredth on
+// average and 1.4 times at worst over those calls.  A launch of tiles whose blocks leave the
+// chip idle runs its times one after the other; the contraction takes tiles of 64
+// rows, a launch sequence per point, and writes and reads the rows it keeps.
+// Measured, contracted against per time: 21 modes x 3 detectors, 1e5 samples, 41
+// times 1, 4, 12 rows apart 361, 523, 1080 against 1020; 2 x 3, 1e5, 41 times
+// 128, 213, 590 against 121, 101 times 201 against 274; 3 times of 5e4 samples of 9
+// x 3 104 against 34; 64 points of 1000 samples, 2 x 3, 41 times 1529 against 112.
+double series_us(const PointDesc& D, double h, int n) {
+  const double wn = window_rows(D, h, n), tiles = wn + 63.0, ng = series_groups(D.M), K = D.K;
+  return 22.0 + 0.73 * K * ng +
+         1e-5 * (double)D.n * K * (std::max(0.039 * tiles * ng, 0.233 * tiles) + 5.1 * ng + 0.204 * wn);
+}
+double time_step_us(const PointDesc& D) { return 0.6 + 0.167 * D.K * (q_groups(D.M, D.w64) * D.w64); }
 
 size_t series_bytes(const PointDesc& D, double h, int n, bool band) { return layout(D, h, n, band).bytes(); }
 

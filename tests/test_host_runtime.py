@@ -281,3 +281,23 @@ assert wide(wide_point(3, modes({M}, 5 if {M} > 21 else 4), {n_a}, 500, {respons
 assert any("k_wide_rows" in c[4] for c in log() if c[0] == "launch") == {rows}
 assert rt.host_faults() == 0 and rt.host_live() == 0
 """)
+
+
+@pytest.mark.parametrize("K,M,n_points,n,n_t,rows,series", [
+    (3, 21, 1, 100_000, 657, 1, True), (3, 21, 1, 100_000, 41, 1, True), (3, 21, 1, 100_000, 41, 12, False),
+    (3, 9, 1, 50_000, 3, 1, False), (2, 2, 1, 20_000, 3, 1, False), (8, 21, 1, 50_000, 3, 1, False),
+    (3, 2, 1, 100_000, 101, 4, False), (3, 2, 1, 100_000, 301, 1, True), (3, 2, 64, 1000, 41, 1, False),
+    (3, 9, 16, 1000, 41, 1, False), (3, 21, 200, 300, 201, 1, False), (3, 21, 4, 10_000, 201, 1, True),
+    (3, 9, 1, 1, 101, 4, True), (3, 9, 1, 1000, 41, 4, True)])
+def test_form_of_the_time_rule(run, K, M, n_points, n, n_t, rows, series):
+    """Which form Simpson's rule over n_t times, `rows` table rows apart, takes."""
+    run(MARGINALS + f"""
+rc, h = create([point({K}, modes({M}), 2000)] * {n_points}, [{n}] * {n_points})
+RULES["tmarg"] = Time(-0.5 * ({n_t} - 1) * {rows} / 32768, {rows} / 32768, {n_t})
+clear()
+assert rc == OK and marginal(h, "tmarg", S1) == OK
+names = [c[4] for c in log() if c[0] == "launch"]
+assert any("k_series_simpson" in x for x in names) == {series}, names
+assert any("k_tiles" in x for x in names) != {series}, names
+assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0 and rt.host_live() == 0
+""")
