@@ -301,3 +301,29 @@ assert any("k_series_simpson" in x for x in names) == {series}, names
 assert any("k_tiles" in x for x in names) != {series}, names
 assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0 and rt.host_live() == 0
 """)
+
+
+def test_marginals_on_the_null_stream(run):
+    """Calls on the null stream need no event between them; one that follows on
+    another stream waits for an event that the null stream gets then."""
+    run(MARGINALS + """
+rc, h = create([point(3, modes(9), 900)], [5000])
+def call(name, stream):
+    clear()
+    assert marginal(h, name, stream) == OK
+    calls = [c for c in log() if c[0] in ("wait", "record", "launch", "free_async") + HOST]
+    assert not [c for c in calls if c[0] in HOST]
+    first, last = calls[0], calls[-1]
+    return [(c[0], c[3]) for c in calls if c[0] in ("wait", "record")], first, last
+assert call("pmarg", None)[0] == [] and call("pmarg", None)[0] == [] and call("erai", None)[0] == []
+events, first, last = call("pmarg", S1)
+assert events == [("record", 0), ("wait", S1), ("record", S1)] and first[0] == "record" and last[:1] == ("record",)
+events, first, last = call("tband", None)
+assert events == [("wait", 0)] and first[0] == "wait"
+assert call("erai", None)[0] == [] and call("tmarg", None)[0] == []
+assert [e for e in call("tmarg", S2)[0]] == [("record", 0), ("wait", S2), ("record", S2)]
+clear()
+assert marginal(h, "pmarg", None) == OK and lib.rift_ile_plan_destroy(h) == OK
+kinds = [c[0] for c in log()]
+assert kinds.index("event_sync") > kinds.index("record") and rt.host_faults() == 0 and rt.host_live() == 0
+""")
