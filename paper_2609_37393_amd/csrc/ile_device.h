@@ -37,19 +37,42 @@ constexpr int MMAX = 25;   // modes
 constexpr int LMAXC = 8;   // largest l
 constexpr int QPAD = 4;    // zero rows on each side of every Q series
 // Q tables hold W consecutive (internal) modes per time row.  FP64: W = 8, a row
-// of a group one aligned 128-byte line, from 13 modes on; fewer modes take W = 2,
-// whose four stencil rows of a group are 128 bytes at any multiple of 32.  Per
-// detector the reads are 4 units of 128 bytes per eight modes against one per two:
-// 12 against 11 at 21 modes, where every line is used whole (12 lines against 19)
-// and the contraction runs between the units (headline batch 245 -> 232 us), but 8
-// against 5 at 9 modes (3 detectors, 5e5 samples: 111 us against 95) and 4 against
-// 1 at 2 (10^4 samples: the kernel 10.8 us against 9.2).  FP32: W = 4, 32-byte rows.
+// of a group one aligned 128-byte line, where q_width64 says so; otherwise W = 2,
+// whose four stencil rows of a group are 128 bytes at any multiple of 32.  FP32: W = 4,
+// 32-byte rows.
 constexpr int QW64 = 8;
 constexpr int QW64_SHORT = 2;
 constexpr int QW64_SHORT_MODES = 12;
 constexpr int QW32 = 4;
 __host__ __device__ constexpr int q_groups(int M, int W) { return (M + W - 1) / W; }
-__host__ __device__ constexpr int q_width64(int M) { return M <= QW64_SHORT_MODES ? QW64_SHORT : QW64; }
+// The width of a point's FP64 rows, of M modes and K detectors in class L, KT the
+// plan's detector class.  Per detector the reads are 4 units of 128 bytes per eight modes against
+// one per two: 12 against 11 at 21 modes, where every line is used whole (12 lines
+// against 19) and the contraction runs between the units.  Measured, rows of eight
+// against rows of two (lnL and ln Z of 3e5 samples; the tile form of the time rules,
+// 6e4 x 11 times, which the units bound; in brackets the class l <= 8):
+//   KT 2:  13 modes 0.90, 0.72; 17 0.91, 0.78; 21 0.82, 0.67; (25 0.50, 0.79); two
+//          detectors 21 0.94; 17 tile form 1.11, recompute of a mixed plan 1.14
+//   KT 3:  13 0.99, 1.11; 14 0.98, 1.11; 15 0.93, 1.02; 16 0.97, 1.02; 17 1.06, 1.28;
+//          18 1.08, 1.28; 20 0.98, 1.18; 21 0.93, 1.09; (22 0.86, 1.03; 25 0.95, 1.15;
+//          their small batches 0.68)
+//   KT 5:  13 1.01, 1.03; 16 0.91, 0.92; 17 1.20, 1.17; 18 1.31, 1.23; 20 1.12, 1.08;
+//          21 1.01, 0.99 (small batches 0.92, 0.89); (22 1.09, 0.97; 25 1.13, 1.03)
+//   KT 8:  13 1.00, 1.02; 16 0.95, 0.93; 17 1.06, 1.15; 20 1.02, 1.06; 21 0.98, 0.99;
+//          (25 0.94, 0.94)
+// Up to 12 modes rows of two: 9 modes, KT 3, 5e5 samples 111 us against 95.  A mixed
+// plan, whose recompute alone reads the table (rows of eight 1.05 - 1.07 at 15 to 21
+// modes, KT 3), takes the same rows: its recomputed samples are the FP64 plan's
+// values bit for bit.
+__host__ __device__ constexpr int q_width64(int M, int K, int L, int KT) {
+  if (M <= QW64_SHORT_MODES) return QW64_SHORT;
+  const int empty = q_groups(M, QW64) * QW64 - M;
+  bool eight = empty <= 3;                                             // 13 - 16, 21 - 24
+  if (KT == 2) eight = K == 1 || L == 8 || empty <= 5;
+  else if (KT == 3) eight = L == 8 || M > 20 || (M > 14 && eight);
+  else if (KT == 8) eight = eight || (L == 8 && M > 24);
+  return eight ? QW64 : QW64_SHORT;
+}
 // LDS staging of the data term: one unit is the 128-byte stencil block of a
 // (mode group, detector) pair for each of the 64 lanes of a wavefront; every
 // wavefront owns two unit buffers.
@@ -1362,8 +1385,8 @@ __device__ __forceinline__ void incl_harmonics(R ci, R si, R* cn, R* sn) {
 }
 
 // The data term of one sample in FP64 and, with NORM, the model-norm contraction
-// acc: from 13 modes on by rows, up to three detectors with the contraction between
-// the units; otherwise one after the other.
+// acc: by rows where they hold eight modes, up to three detectors with the
+// contraction between the units; otherwise one after the other.
 template <int KT, int L, bool NORM, bool CPLX>
 __device__ __forceinline__ double data_norm(PDesc P, double* __restrict__ trig, int ts, RIFT_LDS unsigned char* stage,
                                             const int32_t* row, const double* sfr, const double* Fre,

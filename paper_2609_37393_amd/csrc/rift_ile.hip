@@ -974,8 +974,8 @@ namespace {
 constexpr size_t SLAB_BYTES = (size_t)256 << 10, SLAB_PIECE = (size_t)32 << 10;
 // `count`, if given, is what an allocation in the fixed scratch counts against
 // its limit: the FP64 tables count as rows of two modes, the least that holds
-// them, whatever the rows that the reads take (24 against 18 at 17 modes, the
-// most; the array is half as long again as the limit).
+// them, whatever the rows that the reads take (24 against 18 at 17 modes with two
+// detectors, the most; the array is half as long again as the limit).
 int palloc(rift_ile_plan p, size_t bytes, void** out, size_t count = 0) {
   if (p->arena) {
     auto next = [](size_t at, size_t len) { return ((at + 255) & ~(size_t)255) + (len < 256 ? 256 : len); };
@@ -1511,7 +1511,7 @@ int plan_create_impl(const rift_ile_point* pts, int32_t n_points, const int64_t*
     D.m_min = D.m[0];
     // device tables
     const int64_t qrows = (int64_t)KT * (pt.n_t + 2 * QPAD);
-    D.w64 = q_width64(M);
+    D.w64 = q_width64(M, K, D.L, KT);
     PCHK(palloc(p, sizeof(double) * 2 * qrows * q_groups(M, D.w64) * D.w64, &v,
                 sizeof(double) * 2 * qrows * q_groups(M, 2) * 2));
     D.Q64 = (const double*)v;

@@ -371,7 +371,7 @@ bool series_holds(const PointDesc& D, double t0, double h, int n) {
 // chip idle runs its times one after the other; the contraction takes tiles of 64
 // rows, a launch sequence per point, and writes and reads the rows it keeps.
 // Measured, contracted against per time: 21 modes x 3 detectors, 1e5 samples, 41
-// times 1, 4, 12 rows apart 361, 523, 1080 against 1020; 2 x 3, 1e5, 41 times
+// times 1, 4, 12 rows apart 352, 485, 1018 against 922; 2 x 3, 1e5, 41 times
 // 128, 213, 590 against 121, 101 times 201 against 274; 3 times of 5e4 samples of 9
 // x 3 104 against 34; 64 points of 1000 samples, 2 x 3, 41 times 1529 against 112.
 double series_us(const PointDesc& D, double h, int n) {

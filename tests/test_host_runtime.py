@@ -327,3 +327,20 @@ assert marginal(h, "pmarg", None) == OK and lib.rift_ile_plan_destroy(h) == OK
 kinds = [c[0] for c in log()]
 assert kinds.index("event_sync") > kinds.index("record") and rt.host_faults() == 0 and rt.host_live() == 0
 """)
+
+
+@pytest.mark.parametrize("K,M,lmax,prec,slots", [
+    (3, 12, 4, "FP64", 12), (3, 13, 4, "FP64", 14), (3, 14, 4, "FP64", 14), (3, 15, 4, "FP64", 16), (3, 17, 4, "FP64", 18),
+    (3, 20, 4, "FP64", 20), (3, 21, 4, "FP64", 24), (3, 21, 4, "MIXED", 24), (3, 13, 8, "FP64", 16), (3, 25, 8, "MIXED", 32),
+    (2, 17, 4, "FP64", 18), (1, 17, 4, "FP64", 24), (2, 21, 4, "FP64", 24), (1, 13, 4, "MIXED", 16), (5, 13, 4, "FP64", 16), (5, 20, 4, "FP64", 20), (5, 21, 4, "MIXED", 24),
+    (5, 25, 8, "FP64", 26), (8, 17, 4, "FP64", 18), (8, 25, 8, "FP64", 32)])
+def test_width_of_the_table(run, K, M, lmax, prec, slots):
+    """Modes a row of the FP64 table is padded to: the first allocation over 1 MB."""
+    run(f"""
+KT = {{1: 2, 2: 2, 3: 3, 5: 5, 8: 8}}[{K}]
+rc, h = create([point({K}, modes({M}, {lmax}), 4000)], [100], {prec})
+assert rc == OK
+big = [c[2] for c in log() if c[0] == "malloc" and c[2] > 1 << 20]
+assert big[0] == 16 * KT * 4008 * {slots}, (big[0] / (16 * KT * 4008))
+assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0
+""")
