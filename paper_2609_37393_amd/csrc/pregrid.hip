@@ -50,6 +50,8 @@ namespace {
 constexpr int PG_IC = 128;    // i per staged chunk
 constexpr int PG_STEPS = 8;   // steps of four i whose operands are loaded together
 constexpr int PG_PHASES = 4;  // phases (wavefronts) per block
+constexpr int PG_LANES = 64;  // refined samples per block, and
+constexpr int PG_S = 4;       // series, of the form for short series
 
 // g[b][m + 2n - 1] = D(m + b / r), b < r, m in [-(2n-1), n-1].
 __global__ void k_pregrid_table(int n, int r, double* __restrict__ g) {
@@ -183,6 +185,70 @@ __global__ void __launch_bounds__(64 * PG_PHASES) k_pregrid(const double* __rest
   }
 }
 
+// The form for short series: a lane per refined sample and four series, the series'
+// native samples uniform across the block (scalar loads), two table reads per tap.
+__global__ void __launch_bounds__(PG_LANES) k_pregrid_lanes(const double* __restrict__ q, int64_t S, int n,
+                                                            int r, const double* __restrict__ g,
+                                                            double* __restrict__ fine) {
+  const int64_t Nf = (int64_t)(n - 1) * r + 1;
+  const int64_t j0 = (int64_t)blockIdx.x * PG_LANES + threadIdx.x;
+  const bool live = j0 < Nf;
+  const int64_t j = live ? j0 : Nf - 1;
+  const int a = (int)(j / r), b = (int)(j - (int64_t)(j / r) * r);
+  const int W = 3 * n - 1;
+  const double* gb = g + (int64_t)b * W + (2 * n - 1);  // gb[m], m in [-(2n-1), n-1]
+  const int64_t s0 = (int64_t)blockIdx.y * PG_S;
+  const int ns = (int)std::min<int64_t>(PG_S, S - s0);
+  double acc[2 * PG_S];
+#pragma unroll
+  for (int c = 0; c < 2 * PG_S; ++c) acc[c] = 0.0;
+  const double* qs = q + 2 * s0 * (int64_t)n;
+  int i = 0;
+  for (; i + 4 <= n; i += 4) {
+    double t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = gb[a - (i + u)] + gb[a + (i + u) + 1 - 2 * n];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int c = 0; c < PG_S; ++c) {
+        if (c < ns) {
+          acc[2 * c] = fma(t[u], qs[2 * ((int64_t)c * n + i + u)], acc[2 * c]);
+          acc[2 * c + 1] = fma(t[u], qs[2 * ((int64_t)c * n + i + u) + 1], acc[2 * c + 1]);
+        }
+      }
+  }
+  for (; i < n; ++i) {
+    const double t = gb[a - i] + gb[a + i + 1 - 2 * n];
+#pragma unroll
+    for (int c = 0; c < PG_S; ++c) {
+      if (c < ns) {
+        acc[2 * c] = fma(t, qs[2 * ((int64_t)c * n + i)], acc[2 * c]);
+        acc[2 * c + 1] = fma(t, qs[2 * ((int64_t)c * n + i) + 1], acc[2 * c + 1]);
+      }
+    }
+  }
+  if (!live) return;
+#pragma unroll
+  for (int c = 0; c < PG_S; ++c) {
+    if (c < ns) {
+      double* o = fine + 2 * ((s0 + c) * Nf + j);
+      o[0] = acc[2 * c];
+      o[1] = acc[2 * c + 1];
+    }
+  }
+}
+
+// The matrix form pads the halves to 128 and a tile to 16 samples, and takes two
+// set-up launches; a lane per sample has neither.  Measured (us, lanes against
+// matrix): 2e5 series of 8, r = 4 84, 741; of 24, r = 2 153, 1111; 2e4 of 32, r = 2 38,
+// 106; 2e5 of 48, r = 3 948, 1719; 16 of 64, r = 8 29, 42; 1000 of 96, r = 4 34, 43; but
+// 2e4 of 64, r = 4 323, 212; 1000 of 96, r = 16 76, 42; 2e5 of 48 copied (r = 1) 503,
+// 386; 168 of 128, r = 8 42, 35.
+bool pregrid_by_lanes(int64_t S, int n, int r) {
+  return n <= 32 || (n <= 48 && r > 1) || (n <= 96 && (double)S * n * n * r <= 5.0e7);
+}
+
 }  // namespace
 
 extern "C" int rift_ile_pregrid(const double* q, int64_t n_series, int32_t n, int32_t r, double* fine, void* stream) {
@@ -193,21 +259,31 @@ extern "C" int rift_ile_pregrid(const double* q, int64_t n_series, int32_t n, in
   if ((n_series + 3) / 4 > 65535) return RIFT_EUNSUPPORTED;
   hipStream_t st = (hipStream_t)stream;
   const int64_t tab = (int64_t)r * (3 * n - 1);
+  const bool lanes = pregrid_by_lanes(n_series, n, r);
   const int HP = ((n + 1) / 2 + PG_IC - 1) / PG_IC * PG_IC;
   const int64_t CP = (2 * n_series + 15) / 16 * 16;
   double* g = nullptr;
-  if (hipMallocAsync((void**)&g, sizeof(double) * (tab + 2 * HP * CP), st) != hipSuccess) return RIFT_ENOMEM;
-  double* eo = g + tab;
+  if (hipMallocAsync((void**)&g, sizeof(double) * (tab + (lanes ? 0 : 2 * HP * CP)), st) != hipSuccess) {
+    (void)hipGetLastError();
+    return RIFT_ENOMEM;
+  }
   hipLaunchKernelGGL(k_pregrid_table, dim3((unsigned)std::min<int64_t>((tab + 255) / 256, 4096)), dim3(256), 0, st, n,
                      r, g);
-  hipLaunchKernelGGL(k_pregrid_halves, dim3((unsigned)std::min<int64_t>((HP * CP + 255) / 256, 4096)), dim3(256), 0,
-                     st, q, n_series, (int)n, (int)r, HP, CP, eo, fine);
-  const int phases = r / 2;  // 1 .. r / 2
-  if (phases > 0)
-    hipLaunchKernelGGL(k_pregrid,
-                       dim3((unsigned)((n - 1 + 15) / 16), (unsigned)(CP / 16), (unsigned)((phases + PG_PHASES - 1) / PG_PHASES)),
-                       dim3(64 * PG_PHASES), 0, st, (const double*)eo, n_series, (int)n, (int)r, HP, CP,
-                       (const double*)g, fine);
+  if (lanes) {
+    const int64_t Nf = (int64_t)(n - 1) * r + 1;
+    hipLaunchKernelGGL(k_pregrid_lanes, dim3((unsigned)((Nf + PG_LANES - 1) / PG_LANES), (unsigned)((n_series + PG_S - 1) / PG_S)),
+                       dim3(PG_LANES), 0, st, q, n_series, (int)n, (int)r, (const double*)g, fine);
+  } else {
+    double* eo = g + tab;
+    hipLaunchKernelGGL(k_pregrid_halves, dim3((unsigned)std::min<int64_t>((HP * CP + 255) / 256, 4096)), dim3(256), 0,
+                       st, q, n_series, (int)n, (int)r, HP, CP, eo, fine);
+    const int phases = r / 2;  // 1 .. r / 2
+    if (phases > 0)
+      hipLaunchKernelGGL(k_pregrid,
+                         dim3((unsigned)((n - 1 + 15) / 16), (unsigned)(CP / 16), (unsigned)((phases + PG_PHASES - 1) / PG_PHASES)),
+                         dim3(64 * PG_PHASES), 0, st, (const double*)eo, n_series, (int)n, (int)r, HP, CP,
+                         (const double*)g, fine);
+  }
   int rc = hipGetLastError() == hipSuccess ? RIFT_OK : RIFT_EDEVICE;
   if (hipFreeAsync(g, st) != hipSuccess && !rc) rc = RIFT_EDEVICE;
   return rc;

@@ -23,3 +23,10 @@ def test_refine_tiles(oracle_mod, S, n, r):
     lam = 2.0 / math.pi * math.log(2 * n) + 2.0
     assert np.all(np.abs(got - want) <= 8 * n * 2.0 ** -53 * lam * np.abs(q).max(axis=-1, keepdims=True))
     assert np.array_equal(got[:, ::r], q)
+
+
+@pytest.mark.parametrize("S,n,r", [(1, 97, 2), (3, 97, 3), (9, 113, 6), (5, 128, 5), (3, 129, 64), (1200, 81, 10),
+                                   (300, 64, 64), (3, 96, 64), (5, 40, 7), (4097, 49, 1)])
+def test_refine_forms(oracle_mod, S, n, r):
+    """Both forms beside the lines between them, with remainders of series and samples."""
+    test_refine_tiles(oracle_mod, S, n, r)

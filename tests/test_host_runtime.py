@@ -344,3 +344,18 @@ big = [c[2] for c in log() if c[0] == "malloc" and c[2] > 1 << 20]
 assert big[0] == 16 * KT * 4008 * {slots}, (big[0] / (16 * KT * 4008))
 assert lib.rift_ile_plan_destroy(h) == OK and rt.host_faults() == 0
 """)
+
+
+@pytest.mark.parametrize("S,n,r,lanes", [
+    (63, 820, 8, False), (200_000, 8, 4, True), (200_000, 32, 1, True), (20_000, 48, 2, True), (200_000, 48, 1, False),
+    (16, 64, 8, True), (20_000, 64, 4, False), (1000, 96, 4, True), (1000, 96, 16, False), (1, 97, 2, False)])
+def test_form_of_the_refinement(run, S, n, r, lanes):
+    """Short series are refined a lane per sample, without the halves' scratch."""
+    run(f"""
+assert lib.rift_ile_pregrid(vp(PTR), i64({S}), {n}, {r}, vp(PTR), vp(0x111000)) == OK
+names = [c[4] for c in log() if c[0] == "launch"]
+size = [c[2] for c in log() if c[0] == "malloc_async"][0]
+assert any("k_pregrid_lanes" in x for x in names) == {lanes} and any("k_pregrid_halves" in x for x in names) != {lanes}
+assert (size == 8 * {r} * (3 * {n} - 1)) == {lanes}
+assert rt.host_faults() == 0 and rt.host_live() == 0
+""")
