@@ -543,6 +543,8 @@ typedef void (*grad_dm_fn)(const PointDesc*, const double*, int64_t, double*, do
   tile_fn get_tiles32_kt##KT(int lset);              \
   tile_fn get_tilesdm_kt##KT(int lset);              \
   tile_fn get_tilestm_kt##KT(int lset);              \
+  tile_fn get_tilestm8_kt##KT();                     \
+  tile_fn get_tilestb8_kt##KT();                     \
   tile_fn get_tilespm_kt##KT(int lset);              \
   tile_fn get_tilestb_kt##KT(int lset);              \
   tile_fn get_tilesea_kt##KT(int lset);              \

@@ -4,7 +4,9 @@
 // distance marginal, 5: FP64 tiles of the time marginal, 6: FP64 tiles of
 // the polarisation marginal's data pass, 7: FP64 data pass of the band-limited time
 // rule, 8: FP64 data pass of the joint phiref / psi marginal, 9: coefficients
-// of the time marginals' contracted series).  The build compiles this file once per (class, kind) so the instances build in parallel.
+// of the time marginals' contracted series, 10 and 11: the l <= 8 class of 5 and
+// 7, which takes other flags).  The build compiles this file once per (class,
+// kind) so the instances build in parallel.
 #include "ile_kernels.h"
 #include "ile_series.h"
 
@@ -49,16 +51,27 @@ namespace rift {
 #define RIFT_MODE MODE_PASS32
 #define RIFT_NAME RIFT_CAT(get_tiles32_kt, RIFT_KT)
 #endif
+#if RIFT_KIND == 5
+#define RIFT_L8 RIFT_CAT(get_tilestm8_kt, RIFT_KT)()
+#elif RIFT_KIND == 7
+#define RIFT_L8 RIFT_CAT(get_tilestb8_kt, RIFT_KT)()
+#else
+#define RIFT_L8 k_tiles<RIFT_R, RIFT_KT, 8, RIFT_MODE>
+#endif
 tile_fn RIFT_NAME(int lset) {
   switch (lset) {
     case 1: return k_tiles<RIFT_R, RIFT_KT, 1, RIFT_MODE>;
     case 2: return k_tiles<RIFT_R, RIFT_KT, 2, RIFT_MODE>;
     case 4: return k_tiles<RIFT_R, RIFT_KT, 4, RIFT_MODE>;
     case 7: return k_tiles<RIFT_R, RIFT_KT, 7, RIFT_MODE>;
-    case 8: return k_tiles<RIFT_R, RIFT_KT, 8, RIFT_MODE>;
+    case 8: return RIFT_L8;
     default: return nullptr;
   }
 }
+#elif RIFT_KIND == 10
+tile_fn RIFT_CAT(get_tilestm8_kt, RIFT_KT)() { return k_tiles<double, RIFT_KT, 8, MODE_TMARG64>; }
+#elif RIFT_KIND == 11
+tile_fn RIFT_CAT(get_tilestb8_kt, RIFT_KT)() { return k_tiles<double, RIFT_KT, 8, MODE_TBAND64>; }
 #elif RIFT_KIND == 2
 refine_fn RIFT_CAT(get_refine_kt, RIFT_KT)(int lset) {
   switch (lset) {
