@@ -287,10 +287,14 @@ typedef struct {
  * calls enqueue on `stream` and return: the host arrays of *pt are read
  * before return; Q, U, V, theta and lnw must stay valid until the stream has
  * run the work.  Per call the library takes stream-ordered scratch
- * (hipMallocAsync / hipFreeAsync on `stream`) for U and V packed in the
- * order of the contraction, 32 K n_terms (n_terms + 1) / 2 C^2 bytes with
- * C = 5, 12 or 25 the mode capacity at or above M, and 16 bytes per 256
- * samples for ln Z; RIFT_ENOMEM when that fails. */
+ * (hipMallocAsync / hipFreeAsync on `stream`): the quadratic form's operands,
+ * with s = 2 n_terms ceil(M / 4) and t = ceil(s / 4) at most
+ * 512 K t (s - 2 t + 2) + 1024 bytes (21 modes of l <= 4 in large batches
+ * 2320 K n_terms (n_terms + 1) instead); 16 bytes per 64 samples for ln Z; and,
+ * where reading Q by rows pays, a copy of Q by rows, 128 K n_t
+ * ceil(n_terms S / 8) bytes with S = 4 slots a term up to 4 modes, else the next
+ * multiple of 8.  Where that copy does not fit, Q is read as it is; RIFT_ENOMEM
+ * when the rest does not. */
 int rift_ile_wide_lnL(const rift_ile_point_wide *pt, int64_t n, const double *theta, double *lnL,
                       void *stream);
 /* ln Z and n_eff (DEVICE [1] each, neff may be NULL) of n >= 1 samples with
@@ -357,8 +361,10 @@ int rift_ile_plan_grad_dmarg(rift_ile_plan plan, int32_t point, int64_t n, const
  * [t_start, t_start + (n_t - 1) h]:
  *   ln L_t = ln[(h / T) sum_k w_k e^{lnL(t_start + k h)}],  T = (n_t - 1) h,
  * with composite Simpson weights w = (1, 4, 2, 4, ..., 2, 4, 1) / 3 (n_t odd).
- * The model-norm term is evaluated once per sample, the data term at each
- * time.  The rule resolves the peak only where h is below its width,
+ * The model-norm term is evaluated once per sample.  The data term is evaluated
+ * at each time or, where the times share table rows, its modes are summed once per
+ * row and each time reads four rows' values.  The rule resolves the peak only
+ * where h is below its width,
  * 1 / (2 pi rho sigma_f) (Eq. (ap:sigmat)); choosing h is the caller's. */
 typedef struct {
   double t_start, h; /* first time (s, the axis of t_ref) and spacing (s), h > 0 */
@@ -368,7 +374,10 @@ typedef struct {
 /* ln L_t per sample (lnLt: DEVICE [N] or NULL) and, per point, ln Z_t and
  * n_eff over the plan's batch, as rift_ile_plan_lnZ_dmarg; theta's t_ref row
  * is not read.  FP64; enqueues and returns (capturable); RIFT_EINVAL for a
- * bad rule.  Cost per sample: one model-norm term and n_t data terms. */
+ * bad rule.  Rules whose times share rows take working memory, at most 224 MiB
+ * (64 samples' rows if those are more) and, without lnLt, 8 N bytes;
+ * RIFT_ENOMEM when that fails.  Cost per sample: one model-norm term and n_t data
+ * terms, or the rows of the window and four of them per time. */
 int rift_ile_plan_lnZ_tmarg(rift_ile_plan plan, const double *theta, const double *lnw,
                             const rift_ile_time_rule *rule, double *lnZ, double *neff, double *lnLt,
                             void *stream);
@@ -394,10 +403,11 @@ typedef struct {
 
 /* ln L_t per sample (lnLt: DEVICE [N] or NULL) and, per point, ln Z_t and
  * n_eff over the plan's batch, as rift_ile_plan_lnZ_tmarg; theta's t_ref row is
- * not read.  FP64; enqueues and returns, with stream-ordered scratch of at
- * most 8 (n_t N + 127 n_fine + N) bytes; RIFT_EINVAL for a bad rule.  Cost per
- * sample: one model-norm term, n_t data terms, then ((n_t - 1) n_fine + 1)
- * sums of at most 64 products and one exp each. */
+ * not read.  FP64; enqueues and returns (capturable), with working memory as
+ * rift_ile_plan_lnZ_tmarg or, for nodes that share no rows, 8 n_t N bytes, and
+ * at most 8 * 64 ((n_t - 1) n_fine / 2 + 16) bytes of weights; RIFT_EINVAL for a
+ * bad rule.  Cost per sample: one model-norm term, n_t data terms, then
+ * ((n_t - 1) n_fine + 1) sums of at most 32 products and one exp each. */
 int rift_ile_plan_lnZ_tband(rift_ile_plan plan, const double *theta, const double *lnw,
                             const rift_ile_band_rule *rule, double *lnZ, double *neff, double *lnLt,
                             void *stream);
@@ -432,8 +442,10 @@ typedef struct {
 /* ln L_psi per sample (lnLp: DEVICE [N] or NULL) and, per point, ln Z_psi and
  * n_eff over the plan's batch, as rift_ile_plan_lnZ_dmarg; theta's psi row
  * only sets where the rule's points start (the integral covers the whole
- * period).  FP64; enqueues and returns (capturable); RIFT_EINVAL for a bad
- * rule. */
+ * period).  FP64; enqueues and returns (capturable), with working memory for a
+ * piece of the batch (40 bytes a sample, at most 96 MiB or one tile), the
+ * rule's points (32 bytes each) and, without lnLp, 8 N bytes; RIFT_EINVAL for a
+ * bad rule, RIFT_ENOMEM when the memory fails. */
 int rift_ile_plan_lnZ_pmarg(rift_ile_plan plan, const double *theta, const double *lnw,
                             const rift_ile_psi_rule *rule, double *lnZ, double *neff, double *lnLp, void *stream);
 
@@ -443,9 +455,9 @@ int rift_ile_plan_lnZ_pmarg(rift_ile_plan plan, const double *theta, const doubl
  * on [0, 2 pi) and psi on [0, pi).  At fixed sky, inclination, time and
  * distance, lnL is a finite trigonometric polynomial in (phiref, 2 psi): of
  * degree 2 in 2 psi and 2 m_max in phiref (m_max the largest |m| of the
- * plan's modes).  Its coefficients are fixed exactly by the data term at
- * 2 m_max + 1 and the model norm at 4 m_max + 1 phases (one gather of the
- * correlation tables per data-term phase, the psi dependence analytic); the
+ * plan's modes).  Its coefficients come exactly from one gather of the
+ * correlation tables, the sums of each m kept apart, and one contraction of the
+ * model norm, those of each harmonic kept apart (the psi dependence analytic); the
  * exponential of the reconstructed model is then averaged over the periodic
  * grid of n_phi x n_psi offsets from the sample's (phiref, psi):
  *   ln L = ln[(1 / (n_phi n_psi)) sum_{a, b} e^{lnL(phi + 2 pi a / n_phi,
@@ -458,11 +470,12 @@ typedef struct {
 
 /* ln L per sample (lnLa: DEVICE [N] or NULL) and, per point, ln Z and n_eff
  * over the plan's batch; theta's phiref and psi rows set where the grid
- * starts.  FP64; enqueues and returns, with stream-ordered scratch of
- * 8 ((4 m_max + 2 + 3 (4 m_max + 1)) N + 26 n_phi + 4 n_psi + N) bytes at
- * most; RIFT_EINVAL for a bad rule, RIFT_EUNSUPPORTED for modes with
- * |m| > 4.  Cost per sample: 2 m_max + 1 data terms, 4 m_max + 1 model-norm
- * contractions, then n_phi n_psi exponentials. */
+ * starts.  FP64; enqueues and returns (capturable), with working memory for a
+ * piece of the batch (8 (16 m_max + 5) bytes a sample, at most 96 MiB or one
+ * tile), 8 (26 n_phi + 4 n_psi) bytes of tables and, without lnLa, 8 N bytes;
+ * RIFT_EINVAL for a bad rule, RIFT_EUNSUPPORTED for modes with |m| > 4,
+ * RIFT_ENOMEM when the memory fails.  Cost per sample: one data term and one
+ * model-norm contraction, then n_phi n_psi exponentials. */
 int rift_ile_plan_lnZ_erai(rift_ile_plan plan, const double *theta, const double *lnw,
                            const rift_ile_angle_rule *rule, double *lnZ, double *neff, double *lnLa, void *stream);
 
@@ -480,8 +493,9 @@ int rift_ile_gauss_hermite(int n, double *nodes, double *weights);
  * period 2n in closed form) applied to every series.
  * q: DEVICE [n_series][n] complex; fine: DEVICE [n_series][(n - 1) r + 1]
  * complex (not overlapping q).  2 <= n, 1 <= r <= 64, (n - 1) r + 1 <= 2^28.
- * Enqueues and returns; stream-ordered scratch of 8 r (3n - 1) bytes
- * (hipMallocAsync / hipFreeAsync on `stream`). */
+ * Enqueues and returns; stream-ordered scratch (hipMallocAsync / hipFreeAsync on
+ * `stream`) of 8 r (3n - 1) bytes and, but for short series (n up to 96),
+ * 2048 ceil((n + 1) / 256) (2 n_series + 15) more. */
 int rift_ile_pregrid(const double *q, int64_t n_series, int32_t n, int32_t r, double *fine, void *stream);
 
 /* ------------------------------------------------------------------------ */

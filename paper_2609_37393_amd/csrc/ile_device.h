@@ -19,8 +19,9 @@
 //               sin(n incl) [cos(q phi) | sin(q phi)],     q odd },
 // n <= 2L, q <= 2L, and the per-sample work is one contraction of the basis
 // values with the uniform coefficient table C (scalar loads).  C is exact up
-// to rounding: a setup kernel samples g_c on a grid finer than twice the
-// degree and projects (discrete orthogonality).  The finite angular harmonic
+// to rounding: a setup kernel takes the phi dependence of every pair of modes as it
+// stands and projects that in incl on a grid finer than twice the degree
+// (discrete orthogonality).  The finite angular harmonic
 // content this relies on is the paper's Eq. (ap:angleharm) argument applied to
 // (incl, phiref).
 #pragma once
@@ -220,8 +221,8 @@ __device__ __forceinline__ T by_det(const T* v, int k) {
   }
   return r;
 }
-// sin and cos of N angles at once: reduction by pi/2 in three parts with fused
-// multiply-adds, then the Taylor series through r^17 and r^18 on |r| <= pi/4
+// sin and cos of N angles at once: Cody and Waite's reduction by pi/2 in three
+// parts with fused multiply-adds, then the Taylor series through r^17 and r^18 on |r| <= pi/4
 // (truncation below 1e-18), the N angles side by side, so that each constant is
 // fetched once and the chains of one angle fill the latencies of another's:
 // 36 vector operations an angle, where the library's function takes 105.

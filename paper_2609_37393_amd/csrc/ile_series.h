@@ -10,10 +10,11 @@
 // consecutive rows) instead of by a gather at every lane's own place.
 //
 // 3 detectors, 21 modes, 1e5 samples: 657 times at the table's spacing take
-// 1.39 ms (per time 16.4 ms), of which the contraction 0.8 ms (three times its
+// 1.43 ms (per time 16.4 ms), of which the contraction 0.8 ms (three times its
 // matrix-core time; 1.6 GB written), the rule's reads of it 0.5 ms; the band
-// rule on 64 nodes with 16 fine intervals 1.36 ms (2.2 ms), of which its
-// reconstruction 0.34 ms.
+// rule on 64 nodes with 16 fine intervals 1.39 ms (2.2 ms), of which its
+// reconstruction 0.34 ms.  Where few times share a row, series_us and
+// time_step_us decide for the per-time form.
 //
 // Per chunk of samples, with every array in one workspace:
 //   k_series_coef    a lane per sample: x F_k Y_i, the delays, the first row

@@ -367,9 +367,10 @@ bool series_holds(const PointDesc& D, double t0, double h, int n) {
 // The two estimates (us) are fits to 321 calls of 1 to 1e5 samples a point, 1 to 64
 // points, 1 to 8 detectors, 2 to 21 modes, 2 to 301 times 1 to 30 rows apart,
 // each timed both ways; they hold to 20 - 30%, and the choice costs a hundredth on
-// average and 1.4 times at worst over those calls.  A launch of tiles whose blocks leave the
-// chip idle runs its times one after the other; the contraction takes tiles of 64
-// rows, a launch sequence per point, and writes and reads the rows it keeps.
+// average and 1.4 times at worst over those calls.  A launch of tiles whose blocks
+// leave the chip idle runs its times one after the other; the contraction takes
+// tiles of 64 rows, a launch sequence per point, and writes and reads the rows it
+// keeps.
 // Measured, contracted against per time: 21 modes x 3 detectors, 1e5 samples, 41
 // times 1, 4, 12 rows apart 352, 485, 1018 against 922; 2 x 3, 1e5, 41 times
 // 128, 213, 590 against 121, 101 times 201 against 274; 3 times of 5e4 samples of 9
