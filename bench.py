@@ -694,14 +694,19 @@ def extra_tmarg(ile, synth, torch, steps, cpu=True):
     kms, nl = plan.profile_read()
     plan.profile(False)
     plan.close()
-    # the contracted series run no likelihood kernel: the call's own time then
-    kms = kms / nl if nl else 1e3 * per
-    # the model-norm term once, the data term (antenna, stencils, gather, interpolation, coefficients) per time
-    fps = survey_flops_per_sample(3, 21) + (n_t - 1) * 3 * (57 + 26 * 21)
+    if nl:  # time by time in the likelihood kernel: the model-norm term once, the data term (antenna, stencils,
+        # gather, interpolation, coefficients) per time
+        kms, form = kms / nl, "per time"
+        fps = survey_flops_per_sample(3, 21) + (n_t - 1) * 3 * (57 + 26 * 21)
+    else:  # contracted series, which run no likelihood kernel: the call's own time; per detector the modes summed
+        # once per table row of the window (a complex product's real part each), a stencil and four taps per time
+        kms, form = 1e3 * per, "contracted series"
+        rows = int((n_t - 1) * h * 32768.0) + 8
+        fps = survey_flops_per_sample(3, 21) + 3 * (rows * 4 * 21 + n_t * 32)
     res = {"workload": "3 detectors, 21 modes (l<=4), Q 6554 samples at 32768 Hz, SNR 600; 1e5 samples of the other "
                        "parameters, Simpson rule on 657 times (32768 Hz) over 20 ms",
            "lnLt_evals_per_s": n / per, "data_terms_per_s": n * n_t / per, "ms_per_call": 1e3 * per,
-           "kernel_ms": kms, "flops_per_sample": fps,
+           "form": form, "kernel_ms": kms, "flops_per_sample": fps,
            "alu_frac": fps * n / (kms / 1e3) / (PEAK_FP64_TFLOPS * 1e12), "lnZt": z.item()}
     if cpu:
         import oracle
@@ -745,11 +750,13 @@ def extra_tband(ile, synth, torch, steps, cpu=True):
         kms, nl = plan.profile_read()
         plan.profile(False)
         fine = 63 * M + 1
-        rest = 1e3 * per - kms  # all of the call where no likelihood kernel runs
-        r = {"lnLt_evals_per_s": n / per, "data_terms_per_s": n * 64 / per, "ms_per_call": 1e3 * per,
-             "data_pass_kernel_ms": kms, "reconstruction_and_reduction_ms": rest, "fine_times": fine,
-             "reconstruction_flops_per_sample": 2 * fine * 64,
-             "reconstruction_tflops": 2 * fine * 64 * n / (rest / 1e3) / 1e12, "lnZt": z.item()}
+        r = {"lnLt_evals_per_s": n / per, "data_terms_per_s": n * 64 / per, "ms_per_call": 1e3 * per, "fine_times": fine,
+             "form": "per time" if nl else "contracted series", "lnZt": z.item()}
+        if nl:  # the rest of the call is the reconstruction (halves of mirrored nodes and points) and the reduction
+            rest = 1e3 * per - kms
+            r.update({"data_pass_kernel_ms": kms, "reconstruction_and_reduction_ms": rest,
+                      "reconstruction_flops_per_sample": fine * 64,
+                      "reconstruction_tflops": fine * 64 * n / (rest / 1e3) / 1e12})
         if cpu:
             import oracle
 
@@ -766,9 +773,9 @@ def extra_tband(ile, synth, torch, steps, cpu=True):
 def extra_erai(ile, synth, torch, steps, cpu=True):
     """The headline point (3 detectors, 21 modes, SNR 600, 1e6 prior samples)
     marginalised jointly over phiref and psi by exact reconstruction
-    (Eqs. (ap:angleharm), (ap:nyquist)): 9 data-term and 17 model-norm phases
-    per sample, then the exponential on a 32 x 16 and a 64 x 32 grid; against
-    the FP64 oracle on a sample."""
+    (Eqs. (ap:angleharm), (ap:nyquist)): the data term's 9 and the model norm's
+    17 harmonics per sample, then the exponential on a 32 x 16 and a 64 x 32
+    grid; against the FP64 oracle on a sample."""
     pt, th = c2_inputs(synth, 1_000_000)
     n = th.shape[1]
     tht = torch.as_tensor(th, device="cuda").contiguous()
@@ -776,7 +783,7 @@ def extra_erai(ile, synth, torch, steps, cpu=True):
     z = torch.empty(1, dtype=torch.float64, device="cuda")
     ll = torch.empty(n, dtype=torch.float64, device="cuda")
     res = {"workload": "3 detectors, 21 modes (l<=4), Q 6554 samples at 32768 Hz, SNR 600, 1e6 prior samples; "
-                       "lnL marginalised over phiref and psi (9 + 17 sampling phases)"}
+                       "lnL marginalised over phiref and psi (9 + 17 harmonics)"}
     for n_phi, n_psi in ((32, 16), (64, 32)):
         def step():
             plan.lnZ_erai(tht, n_phi, n_psi, lnZ_out=z, lnL_out=ll)
@@ -831,7 +838,7 @@ def extra_pmarg(ile, synth, torch, steps, cpu=True):
         step()
         kms, nl = plan.profile_read()
         plan.profile(False)
-        r = {"lnLp_evals_per_s": n / per, "ms_per_step": 1e3 * per, "kernel_ms": kms / max(1, nl), "lnZp": z.item()}
+        r = {"lnLp_evals_per_s": n / per, "ms_per_step": 1e3 * per, "data_pass_kernel_ms": kms / max(1, nl), "lnZp": z.item()}
         if cpu:
             import oracle
 
