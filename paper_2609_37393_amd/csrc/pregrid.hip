@@ -187,6 +187,8 @@ __global__ void __launch_bounds__(64 * PG_PHASES) k_pregrid(const double* __rest
 
 // The form for short series: a lane per refined sample and four series, the series'
 // native samples uniform across the block (scalar loads), two table reads per tap.
+// Native times are copied, as in the matrix form: a sample that is not finite then
+// stays out of the others' native times.
 __global__ void __launch_bounds__(PG_LANES) k_pregrid_lanes(const double* __restrict__ q, int64_t S, int n,
                                                             int r, const double* __restrict__ g,
                                                             double* __restrict__ fine) {
@@ -233,8 +235,9 @@ __global__ void __launch_bounds__(PG_LANES) k_pregrid_lanes(const double* __rest
   for (int c = 0; c < PG_S; ++c) {
     if (c < ns) {
       double* o = fine + 2 * ((s0 + c) * Nf + j);
-      o[0] = acc[2 * c];
-      o[1] = acc[2 * c + 1];
+      const double* node = qs + 2 * ((int64_t)c * n + a);
+      o[0] = b ? acc[2 * c] : node[0];
+      o[1] = b ? acc[2 * c + 1] : node[1];
     }
   }
 }

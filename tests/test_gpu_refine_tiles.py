@@ -30,3 +30,17 @@ def test_refine_tiles(oracle_mod, S, n, r):
 def test_refine_forms(oracle_mod, S, n, r):
     """Both forms beside the lines between them, with remainders of series and samples."""
     test_refine_tiles(oracle_mod, S, n, r)
+
+
+@pytest.mark.parametrize("n,r", [(20, 1), (20, 3), (130, 3)])
+def test_nodes_of_a_series_with_an_infinity(n, r):
+    """Both forms copy native times: what is not finite reaches neither them nor another series."""
+    from paper_2609_37393_amd import ile
+
+    q = np.random.default_rng(n + r).normal(size=(6, n)) + 0j
+    clean = ile.pregrid(q, r).cpu().numpy()
+    q[2, 7] = np.inf
+    got = ile.pregrid(q, r).cpu().numpy()
+    assert np.array_equal(got[:, ::r], q)
+    others = [0, 1, 3, 4, 5]
+    assert np.array_equal(got[others], clean[others])
