@@ -42,8 +42,6 @@ def _loops(kt: int, kind: int) -> bool:
     return kind in LOOP_KINDS or (kt > 3 and kind in (5, 7))
 
 
-FLAGS = ["-mllvm", "-disable-machine-licm"]
-
 FLAGS = [
     "-O3",
     "-std=c++17",
