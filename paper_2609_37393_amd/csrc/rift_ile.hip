@@ -120,10 +120,10 @@ inline int basis_count(int L) {
 // They are taken at NG = 4L + 4 values of incl over [0, 2 pi) (more than twice
 // the degree 2L) and projected on cos, sin(n incl), whose values on that grid
 // are one table of NG entries.  A thread per (incl, q, share of the rows i);
-// 10 us for 21 modes at L = 4, where sampling g_c on an NG x NG grid of (incl,
-// phi) with a sincos per mode and grid point took 640 us (3 blocks of a serial
-// M^2 loop).  U, V in caller order, modes mapped through perm.  Writes columns
-// 3k..3k+2 of C64/C32 [B][3 KT].
+// 26 us for 21 modes at L = 4 (9 us for 9 at L = 3), where sampling g_c on an
+// NG x NG grid of (incl, phi) with a sincos per mode and grid point took 640 us
+// (3 blocks of a serial M^2 loop).  U, V in caller order, modes mapped through
+// perm.  Writes columns 3k..3k+2 of C64/C32 [B][3 KT].
 constexpr int BASIS_BLOCK = 1024;
 constexpr int BASIS_MAX_NG = 4 * LMAXC + 4;
 __global__ void __launch_bounds__(BASIS_BLOCK) k_basis(const PointDesc* __restrict__ P, const double* __restrict__ U,
@@ -1851,9 +1851,10 @@ int series_batch(rift_ile_plan p, const double* theta, int fine, const double* s
 
 // An angular rule over the batch: the data pass `mode` leaves `rows`
 // coefficients per sample, and `rule(count, out)` turns a piece's into its
-// samples' values.  The batch runs in pieces whose coefficients fit ANG_KEEP bytes, each read back while it is in cache; the data pass takes
-// whole tiles, consecutive in samples, or in a binned batch in records (a point's
-// records fill its range of samples).
+// samples' values.  The batch runs in pieces whose coefficients fit ANG_KEEP
+// bytes, each read back while it is in cache; the data pass takes whole tiles,
+// consecutive in samples, or in a binned batch in records (a point's records
+// fill its range of samples).
 constexpr size_t ANG_KEEP = (size_t)96 << 20;
 struct AngPiece {
   int tile, tiles;

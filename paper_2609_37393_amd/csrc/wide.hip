@@ -9,9 +9,9 @@
 // Two responses:
 //   rotation (Path A): a <-> sidereal harmonic n = a - 2, n = -2..2.  F_k over
 //     the Greenwich hour angle g is a degree-2 trigonometric polynomial,
-//     F_k(g) = sum_n A_n e^{i n g} (Eq. (slowrot:Fharm)); A_n is the exact
-//     five-point transform of F_k at g_j = 2 pi j / 5 for the sample's dec and
-//     psi.  C~_n = A_n e^{i n g(t_ref)} e^{i n W (t_k - t_ref)} (the post-phase
+//     F_k(g) = sum_n A_n e^{i n g} (Eq. (slowrot:Fharm)); A_n in closed form
+//     of the sample's dec and psi.
+//     C~_n = A_n e^{i n g(t_ref)} e^{i n W (t_k - t_ref)} (the post-phase
 //     of Eq. (slowrot:postphase), the bank's modulation referenced to the
 //     template's own time), g(t) = gmst + W t - ra; the delay is held at the
 //     arrival time t_k of the sky frame at t_ref.
@@ -38,9 +38,9 @@
 // loads a wavefront for the composite forms, with two wavefronts a SIMD.)
 // Measured (3 detectors, 6554-row windows, a call; the forms on the vector unit
 // before): rotation, 4 modes, 1e6 samples 724 -> 374 us; 9 modes, 1000 and 150k
-// samples 689 -> 131 and 1235 -> 354 us; 21 modes, 1000 and 150k samples
-// 600 -> 409 and 1144 -> 972 us; arms of 12 terms, 4 modes, 1e6 samples
-// 3.6 -> 1.47 ms.  At 1e6 samples of the rotation the rows of Q alone take
+// samples 689 -> 131 and 1235 -> 354 us; 21 modes, 20k and 200k samples
+// 588 -> 354 and 1155 -> 1128 us; 12 terms (the drift to order 1), 4 modes, 1e6
+// samples 3.6 -> 1.47 ms.  At 1e6 samples of the rotation the rows of Q alone take
 // 0.15 ms to read, the matrix products 0.09 and the front about 0.13: a second
 // pair of wavefronts a SIMD (staging halved to make the LDS for it) or products
 // issued between the lines of Q, both of which spill, gave no more.
