@@ -70,6 +70,13 @@ def test_row_contraction_instances(ile, oracle_mod, K, M, lmax):
     _check(ile, oracle_mod, pt, th, (-0.004, 1.0 / 8192, 33), 5, idx)
 
 
+@pytest.mark.parametrize("K,M,lmax", [(3, 7, 3), (2, 8, 4), (3, 11, 3), (3, 12, 3), (2, 13, 4), (8, 14, 4), (5, 17, 4),
+                                      (1, 18, 4), (3, 19, 4), (3, 20, 6), (3, 23, 6)])
+def test_row_contraction_instances_between(ile, oracle_mod, K, M, lmax):
+    """Counts of mode pairs between those above, odd and even numbers of modes."""
+    test_row_contraction_instances(ile, oracle_mod, K, M, lmax)
+
+
 # the table covers +-9.2 ms: windows across its start, its end, all of it and
 # beyond, wholly outside, a spacing well under the table's, and off its grid
 @pytest.mark.parametrize("rule", [(-0.02, 1.0 / 32768, 401), (0.004, 1.0 / 32768, 401), (-0.05, 1.0 / 16384, 1601),
